@@ -46,34 +46,87 @@ struct Dims {
 };
 
 // ----------------------------------------------------------------------------
-// Plain (shape-generic) kernels, T = float or bf16_t storage, fp32 arithmetic.
-// Every launcher enqueues on `s` and returns the launch status.
+// Plain (shape-generic) kernels, T = float or bf16_t storage, fp32 accumulation.
+//
+// Every matrix operand of a contraction lives in *16-row fragment order*, "F(R, K)": tiles of 16
+// rows x 64 bytes of K (16 floats or 32 bf16), 1 KiB each = 64 lanes x 16 bytes; lane l holds row
+// l % 16, 16-byte chunk l / 16.  That is the operand of v_mfma_f32_16x16x32_bf16 as it stands and
+// of four v_mfma_f32_16x16x4_f32 (the i-th takes element i of every lane).  K is padded to whole
+// tiles with zeros (weights: packed so; activations: zeroed once, never written there), rows to
+// whole tiles with anything finite or not: a row only reaches its own output.
 // ----------------------------------------------------------------------------
+template <typename T> __host__ __device__ constexpr int plain_chunk() { return 16 / (int)sizeof(T); }   // elements per 16 bytes
+template <typename T> __host__ __device__ constexpr int plain_tile_k() { return 64 / (int)sizeof(T); }  // K elements per tile
+__host__ __device__ inline int plain_tiles(int k, int es) { return (k * es + 63) / 64; }  // tiles along K
+template <typename T> __host__ __device__ inline size_t plain_offset(size_t row, int k, int tiles) {
+  constexpr int E = plain_chunk<T>();
+  return (((row >> 4) * tiles + k / (4 * E)) * 64 + (size_t)((k / E) & 3) * 16 + (row & 15)) * E + k % E;
+}
+// KV cache of one layer, per (request, KV head): keys F(max_seq, d); values as tiles of 16 keys x
+// 16 features, lane l holding feature l % 16 and keys 4 (l / 16) .. + 3 (the operand of the P V
+// product in the order in which probabilities leave the score accumulators).
+struct PlainCache {
+  int nkv, d, key_blocks;  // 16-key blocks per request
+  __host__ __device__ size_t k_elems(int es) const { return (size_t)key_blocks * plain_tiles(d, es) * (1024 / es); }
+  __host__ __device__ size_t v_elems() const { return (size_t)key_blocks * ((d + 15) / 16) * 256; }
+  __host__ __device__ size_t v_offset(int pos, int f) const {
+    const int w = pos & 15;
+    return ((size_t)(pos >> 4) * ((d + 15) / 16) + (f >> 4)) * 256 + ((w >> 2) * 16 + (f & 15)) * 4 + (w & 3);
+  }
+};
+
+enum { PLAIN_QKV = 0, PLAIN_SWIGLU = 1, PLAIN_RESID = 2, PLAIN_FINAL = 3 };
+
+// out^T[N, rows] = W[N, K] X[rows, K]^T and what follows it in the block
+template <typename T> struct PlainGemm {
+  const T *W = nullptr, *X = nullptr;  // F(N, K), F(rows, K)
+  int N = 0, K = 0, rows = 0;
+  // sums of squares of the rows of the normalised input, [ssq_parts][rows_pad]; null: no norm
+  const float *ssq_in = nullptr;
+  int ssq_parts = 0, rows_pad = 0;
+  float eps = 0.f;
+  // PLAIN_QKV: rotary position, cache append, queries row-major [rows][nq][q_ld]
+  const int *tok_req = nullptr, *tok_pos = nullptr;
+  const float *cos_tab = nullptr, *sin_tab = nullptr;
+  T *q = nullptr, *Kc = nullptr, *Vc = nullptr;
+  int q_ld = 0;
+  PlainCache cache = {};
+  Dims dm = {};
+  // PLAIN_SWIGLU: F(rows, N / 2)
+  T *m = nullptr;
+  // PLAIN_RESID: residual [rows][N], gain of the next norm, y = x * gain -> F(rows, N), sums of squares per 16 features
+  float *xres = nullptr;
+  const T *gain = nullptr;
+  T *y = nullptr;
+  float *ssq_out = nullptr;
+  // PLAIN_FINAL: residual in, stage output out; lens += 1 where given
+  T *hidden_out = nullptr;
+  int *lens_advance = nullptr;
+};
+struct PlainTile { int row0, pos0, n, req; };  // up to 16 consecutive prompt tokens of one request
+
+enum { PLAIN_ROWS = 0, PLAIN_PAIRS_QKV = 1, PLAIN_PAIRS_GATEUP = 2 };
+// dst = F(N, K) of the rows of [src0; src1; src2], row order by `mode` (see plain_src_row)
 template <typename T>
-hipError_t plain_load_hidden(const T *in, float *xres, size_t n, hipStream_t s);
+hipError_t plain_pack_weight(const T *src0, const T *src1, const T *src2, int rows0, int rows1, T *dst, int N, int K,
+                             int mode, int head_dim, int qk_rows, hipStream_t s);
+// x = hidden_in ; xres = x ; y = x * gain -> F(rows, H) ; sums of squares per 16 features
 template <typename T>
-hipError_t plain_store_hidden(const float *xres, T *out, size_t n, hipStream_t s);
+hipError_t plain_begin(const T *hidden_in, float *xres, const T *gain, T *y, float *ssq_out, int rows, int rows_pad, int H,
+                       hipStream_t s);
+template <typename T> hipError_t plain_gemm(int epi, const PlainGemm<T> &g, hipStream_t s);
+// prompt: tiles of up to 16 tokens; out F(rows, nq d)
 template <typename T>
-hipError_t plain_rmsnorm(const float *xres, const T *g, T *y, int rows, int H, float eps,
-                         hipStream_t s);
-// C[M,N] (+)= A[M,K] * B[N,K]^T ; OutT = T or float
-template <typename T, typename OutT>
-hipError_t plain_gemm_nt(const T *A, const T *B, OutT *C, int M, int N, int K, bool accumulate,
-                         hipStream_t s);
-// rotate q and k of qkv[T, qd+2kvd] in place; write k, v to the cache
-// cache layout: [request][kv_head][max_seq][d]
+hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const PlainTile *tiles, int n_tiles,
+                              const PlainCache &cache, const Dims &dm, hipStream_t s);
+// one token per request at position lens[request], whose key is already cached
 template <typename T>
-hipError_t plain_rope_cache(T *qkv, const int *tok_req, const int *tok_pos, const float *cos_tab,
-                            const float *sin_tab, T *Kc, T *Vc, int rows, const Dims &dm,
-                            hipStream_t s);
-template <typename T>
-hipError_t plain_attention(const T *qkv, const int *tok_req, const int *tok_pos, const T *Kc,
-                           const T *Vc, T *out, int rows, const Dims &dm, hipStream_t s);
-template <typename T>
-hipError_t plain_swiglu(const T *gu, T *m, int rows, int I, hipStream_t s);
-hipError_t advance_lens(int *lens, int batch, hipStream_t s);
+hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch,
+                             const PlainCache &cache, const Dims &dm, hipStream_t s);
+hipError_t plain_init();  // kernel attributes
 template <typename T>
 hipError_t plain_export_kv(const T *Kc, const T *Vc, T *k_out, T *v_out, int request, int len,
-                           const Dims &dm, hipStream_t s);
+                           const PlainCache &cache, hipStream_t s);
+hipError_t plain_fill_zero(void *p, size_t bytes, hipStream_t s);
 
 }  // namespace hyp

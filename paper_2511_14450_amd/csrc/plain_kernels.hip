@@ -1,230 +1,500 @@
-// Shape-generic HIP kernels of the decoder block (Sec. III-A of the paper):
-// fp32 arithmetic on float or bf16 storage.  They are the whole fp32 path and
-// serve bf16 stages whose shape the MFMA kernels do not cover.
+// Shape-generic HIP kernels of the decoder block (Sec. III-A of the paper): matrix-core
+// contractions with fp32 accumulation on float or bf16 storage for any width, head size up to 256
+// and batch.  They are the whole fp32 path and serve bf16 stages whose shape the large bf16
+// kernels do not cover.
 #include "common.h"
 
 namespace hyp {
 
 namespace {
 
-constexpr int kWave = 64;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
-__device__ inline float wave_max(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
+// acc += A B over the 64 bytes of K that one fragment of either operand covers
+template <typename T> __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 acc);
+template <> __device__ __forceinline__ f32x4 mma<float>(u32x4 a, u32x4 b, f32x4 acc) {
+  const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], acc, 0, 0, 0);
+  return acc;
 }
-__device__ inline float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+template <> __device__ __forceinline__ f32x4 mma<bf16_t>(u32x4 a, u32x4 b, f32x4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
 }
 
+// four consecutive elements: one wide access where `vec` says the address allows it
+template <typename T> struct Four;
+template <> struct Four<float> { typedef f32x4 V; };
+template <> struct Four<bf16_t> { typedef uint2 V; };
+template <typename T> __device__ __forceinline__ void put4(T *p, const float *v, int n, bool vec) {
+  if (vec && n == 4) {
+    union { T e[4]; typename Four<T>::V v; } u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) store_f32(&u.e[i], v[i]);
+    *(typename Four<T>::V *)p = u.v;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < n) store_f32(p + i, v[i]);
+  }
+}
+
+// packed row -> row of the stacked matrices.  Rows an epilogue combines sit next to each other:
+// the rotary partners i, i + d/2 of every query and key head; gate and up of an FFN feature.
+__device__ inline int plain_src_row(int r, int N, int mode, int d, int qk_rows) {
+  if (mode == PLAIN_PAIRS_QKV && r < qk_rows) {
+    const int head = r / d, w = r % d;
+    return head * d + (w >> 1) + (w & 1) * (d >> 1);
+  }
+  if (mode == PLAIN_PAIRS_GATEUP) return (r >> 1) + (r & 1) * (N >> 1);
+  return r;
+}
+
+// one thread per 16-byte chunk of the destination
 template <typename T>
-__global__ void k_load_hidden(const T *__restrict__ in, float *__restrict__ xres, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) xres[i] = load_f32(in + i);
-}
-
-template <typename T>
-__global__ void k_store_hidden(const float *__restrict__ xres, T *__restrict__ out, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) store_f32(out + i, xres[i]);
-}
-
-// one 256-thread block per row: y = x * rsqrt(mean(x^2) + eps) * g
-template <typename T>
-__global__ void __launch_bounds__(256) k_rmsnorm(const float *__restrict__ xres,
-                                                 const T *__restrict__ g, T *__restrict__ y, int H,
-                                                 float eps) {
-  __shared__ float part[4];
-  const float *x = xres + (size_t)blockIdx.x * H;
-  float ss = 0.f;
-  for (int i = threadIdx.x; i < H; i += 256) ss += x[i] * x[i];
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  float tot = part[0] + part[1] + part[2] + part[3];
-  float r = 1.0f / sqrtf(tot / (float)H + eps);
-  T *yr = y + (size_t)blockIdx.x * H;
-  for (int i = threadIdx.x; i < H; i += 256) store_f32(yr + i, x[i] * r * load_f32(g + i));
-}
-
-// C[M,N] (+)= A[M,K] B[N,K]^T, 64x64 tile, 16-deep LDS stages, 4x4 per thread
-template <typename T, typename OutT>
-__global__ void __launch_bounds__(256) k_gemm_nt(const T *__restrict__ A, const T *__restrict__ B,
-                                                 OutT *__restrict__ C, int M, int N, int K,
-                                                 int accumulate) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
-  int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4];
-  for (int i = 0; i < 4; ++i)
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int e = threadIdx.x; e < 64 * 16; e += 256) {
-      int r = e >> 4, kk = e & 15;
-      int gm = m0 + r, gn = n0 + r, gk = k0 + kk;
-      As[kk][r] = (gm < M && gk < K) ? load_f32(A + (size_t)gm * K + gk) : 0.f;
-      Bs[kk][r] = (gn < N && gk < K) ? load_f32(B + (size_t)gn * K + gk) : 0.f;
+__global__ void __launch_bounds__(256) k_plain_pack(const T *__restrict__ src0, const T *__restrict__ src1,
+                                                    const T *__restrict__ src2, int rows0, int rows1, T *__restrict__ dst,
+                                                    int N, int K, int tiles, int mode, int d, int qk_rows, size_t chunks) {
+  constexpr int E = plain_chunk<T>();
+  const size_t stride = (size_t)gridDim.x * 256;
+  for (size_t c = (size_t)blockIdx.x * 256 + threadIdx.x; c < chunks; c += stride) {
+    const size_t tile = c >> 6;
+    const int lane = c & 63, r = (int)(tile / tiles) * 16 + (lane & 15), k = (int)(tile % tiles) * 4 * E + (lane >> 4) * E;
+    union { T e[E]; u32x4 v; } u;
+    u.v = u32x4{0, 0, 0, 0};
+    if (r < N) {
+      const int sr = plain_src_row(r, N, mode, d, qk_rows);
+      const T *s = sr < rows0 ? src0 + (size_t)sr * K : sr < rows0 + rows1 ? src1 + (size_t)(sr - rows0) * K
+                                                                           : src2 + (size_t)(sr - rows0 - rows1) * K;
+      if (k + E <= K && (uintptr_t)(s + k) % 16 == 0) u.v = *(const u32x4 *)(s + k);
+      else
+        for (int e = 0; e < E; ++e)
+          if (k + e < K) u.e[e] = s[k + e];
     }
+    *(u32x4 *)(dst + c * E) = u.v;
+  }
+}
+
+// x = hidden_in ; residual = x ; y = x * gain -> F(rows, H) ; sum of squares per 16 features.
+// grid (ceil(H16 / 256), rows); a thread per feature, 16 neighbouring lanes share a sum.
+template <typename T>
+__global__ void __launch_bounds__(256) k_plain_begin(const T *__restrict__ in, float *__restrict__ xres,
+                                                     const T *__restrict__ gain, T *__restrict__ y,
+                                                     float *__restrict__ ssq, int H, int rows_pad, int tiles) {
+  const int f = blockIdx.y * 256 + threadIdx.x;
+  const size_t row = blockIdx.x;
+  float x = 0.f;
+  if (f < H) {
+    x = load_f32(in + row * H + f);
+    xres[row * H + f] = x;
+    store_f32(y + plain_offset<T>(row, f, tiles), x * load_f32(gain + f));
+  }
+  // added in the order of the residual epilogue below, so that a stage that starts here gives the
+  // bits of one that comes from the block before
+  float s;
+  {
+#pragma clang fp contract(off)
+    s = x * x;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, 64);
+  }
+  if ((threadIdx.x & 15) == 0 && f < (H + 15) / 16 * 16) ssq[(size_t)(f >> 4) * rows_pad + row] = s;
+}
+
+// ----------------------------------------------------------------------------
+// out^T[N, rows] = W[N, K] X[rows, K]^T on fragment-order operands, features on the MFMA M axis:
+// lane l of a 16 x 16 block holds features 4 (l / 16) .. + 3 of token l % 16 in its four registers.
+//
+// A wave owns WM x WN blocks and takes both operands from L2 straight into registers, U tiles of K
+// ahead of their use; FW x TW waves of a workgroup lie side by side, KW waves share the K loop and
+// meet in LDS, in wave order.  No LDS on the operand path: a float contraction spends 32 cycles of
+// the matrix pipe on every 256 bytes (128-wide wave tiles: 16 bytes per clock and CU), far below
+// what L1 delivers, and a decode step reads every weight tile once anyway.
+//   <1, 1, 1, 1, 8>  up to 16 tokens: a decode step, latency- and weight-bound; 8 waves share K
+//   <1, 2, 1, 1, 8>  up to 32 tokens
+//   <2, 2, 1, 1, 4>  prompts that leave the wide form's grid short of the chip
+//   <4, 4, 2, 2, 1>  long prompts: 128 x 128 per workgroup
+// ----------------------------------------------------------------------------
+template <typename T> struct GemmArgs {
+  PlainGemm<T> g;
+  int tiles;      // tiles along K
+  int ft, tt;     // 16-row tiles of features, of tokens
+  int out_tiles;  // tiles along K of the output matrix in fragment order
+  float inv_K;
+};
+
+template <typename T, int EPI, int WM, int WN, int FW, int TW, int KW>
+__global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a) {
+  constexpr int U = WM * WN >= 16 ? 2 : WM * WN >= 4 ? 2 : 4;
+  constexpr int E = plain_chunk<T>();
+  const PlainGemm<T> &g = a.g;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int kw = wave % KW, fw = wave / KW % FW, tw = wave / KW / FW;
+  const int f_groups = (a.ft + WM * FW - 1) / (WM * FW);
+  const int ft0 = ((int)(blockIdx.x % f_groups) * FW + fw) * WM, tt0 = ((int)(blockIdx.x / f_groups) * TW + tw) * WN;
+
+  f32x4 acc[WM][WN];
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // tiles past the edge reread the last one; what they give is not stored
+  const u32x4 *wp[WM], *xp[WN];
+#pragma unroll
+  for (int i = 0; i < WM; ++i) wp[i] = (const u32x4 *)g.W + (size_t)min(ft0 + i, a.ft - 1) * a.tiles * 64 + lane;
+#pragma unroll
+  for (int j = 0; j < WN; ++j) xp[j] = (const u32x4 *)g.X + (size_t)min(tt0 + j, a.tt - 1) * a.tiles * 64 + lane;
+  u32x4 wf[2][U][WM], xf[2][U][WN];
+  // this wave's tiles are kw, kw + KW, ...; a group past the end rereads the last tile against zeros
+  auto load = [&](u32x4 (&w)[U][WM], u32x4 (&x)[U][WN], int t0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = t0 + u * KW, at = min(t, a.tiles - 1) * 64;
+#pragma unroll
+      for (int i = 0; i < WM; ++i) w[u][i] = wp[i][at];
+#pragma unroll
+      for (int j = 0; j < WN; ++j) x[u][j] = xp[j][at];
+      if (t >= a.tiles) {
+#pragma unroll
+        for (int i = 0; i < WM; ++i) w[u][i] = u32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < WN; ++j) x[u][j] = u32x4{0, 0, 0, 0};
+      }
+    }
+  };
+  auto use = [&](u32x4 (&w)[U][WM], u32x4 (&x)[U][WN]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) acc[i][j] = mma<T>(w[u][i], x[u][j], acc[i][j]);
+  };
+  constexpr int kStep = U * KW;
+  load(wf[0], xf[0], kw);
+  // sums of squares behind the RMS Norm factor of this wave's tokens: requested under the K loop
+  float rs[WN];
+#pragma unroll
+  for (int j = 0; j < WN; ++j) rs[j] = 0.f;
+  for (int t = kw; t < a.tiles; t += 2 * kStep) {
+    load(wf[1], xf[1], t + kStep);
+    use(wf[0], xf[0]);
+    load(wf[0], xf[0], t + 2 * kStep);
+    use(wf[1], xf[1]);
+  }
+
+  const int tl = lane & 15, q4 = (lane >> 4) * 4;
+  if (EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU) {
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      const int tok = min(tt0 + j, a.tt - 1) * 16 + tl;
+      float s0 = 0.f, s1 = 0.f;  // parts of four lane groups, two chains
+      int p = lane >> 4;
+      for (; p + 4 < g.ssq_parts; p += 8) {
+        s0 += g.ssq_in[(size_t)p * g.rows_pad + tok];
+        s1 += g.ssq_in[(size_t)(p + 4) * g.rows_pad + tok];
+      }
+      if (p < g.ssq_parts) s0 += g.ssq_in[(size_t)p * g.rows_pad + tok];
+      float s = s0 + s1;
+      s += __shfl_xor(s, 16, 64);
+      s += __shfl_xor(s, 32, 64);
+      rs[j] = 1.0f / sqrtf(s * a.inv_K + g.eps);
+    }
+  }
+
+  if constexpr (KW > 1) {
+    __shared__ f32x4 red[KW][FW * TW][WM * WN][64];
+    const int slot = fw + FW * tw;
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) red[kw][slot][i * WN + j][lane] = acc[i][j];
     __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-      for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        if ((i * WN + j) % KW != kw) continue;  // block b is finished by wave b % KW
+        f32x4 s = red[0][slot][i * WN + j][lane];
+#pragma unroll
+        for (int w = 1; w < KW; ++w) s += red[w][slot][i * WN + j][lane];
+        acc[i][j] = s;
+      }
   }
-  for (int i = 0; i < 4; ++i) {
-    int gm = m0 + ty * 4 + i;
-    if (gm >= M) continue;
-    for (int j = 0; j < 4; ++j) {
-      int gn = n0 + tx * 4 + j;
-      if (gn >= N) continue;
-      OutT *c = C + (size_t)gm * N + gn;
-      float v = acc[i][j];
-      if (accumulate) v += load_f32(c);
-      store_f32(c, v);
+
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      if (KW > 1 && (i * WN + j) % KW != kw) continue;
+      const int ft = ft0 + i, tok = (tt0 + j) * 16 + tl, f0 = ft * 16 + q4;
+      if (ft >= a.ft || tt0 + j >= a.tt) continue;  // uniform over the wave
+      const bool live = tok < g.rows;
+      if (EPI == PLAIN_QKV) {
+        if (!live || f0 >= g.N) continue;
+        const int d = g.dm.d, half = d >> 1, qk = g.dm.qd + g.dm.kvd;
+        const int req = g.tok_req[tok], pos = g.tok_pos[tok];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int r = f0 + 2 * h;  // a pair of packed rows: every boundary between heads and matrices is even
+          if (r >= g.N) break;
+          float v0 = acc[i][j][2 * h] * rs[j], v1 = acc[i][j][2 * h + 1] * rs[j];
+          if (r < qk) {
+            const int head = r / d, e = (r % d) >> 1;
+            const float c = g.cos_tab[(size_t)pos * half + e], s = g.sin_tab[(size_t)pos * half + e];
+            const float lo = v0 * c - v1 * s, hi = v1 * c + v0 * s;
+            if (head < g.dm.nq) {
+              T *dst = g.q + ((size_t)tok * g.dm.nq + head) * g.q_ld;
+              store_f32(dst + e, lo);
+              store_f32(dst + e + half, hi);
+            } else {
+              const int tk = plain_tiles(d, sizeof(T));
+              T *dst = g.Kc + ((size_t)req * g.dm.nkv + head - g.dm.nq) * g.cache.k_elems(sizeof(T));
+              store_f32(dst + plain_offset<T>(pos, e, tk), lo);
+              store_f32(dst + plain_offset<T>(pos, e + half, tk), hi);
+            }
+          } else {
+            const int head = (r - qk) / d, e = (r - qk) % d;
+            T *dst = g.Vc + ((size_t)req * g.dm.nkv + head) * g.cache.v_elems();
+            store_f32(dst + g.cache.v_offset(pos, e), v0);
+            store_f32(dst + g.cache.v_offset(pos, e + 1), v1);
+          }
+        }
+      } else if (EPI == PLAIN_SWIGLU) {
+        if (!live || f0 >= g.N) continue;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (f0 + 2 * h >= g.N) break;
+          const float gt = acc[i][j][2 * h] * rs[j], up = acc[i][j][2 * h + 1] * rs[j];
+          store_f32(g.m + plain_offset<T>(tok, (f0 >> 1) + h, a.out_tiles), gt / (1.0f + expf(-gt)) * up);
+        }
+      } else {
+        const int n = min(4, g.N - f0);
+        const bool vec = g.N % 4 == 0;
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+        if (live && n > 0) {
+          float *xr = g.xres + (size_t)tok * g.N + f0;
+          if (vec) {
+            const f32x4 old = *(const f32x4 *)xr;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = old[e] + acc[i][j][e];
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (e < n) x[e] = xr[e] + acc[i][j][e];
+          }
+          if (EPI == PLAIN_RESID) {
+            put4(xr, x, n, vec);
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = e < n ? x[e] * load_f32(g.gain + f0 + e) : 0.f;
+            put4(g.y + plain_offset<T>(tok, f0, a.out_tiles), y, n, true);
+          } else {
+            put4(g.hidden_out + (size_t)tok * g.N + f0, x, n, false);
+          }
+        }
+        if (EPI == PLAIN_RESID) {
+          float s;
+          {
+#pragma clang fp contract(off)
+            s = (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
+          }
+          s += __shfl_xor(s, 16, 64);
+          s += __shfl_xor(s, 32, 64);
+          if (lane < 16 && live) g.ssq_out[(size_t)ft * g.rows_pad + tok] = s;
+        }
+      }
     }
-  }
+  if (EPI == PLAIN_FINAL && g.lens_advance && blockIdx.x == 0)
+    for (int b = threadIdx.x; b < g.rows; b += FW * TW * KW * 64) g.lens_advance[b] += 1;
 }
 
-// one block per token: rotate q heads in place, rotate k heads into the cache,
-// copy v heads into the cache
-template <typename T>
-__global__ void __launch_bounds__(256) k_rope_cache(T *__restrict__ qkv,
-                                                    const int *__restrict__ tok_req,
-                                                    const int *__restrict__ tok_pos,
-                                                    const float *__restrict__ cos_tab,
-                                                    const float *__restrict__ sin_tab,
-                                                    T *__restrict__ Kc, T *__restrict__ Vc, Dims dm) {
-  int t = blockIdx.x;
-  int req = tok_req[t], pos = tok_pos[t];
-  int half = dm.d / 2;
-  int ld = dm.qd + 2 * dm.kvd;
-  T *row = qkv + (size_t)t * ld;
-  const float *ct = cos_tab + (size_t)pos * half, *st = sin_tab + (size_t)pos * half;
-  for (int e = threadIdx.x; e < dm.nq * half; e += 256) {
-    int h = e / half, i = e % half;
-    T *p = row + h * dm.d;
-    float a = load_f32(p + i), b = load_f32(p + i + half);
-    float c = ct[i], s = st[i];
-    store_f32(p + i, a * c - b * s);
-    store_f32(p + i + half, b * c + a * s);
-  }
-  for (int e = threadIdx.x; e < dm.nkv * half; e += 256) {
-    int h = e / half, i = e % half;
-    const T *p = row + dm.qd + h * dm.d;
-    T *kdst = Kc + (((size_t)req * dm.nkv + h) * dm.max_seq + pos) * dm.d;
-    float a = load_f32(p + i), b = load_f32(p + i + half);
-    float c = ct[i], s = st[i];
-    store_f32(kdst + i, a * c - b * s);
-    store_f32(kdst + i + half, b * c + a * s);
-  }
-  for (int e = threadIdx.x; e < dm.kvd; e += 256) {
-    int h = e / dm.d, i = e % dm.d;
-    Vc[(((size_t)req * dm.nkv + h) * dm.max_seq + pos) * dm.d + i] = row[dm.qd + dm.kvd + e];
-  }
+// ----------------------------------------------------------------------------
+// Attention over the cache.  A workgroup owns 16 query columns - 16 consecutive prompt tokens of
+// one head, or the query heads of one KV head for a single new token - and its KW waves take the
+// 16-key blocks in turn.  S^T = K q^T (keys on the M axis: a lane holds four keys of one query),
+// online softmax in fp32, O^T += V^T P^T with fp32 probabilities against fp32 products for either
+// storage type; the waves' (max, sum, output) meet in LDS in wave order.
+// ----------------------------------------------------------------------------
+template <typename T> struct AttnArgs {
+  const T *q, *Kc, *Vc;
+  T *out;
+  const PlainTile *tiles;
+  const int *lens;
+  PlainCache cache;
+  int nq, G, q_ld, out_tiles;
+  float scale;
+};
+
+template <typename T> __device__ __forceinline__ f32x4 load_v4(const T *p);
+template <> __device__ __forceinline__ f32x4 load_v4<float>(const float *p) { return *(const f32x4 *)p; }
+template <> __device__ __forceinline__ f32x4 load_v4<bf16_t>(const bf16_t *p) {
+  const uint2 u = *(const uint2 *)p;
+  return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
 }
 
-// one wave per (token, query head); keys in chunks of kChunk with a running
-// (max, sum, accumulator) so that any context length fits
-constexpr int kChunk = 1024;
-constexpr int kMaxDimPerLane = 4;  // head_dim <= 256
-
-template <typename T>
-__global__ void __launch_bounds__(64) k_attention(const T *__restrict__ qkv,
-                                                  const int *__restrict__ tok_req,
-                                                  const int *__restrict__ tok_pos,
-                                                  const T *__restrict__ Kc, const T *__restrict__ Vc,
-                                                  T *__restrict__ out, Dims dm) {
-  __shared__ float q_s[256];
-  __shared__ float sc[kChunk];
-  int t = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-  int req = tok_req[t], nkeys = tok_pos[t] + 1;
-  int kh = h / (dm.nq / dm.nkv);
-  int ld = dm.qd + 2 * dm.kvd;
-  float scale = 1.0f / sqrtf((float)dm.d);
-  for (int i = lane; i < dm.d; i += 64) q_s[i] = load_f32(qkv + (size_t)t * ld + h * dm.d + i);
-  __syncthreads();
-  const T *Kh = Kc + ((size_t)req * dm.nkv + kh) * dm.max_seq * dm.d;
-  const T *Vh = Vc + ((size_t)req * dm.nkv + kh) * dm.max_seq * dm.d;
+// NF: 16-feature blocks the registers hold, a multiple of what d needs
+template <typename T, int NF, int KW, bool DECODE>
+__global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
+  constexpr int NC = NF * (int)sizeof(T) / 4;  // K tiles: 16 floats or 32 bf16 each
+  extern __shared__ __attribute__((aligned(16))) f32x4 o_s[];  // [KW][nf][64]
+  __shared__ float m_s[KW][16], l_s[KW][16];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, tl = lane & 15, g4 = (lane >> 4) * 4;
+  const int d = a.cache.d, nf = (d + 15) / 16, nc = plain_tiles(d, sizeof(T));
+  int req, kvh, row, head, qpos, last;
+  bool live;
+  if (DECODE) {
+    req = blockIdx.x; kvh = blockIdx.y;
+    const int c = blockIdx.z * 16 + tl;
+    live = c < a.G;
+    head = kvh * a.G + min(c, a.G - 1);
+    row = req;
+    qpos = last = a.lens[req];
+  } else {
+    const PlainTile t = a.tiles[blockIdx.x];
+    head = blockIdx.y;
+    kvh = head / a.G; req = t.req;
+    live = tl < t.n;
+    row = t.row0 + min(tl, t.n - 1);
+    qpos = t.pos0 + min(tl, t.n - 1);
+    last = t.pos0 + t.n - 1;
+  }
+  const u32x4 *kp = (const u32x4 *)(a.Kc + ((size_t)req * a.cache.nkv + kvh) * a.cache.k_elems(sizeof(T))) + lane;
+  const T *vp = a.Vc + ((size_t)req * a.cache.nkv + kvh) * a.cache.v_elems() + lane * 4;
+  const u32x4 *qp = (const u32x4 *)(a.q + ((size_t)row * a.nq + head) * a.q_ld) + (lane >> 4);
+  u32x4 qf[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    if (c < nc) qf[c] = qp[c * 4];
+  f32x4 o[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) o[f] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
-  float acc[kMaxDimPerLane] = {0.f, 0.f, 0.f, 0.f};
-  for (int c0 = 0; c0 < nkeys; c0 += kChunk) {
-    int n = min(kChunk, nkeys - c0);
-    float lmax = -INFINITY;
-    for (int j = lane; j < n; j += 64) {
-      const T *kr = Kh + (size_t)(c0 + j) * dm.d;
-      float s = 0.f;
-      for (int i = 0; i < dm.d; ++i) s = fmaf(q_s[i], load_f32(kr + i), s);
-      s *= scale;
-      sc[j] = s;
-      lmax = fmaxf(lmax, s);
+  const int n_kb = (last >> 4) + 1;
+  for (int kb = wave; kb < n_kb; kb += KW) {
+    u32x4 kf[NC];
+    f32x4 vf[NF];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (c < nc) kf[c] = kp[((size_t)kb * nc + c) * 64];
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+      if (f < nf) vf[f] = load_v4<T>(vp + ((size_t)kb * nf + f) * 256);
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (c < nc) s = mma<T>(kf[c], qf[c], s);
+    const bool edge = kb == n_kb - 1;  // the only block with keys some query must not see
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[i] *= a.scale;
+      if (edge && kb * 16 + g4 + i > qpos) s[i] = -INFINITY;
+      mx = fmaxf(mx, s[i]);
     }
-    float m_new = fmaxf(m_run, wave_max(lmax));
-    float lsum = 0.f;
-    for (int j = lane; j < n; j += 64) {
-      float p = expf(sc[j] - m_new);
-      sc[j] = p;
-      lsum += p;
-    }
-    lsum = wave_sum(lsum);
-    float corr = (m_run == -INFINITY) ? 0.f : expf(m_run - m_new);
-    l_run = l_run * corr + lsum;
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);
+    const float ref = m_new == -INFINITY ? 0.f : m_new;  // nothing visible yet
+    const float corr = expf(m_run - ref);
+    float p[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = expf(s[i] - ref);
+    l_run = l_run * corr + ((p[0] + p[1]) + (p[2] + p[3]));
     m_run = m_new;
-    __syncthreads();
-    for (int c = 0; c < kMaxDimPerLane; ++c) {
-      int dim = lane + 64 * c;
-      if (dim >= dm.d) break;
-      float a = acc[c] * corr;
-      for (int j = 0; j < n; ++j) a = fmaf(sc[j], load_f32(Vh + (size_t)(c0 + j) * dm.d + dim), a);
-      acc[c] = a;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) o[f] *= corr;
+    bool shared = true;
+    if (edge) {
+      // slots past the last cached key hold anything: no product may meet them
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (f < nf && kb * 16 + g4 + i > last) vf[f][i] = 0.f;
+      if (!DECODE) {
+        // a value that is not finite must not reach the queries in front of it (0 * inf): such a
+        // block - no ordinary one - is added key by key
+        bool odd = false;
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) odd |= f < nf && !(fabsf(vf[f][i]) < INFINITY);
+        shared = !__any(odd);
+        if (!shared) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const float pj = __shfl(p[j & 3], (j >> 2) * 16 + tl, 64);
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+              if (f < nf)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                  const float v = __shfl(vf[f][j & 3], (j >> 2) * 16 + g4 + i, 64);
+                  if (kb * 16 + j <= qpos) o[f][i] = fmaf(pj, v, o[f][i]);
+                }
+          }
+        }
+      }
     }
-    __syncthreads();
+    if (shared)
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+        if (f < nf)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[f][i], p[i], o[f], 0, 0, 0);
   }
-  for (int c = 0; c < kMaxDimPerLane; ++c) {
-    int dim = lane + 64 * c;
-    if (dim >= dm.d) break;
-    store_f32(out + (size_t)t * dm.qd + h * dm.d + dim, acc[c] / l_run);
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (lane < 16) { m_s[wave][tl] = m_run; l_s[wave][tl] = l_run; }
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+    if (f < nf) o_s[(wave * nf + f) * 64 + lane] = o[f];
+  __syncthreads();
+  float m = m_s[0][tl];
+#pragma unroll
+  for (int w = 1; w < KW; ++w) m = fmaxf(m, m_s[w][tl]);
+  float wgt[KW], l = 0.f;
+#pragma unroll
+  for (int w = 0; w < KW; ++w) {
+    wgt[w] = m_s[w][tl] == -INFINITY ? 0.f : expf(m_s[w][tl] - m);
+    l += wgt[w] * l_s[w][tl];
+  }
+  for (int f = wave; f < nf; f += KW) {
+    f32x4 r = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < KW; ++w)
+      if (w < n_kb) r += o_s[(w * nf + f) * 64 + lane] * wgt[w];
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = r[i] / l;
+    const int f0 = f * 16 + g4, n = min(4, d - f0), k = head * d + f0;
+    if (!live || n <= 0) continue;
+    if (d % 4 == 0) put4(a.out + plain_offset<T>(row, k, a.out_tiles), v, n, true);
+    else
+      for (int i = 0; i < n; ++i) store_f32(a.out + plain_offset<T>(row, k + i, a.out_tiles), v[i]);
   }
 }
 
 template <typename T>
-__global__ void k_swiglu(const T *__restrict__ gu, T *__restrict__ m, int rows, int I) {
-  size_t n = (size_t)rows * I;
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) {
-    size_t r = i / I, c = i % I;
-    float g = load_f32(gu + r * 2 * I + c), u = load_f32(gu + r * 2 * I + I + c);
-    store_f32(m + i, g / (1.0f + expf(-g)) * u);
+__global__ void k_plain_export_kv(const T *__restrict__ Kc, const T *__restrict__ Vc, T *__restrict__ k_out,
+                                  T *__restrict__ v_out, int request, int len, PlainCache c) {
+  const int kvd = c.nkv * c.d, tk = plain_tiles(c.d, sizeof(T));
+  const size_t n = (size_t)len * kvd, stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const int pos = (int)(i / kvd), e = (int)(i % kvd), h = e / c.d, f = e % c.d;
+    const size_t rh = (size_t)request * c.nkv + h;
+    k_out[i] = Kc[rh * c.k_elems(sizeof(T)) + plain_offset<T>(pos, f, tk)];
+    v_out[i] = Vc[rh * c.v_elems() + c.v_offset(pos, f)];
   }
 }
 
-__global__ void k_advance_lens(int *lens, int batch) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < batch) lens[i] += 1;
-}
-
-template <typename T>
-__global__ void k_export_kv(const T *__restrict__ Kc, const T *__restrict__ Vc, T *__restrict__ k_out,
-                            T *__restrict__ v_out, int request, int len, Dims dm) {
-  size_t n = (size_t)len * dm.kvd;
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) {
-    int pos = (int)(i / dm.kvd), e = (int)(i % dm.kvd);
-    int h = e / dm.d, dd = e % dm.d;
-    size_t src = (((size_t)request * dm.nkv + h) * dm.max_seq + pos) * dm.d + dd;
-    k_out[i] = Kc[src];
-    v_out[i] = Vc[src];
-  }
+__global__ void k_plain_fill_zero(uint4 *p, size_t n16) {
+  const size_t stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += stride) p[i] = uint4{0, 0, 0, 0};
 }
 
 inline int grid_for(size_t n, int block) {
@@ -237,83 +507,132 @@ inline int grid_for(size_t n, int block) {
 }  // namespace
 
 template <typename T>
-hipError_t plain_load_hidden(const T *in, float *xres, size_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_load_hidden<T><<<grid_for(n, 256), 256, 0, s>>>(in, xres, n);
-  return hipGetLastError();
-}
-template <typename T>
-hipError_t plain_store_hidden(const float *xres, T *out, size_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_store_hidden<T><<<grid_for(n, 256), 256, 0, s>>>(xres, out, n);
-  return hipGetLastError();
-}
-template <typename T>
-hipError_t plain_rmsnorm(const float *xres, const T *g, T *y, int rows, int H, float eps,
-                         hipStream_t s) {
-  if (rows == 0) return hipSuccess;
-  k_rmsnorm<T><<<rows, 256, 0, s>>>(xres, g, y, H, eps);
-  return hipGetLastError();
-}
-template <typename T, typename OutT>
-hipError_t plain_gemm_nt(const T *A, const T *B, OutT *C, int M, int N, int K, bool accumulate,
-                         hipStream_t s) {
-  if (M == 0 || N == 0) return hipSuccess;
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  k_gemm_nt<T, OutT><<<grid, 256, 0, s>>>(A, B, C, M, N, K, accumulate ? 1 : 0);
-  return hipGetLastError();
-}
-template <typename T>
-hipError_t plain_rope_cache(T *qkv, const int *tok_req, const int *tok_pos, const float *cos_tab,
-                            const float *sin_tab, T *Kc, T *Vc, int rows, const Dims &dm,
-                            hipStream_t s) {
-  if (rows == 0) return hipSuccess;
-  k_rope_cache<T><<<rows, 256, 0, s>>>(qkv, tok_req, tok_pos, cos_tab, sin_tab, Kc, Vc, dm);
-  return hipGetLastError();
-}
-template <typename T>
-hipError_t plain_attention(const T *qkv, const int *tok_req, const int *tok_pos, const T *Kc,
-                           const T *Vc, T *out, int rows, const Dims &dm, hipStream_t s) {
-  if (rows == 0) return hipSuccess;
-  // grid.x carries the token index (up to 2^31-1), grid.y the head
-  k_attention<T><<<dim3(rows, dm.nq), 64, 0, s>>>(qkv, tok_req, tok_pos, Kc, Vc, out, dm);
-  return hipGetLastError();
-}
-template <typename T>
-hipError_t plain_swiglu(const T *gu, T *m, int rows, int I, hipStream_t s) {
-  if (rows == 0) return hipSuccess;
-  k_swiglu<T><<<grid_for((size_t)rows * I, 256), 256, 0, s>>>(gu, m, rows, I);
-  return hipGetLastError();
-}
-hipError_t advance_lens(int *lens, int batch, hipStream_t s) {
-  k_advance_lens<<<(batch + 63) / 64, 64, 0, s>>>(lens, batch);
-  return hipGetLastError();
-}
-template <typename T>
-hipError_t plain_export_kv(const T *Kc, const T *Vc, T *k_out, T *v_out, int request, int len,
-                           const Dims &dm, hipStream_t s) {
-  if (len == 0) return hipSuccess;
-  k_export_kv<T><<<grid_for((size_t)len * dm.kvd, 256), 256, 0, s>>>(Kc, Vc, k_out, v_out, request,
-                                                                    len, dm);
+hipError_t plain_pack_weight(const T *src0, const T *src1, const T *src2, int rows0, int rows1, T *dst, int N, int K,
+                             int mode, int head_dim, int qk_rows, hipStream_t s) {
+  const int tiles = plain_tiles(K, sizeof(T));
+  const size_t chunks = (size_t)((N + 15) / 16) * tiles * 64;
+  k_plain_pack<T><<<grid_for(chunks, 256), 256, 0, s>>>(src0, src1, src2, rows0, rows1, dst, N, K, tiles, mode, head_dim, qk_rows, chunks);
   return hipGetLastError();
 }
 
-#define HYP_INSTANTIATE(T)                                                                          \
-  template hipError_t plain_load_hidden<T>(const T *, float *, size_t, hipStream_t);                \
-  template hipError_t plain_store_hidden<T>(const float *, T *, size_t, hipStream_t);               \
-  template hipError_t plain_rmsnorm<T>(const float *, const T *, T *, int, int, float, hipStream_t); \
-  template hipError_t plain_gemm_nt<T, T>(const T *, const T *, T *, int, int, int, bool,           \
-                                          hipStream_t);                                             \
-  template hipError_t plain_rope_cache<T>(T *, const int *, const int *, const float *,             \
-                                          const float *, T *, T *, int, const Dims &, hipStream_t); \
-  template hipError_t plain_attention<T>(const T *, const int *, const int *, const T *, const T *, \
-                                         T *, int, const Dims &, hipStream_t);                      \
-  template hipError_t plain_swiglu<T>(const T *, T *, int, int, hipStream_t);                       \
-  template hipError_t plain_export_kv<T>(const T *, const T *, T *, T *, int, int, const Dims &,    \
-                                         hipStream_t);
+template <typename T>
+hipError_t plain_begin(const T *hidden_in, float *xres, const T *gain, T *y, float *ssq_out, int rows, int rows_pad, int H,
+                       hipStream_t s) {
+  if (rows == 0) return hipSuccess;
+  // grid.x carries the row (up to 2^31 - 1)
+  k_plain_begin<T><<<dim3(rows, (H + 255) / 256), 256, 0, s>>>(hidden_in, xres, gain, y, ssq_out, H, rows_pad, plain_tiles(H, sizeof(T)));
+  return hipGetLastError();
+}
+
+template <typename T, int EPI>
+static hipError_t launch_gemm(const PlainGemm<T> &g, hipStream_t s) {
+  GemmArgs<T> a;
+  a.g = g;
+  a.tiles = plain_tiles(g.K, sizeof(T));
+  a.ft = (g.N + 15) / 16; a.tt = (g.rows + 15) / 16;
+  a.out_tiles = plain_tiles(EPI == PLAIN_SWIGLU ? g.N / 2 : g.N, sizeof(T));
+  a.inv_K = 1.0f / (float)g.K;
+  auto groups = [](int n, int per) { return (unsigned)((n + per - 1) / per); };
+  // The widest form whose workgroups still fill the chip twice over; below that latency counts, and
+  // more, smaller workgroups with their K loop shared by the waves win.
+  const size_t wide = (size_t)groups(a.ft, 8) * groups(a.tt, 8);
+  if (a.tt == 1) k_plain_gemm<T, EPI, 1, 1, 1, 1, 8><<<a.ft, 512, 0, s>>>(a);
+  else if (a.tt == 2) k_plain_gemm<T, EPI, 1, 2, 1, 1, 8><<<a.ft, 512, 0, s>>>(a);
+  else if (wide >= 512) k_plain_gemm<T, EPI, 4, 4, 2, 2, 1><<<groups(a.ft, 8) * groups(a.tt, 8), 256, 0, s>>>(a);
+  else k_plain_gemm<T, EPI, 2, 2, 1, 1, 4><<<groups(a.ft, 2) * groups(a.tt, 2), 256, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+template <typename T> hipError_t plain_gemm(int epi, const PlainGemm<T> &g, hipStream_t s) {
+  if (g.rows == 0) return hipSuccess;
+  switch (epi) {
+    case PLAIN_QKV: return launch_gemm<T, PLAIN_QKV>(g, s);
+    case PLAIN_SWIGLU: return launch_gemm<T, PLAIN_SWIGLU>(g, s);
+    case PLAIN_RESID: return launch_gemm<T, PLAIN_RESID>(g, s);
+    case PLAIN_FINAL: return launch_gemm<T, PLAIN_FINAL>(g, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+// (register blocks, waves): enough for d features; the waves' outputs pass 64 KiB of LDS at 8 waves of 128 features and more
+#define HYP_PLAIN_ATTN(X) X(4, 8) X(8, 8) X(16, 4)
+
+template <typename T, bool DECODE>
+static hipError_t launch_attn(const AttnArgs<T> &a, dim3 grid, hipStream_t s) {
+  const int nf = (a.cache.d + 15) / 16, nf_tiles = plain_tiles(a.cache.d, sizeof(T)) * 4 / (int)sizeof(T);
+#define X(NF, KW)                                                                              \
+  if (nf_tiles <= NF) {                                                                         \
+    k_plain_attn<T, NF, KW, DECODE><<<grid, KW * 64, (size_t)KW * nf * 1024, s>>>(a);           \
+    return hipGetLastError();                                                                  \
+  }
+  HYP_PLAIN_ATTN(X)
+#undef X
+  return hipErrorInvalidValue;
+}
+
+hipError_t plain_init() {
+  hipError_t e = hipSuccess;
+#define X(NF, KW)                                                                                                              \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<float, NF, KW, false>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);  \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<float, NF, KW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);   \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<bf16_t, NF, KW, false>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024); \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<bf16_t, NF, KW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);
+  HYP_PLAIN_ATTN(X)
+#undef X
+  return e;
+}
+
+template <typename T>
+static AttnArgs<T> attn_args(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const PlainCache &cache, const Dims &dm) {
+  AttnArgs<T> a = {};
+  a.q = q; a.Kc = Kc; a.Vc = Vc; a.out = out; a.cache = cache;
+  a.nq = dm.nq; a.G = dm.nq / dm.nkv; a.q_ld = q_ld; a.out_tiles = plain_tiles(dm.qd, sizeof(T));
+  a.scale = 1.0f / sqrtf((float)dm.d);
+  return a;
+}
+
+template <typename T>
+hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const PlainTile *tiles, int n_tiles,
+                              const PlainCache &cache, const Dims &dm, hipStream_t s) {
+  if (n_tiles == 0) return hipSuccess;
+  AttnArgs<T> a = attn_args<T>(q, q_ld, Kc, Vc, out, cache, dm);
+  a.tiles = tiles;
+  return launch_attn<T, false>(a, dim3(n_tiles, dm.nq), s);
+}
+
+template <typename T>
+hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch,
+                             const PlainCache &cache, const Dims &dm, hipStream_t s) {
+  if (batch == 0) return hipSuccess;
+  AttnArgs<T> a = attn_args<T>(q, q_ld, Kc, Vc, out, cache, dm);
+  a.lens = lens;
+  return launch_attn<T, true>(a, dim3(batch, dm.nkv, (a.G + 15) / 16), s);
+}
+
+template <typename T>
+hipError_t plain_export_kv(const T *Kc, const T *Vc, T *k_out, T *v_out, int request, int len,
+                           const PlainCache &cache, hipStream_t s) {
+  if (len == 0) return hipSuccess;
+  k_plain_export_kv<T><<<grid_for((size_t)len * cache.nkv * cache.d, 256), 256, 0, s>>>(Kc, Vc, k_out, v_out, request, len, cache);
+  return hipGetLastError();
+}
+
+hipError_t plain_fill_zero(void *p, size_t bytes, hipStream_t s) {
+  const size_t n16 = bytes / 16;
+  if (n16) k_plain_fill_zero<<<grid_for(n16, 256), 256, 0, s>>>((uint4 *)p, n16);
+  return hipGetLastError();
+}
+
+#define HYP_INSTANTIATE(T)                                                                                                   \
+  template hipError_t plain_pack_weight<T>(const T *, const T *, const T *, int, int, T *, int, int, int, int, int, hipStream_t); \
+  template hipError_t plain_begin<T>(const T *, float *, const T *, T *, float *, int, int, int, hipStream_t);               \
+  template hipError_t plain_gemm<T>(int, const PlainGemm<T> &, hipStream_t);                                                 \
+  template hipError_t plain_attn_prefill<T>(const T *, int, const T *, const T *, T *, const PlainTile *, int,               \
+                                            const PlainCache &, const Dims &, hipStream_t);                                  \
+  template hipError_t plain_attn_decode<T>(const T *, int, const T *, const T *, T *, const int *, int, const PlainCache &,  \
+                                           const Dims &, hipStream_t);                                                       \
+  template hipError_t plain_export_kv<T>(const T *, const T *, T *, T *, int, int, const PlainCache &, hipStream_t);
 HYP_INSTANTIATE(float)
 HYP_INSTANTIATE(bf16_t)
-template hipError_t plain_gemm_nt<bf16_t, float>(const bf16_t *, const bf16_t *, float *, int, int,
-                                                 int, bool, hipStream_t);
 
 }  // namespace hyp

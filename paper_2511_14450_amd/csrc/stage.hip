@@ -60,13 +60,17 @@ struct LayerPtrs {
 // Where everything lives inside the caller's workspace.
 struct Layout {
   std::vector<LayerPtrs> layers;
-  size_t Kc = 0, Vc = 0, kv_layer_stride = 0;  // per-layer stride in bytes
+  size_t Kc = 0, Vc = 0, kv_layer_stride = 0;  // per-layer stride in bytes (plain path: of Kc)
   size_t cos_tab = 0, sin_tab = 0;
-  size_t xres = 0, y = 0, qkv = 0, attn = 0, gu = 0, m = 0;
+  size_t xres = 0, y = 0, attn = 0, m = 0, tiles = 0, ssq = 0;
   size_t tok_req = 0, tok_pos = 0, lens = 0, iota = 0;
+  // plain path only: stride of Vc, row length of a query head, rows in whole 16-row tiles, end of the padded activations
+  size_t v_layer_stride = 0, act_end = 0;
+  int q_ld = 0, rows_pad = 0;
+  PlainCache cache = {};
   // MFMA path only
-  size_t q = 0, delta = 0, row_ext = 0, row_pos = 0, row_req = 0, tiles = 0, req_len = 0, row_ext_dec = 0, qdec = 0,
-         partial = 0, attn_part = 0, counters = 0, gemm_counters = 0, ssq = 0, rstd = 0, ssq_part = 0, gemm_ws = 0;
+  size_t q = 0, delta = 0, row_ext = 0, row_pos = 0, row_req = 0, req_len = 0, row_ext_dec = 0, qdec = 0,
+         partial = 0, attn_part = 0, counters = 0, gemm_counters = 0, rstd = 0, ssq_part = 0, gemm_ws = 0;
   size_t kv_bytes = 0;  // bytes of each of Kc, Vc over all layers
   int rows_cap = 0;     // internal rows the scratch holds
   int key_blocks = 0;   // 32-key blocks per (request, kv head)
@@ -144,17 +148,22 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
   size_t I = c.ffn_dim, R = (size_t)max_rows(c);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
+  const bool mfma = mfma_applies(c);
+  // bytes of a [rows, K] operand: as it is, or in whole 16-row tiles of 64 bytes of K
+  auto operand = [&](size_t rows, size_t K) {
+    return mfma ? es * rows * K : (rows + 15) / 16 * (size_t)plain_tiles((int)K, (int)es) * 1024;
+  };
   L.layers.resize(n_layers);
   for (int l = 0; l < n_layers; ++l) {
     LayerPtrs &p = L.layers[l];
     p.g1 = take(es * H);
-    p.wqkv = take(es * (qd + 2 * kvd) * H);
-    p.wo = take(es * H * qd);
+    p.wqkv = take(operand(qd + 2 * kvd, H));
+    p.wo = take(operand(H, qd));
     p.g2 = take(es * H);
-    p.wgu = take(es * 2 * I * H);
-    p.wd = take(es * H * I);
+    p.wgu = take(operand(2 * I, H));
+    p.wd = take(operand(H, I));
   }
-  if (mfma_applies(c)) {
+  if (mfma) {
     // every request's rows are padded to a multiple of 64 (one query tile)
     L.rows_cap = round_up((int)c.max_prefill_tokens + 63 * c.max_batch, 64);
     if (L.rows_cap < 64) L.rows_cap = 64;
@@ -211,20 +220,27 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
     L.total = off;
     return;
   }
-  L.kv_layer_stride = align_up(es * (size_t)c.max_batch * kvd * c.max_seq);
+  L.cache.nkv = c.n_kv_heads; L.cache.d = c.head_dim; L.cache.key_blocks = (c.max_seq + 15) / 16;
+  const size_t heads = (size_t)c.max_batch * c.n_kv_heads;
+  L.kv_layer_stride = align_up(es * heads * L.cache.k_elems((int)es));
+  L.v_layer_stride = align_up(es * heads * L.cache.v_elems());
   L.Kc = take(L.kv_layer_stride * n_layers);
-  L.Vc = take(L.kv_layer_stride * n_layers);
+  L.Vc = take(L.v_layer_stride * n_layers);
   size_t tab = sizeof(float) * (size_t)c.max_seq * (c.head_dim / 2);
   L.cos_tab = take(tab);
   L.sin_tab = take(tab);
+  L.rows_pad = (int)((R + 15) / 16 * 16);
+  L.q_ld = plain_tiles(c.head_dim, (int)es) * (64 / (int)es);
   L.xres = take(sizeof(float) * R * H);
-  L.y = take(es * R * H);
-  L.qkv = take(es * R * (qd + 2 * kvd));
-  L.attn = take(es * R * qd);
-  L.gu = take(es * R * 2 * I);
-  L.m = take(es * R * I);
+  L.y = take(operand(R, H));
+  L.q = take(es * R * (size_t)c.n_q_heads * L.q_ld);
+  L.attn = take(operand(R, qd));
+  L.m = take(operand(R, I));
+  L.act_end = off;
+  L.ssq = take(sizeof(float) * (size_t)L.rows_pad * ((H + 15) / 16));
   L.tok_req = take(sizeof(int) * R);
   L.tok_pos = take(sizeof(int) * R);
+  L.tiles = take(sizeof(PlainTile) * (R / 16 + c.max_batch));
   L.lens = take(sizeof(int) * c.max_batch);
   L.iota = take(sizeof(int) * c.max_batch);
   L.total = off;
@@ -316,31 +332,32 @@ hipError_t prof_end(hyp_stage *st, int slot) {
 
 template <typename T> T *at(hyp_stage *st, size_t off) { return reinterpret_cast<T *>(st->ws + off); }
 
-// Copy the caller's matrices into the workspace: wq|wk|wv stacked into one
-// [qd+2kvd, H] matrix and gate|up into one [2I, H] matrix.
-hyp_status_t copy_weights(hyp_stage *st, const hyp_layer_weights_t *layers) {
-  size_t es = st->bf16 ? 2 : 4;
+// Plain path: repack every matrix into 16-row fragment order, rows that an epilogue combines side by side.
+template <typename T>
+hyp_status_t pack_weights_plain(hyp_stage *st, const hyp_layer_weights_t *layers) {
   const Dims &d = st->dm;
+  const Layout &L = st->L;
+  hipStream_t s = st->stream;
+  const int N = d.qd + 2 * d.kvd, qk = d.qd + d.kvd;
   for (int l = 0; l < st->n_layers; ++l) {
     const hyp_layer_weights_t &w = layers[l];
     const void *ptrs[] = {w.attn_norm_g, w.wq, w.wk, w.wv, w.wo, w.ffn_norm_g, w.w_gate, w.w_up, w.w_down};
     for (const void *p : ptrs)
       if (!p) return fail(st, HYP_EINVAL, "a weight pointer of layer " + std::to_string(l) + " is NULL");
-    const LayerPtrs &p = st->L.layers[l];
-    auto cp = [&](size_t dst, const void *src, size_t bytes) {
-      return hipMemcpyAsync(st->ws + dst, src, bytes, hipMemcpyDeviceToDevice, st->stream);
-    };
-    size_t H = d.H;
-    HIP_TRY(st, cp(p.g1, w.attn_norm_g, es * H));
-    HIP_TRY(st, cp(p.wqkv, w.wq, es * d.qd * H));
-    HIP_TRY(st, cp(p.wqkv + es * d.qd * H, w.wk, es * d.kvd * H));
-    HIP_TRY(st, cp(p.wqkv + es * (d.qd + d.kvd) * H, w.wv, es * d.kvd * H));
-    HIP_TRY(st, cp(p.wo, w.wo, es * H * d.qd));
-    HIP_TRY(st, cp(p.g2, w.ffn_norm_g, es * H));
-    HIP_TRY(st, cp(p.wgu, w.w_gate, es * (size_t)d.I * H));
-    HIP_TRY(st, cp(p.wgu + es * (size_t)d.I * H, w.w_up, es * (size_t)d.I * H));
-    HIP_TRY(st, cp(p.wd, w.w_down, es * H * (size_t)d.I));
+    const LayerPtrs &p = L.layers[l];
+    HIP_TRY(st, hipMemcpyAsync(st->ws + p.g1, w.attn_norm_g, sizeof(T) * (size_t)d.H, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(st, hipMemcpyAsync(st->ws + p.g2, w.ffn_norm_g, sizeof(T) * (size_t)d.H, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(st, plain_pack_weight<T>((const T *)w.wq, (const T *)w.wk, (const T *)w.wv, d.qd, d.kvd, at<T>(st, p.wqkv), N, d.H,
+                                     PLAIN_PAIRS_QKV, d.d, qk, s));
+    HIP_TRY(st, plain_pack_weight<T>((const T *)w.wo, nullptr, nullptr, d.H, 0, at<T>(st, p.wo), d.H, d.qd, PLAIN_ROWS, d.d, 0, s));
+    HIP_TRY(st, plain_pack_weight<T>((const T *)w.w_gate, (const T *)w.w_up, nullptr, d.I, d.I, at<T>(st, p.wgu), 2 * d.I, d.H,
+                                     PLAIN_PAIRS_GATEUP, d.d, 0, s));
+    HIP_TRY(st, plain_pack_weight<T>((const T *)w.w_down, nullptr, nullptr, d.H, 0, at<T>(st, p.wd), d.H, d.I, PLAIN_ROWS, d.d, 0, s));
   }
+  // the padding along K meets the weights' zeros (queries': the keys' padding) and must be finite; nothing writes it later
+  auto padded = [](int k) { return k * (int)sizeof(T) % 64 != 0; };
+  if (padded(d.H) || padded(d.d) || padded(d.qd) || padded(d.I)) HIP_TRY(st, plain_fill_zero(st->ws + L.y, L.act_end - L.y, s));
+  if (padded(d.d)) HIP_TRY(st, plain_fill_zero(st->ws + L.Kc, L.kv_layer_stride * st->n_layers, s));
   return HYP_OK;
 }
 
@@ -536,32 +553,51 @@ hyp_status_t run_decode_mfma(hyp_stage *st, const void *hidden_in, void *hidden_
   return HYP_OK;
 }
 
-// rows tokens through every block with the shape-generic kernels
+// rows tokens through every block with the shape-generic kernels: a prompt in `n_tiles` query tiles, or
+// (n_tiles == 0) one token of every resident request.  1 + 5 launches per block.
 template <typename T>
-hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, int rows,
-                       const int *tok_req, const int *tok_pos) {
+hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, int rows, int n_tiles) {
   const Dims &d = st->dm;
+  const Layout &L = st->L;
   hipStream_t s = st->stream;
-  float *xres = at<float>(st, st->L.xres);
-  T *y = at<T>(st, st->L.y), *qkv = at<T>(st, st->L.qkv), *attn = at<T>(st, st->L.attn);
-  T *gu = at<T>(st, st->L.gu), *m = at<T>(st, st->L.m);
-  const float *ct = at<float>(st, st->L.cos_tab), *sn = at<float>(st, st->L.sin_tab);
-  HIP_TRY(st, plain_load_hidden<T>((const T *)hidden_in, xres, (size_t)rows * d.H, s));
+  const bool decode = n_tiles == 0;
+  float *xres = at<float>(st, L.xres), *ssq = at<float>(st, L.ssq);
+  T *y = at<T>(st, L.y), *q = at<T>(st, L.q), *attn = at<T>(st, L.attn), *m = at<T>(st, L.m);
+  int *lens = at<int>(st, L.lens);
+  HIP_TRY(st, plain_begin<T>((const T *)hidden_in, xres, at<T>(st, L.layers[0].g1), y, ssq, rows, L.rows_pad, d.H, s));
+  PlainGemm<T> base;
+  base.rows = rows; base.rows_pad = L.rows_pad; base.eps = d.eps; base.dm = d; base.xres = xres;
   for (int l = 0; l < st->n_layers; ++l) {
-    const LayerPtrs &p = st->L.layers[l];
-    T *Kc = at<T>(st, st->L.Kc + st->L.kv_layer_stride * l);
-    T *Vc = at<T>(st, st->L.Vc + st->L.kv_layer_stride * l);
-    HIP_TRY(st, plain_rmsnorm<T>(xres, at<T>(st, p.g1), y, rows, d.H, d.eps, s));
-    HIP_TRY(st, (plain_gemm_nt<T, T>(y, at<T>(st, p.wqkv), qkv, rows, d.qd + 2 * d.kvd, d.H, false, s)));
-    HIP_TRY(st, plain_rope_cache<T>(qkv, tok_req, tok_pos, ct, sn, Kc, Vc, rows, d, s));
-    HIP_TRY(st, plain_attention<T>(qkv, tok_req, tok_pos, Kc, Vc, attn, rows, d, s));
-    HIP_TRY(st, (plain_gemm_nt<T, float>(attn, at<T>(st, p.wo), xres, rows, d.H, d.qd, true, s)));
-    HIP_TRY(st, plain_rmsnorm<T>(xres, at<T>(st, p.g2), y, rows, d.H, d.eps, s));
-    HIP_TRY(st, (plain_gemm_nt<T, T>(y, at<T>(st, p.wgu), gu, rows, 2 * d.I, d.H, false, s)));
-    HIP_TRY(st, plain_swiglu<T>(gu, m, rows, d.I, s));
-    HIP_TRY(st, (plain_gemm_nt<T, float>(m, at<T>(st, p.wd), xres, rows, d.H, d.I, true, s)));
+    const LayerPtrs &p = L.layers[l];
+    T *Kc = at<T>(st, L.Kc + L.kv_layer_stride * l), *Vc = at<T>(st, L.Vc + L.v_layer_stride * l);
+    PlainGemm<T> a = base;
+    a.W = at<T>(st, p.wqkv); a.X = y; a.N = d.qd + 2 * d.kvd; a.K = d.H;
+    a.ssq_in = ssq; a.ssq_parts = (d.H + 15) / 16;
+    a.tok_req = at<int>(st, decode ? L.iota : L.tok_req); a.tok_pos = decode ? lens : at<int>(st, L.tok_pos);
+    a.cos_tab = at<float>(st, L.cos_tab); a.sin_tab = at<float>(st, L.sin_tab);
+    a.q = q; a.q_ld = L.q_ld; a.Kc = Kc; a.Vc = Vc; a.cache = L.cache;
+    HIP_TRY(st, plain_gemm<T>(PLAIN_QKV, a, s));
+    if (decode) HIP_TRY(st, plain_attn_decode<T>(q, L.q_ld, Kc, Vc, attn, lens, rows, L.cache, d, s));
+    else HIP_TRY(st, plain_attn_prefill<T>(q, L.q_ld, Kc, Vc, attn, at<PlainTile>(st, L.tiles), n_tiles, L.cache, d, s));
+    PlainGemm<T> o = base;
+    o.W = at<T>(st, p.wo); o.X = attn; o.N = d.H; o.K = d.qd;
+    o.gain = at<T>(st, p.g2); o.y = y; o.ssq_out = ssq;
+    HIP_TRY(st, plain_gemm<T>(PLAIN_RESID, o, s));
+    PlainGemm<T> g = base;
+    g.W = at<T>(st, p.wgu); g.X = y; g.N = 2 * d.I; g.K = d.H;
+    g.ssq_in = ssq; g.ssq_parts = (d.H + 15) / 16; g.m = m;
+    HIP_TRY(st, plain_gemm<T>(PLAIN_SWIGLU, g, s));
+    PlainGemm<T> w = base;
+    w.W = at<T>(st, p.wd); w.X = m; w.N = d.H; w.K = d.I;
+    if (l + 1 < st->n_layers) {
+      w.gain = at<T>(st, L.layers[l + 1].g1); w.y = y; w.ssq_out = ssq;
+      HIP_TRY(st, plain_gemm<T>(PLAIN_RESID, w, s));
+    } else {
+      w.hidden_out = (T *)hidden_out;
+      if (decode) w.lens_advance = lens;
+      HIP_TRY(st, plain_gemm<T>(PLAIN_FINAL, w, s));
+    }
   }
-  HIP_TRY(st, plain_store_hidden<T>(xres, (T *)hidden_out, (size_t)rows * d.H, s));
   return HYP_OK;
 }
 
@@ -652,7 +688,7 @@ hyp_status_t do_stage_create(const hyp_stage_config_t *cfg, int32_t l_start, int
   };
 
   st->h_stage_ints = st->mfma ? 3 * (size_t)st->L.rows_cap + 3 * ((size_t)st->L.rows_cap / 64) + 2 * (size_t)cfg->max_batch + 32
-                              : 2 * (size_t)max_rows(*cfg) + 2 * (size_t)cfg->max_batch;
+                              : 2 * (size_t)max_rows(*cfg) + (size_t)cfg->max_batch + 4 * ((size_t)max_rows(*cfg) / 16 + cfg->max_batch);
   if (hipHostMalloc((void **)&st->h_stage, sizeof(int) * st->h_stage_ints, hipHostMallocDefault) != hipSuccess) {
     st->h_stage = nullptr; st->err = "hipHostMalloc failed";
     return bail(HYP_ENOMEM);
@@ -704,7 +740,9 @@ hyp_status_t do_stage_create(const hyp_stage_config_t *cfg, int32_t l_start, int
       rc = upload_page_table(st);
     }
   } else {
-    rc = copy_weights(st, layers);
+    hipError_t e = plain_init();
+    if (e != hipSuccess) { st->err = std::string("kernel attributes: ") + hipGetErrorString(e); return bail(HYP_EDEVICE); }
+    rc = st->bf16 ? pack_weights_plain<bf16_t>(st, layers) : pack_weights_plain<float>(st, layers);
   }
   if (rc != HYP_OK) return bail(rc);
 
@@ -801,20 +839,28 @@ hyp_status_t do_stage_prefill(hyp_stage_t *st, const void *hidden_in, const int3
     rc = run_prefill_mfma(st, hidden_in, hidden_out, R, n_tiles);
   } else {
     int *h_req = st->h_stage, *h_pos = st->h_stage + rows, *h_len = st->h_stage + 2 * (size_t)rows;
+    PlainTile *h_tiles = (PlainTile *)(h_len + batch);
+    int n_tiles = 0;
     {
       int t = 0;
-      for (int b = 0; b < batch; ++b)
+      for (int b = 0; b < batch; ++b) {
+        for (int p = 0; p < seq_lens[b]; p += 16) h_tiles[n_tiles++] = PlainTile{t + p, p, std::min(16, seq_lens[b] - p), b};
         for (int p = 0; p < seq_lens[b]; ++p, ++t) { h_req[t] = b; h_pos[t] = p; }
-      for (int b = 0; b < batch; ++b) h_len[b] = seq_lens[b];
+        h_len[b] = seq_lens[b];
+      }
     }
+    // a tile's work grows with its position in its request: longest first, so that the launch ends on short ones
+    std::sort(h_tiles, h_tiles + n_tiles, [](const PlainTile &a, const PlainTile &b) {
+      return a.pos0 != b.pos0 ? a.pos0 > b.pos0 : a.row0 < b.row0;
+    });
     HIP_TRY(st, hipMemcpyAsync(st->ws + st->L.tok_req, h_req, sizeof(int) * rows, hipMemcpyHostToDevice, s));
     HIP_TRY(st, hipMemcpyAsync(st->ws + st->L.tok_pos, h_pos, sizeof(int) * rows, hipMemcpyHostToDevice, s));
     HIP_TRY(st, hipMemcpyAsync(st->ws + st->L.lens, h_len, sizeof(int) * batch, hipMemcpyHostToDevice, s));
+    HIP_TRY(st, hipMemcpyAsync(st->ws + st->L.tiles, h_tiles, sizeof(PlainTile) * n_tiles, hipMemcpyHostToDevice, s));
     HIP_TRY(st, hipEventRecord(st->upload_done, s));
     st->upload_pending = true;
-    const int *tok_req = at<int>(st, st->L.tok_req), *tok_pos = at<int>(st, st->L.tok_pos);
-    rc = st->bf16 ? run_plain<bf16_t>(st, hidden_in, hidden_out, rows, tok_req, tok_pos)
-                  : run_plain<float>(st, hidden_in, hidden_out, rows, tok_req, tok_pos);
+    rc = st->bf16 ? run_plain<bf16_t>(st, hidden_in, hidden_out, rows, n_tiles)
+                  : run_plain<float>(st, hidden_in, hidden_out, rows, n_tiles);
   }
   if (rc != HYP_OK) return rc;
   st->lens.assign(seq_lens, seq_lens + batch);
@@ -842,12 +888,10 @@ hyp_status_t do_stage_decode_step(hyp_stage_t *st, const void *hidden_in, void *
   LIVE_OR_RETURN(st);
   hyp_status_t rc = check_decode_args(st, hidden_in, hidden_out);
   if (rc != HYP_OK) return rc;
-  const int *iota = at<int>(st, st->L.iota), *lens = at<int>(st, st->L.lens);
   rc = st->mfma   ? run_decode_mfma(st, hidden_in, hidden_out)
-       : st->bf16 ? run_plain<bf16_t>(st, hidden_in, hidden_out, st->batch, iota, lens)
-                  : run_plain<float>(st, hidden_in, hidden_out, st->batch, iota, lens);
+       : st->bf16 ? run_plain<bf16_t>(st, hidden_in, hidden_out, st->batch, 0)
+                  : run_plain<float>(st, hidden_in, hidden_out, st->batch, 0);
   if (rc != HYP_OK) return rc;
-  if (!st->mfma) HIP_TRY(st, advance_lens(at<int>(st, st->L.lens), st->batch, st->stream));  // the MFMA path's last kernel does it
   for (int b = 0; b < st->batch; ++b) st->lens[b] += 1;
   return HYP_OK;
 }
@@ -912,11 +956,11 @@ hyp_status_t do_stage_export_kv(hyp_stage_t *st, int32_t layer, int32_t request,
     HIP_TRY(st, mfma_export_kv(at<bf16_t>(st, st->L.Kc + off), at<bf16_t>(st, st->L.Vc + off), cache_geom(st),
                                (bf16_t *)k_out, (bf16_t *)v_out, request, len, st->dm.nkv, st->stream));
   else if (st->bf16)
-    HIP_TRY(st, plain_export_kv<bf16_t>(at<bf16_t>(st, st->L.Kc + off), at<bf16_t>(st, st->L.Vc + off),
-                                        (bf16_t *)k_out, (bf16_t *)v_out, request, len, st->dm, st->stream));
+    HIP_TRY(st, plain_export_kv<bf16_t>(at<bf16_t>(st, st->L.Kc + off), at<bf16_t>(st, st->L.Vc + st->L.v_layer_stride * layer),
+                                        (bf16_t *)k_out, (bf16_t *)v_out, request, len, st->L.cache, st->stream));
   else
-    HIP_TRY(st, plain_export_kv<float>(at<float>(st, st->L.Kc + off), at<float>(st, st->L.Vc + off),
-                                       (float *)k_out, (float *)v_out, request, len, st->dm, st->stream));
+    HIP_TRY(st, plain_export_kv<float>(at<float>(st, st->L.Kc + off), at<float>(st, st->L.Vc + st->L.v_layer_stride * layer),
+                                       (float *)k_out, (float *)v_out, request, len, st->L.cache, st->stream));
   return HYP_OK;
 }
 

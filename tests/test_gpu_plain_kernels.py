@@ -1,0 +1,80 @@
+"""Shape-generic kernels at the sizes where they can go wrong: rows around the 16-token tiles that
+choose a GEMM form, widths off the 64-byte K tiles, head sizes and groups off the 16-wide blocks,
+the wide form, and values that are not finite behind a query (Sec. III-A block against the oracle)."""
+import numpy as np
+import pytest
+
+from oracle import hyp_oracle as orc
+from workloads import synth
+from tests.helpers import make_gpu_stage, rel_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+TOL = {"f32": 1e-4, "bf16": 2e-2}
+
+SHAPES = {
+    "odd": dict(hidden=10, n_q_heads=3, n_kv_heads=3, head_dim=2, ffn_dim=5),
+    "k_remainder": dict(hidden=72, n_q_heads=6, n_kv_heads=2, head_dim=10, ffn_dim=100),
+    "head80": dict(hidden=168, n_q_heads=4, n_kv_heads=1, head_dim=80, ffn_dim=264),
+    "head256": dict(hidden=96, n_q_heads=2, n_kv_heads=1, head_dim=256, ffn_dim=64),
+    "group20": dict(hidden=64, n_q_heads=20, n_kv_heads=1, head_dim=18, ffn_dim=130),
+    "wide": dict(hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn_dim=16384),
+}
+ROWS = {"tile": [16], "two": [1, 15, 16], "ragged": [17, 1, 33, 130], "wide": [130, 127, 9]}
+
+
+def check(got, ref, x, dtype, what):
+    """TOL on the output and on the update; narrow blocks add little to their input, so the update also gets the half
+    unit in the last place that storing the output in bf16 costs: at most 2^-8 of the largest output (eight significant bits)."""
+    assert rel_err(got, ref) <= TOL[dtype], what
+    store = 2.0 ** -8 * np.abs(ref).max() / np.abs(ref - x).max() if dtype == "bf16" else 0.0
+    assert rel_err(got - x, ref - x) <= TOL[dtype] + store, what
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,rows", [("odd", "two"), ("odd", "ragged"), ("k_remainder", "tile"), ("k_remainder", "ragged"),
+                                        ("head80", "two"), ("head80", "ragged"), ("head256", "ragged"), ("group20", "ragged"),
+                                        ("wide", "wide")])
+def test_generic_block_against_oracle(shape, rows, dtype):
+    from paper_2511_14450_amd import binding
+    shp = synth.BlockShape(dtype=dtype, **SHAPES[shape])
+    lens, n_layers = ROWS[rows], 1 if shape == "wide" else 2
+    B, T, cap = len(lens), sum(lens), max(lens) + 4
+    layers = [synth.layer_weights(shp, l, 31_000, sigma=0.05) for l in range(n_layers)]
+    x = synth.hidden_states(T, shp, 31_001)
+    ost = orc.Stage(shp, layers, B, cap, "f32")
+    gst = make_gpu_stage(shp, layers, B, cap, T, flags=binding.HYP_FLAG_PLAIN_KERNELS)
+    assert not gst.uses_mfma()
+    tol = TOL[dtype]
+    check(to_host(gst.prefill(to_dev(x, dtype), lens)), ost.prefill(x, lens), x, dtype, "prefill")
+    for s in range(3):
+        xd = synth.hidden_states(B, shp, 31_002 + s)
+        check(to_host(gst.decode_step(to_dev(xd, dtype))), ost.decode_step(xd), xd, dtype, f"decode step {s}")
+    for b in range(B):
+        k, v = gst.export_kv(n_layers - 1, b)
+        n = lens[b] + 3
+        assert rel_err(to_host(k), ost.K[n_layers - 1, b, :n]) <= tol
+        assert rel_err(to_host(v), ost.V[n_layers - 1, b, :n]) <= tol
+    gst.destroy()
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_values_that_are_not_finite_stay_behind_earlier_queries(bad):
+    # token 21 of request 0 is not finite: tokens before it, the other request and a later prefill do not notice
+    shp = synth.BlockShape(hidden=64, n_q_heads=4, n_kv_heads=2, head_dim=16, ffn_dim=96, dtype="f32")
+    layers = [synth.layer_weights(shp, l, 32_000, sigma=0.05) for l in range(2)]
+    lens = [30, 18]
+    x = synth.hidden_states(48, shp, 32_001)
+    y = x.copy()
+    y[21] = bad
+    st = make_gpu_stage(shp, layers, 2, 40, 48)
+    clean = to_host(st.prefill(to_dev(x, "f32"), lens))
+    got = to_host(st.prefill(to_dev(y, "f32"), lens))
+    assert np.array_equal(np.isfinite(got).all(1), np.r_[np.ones(21, bool), np.zeros(9, bool), np.ones(18, bool)])
+    assert np.allclose(got[:21], clean[:21], rtol=1e-5, atol=1e-5) and np.array_equal(got[30:], clean[30:])
+    # the slots of the first prefill's tail still hold such values; a shorter prompt and its decode steps do not see them
+    short = to_host(st.prefill(to_dev(x[:19], "f32"), [19]))
+    step = to_host(st.decode_step(to_dev(x[40:41], "f32")))
+    fresh = make_gpu_stage(shp, layers, 2, 40, 48)
+    assert np.array_equal(short, to_host(fresh.prefill(to_dev(x[:19], "f32"), [19])))
+    assert np.array_equal(step, to_host(fresh.decode_step(to_dev(x[40:41], "f32"))))
+    st.destroy(); fresh.destroy()
