@@ -119,10 +119,11 @@ template <typename T> hipError_t plain_gemm(int epi, const PlainGemm<T> &g, hipS
 template <typename T>
 hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const PlainTile *tiles, int n_tiles,
                               const PlainCache &cache, const Dims &dm, hipStream_t s);
-// one token per request at position lens[request], whose key is already cached
+// one token per request at position lens[request] <= longest, whose key is already cached; part: plain_attn_part_floats()
 template <typename T>
-hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch,
-                             const PlainCache &cache, const Dims &dm, hipStream_t s);
+hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch, int longest,
+                             float *part, const PlainCache &cache, const Dims &dm, hipStream_t s);
+size_t plain_attn_part_floats(int nq, int batch, int d);
 hipError_t plain_init();  // kernel attributes
 template <typename T>
 hipError_t plain_export_kv(const T *Kc, const T *Vc, T *k_out, T *v_out, int request, int len,

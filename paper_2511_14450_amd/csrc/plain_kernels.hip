@@ -2,6 +2,8 @@
 // contractions with fp32 accumulation on float or bf16 storage for any width, head size up to 256
 // and batch.  They are the whole fp32 path and serve bf16 stages whose shape the large bf16
 // kernels do not cover.
+#include <type_traits>
+
 #include "common.h"
 
 namespace hyp {
@@ -12,15 +14,14 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
-// acc += A B over the 64 bytes of K that one fragment of either operand covers
-template <typename T> __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 acc);
-template <> __device__ __forceinline__ f32x4 mma<float>(u32x4 a, u32x4 b, f32x4 acc) {
-  const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], acc, 0, 0, 0);
-  return acc;
+// MFMA steps that the 64 bytes of K of one fragment pair take, and the i-th of them: acc += A B
+template <typename T> constexpr int kMmaSteps = 1;
+template <> constexpr int kMmaSteps<float> = 4;
+template <typename T> __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 acc, int i);
+template <> __device__ __forceinline__ f32x4 mma<float>(u32x4 a, u32x4 b, f32x4 acc, int i) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[i]), __uint_as_float(b[i]), acc, 0, 0, 0);
 }
-template <> __device__ __forceinline__ f32x4 mma<bf16_t>(u32x4 a, u32x4 b, f32x4 acc) {
+template <> __device__ __forceinline__ f32x4 mma<bf16_t>(u32x4 a, u32x4 b, f32x4 acc, int) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
 }
 
@@ -148,45 +149,80 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
 #pragma unroll
   for (int j = 0; j < WN; ++j) xp[j] = (const u32x4 *)g.X + (size_t)min(tt0 + j, a.tt - 1) * a.tiles * 64 + lane;
   u32x4 wf[2][U][WM], xf[2][U][WN];
-  // this wave's tiles are kw, kw + KW, ...; a group past the end rereads the last tile against zeros
+  // this wave's tiles are kw, kw + KW, ...; a load past the end rereads the last one, which is not used
   auto load = [&](u32x4 (&w)[U][WM], u32x4 (&x)[U][WN], int t0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * KW, at = min(t, a.tiles - 1) * 64;
+      const size_t at = (size_t)min(t0 + u * KW, a.tiles - 1) * 64;
 #pragma unroll
       for (int i = 0; i < WM; ++i) w[u][i] = wp[i][at];
 #pragma unroll
       for (int j = 0; j < WN; ++j) x[u][j] = xp[j][at];
-      if (t >= a.tiles) {
-#pragma unroll
-        for (int i = 0; i < WM; ++i) w[u][i] = u32x4{0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < WN; ++j) x[u][j] = u32x4{0, 0, 0, 0};
-      }
     }
   };
-  auto use = [&](u32x4 (&w)[U][WM], u32x4 (&x)[U][WN]) {
+  auto use = [&](auto whole, u32x4 (&w)[U][WM], u32x4 (&x)[U][WN], int t0) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
+      if (decltype(whole)::value || t0 + u * KW < a.tiles)
 #pragma unroll
-      for (int i = 0; i < WM; ++i)
+        for (int e = 0; e < kMmaSteps<T>; ++e)  // neighbouring MFMAs on different accumulators
 #pragma unroll
-        for (int j = 0; j < WN; ++j) acc[i][j] = mma<T>(w[u][i], x[u][j], acc[i][j]);
+          for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j) acc[i][j] = mma<T>(w[u][i], x[u][j], acc[i][j], e);
   };
   constexpr int kStep = U * KW;
-  load(wf[0], xf[0], kw);
-  // sums of squares behind the RMS Norm factor of this wave's tokens: requested under the K loop
-  float rs[WN];
-#pragma unroll
-  for (int j = 0; j < WN; ++j) rs[j] = 0.f;
-  for (int t = kw; t < a.tiles; t += 2 * kStep) {
-    load(wf[1], xf[1], t + kStep);
-    use(wf[0], xf[0]);
-    load(wf[0], xf[0], t + 2 * kStep);
-    use(wf[1], xf[1]);
-  }
-
+  // A group's registers are refilled before the other group is used, or right after its own use: the wide float
+  // form is 22 % faster the second way, the wide bf16 form 29 % the first.
+  constexpr bool kLate = sizeof(T) == 4 && WM * WN >= 16;
   const int tl = lane & 15, q4 = (lane >> 4) * 4;
+  load(wf[0], xf[0], kw);
+  if (kLate) load(wf[1], xf[1], kw + kStep);
+  // What the epilogue of the small forms (registers) needs from memory is requested under the first
+  // tiles: positions, rotary angles, residual and gain of the blocks this wave finishes.
+  constexpr bool kAhead = KW >= WM * WN;  // at most one block per wave: kw / WN, kw % WN
+  int pf_req = 0, pf_pos = 0;
+  float pf_c[2] = {0.f, 0.f}, pf_s[2] = {0.f, 0.f};
+  f32x4 pf_x = {0.f, 0.f, 0.f, 0.f}, pf_g = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (kAhead) {
+    const int f0 = (ft0 + kw / WN) * 16 + q4, tok = (tt0 + kw % WN) * 16 + tl;
+    if (kw < WM * WN && tok < g.rows && f0 < g.N) {
+      if (EPI == PLAIN_QKV) {
+        pf_req = g.tok_req[tok]; pf_pos = g.tok_pos[tok];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if (f0 + 2 * h < g.dm.qd + g.dm.kvd) {
+            const size_t at = (size_t)pf_pos * (g.dm.d >> 1) + ((f0 + 2 * h) % g.dm.d >> 1);
+            pf_c[h] = g.cos_tab[at]; pf_s[h] = g.sin_tab[at];
+          }
+      } else if (EPI == PLAIN_RESID || EPI == PLAIN_FINAL) {
+        const float *xr = g.xres + (size_t)tok * g.N + f0;
+        if (g.N % 4 == 0) pf_x = *(const f32x4 *)xr;
+        else
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (f0 + e < g.N) pf_x[e] = xr[e];
+        if (EPI == PLAIN_RESID)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (f0 + e < g.N) pf_g[e] = load_f32(g.gain + f0 + e);
+      }
+    }
+  }
+  // pairs of whole groups, then what is left (checked tile by tile)
+  int t = kw;
+  for (; t + 2 * kStep - KW < a.tiles; t += 2 * kStep) {
+    if (!kLate) load(wf[1], xf[1], t + kStep);
+    use(std::true_type(), wf[0], xf[0], t);
+    load(wf[0], xf[0], t + 2 * kStep);
+    use(std::true_type(), wf[1], xf[1], t + kStep);
+    if (kLate) load(wf[1], xf[1], t + 3 * kStep);
+  }
+  if (!kLate) load(wf[1], xf[1], t + kStep);
+  use(std::false_type(), wf[0], xf[0], t);
+  use(std::false_type(), wf[1], xf[1], t + kStep);
+  // RMS Norm factor of this wave's tokens from the sums of squares
+  float rs[WN];
   if (EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU) {
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
@@ -236,7 +272,7 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
       if (EPI == PLAIN_QKV) {
         if (!live || f0 >= g.N) continue;
         const int d = g.dm.d, half = d >> 1, qk = g.dm.qd + g.dm.kvd;
-        const int req = g.tok_req[tok], pos = g.tok_pos[tok];
+        const int req = kAhead ? pf_req : g.tok_req[tok], pos = kAhead ? pf_pos : g.tok_pos[tok];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int r = f0 + 2 * h;  // a pair of packed rows: every boundary between heads and matrices is even
@@ -244,7 +280,7 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
           float v0 = acc[i][j][2 * h] * rs[j], v1 = acc[i][j][2 * h + 1] * rs[j];
           if (r < qk) {
             const int head = r / d, e = (r % d) >> 1;
-            const float c = g.cos_tab[(size_t)pos * half + e], s = g.sin_tab[(size_t)pos * half + e];
+            const float c = kAhead ? pf_c[h] : g.cos_tab[(size_t)pos * half + e], s = kAhead ? pf_s[h] : g.sin_tab[(size_t)pos * half + e];
             const float lo = v0 * c - v1 * s, hi = v1 * c + v0 * s;
             if (head < g.dm.nq) {
               T *dst = g.q + ((size_t)tok * g.dm.nq + head) * g.q_ld;
@@ -277,7 +313,11 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
         float x[4] = {0.f, 0.f, 0.f, 0.f};
         if (live && n > 0) {
           float *xr = g.xres + (size_t)tok * g.N + f0;
-          if (vec) {
+          if (kAhead) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (e < n) x[e] = pf_x[e] + acc[i][j][e];
+          } else if (vec) {
             const f32x4 old = *(const f32x4 *)xr;
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = old[e] + acc[i][j][e];
@@ -290,7 +330,7 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
             put4(xr, x, n, vec);
             float y[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = e < n ? x[e] * load_f32(g.gain + f0 + e) : 0.f;
+            for (int e = 0; e < 4; ++e) y[e] = e < n ? x[e] * (kAhead ? pf_g[e] : load_f32(g.gain + f0 + e)) : 0.f;
             put4(g.y + plain_offset<T>(tok, f0, a.out_tiles), y, n, true);
           } else {
             put4(g.hidden_out + (size_t)tok * g.N + f0, x, n, false);
@@ -319,6 +359,7 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
 // online softmax in fp32, O^T += V^T P^T with fp32 probabilities against fp32 products for either
 // storage type; the waves' (max, sum, output) meet in LDS in wave order.
 // ----------------------------------------------------------------------------
+constexpr int kPlainMaxSplit = 8;
 template <typename T> struct AttnArgs {
   const T *q, *Kc, *Vc;
   T *out;
@@ -327,12 +368,16 @@ template <typename T> struct AttnArgs {
   PlainCache cache;
   int nq, G, q_ld, out_tiles;
   float scale;
+  int split;    // decode: workgroups that share the keys of a (request, head group)
+  float *part;  // split > 1: [request][head][split][2 + d] = max, sum, unnormalised output
 };
 
-template <typename T> __device__ __forceinline__ f32x4 load_v4(const T *p);
-template <> __device__ __forceinline__ f32x4 load_v4<float>(const float *p) { return *(const f32x4 *)p; }
-template <> __device__ __forceinline__ f32x4 load_v4<bf16_t>(const bf16_t *p) {
-  const uint2 u = *(const uint2 *)p;
+template <typename T> struct VRaw;
+template <> struct VRaw<float> { typedef f32x4 V; };
+template <> struct VRaw<bf16_t> { typedef uint2 V; };
+template <typename T> __device__ __forceinline__ f32x4 widen_v4(typename VRaw<T>::V u);
+template <> __device__ __forceinline__ f32x4 widen_v4<float>(f32x4 u) { return u; }
+template <> __device__ __forceinline__ f32x4 widen_v4<bf16_t>(uint2 u) {
   return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
 }
 
@@ -347,7 +392,7 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
   int req, kvh, row, head, qpos, last;
   bool live;
   if (DECODE) {
-    req = blockIdx.x; kvh = blockIdx.y;
+    req = blockIdx.x / a.split; kvh = blockIdx.y;
     const int c = blockIdx.z * 16 + tl;
     live = c < a.G;
     head = kvh * a.G + min(c, a.G - 1);
@@ -374,19 +419,35 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
   for (int f = 0; f < NF; ++f) o[f] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
   const int n_kb = (last >> 4) + 1;
-  for (int kb = wave; kb < n_kb; kb += KW) {
-    u32x4 kf[NC];
-    f32x4 vf[NF];
+  // this wave's blocks: every step-th from `first` on
+  const int share = DECODE ? (int)(blockIdx.x % a.split) : 0, first = share * KW + wave, step = DECODE ? a.split * KW : KW;
+  // a wave's next block is requested before the current one is used, where the registers allow it
+  constexpr int kSets = NF * (int)sizeof(T) <= 16 ? 2 : 1;
+  u32x4 kS[kSets][NC];
+  typename VRaw<T>::V vS[kSets][NF];
+  auto load = [&](u32x4 (&k)[NC], typename VRaw<T>::V (&v)[NF], int kb) {
 #pragma unroll
     for (int c = 0; c < NC; ++c)
-      if (c < nc) kf[c] = kp[((size_t)kb * nc + c) * 64];
+      if (c < nc) k[c] = kp[((size_t)kb * nc + c) * 64];
 #pragma unroll
     for (int f = 0; f < NF; ++f)
-      if (f < nf) vf[f] = load_v4<T>(vp + ((size_t)kb * nf + f) * 256);
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+      if (f < nf) v[f] = *(const typename VRaw<T>::V *)(vp + ((size_t)kb * nf + f) * 256);
+  };
+  auto block = [&](u32x4 (&kf)[NC], typename VRaw<T>::V (&v)[NF], int kb) {
+    f32x4 s = {0.f, 0.f, 0.f, 0.f}, s1 = s;  // two chains
 #pragma unroll
     for (int c = 0; c < NC; ++c)
-      if (c < nc) s = mma<T>(kf[c], qf[c], s);
+      if (c < nc)
+#pragma unroll
+        for (int e = 0; e < kMmaSteps<T>; ++e) {
+          if ((c * kMmaSteps<T> + e) & 1) s1 = mma<T>(kf[c], qf[c], s1, e);
+          else s = mma<T>(kf[c], qf[c], s, e);
+        }
+    s += s1;
+    f32x4 vf[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+      if (f < nf) vf[f] = widen_v4<T>(v[f]);
     const bool edge = kb == n_kb - 1;  // the only block with keys some query must not see
     float mx = -INFINITY;
 #pragma unroll
@@ -425,27 +486,44 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
           for (int i = 0; i < 4; ++i) odd |= f < nf && !(fabsf(vf[f][i]) < INFINITY);
         shared = !__any(odd);
         if (!shared) {
+#pragma unroll 1
+          for (int jq = 0; jq < 4; ++jq)
 #pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            const float pj = __shfl(p[j & 3], (j >> 2) * 16 + tl, 64);
+            for (int j = 0; j < 4; ++j) {
+              const float pj = __shfl(p[j], jq * 16 + tl, 64);
 #pragma unroll
-            for (int f = 0; f < NF; ++f)
-              if (f < nf)
+              for (int f = 0; f < NF; ++f)
+                if (f < nf)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                  const float v = __shfl(vf[f][j & 3], (j >> 2) * 16 + g4 + i, 64);
-                  if (kb * 16 + j <= qpos) o[f][i] = fmaf(pj, v, o[f][i]);
-                }
-          }
+                  for (int i = 0; i < 4; ++i) {
+                    const float v = __shfl(vf[f][j], jq * 16 + g4 + i, 64);
+                    if (kb * 16 + 4 * jq + j <= qpos) o[f][i] = fmaf(pj, v, o[f][i]);
+                  }
+            }
         }
       }
     }
     if (shared)
 #pragma unroll
-      for (int f = 0; f < NF; ++f)
-        if (f < nf)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) o[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[f][i], p[i], o[f], 0, 0, 0);
+        for (int f = 0; f < NF; ++f)
+          if (f < nf) o[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[f][i], p[i], o[f], 0, 0, 0);
+  };
+  if constexpr (kSets == 2) {
+    if (first < n_kb) load(kS[0], vS[0], first);
+    for (int kb = first; kb < n_kb; kb += 2 * step) {
+      load(kS[1], vS[1], min(kb + step, n_kb - 1));  // past the end: the last block again, not used
+      block(kS[0], vS[0], kb);
+      if (kb + step >= n_kb) break;
+      load(kS[0], vS[0], min(kb + 2 * step, n_kb - 1));
+      block(kS[1], vS[1], kb + step);
+    }
+  } else {
+    for (int kb = first; kb < n_kb; kb += step) {
+      load(kS[0], vS[0], kb);
+      block(kS[0], vS[0], kb);
+    }
   }
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
@@ -454,7 +532,7 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
   for (int f = 0; f < NF; ++f)
     if (f < nf) o_s[(wave * nf + f) * 64 + lane] = o[f];
   __syncthreads();
-  float m = m_s[0][tl];
+  float m = m_s[0][tl];  // -inf: a share without a key, whose weights and sums are 0
 #pragma unroll
   for (int w = 1; w < KW; ++w) m = fmaxf(m, m_s[w][tl]);
   float wgt[KW], l = 0.f;
@@ -467,16 +545,45 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
     f32x4 r = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < KW; ++w)
-      if (w < n_kb) r += o_s[(w * nf + f) * 64 + lane] * wgt[w];
+      if (share * KW + w < n_kb) r += o_s[(w * nf + f) * 64 + lane] * wgt[w];
     float v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[i] = r[i] / l;
     const int f0 = f * 16 + g4, n = min(4, d - f0), k = head * d + f0;
     if (!live || n <= 0) continue;
+    if (DECODE && a.split > 1) {
+      float *dst = a.part + (((size_t)req * a.nq + head) * a.split + share) * (2 + d);
+      if (f0 == 0) { dst[0] = m; dst[1] = l; }
+      for (int i = 0; i < n; ++i) dst[2 + f0 + i] = r[i];
+      continue;
+    }
     if (d % 4 == 0) put4(a.out + plain_offset<T>(row, k, a.out_tiles), v, n, true);
     else
       for (int i = 0; i < n; ++i) store_f32(a.out + plain_offset<T>(row, k + i, a.out_tiles), v[i]);
   }
+}
+
+// one workgroup per (head, request): the shares of a split decode attention in order
+// (a thread per feature; everything is requested before the first value is used)
+template <typename T> __global__ void __launch_bounds__(256) k_plain_attn_merge(AttnArgs<T> a) {
+  const int head = blockIdx.x, req = blockIdx.y, d = a.cache.d, f = min((int)threadIdx.x, d - 1);
+  const float *src = a.part + ((size_t)req * a.nq + head) * a.split * (2 + d);
+  float ms[kPlainMaxSplit], ls[kPlainMaxSplit], os[kPlainMaxSplit];
+#pragma unroll
+  for (int s = 0; s < kPlainMaxSplit; ++s) {
+    const float *p = src + min(s, a.split - 1) * (2 + d);
+    ms[s] = p[0]; ls[s] = p[1]; os[s] = p[2 + f];
+  }
+  float m = ms[0];
+#pragma unroll
+  for (int s = 1; s < kPlainMaxSplit; ++s) m = fmaxf(m, ms[s]);  // slots past the last repeat it
+  float l = 0.f, o = 0.f;
+#pragma unroll
+  for (int s = 0; s < kPlainMaxSplit; ++s) {
+    const float w = s >= a.split || ms[s] == -INFINITY ? 0.f : expf(ms[s] - m);
+    if (s < a.split) { l += w * ls[s]; o += w * os[s]; }
+  }
+  if ((int)threadIdx.x < d) store_f32(a.out + plain_offset<T>(req, head * d + f, a.out_tiles), o / l);
 }
 
 template <typename T>
@@ -600,13 +707,30 @@ hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T 
   return launch_attn<T, false>(a, dim3(n_tiles, dm.nq), s);
 }
 
+size_t plain_attn_part_floats(int nq, int batch, int d) { return (size_t)batch * nq * kPlainMaxSplit * (2 + d); }
+
 template <typename T>
-hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch,
-                             const PlainCache &cache, const Dims &dm, hipStream_t s) {
+hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch, int longest,
+                             float *part, const PlainCache &cache, const Dims &dm, hipStream_t s) {
   if (batch == 0) return hipSuccess;
   AttnArgs<T> a = attn_args<T>(q, q_ld, Kc, Vc, out, cache, dm);
-  a.lens = lens;
-  return launch_attn<T, true>(a, dim3(batch, dm.nkv, (a.G + 15) / 16), s);
+  a.lens = lens; a.part = part;
+  const int groups = (a.G + 15) / 16, nf = (dm.d + 15) / 16, nc = plain_tiles(dm.d, sizeof(T));
+  // Few (request, KV head) pairs leave most CUs idle while one CU's matrix pipes work through 16 query columns of
+  // which the group fills a few: its keys are dealt to `split` workgroups where the rounds of blocks that this saves
+  // (their MFMAs at two waves per SIMD, 2.4 GHz, plus 0.6 us of latency each) pay for the merging launch (5 us).
+  const double round_us = (nc * kMmaSteps<T> + nf * 4) * 64.0 / 2400.0 + 0.6;
+  const int blocks = longest / 16 + 1, kw = 8;
+  a.split = 1;
+  double best = (blocks + kw - 1) / kw * round_us;
+  for (int c = 2; c <= kPlainMaxSplit && (size_t)batch * dm.nkv * groups * c <= 512; c *= 2) {
+    const double t = (blocks + kw * c - 1) / (kw * c) * round_us + 5.0;
+    if (t < best) { best = t; a.split = c; }
+  }
+  hipError_t e = launch_attn<T, true>(a, dim3(batch * a.split, dm.nkv, groups), s);
+  if (e != hipSuccess || a.split == 1) return e;
+  k_plain_attn_merge<T><<<dim3(dm.nq, batch), (dm.d + 63) / 64 * 64, 0, s>>>(a);
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -629,8 +753,8 @@ hipError_t plain_fill_zero(void *p, size_t bytes, hipStream_t s) {
   template hipError_t plain_gemm<T>(int, const PlainGemm<T> &, hipStream_t);                                                 \
   template hipError_t plain_attn_prefill<T>(const T *, int, const T *, const T *, T *, const PlainTile *, int,               \
                                             const PlainCache &, const Dims &, hipStream_t);                                  \
-  template hipError_t plain_attn_decode<T>(const T *, int, const T *, const T *, T *, const int *, int, const PlainCache &,  \
-                                           const Dims &, hipStream_t);                                                       \
+  template hipError_t plain_attn_decode<T>(const T *, int, const T *, const T *, T *, const int *, int, int, float *,         \
+                                           const PlainCache &, const Dims &, hipStream_t);                                   \
   template hipError_t plain_export_kv<T>(const T *, const T *, T *, T *, int, int, const PlainCache &, hipStream_t);
 HYP_INSTANTIATE(float)
 HYP_INSTANTIATE(bf16_t)

@@ -238,6 +238,7 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
   L.m = take(operand(R, I));
   L.act_end = off;
   L.ssq = take(sizeof(float) * (size_t)L.rows_pad * ((H + 15) / 16));
+  L.attn_part = take(sizeof(float) * plain_attn_part_floats(c.n_q_heads, c.max_batch, c.head_dim));
   L.tok_req = take(sizeof(int) * R);
   L.tok_pos = take(sizeof(int) * R);
   L.tiles = take(sizeof(PlainTile) * (R / 16 + c.max_batch));
@@ -561,6 +562,9 @@ hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, i
   const Layout &L = st->L;
   hipStream_t s = st->stream;
   const bool decode = n_tiles == 0;
+  int longest = 0;
+  if (decode)
+    for (int b = 0; b < rows; ++b) longest = std::max(longest, st->lens[b]);
   float *xres = at<float>(st, L.xres), *ssq = at<float>(st, L.ssq);
   T *y = at<T>(st, L.y), *q = at<T>(st, L.q), *attn = at<T>(st, L.attn), *m = at<T>(st, L.m);
   int *lens = at<int>(st, L.lens);
@@ -577,7 +581,7 @@ hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, i
     a.cos_tab = at<float>(st, L.cos_tab); a.sin_tab = at<float>(st, L.sin_tab);
     a.q = q; a.q_ld = L.q_ld; a.Kc = Kc; a.Vc = Vc; a.cache = L.cache;
     HIP_TRY(st, plain_gemm<T>(PLAIN_QKV, a, s));
-    if (decode) HIP_TRY(st, plain_attn_decode<T>(q, L.q_ld, Kc, Vc, attn, lens, rows, L.cache, d, s));
+    if (decode) HIP_TRY(st, plain_attn_decode<T>(q, L.q_ld, Kc, Vc, attn, lens, rows, longest, at<float>(st, L.attn_part), L.cache, d, s));
     else HIP_TRY(st, plain_attn_prefill<T>(q, L.q_ld, Kc, Vc, attn, at<PlainTile>(st, L.tiles), n_tiles, L.cache, d, s));
     PlainGemm<T> o = base;
     o.W = at<T>(st, p.wo); o.X = attn; o.N = d.H; o.K = d.qd;
