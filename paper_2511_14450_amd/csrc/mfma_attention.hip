@@ -457,6 +457,114 @@ __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ q
   }
 }
 
+// ----------------------------------------------------------------------------
+// Decode attention while every context is short (kShortKeys): one workgroup per (request, KV
+// head), whose 8 waves take the 32-key blocks in turn (at most kShortKeys / 256 each, all
+// requested at once) and meet in LDS in wave order.  No partial results in memory and no merging
+// launch, which is what a short context costs: at 16 requests of up to 440 keys of a stage with
+// room for 4043 the chunked pair of kernels takes 15.2 + 5.3 us, at one request of 64 - 192 keys
+// 5.9 + 5.4 us.
+// ----------------------------------------------------------------------------
+constexpr int kShortWaves = 8;
+
+template <int BLOCKS>  // 32-key blocks per wave
+__global__ void __launch_bounds__(kShortWaves * 64) k_attn_decode_short(const bf16_t *__restrict__ qdec,
+                                                    const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc,
+                                                    CacheGeom geom, const int *__restrict__ lens,
+                                                    bf16_t *__restrict__ out, int nq, int G) {
+  __shared__ float m_s[kShortWaves][4], l_s[kShortWaves][4];
+  __shared__ float o_s[kShortWaves][4][132];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hh = lane >> 5, tl = lane & 31;
+  const int kvh = blockIdx.x, req = blockIdx.y;
+  const float c = kLog2e * 0.08838834764831845f;
+  bf16x8_t qf[8];
+  const bf16_t *qb = qdec + ((size_t)req * geom.nkv + kvh) * (32 * 128);
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) qf[dt] = *(const bf16x8_t *)(qb + dt * kTileElems + lane * 8);
+  const int nkeys = lens[req] + 1;  // the new token's key is already in the cache
+  const int n_kb = (nkeys + 31) >> 5;
+  f32x16_t o[4];
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  bf16x8_t kS[BLOCKS][8], vS[BLOCKS][8];
+#pragma unroll
+  for (int u = 0; u < BLOCKS; ++u) {
+    const int kb = wave + u * kShortWaves;
+    if (kb < n_kb) {
+      const size_t off = geom.off(req, kvh, kb) + lane * 8;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) kS[u][t] = __builtin_nontemporal_load((const bf16x8_t *)(Kc + off + t * kTileElems));
+#pragma unroll
+      for (int t = 0; t < 8; ++t) vS[u][t] = __builtin_nontemporal_load((const bf16x8_t *)(Vc + off + t * kTileElems));
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < BLOCKS; ++u) {
+    const int kb = wave + u * kShortWaves;
+    if (kb >= n_kb) continue;
+    f32x16_t s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kS[u][dt], qf[dt], s, 0, 0, 0);
+    float p[16], mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int kpos = kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
+      p[r] = kpos < nkeys ? s[r] : -INFINITY;
+      mx = fmaxf(mx, p[r]);
+    }
+    const float m_new = fmaxf(m_run, xhalf_max(mx));  // finite: a block that is taken holds a key
+    const float mc = m_new * c, alpha = fast_exp2(m_run * c - mc);  // 0 on the first block
+    float rowsum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      p[r] = fast_exp2(p[r] * c - mc);
+      rowsum += p[r];
+    }
+    l_run = l_run * alpha + rowsum;
+    m_run = m_new;
+    if (u > 0) {
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+    }
+    const bf16x8_t pf0 = probs_operand(p, 0), pf1 = probs_operand(p, 1);
+#pragma unroll
+    for (int db = 0; db < 4; ++db) {
+      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vS[u][db], pf0, o[db], 0, 0, 0);
+      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vS[u][4 + db], pf1, o[db], 0, 0, 0);
+    }
+  }
+  const float l_tot = xhalf_sum(l_run);
+  if (tl < G) {  // lanes tl < G hold real heads
+    if (hh == 0) { m_s[wave][tl] = m_run; l_s[wave][tl] = l_tot; }
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *(f32x4_t *)&o_s[wave][tl][db * 32 + 8 * q + 4 * hh] = f32x4_t{o[db][4 * q], o[db][4 * q + 1], o[db][4 * q + 2], o[db][4 * q + 3]};
+  }
+  __syncthreads();
+  const int g = threadIdx.x >> 7, d = threadIdx.x & 127;
+  if (g >= G) return;
+  float m = m_s[0][g];
+#pragma unroll
+  for (int w = 1; w < kShortWaves; ++w) m = fmaxf(m, m_s[w][g]);
+  float acc = 0.f, l = 0.f;
+#pragma unroll
+  for (int w = 0; w < kShortWaves; ++w) {
+    const float wgt = w < n_kb ? fast_exp2((m_s[w][g] - m) * c) : 0.f;  // waves without a block hold zeros
+    l += wgt * l_s[w][g];
+    acc += wgt * o_s[w][g][d];
+  }
+  out[frag_offset(req, (kvh * G + g) * 128 + d, nq * 128)] = f2bf_dev(acc / l);
+}
+
 // One 128-thread block per (request, query head): combine its chunks in chunk
 // order.  Lane i of the first wave takes chunk i (max, sum -> weight); then thread
 // d accumulates output feature d over all chunks, eight loads in flight at a time.
@@ -538,8 +646,13 @@ size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks) {
 
 hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
-                            int max_chunks, int chunk_keys, hipStream_t s) {
+                            int max_chunks, int chunk_keys, int short_blocks, hipStream_t s) {
   int G = nq / nkv;
+  if (short_blocks) {
+    if (short_blocks == 1) k_attn_decode_short<1><<<dim3(nkv, batch), kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G);
+    else k_attn_decode_short<2><<<dim3(nkv, batch), kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G);
+    return hipGetLastError();
+  }
   k_attn_decode<2><<<dim3(max_chunks, nkv, batch), 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, max_chunks, chunk_keys);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -107,7 +107,11 @@ hipError_t mfma_dec_begin(const bf16_t *hidden_in, float *xres, const bf16_t *ga
 // split-KV decode attention + fixed-order merge; out row b of P(32, nq*128)
 hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
-                            int max_chunks, int chunk_keys, hipStream_t s);
+                            int max_chunks, int chunk_keys, int short_blocks, hipStream_t s);
+// blocks of 32 keys per wave of the one-workgroup form, which serves steps whose longest context (the new token's
+// key included) is at most kShortKeys; 0: the chunked form
+constexpr int kShortKeys = 512;
+inline int mfma_decode_short_blocks(int longest) { return longest > kShortKeys ? 0 : longest > kShortKeys / 2 ? 2 : 1; }
 size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks);
 // keys per decode-attention chunk (one wave each, one wave per SIMD): the largest power-of-two
 // multiple of 128 up to 1024 that still gives the longest context about 512 waves over all

@@ -277,6 +277,7 @@ struct hyp_stage {
     hipGraphExec_t exec = nullptr;
     int batch = 0;
     void *out = nullptr;
+    int attn = 0;  // short_blocks() at recording
   };
   std::vector<DecGraph> dec_graphs;
   hipStream_t cap_stream = nullptr;  // recording only (the null stream cannot be captured); nothing runs on it
@@ -451,11 +452,19 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
   return HYP_OK;
 }
 
+// The form of decode attention that this step's contexts get.  A step that the caller records is replayed at
+// contexts the host does not see: it gets a form that serves the stage's whole capacity.
+int short_blocks(const hyp_stage *st, bool recorded_by_caller) {
+  int longest = 0;
+  for (int b = 0; b < st->batch; ++b) longest = std::max(longest, st->lens[b] + 1);
+  return mfma_decode_short_blocks(recorded_by_caller ? st->cfg.max_seq : longest);
+}
+
 // One decode step through the MFMA kernels (a single block of 32 token rows):
 // 1 + 5 launches per block, every reduction finished inside the kernel that
 // produced it.
 hyp_status_t decode_step_mfma(hyp_stage *st, hipStream_t s, const DecScratch &sc, const void *hidden_in, void *hidden_out,
-                              bool begin, bool layers) {
+                              int attn_form, bool begin, bool layers) {
   const Dims &d = st->dm;
   const Layout &L = st->L;
   DecGemv base;
@@ -483,7 +492,7 @@ hyp_status_t decode_step_mfma(hyp_stage *st, hipStream_t s, const DecScratch &sc
     PROF(st, HYP_K_GEMV_QKV, mfma_dec_gemv(DEC_QKV, HYP_K_GEMV_QKV, a, s));
     PROF(st, HYP_K_ATTN_DECODE, mfma_attn_decode(a.qdec, Kc, Vc, geom, a.lens, sc.attn_part,
                                                  attn, d.nq, d.nkv, st->batch,
-                                                 L.max_chunks, L.chunk_keys, s));
+                                                 L.max_chunks, L.chunk_keys, attn_form, s));
     DecGemv o = base;
     o.W = at<bf16_t>(st, p.wo); o.x = attn; o.N = d.H; o.K = d.qd; o.plan = L.g_o;
     o.gain = at<bf16_t>(st, p.g2); o.y_out = y; o.ssq_out = ssq;
@@ -515,7 +524,7 @@ void drop_decode_graph(hyp_stage::DecGraph &g) {
 
 // The launches of a decode step are latency-bound next to ~0.1 ms of streaming
 // per block, so the step is recorded into a HIP graph (kernel nodes only) the
-// first time a (batch, output buffer) pair is seen and replayed afterwards;
+// first time a (batch, output buffer, attention form) is seen and replayed afterwards;
 // while kernel classes are being timed, or when the caller is itself capturing
 // the stream, it is launched kernel by kernel instead.
 hyp_status_t run_decode_mfma(hyp_stage *st, const void *hidden_in, void *hidden_out) {
@@ -523,25 +532,26 @@ hyp_status_t run_decode_mfma(hyp_stage *st, const void *hidden_in, void *hidden_
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   HIP_TRY(st, hipStreamIsCapturing(s, &cap));
   bool use_graph = st->prof_mask == 0 && cap == hipStreamCaptureStatusNone && !(st->cfg.flags & HYP_FLAG_NO_GRAPH);
-  if (!use_graph) return decode_step_mfma(st, s, st->dec_ws, hidden_in, hidden_out, true, true);
+  const int attn = short_blocks(st, cap != hipStreamCaptureStatusNone);
+  if (!use_graph) return decode_step_mfma(st, s, st->dec_ws, hidden_in, hidden_out, attn, true, true);
   // the first kernel reads the caller's input and stays outside the recording, so a
   // new input address every step does not force a new graph
-  hyp_status_t rc0 = decode_step_mfma(st, s, st->dec_ws, hidden_in, hidden_out, true, false);
+  hyp_status_t rc0 = decode_step_mfma(st, s, st->dec_ws, hidden_in, hidden_out, attn, true, false);
   if (rc0 != HYP_OK) return rc0;
   // a few recorded graphs, keyed by what is baked into their kernel arguments
   hyp_stage::DecGraph *g = nullptr;
   for (auto &c : st->dec_graphs)
-    if (c.batch == st->batch && c.out == hidden_out) g = &c;
+    if (c.batch == st->batch && c.out == hidden_out && c.attn == attn) g = &c;
   if (!g) {
     if (st->dec_graphs.size() >= 4) {
       drop_decode_graph(st->dec_graphs.front());
       st->dec_graphs.erase(st->dec_graphs.begin());
     }
     hyp_stage::DecGraph n;
-    n.batch = st->batch; n.out = hidden_out;
+    n.batch = st->batch; n.out = hidden_out; n.attn = attn;
     if (!st->cap_stream) HIP_TRY(st, hipStreamCreateWithFlags(&st->cap_stream, hipStreamNonBlocking));
     HIP_TRY(st, hipStreamBeginCapture(st->cap_stream, hipStreamCaptureModeThreadLocal));
-    hyp_status_t rc = decode_step_mfma(st, st->cap_stream, st->dec_ws, hidden_in, hidden_out, false, true);
+    hyp_status_t rc = decode_step_mfma(st, st->cap_stream, st->dec_ws, hidden_in, hidden_out, attn, false, true);
     hipError_t e = hipStreamEndCapture(st->cap_stream, &n.graph);
     if (rc != HYP_OK) { drop_decode_graph(n); return rc; }
     if (e != hipSuccess) { drop_decode_graph(n); return fail(st, HYP_EDEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e)); }
@@ -913,8 +923,11 @@ hyp_status_t do_stage_decode_step_noalloc(hyp_stage_t *st, const void *hidden_in
   // the array keeps whatever the last call on this GPU left: the arrival counters must start at zero
   // (a fill kernel, not a memset node, so that the call can be captured into a graph)
   HIP_TRY(st, mfma_fill_zero(st->dec_static.counters, align_up(st->L.counters_bytes), st->stream));
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIP_TRY(st, hipStreamIsCapturing(st->stream, &cap));
   st->prof_off = true;
-  rc = decode_step_mfma(st, st->stream, st->dec_static, hidden_in, hidden_out, true, true);
+  rc = decode_step_mfma(st, st->stream, st->dec_static, hidden_in, hidden_out,
+                        short_blocks(st, cap != hipStreamCaptureStatusNone), true, true);
   st->prof_off = false;
   if (rc != HYP_OK) return rc;
   for (int b = 0; b < st->batch; ++b) st->lens[b] += 1;
