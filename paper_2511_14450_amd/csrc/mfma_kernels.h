@@ -19,6 +19,9 @@ struct GemmEpilogue {
   const int *row_pos = nullptr, *row_req = nullptr;    // per internal row
   // EPI_QKV, EPI_SWIGLU: RMS Norm factor of every input row (the rows carry the gain only)
   const float *rstd = nullptr;
+  // up to kShortRows rows: the sums of squares (ssq_part of the GEMM before) instead, null where rstd is given; row_ext too
+  const float *ssq_in = nullptr;
+  float eps = 0.f;
   // EPI_RESID: residual stream A(T', N), gains of the following norm, padding map,
   // sums of squares out [N / 64][T']
   float *xres = nullptr;
@@ -27,10 +30,12 @@ struct GemmEpilogue {
   float *ssq_part = nullptr;
   // any epilogue: scratch for GEMMs whose K loop is split across workgroups (few output tiles)
   float *split_ws = nullptr;          // mfma_gemm_split_ws_bytes()
-  unsigned *split_counters = nullptr;  // kGemmSplitMaxTiles, zero between launches
+  unsigned *split_counters = nullptr;  // kGemmShortMaxTiles + 1, zero between launches
 };
 
-constexpr int kGemmSplitMaxTiles = 255;  // GEMMs with at least a round of output tiles are never split
+constexpr int kShortRows = 128;          // prompts of up to so many internal rows run the GEMM's short forms
+constexpr int kGemmSplitMaxTiles = 255;  // wide GEMMs with at least a round of output tiles are never split
+constexpr int kGemmShortMaxTiles = 511;  // short forms: tiles that may be split, and counters
 size_t mfma_gemm_split_ws_bytes();
 
 // dst = P(N, K) of the row-permuted concatenation [src0; src1; src2]

@@ -2,6 +2,7 @@
 // at the two ends of the residual stream, the LDS-staged GEMM with its four
 // epilogues (RoPE + KV-cache write, SwiGLU, residual add + next RMS Norm's gain
 // and statistics, plain), for the decoder block of Sec. III-A.
+#include <algorithm>
 #include <type_traits>
 #include "mfma_common.h"
 #include "mfma_kernels.h"
@@ -56,19 +57,22 @@ __global__ void __launch_bounds__(256) k_pack_weight(const bf16_t *__restrict__ 
 //           y' = x * g -> P(rows, H) ; rstd = rsqrt(mean(x^2) + eps)
 //           (the norm factor is applied by the consuming GEMM's epilogue)
 //   MODE 1  hidden_out[row_ext] = residual + delta, delta = P(rows, H) bf16 of the last GEMM
-// A 256-thread block owns RPW consecutive rows (8, or 1 when there are only a few
+// A 1024-thread block owns RPW consecutive rows (8, or 1 when there are only a few
 // rows so that more workgroups share the work); thread t works on row t % RPW.
+// (2048 rows are 256 workgroups: with 256 threads each the chip held four waves per CU,
+// every one a chain of 20 round trips.)
 // ----------------------------------------------------------------------------
+constexpr int kEndThreads = 1024;
 template <int MODE, int RPW>  // MODE 0: first block's input ; 1: stage output
-__global__ void __launch_bounds__(256) k_add_norm(const bf16_t *__restrict__ hidden_in,
+__global__ void __launch_bounds__(kEndThreads) k_add_norm(const bf16_t *__restrict__ hidden_in,
                                                   float *__restrict__ xres,
                                                   const bf16_t *__restrict__ delta_bf,
                                                   const bf16_t *__restrict__ gain,
                                                   bf16_t *__restrict__ y, float *__restrict__ rstd,
                                                   bf16_t *__restrict__ hidden_out,
                                                   const int *__restrict__ row_ext, int H, float eps) {
-  constexpr int CPR = 256 / RPW;  // threads per row
-  __shared__ float red[RPW][CPR + 1];
+  constexpr int CPR = kEndThreads / RPW;  // threads per row
+  __shared__ float red[kEndThreads / 64][RPW];
   int r8 = threadIdx.x % RPW, cg = threadIdx.x / RPW;
   int row = blockIdx.x * RPW + r8;
   int ext = row_ext[row];
@@ -105,11 +109,15 @@ __global__ void __launch_bounds__(256) k_add_norm(const bf16_t *__restrict__ hid
     }
   }
   if (MODE == 1) return;
-  red[r8][cg] = ss;
+  // the lanes of a wave that share a row, then the waves in order
+#pragma unroll
+  for (int o = RPW; o < 64; o <<= 1) ss += __shfl_xor(ss, o, 64);
+  if ((threadIdx.x & 63) < RPW) red[threadIdx.x >> 6][r8] = ss;
   __syncthreads();
   if (cg == 0) {
     float tot = 0.f;
-    for (int i = 0; i < CPR; ++i) tot += red[r8][i];
+#pragma unroll
+    for (int i = 0; i < kEndThreads / 64; ++i) tot += red[i][r8];
     rstd[row] = ext < 0 ? 0.f : 1.0f / sqrtf(tot / (float)H + eps);  // padding rows stay zero also when eps == 0
   }
 }
@@ -153,11 +161,26 @@ __global__ void __launch_bounds__(256) k_rstd(const float *__restrict__ ssq_part
 // consecutive feature tiles and share operand panels in that XCD's L2.  A GEMM of 64
 // rounds or more leaves its last rounds to workgroups that draw a tile each from a counter.
 // ----------------------------------------------------------------------------
-constexpr int WF = 4, WT = 2, FB = 2, TB = 4, KTS = 2, NST = 4;
-constexpr int XB = WT * TB, NBK = WF * FB;           // 8 token blocks, 8 feature blocks
-constexpr int STAGE_BYTES = (XB + NBK) * KTS * 1024;  // 32 KiB
-constexpr int LPW = (XB + NBK) * KTS / (WF * WT);     // 4 wave loads per wave and stage
-constexpr int GEMM_LDS = STAGE_BYTES * NST;           // 128 KiB
+constexpr int FB = 2, KTS = 2;
+// How a workgroup is laid out: WF waves along the features (FB blocks of 32 each) times WT along the tokens (TB
+// blocks each), NST stages in LDS.
+//   <4, 2, 4, 4>  256 features x 256 tokens: the form described above
+//   <2, 2, 1, 6>  128 features x 64 tokens: a short prompt.  It is bound by the weights' way out of HBM, and the wide
+//                 form multiplies three tokens of padding for every live one on top (gate/up of 64 tokens: 94 GFLOP,
+//                 100 us, for 367 MB).  Twice as many tiles as 256 features would give put a workgroup on every CU
+//                 (two fit) with fewer K slices; each keeps five stages of 12 KiB on their way.
+//   <2, 2, 2, 4>  128 features x 128 tokens: the same, stages of 16 KiB
+template <int WF_, int WT_, int TB_, int NST_> struct GemmForm {
+  static constexpr int WF = WF_, WT = WT_, TB = TB_, NST = NST_;
+  static constexpr int XB = WT * TB, NBK = WF * FB;                 // token and feature blocks
+  static constexpr int STAGE_BYTES = (XB + NBK) * KTS * 1024;
+  static constexpr int LPW = (XB + NBK) * KTS / (WF * WT);          // wave loads per wave and stage
+  static constexpr int LDS = STAGE_BYTES * NST;
+  static_assert(LPW * WF * WT == (XB + NBK) * KTS, "every wave issues the same number of loads");
+};
+typedef GemmForm<4, 2, 4, 4> WideForm;
+typedef GemmForm<2, 2, 1, 6> Form64;
+typedef GemmForm<2, 2, 2, 4> Form128;
 
 struct GemmParams {
   const bf16_t *X;   // P(T', K)
@@ -183,6 +206,10 @@ struct GemmParams {
   float *ssq_part;                 // [N / 64][T']
   // K loop split over `ksplit` workgroups per tile (GEMMs with few tiles): fp32 partial tiles and arrival counters
   int ksplit, tiles_grid;
+  int first, ksplit2;              // short forms: tiles from `first` on are split over ksplit2 workgroups each
+  const float *ssq_in;             // short forms: sums of squares [ssq_groups][T'] instead of rstd
+  int ssq_groups;
+  float inv_H, eps;
   int n_static, pool_wgs;          // unsplit GEMMs of many rounds: tiles assigned by position / workgroups that draw the rest
   float *split_ws;
   unsigned *split_counters;
@@ -205,16 +232,26 @@ __device__ __forceinline__ void store4(bf16_t *out, int out_K, int row, int f0, 
 
 // CLS (a hyp_kernel_class_t) does not change the code: it gives each GEMM of a block a kernel name of its
 // own, so that a trace tells the O projection from the down projection, which share an epilogue.
-template <int EPI, int CLS>
-__global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
+template <int EPI, int CLS, typename F>
+__global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
+  constexpr int WF = F::WF, WT = F::WT, TB = F::TB, NST = F::NST, XB = F::XB, NBK = F::NBK, STAGE_BYTES = F::STAGE_BYTES, LPW = F::LPW;
+  constexpr bool kWide = std::is_same<F, WideForm>::value;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;  // wave-uniform: scalar registers
   const int wf = wave / WT, wt = wave % WT;
   // tile of this workgroup
   __shared__ unsigned split_last;
-  const int nwg = p.tiles_grid, id = blockIdx.x % p.tiles_grid, slice = blockIdx.x / p.tiles_grid;
-  int q;
-  if (p.pool_wgs == 0) {
+  const int nwg = p.tiles_grid, id = blockIdx.x % p.tiles_grid;
+  int slice = blockIdx.x / p.tiles_grid, ksplit = p.ksplit, q;
+  if constexpr (!kWide) {
+    const int in_first = p.first * p.ksplit, b = blockIdx.x;
+    if (b < in_first) {
+      q = b % p.first; slice = b / p.first;
+    } else {
+      const int rest = p.n_tiles - p.first;
+      q = p.first + (b - in_first) % rest; slice = (b - in_first) / rest; ksplit = p.ksplit2;
+    }
+  } else if (p.pool_wgs == 0) {
     q = (id % 8) * (nwg / 8) + id / 8;
   } else if (id < p.n_static) {
     // a large unsplit GEMM: most tiles belong to an XCD by position, as above ...
@@ -254,7 +291,7 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[i][fh][j][th][e] = 0.f;
 
-  const int nsteps = KT / KTS / p.ksplit;  // stages of this workgroup's K slice, >= NST guaranteed by the host
+  const int nsteps = KT / KTS / ksplit;  // stages of this workgroup's K slice, >= NST guaranteed by the host
   const size_t k_first = (size_t)slice * nsteps * KTS * kTileElems;
   const bf16_t *src[LPW];
 #pragma unroll
@@ -272,6 +309,37 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
     __builtin_amdgcn_global_load_lds((gbl_ptr_t *)(src[i] + (size_t)step * KTS * kTileElems),
                                      (lds_ptr_t *)(lds + buf * STAGE_BYTES + (wave * LPW + i) * 1024), 16, 0, 0);
   };
+  const char *frag_base = lds + (lane >> 4) * 512 + (lane & 15) * 16;
+  if constexpr (!kWide) {
+    // Short prompts: a plain multi-stage loop.  A barrier opens a stage: everybody's part of it has landed, and
+    // everybody has read the stage before, whose buffer the loads NST - 1 stages ahead take over.
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s)
+#pragma unroll
+      for (int i = 0; i < LPW; ++i) issue1(i, s, s);
+    int buf = 0;
+    for (int s = 0; s < nsteps; ++s) {
+      __builtin_amdgcn_s_waitcnt(0x0070 | (((NST - 2) * LPW) & 15) | ((((NST - 2) * LPW) >> 4) << 14));
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      const int lstep = min(s + NST - 1, nsteps - 1), lbuf = buf == 0 ? NST - 1 : buf - 1;  // past the end: a buffer nobody reads again
+#pragma unroll
+      for (int i = 0; i < LPW; ++i) issue1(i, lstep, lbuf);
+      const char *base = frag_base + buf * STAGE_BYTES;
+      bf16x8_t wfr[2 * FB], xfr[2 * TB];
+#pragma unroll
+      for (int a = 0; a < 2 * FB; ++a) wfr[a] = *(const bf16x8_t *)(base + (XB + wf * FB + (a >> 1)) * (KTS * 1024) + (a & 1) * 256);
+#pragma unroll
+      for (int b = 0; b < 2 * TB; ++b) xfr[b] = *(const bf16x8_t *)(base + (wt * TB + (b >> 1)) * (KTS * 1024) + (b & 1) * 256);
+#pragma unroll
+      for (int b = 0; b < 2 * TB; ++b)
+#pragma unroll
+        for (int a = 0; a < 2 * FB; ++a)
+          acc[a >> 1][a & 1][b >> 1][b & 1] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfr[a], xfr[b], acc[a >> 1][a & 1][b >> 1][b & 1], 0, 0, 0);
+      buf = buf + 1 == NST ? 0 : buf + 1;
+    }
+  } else {
 #pragma unroll
   for (int s = 0; s < NST; ++s)
 #pragma unroll
@@ -285,7 +353,6 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
   // bytes, no bank conflicts.  The four feature fragments of a stage (a = 2 i + fh) stay in registers for the
   // whole stage (double-buffered); the eight token fragments (b = 2 j + th) pass through four slots, each read
   // three groups of four MFMAs ahead of its use.
-  const char *frag_base = lds + (lane >> 4) * 512 + (lane & 15) * 16;
   bf16x8_t afr[2][2 * FB], bfr[4];
   auto read_a = [&](int which, int buf, int a) {
     afr[which][a] = *(const bf16x8_t *)(frag_base + buf * STAGE_BYTES + (XB + wf * FB + (a >> 1)) * (KTS * 1024) + (a & 1) * 256);
@@ -344,7 +411,7 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
     }
     buf = nbuf;
   };
-  static_assert(LPW == 4 && FB == 2 && TB == 4, "the pinned slots above assume 4 loads, 4 + 8 fragments per stage");
+  static_assert(!kWide || (LPW == 4 && FB == 2 && TB == 4), "the pinned slots above assume 4 loads, 4 + 8 fragments per stage");
   // Stages run in pairs (the feature fragments alternate between two register sets); an odd count starts with a
   // single stage and one copy of its set.  The very last stage requests nothing beyond itself.
   {
@@ -368,17 +435,21 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
         if (a == 0 && b < 5) read_b(buf, b + 3);
       }
   }
+  }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // drain the tail refills before the wave ends
 
-  constexpr int kAccRegs = FB * 2 * TB * 2 * 4;  // 128
+  constexpr int kAccRegs = FB * 2 * TB * 2 * 4;  // 128 in the wide form
+  const float *rstd = p.rstd;
+  int rstd0 = 0;  // row that rstd[0] belongs to
   // ------------------------------------------------------------------ split K: the last workgroup of a tile adds up
-  if (p.ksplit > 1) {
+  if (ksplit > 1) {
+    const size_t unit0 = kWide || q < p.first ? (size_t)q * ksplit : (size_t)p.first * p.ksplit + (size_t)(q - p.first) * ksplit;
     // Every workgroup of a tile leaves its fp32 accumulators of the live token blocks in the
     // scratch area (write-through stores, completed before its arrival is counted); the one
     // that arrives last reads all slices back in slice order - so the sum does not depend on
     // which one that is - and goes on to the epilogue.  Plain loads suffice: every line has one
     // writer in this launch and no reader before the counter says so.
-    float *mine = p.split_ws + (((size_t)q * p.ksplit + slice) * (WF * WT) + wave) * (kAccRegs * 64);
+    float *mine = p.split_ws + ((unit0 + slice) * (WF * WT) + wave) * (kAccRegs * 64);
 #pragma unroll
     for (int j = 0; j < TB; ++j) {
       if (tb0 + wt * TB + j >= p.tok_blocks) continue;
@@ -395,12 +466,12 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
     __syncthreads();
     if (threadIdx.x == 0) {
       unsigned old = atomicAdd(&p.split_counters[q], 1u);
-      split_last = old == (unsigned)p.ksplit - 1 ? 1u : 0u;
+      split_last = old == (unsigned)ksplit - 1 ? 1u : 0u;
       if (split_last) p.split_counters[q] = 0;  // ready for the next launch
     }
     __syncthreads();
     if (!split_last) return;
-    const float *tile_ws = p.split_ws + ((size_t)q * p.ksplit * (WF * WT) + wave) * (kAccRegs * 64);
+    const float *tile_ws = p.split_ws + (unit0 * (WF * WT) + wave) * (kAccRegs * 64);
     const size_t slice_stride = (size_t)(WF * WT) * (kAccRegs * 64);
 #pragma unroll
     for (int j = 0; j < TB; ++j) {
@@ -410,13 +481,13 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
         float sum[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) sum[r] = 0.f;
-        for (int s0 = 0; s0 < p.ksplit; s0 += 4) {  // 4 slices x 16 values in flight
+        for (int s0 = 0; s0 < ksplit; s0 += 4) {  // 4 slices x 16 values in flight
           float v[4][16];
 #pragma unroll
           for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              v[u][r] = s0 + u < p.ksplit ? tile_ws[(size_t)(s0 + u) * slice_stride + ((i * TB + j) * 16 + r) * 64 + lane] : 0.f;
+              v[u][r] = s0 + u < ksplit ? tile_ws[(size_t)(s0 + u) * slice_stride + ((i * TB + j) * 16 + r) * 64 + lane] : 0.f;
 #pragma unroll
           for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -425,6 +496,38 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][(r >> 3) & 1][j][(r >> 2) & 1][r & 3] = sum[r];
       }
+    }
+  }
+
+  if constexpr (!kWide && (EPI == EPI_QKV || EPI == EPI_SWIGLU)) {
+    // The RMS Norm factors of the tile's tokens from the sums of squares that the residual epilogue before this GEMM
+    // left: a launch of its own costs 5 us for at most 128 rows.  LDS is free here (the drained loop's stages).
+    if (p.ssq_in) {
+      constexpr int kTok = XB * 32, kParts = WF * WT * 64 / kTok;
+      float *part = (float *)lds, *factor = part + WF * WT * 64;
+      const int tkn = threadIdx.x % kTok, row = tb0 * 32 + tkn, rows = p.tok_blocks * 32;
+      float sum = 0.f;
+      if (row < rows)
+        for (int g0 = threadIdx.x / kTok; g0 < p.ssq_groups; g0 += 16 * kParts) {
+          float v[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) v[u] = g0 + u * kParts < p.ssq_groups ? p.ssq_in[(size_t)(g0 + u * kParts) * rows + row] : 0.f;
+#pragma unroll
+          for (int u = 0; u < 16; ++u) sum += v[u];
+        }
+      __syncthreads();  // every wave has left the loop
+      part[threadIdx.x] = sum;
+      __syncthreads();
+      if (threadIdx.x < kTok) {
+        float tot = 0.f;
+#pragma unroll
+        for (int i = 0; i < kParts; ++i) tot += part[i * kTok + threadIdx.x];
+        // a padding row's factor is 0: its sum is 0, and no 1/0 when eps == 0
+        factor[threadIdx.x] = row < rows && p.row_ext[row] >= 0 ? 1.0f / sqrtf(tot * p.inv_H + p.eps) : 0.f;
+      }
+      __syncthreads();
+      rstd = factor;
+      rstd0 = tb0 * 32;
     }
   }
 
@@ -445,12 +548,12 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
             store4(p.out, p.out_K, tb * 32 + 16 * th + t16, (nb0 + wf * FB + i) * 32 + 16 * fh + q4, acc[i][fh][j][th]);
     }
   } else if (EPI == EPI_SWIGLU) {
-    // block 0 = gate, block 1 = up of FFN features [(tile_n*4 + wf)*32, +32)
+    // block 0 = gate, block 1 = up of FFN features [(tile_n*WF + wf)*32, +32)
     float rs_all[TB][2];  // requested together: one round trip for the whole epilogue
 #pragma unroll
     for (int j = 0; j < TB; ++j)
 #pragma unroll
-      for (int th = 0; th < 2; ++th) rs_all[j][th] = p.rstd[min(tb0 + wt * TB + j, p.tok_blocks - 1) * 32 + 16 * th + t16];
+      for (int th = 0; th < 2; ++th) rs_all[j][th] = rstd[min(tb0 + wt * TB + j, p.tok_blocks - 1) * 32 + 16 * th + t16 - rstd0];
 #pragma unroll
     for (int j = 0; j < TB; ++j) {
       int tb = tb0 + wt * TB + j;
@@ -467,7 +570,7 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
             float g = acc[0][fh][j][th][e] * rs, u = acc[1][fh][j][th][e] * rs;
             v[e] = g / (1.0f + __expf(-g)) * u;
           }
-          store4(p.out, p.out_K, row, (tile_n * 4 + wf) * 32 + 16 * fh + q4, v);
+          store4(p.out, p.out_K, row, (tile_n * WF + wf) * 32 + 16 * fh + q4, v);
         }
       }
     }
@@ -530,7 +633,7 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
       if (j + 2 < TB) fetch(j + 2);  // into the set this block has just left
     }
   } else {  // EPI_QKV
-    const int n0 = tile_n * 256;              // first packed row of this tile
+    const int n0 = tile_n * (NBK * 32);       // first packed row of this tile
     const int head_in_tile = wf >> 1, ib = (wf & 1) * 32;
     const bool rotary = n0 < p.qd + p.kvd;
     // what the epilogue needs per token is requested up front (one round trip), the rotary table's entries - which
@@ -542,7 +645,7 @@ __global__ void __launch_bounds__(WF * WT * 64) k_gemm(GemmParams p) {
 #pragma unroll
       for (int th = 0; th < 2; ++th) {
         const int row = min(tb0 + wt * TB + j, p.tok_blocks - 1) * 32 + 16 * th + t16;
-        pos_all[j][th] = p.row_pos[row]; req_all[j][th] = p.row_req[row]; rs_all[j][th] = p.rstd[row];
+        pos_all[j][th] = p.row_pos[row]; req_all[j][th] = p.row_req[row]; rs_all[j][th] = rstd[row - rstd0];
       }
     f32x4_t cs[2][2][2];  // [parity of the token half][fh][cos, sin]
     auto fetch_cs = [&](int h) {  // h = 2 j + th
@@ -625,8 +728,8 @@ hipError_t mfma_pack_weight(const bf16_t *src0, const bf16_t *src1, const bf16_t
 hipError_t mfma_prefill_begin(const bf16_t *hidden_in, float *xres, const bf16_t *gain, bf16_t *y, float *rstd,
                               const int *row_ext, int rows, int H, float eps, hipStream_t s) {
   if (rows == 0) return hipSuccess;
-  if (rows <= 64) k_add_norm<0, 1><<<rows, 256, 0, s>>>(hidden_in, xres, nullptr, gain, y, rstd, nullptr, row_ext, H, eps);
-  else k_add_norm<0, 8><<<rows / 8, 256, 0, s>>>(hidden_in, xres, nullptr, gain, y, rstd, nullptr, row_ext, H, eps);
+  if (rows <= 64) k_add_norm<0, 1><<<rows, kEndThreads, 0, s>>>(hidden_in, xres, nullptr, gain, y, rstd, nullptr, row_ext, H, eps);
+  else k_add_norm<0, 8><<<rows / 8, kEndThreads, 0, s>>>(hidden_in, xres, nullptr, gain, y, rstd, nullptr, row_ext, H, eps);
   return hipGetLastError();
 }
 
@@ -634,8 +737,8 @@ hipError_t mfma_prefill_end(const float *xres, const bf16_t *delta_bf, bf16_t *h
                             int rows, int H, hipStream_t s) {
   if (rows == 0) return hipSuccess;
   float *x = const_cast<float *>(xres);
-  if (rows <= 64) k_add_norm<1, 1><<<rows, 256, 0, s>>>(nullptr, x, delta_bf, nullptr, nullptr, nullptr, hidden_out, row_ext, H, 0.f);
-  else k_add_norm<1, 8><<<rows / 8, 256, 0, s>>>(nullptr, x, delta_bf, nullptr, nullptr, nullptr, hidden_out, row_ext, H, 0.f);
+  if (rows <= 64) k_add_norm<1, 1><<<rows, kEndThreads, 0, s>>>(nullptr, x, delta_bf, nullptr, nullptr, nullptr, hidden_out, row_ext, H, 0.f);
+  else k_add_norm<1, 8><<<rows / 8, kEndThreads, 0, s>>>(nullptr, x, delta_bf, nullptr, nullptr, nullptr, hidden_out, row_ext, H, 0.f);
   return hipGetLastError();
 }
 
@@ -649,7 +752,7 @@ constexpr int kGemmSplitCus = 256;    // workgroups that run at once (one per CU
 constexpr int kGemmSplitUnits = 512;  // most (tile, slice) pairs of a split GEMM
 
 // largest scratch a split GEMM can use: kGemmSplitUnits partial tiles of 256 x 256 fp32
-size_t mfma_gemm_split_ws_bytes() { return (size_t)kGemmSplitUnits * (WF * WT) * (FB * TB * 16 * 64) * sizeof(float); }
+size_t mfma_gemm_split_ws_bytes() { return (size_t)kGemmSplitUnits * (WideForm::WF * WideForm::WT) * (FB * WideForm::TB * 16 * 64) * sizeof(float); }
 
 // the (epilogue, class) pairs a block uses
 #define HYP_GEMM_VARIANTS(X)                                                                        \
@@ -659,7 +762,9 @@ size_t mfma_gemm_split_ws_bytes() { return (size_t)kGemmSplitUnits * (WF * WT) *
 hipError_t mfma_gemm_init() {
   hipError_t e = hipSuccess;
 #define X(EPI, CLS) \
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_gemm<EPI, CLS>, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_gemm<EPI, CLS, WideForm>, hipFuncAttributeMaxDynamicSharedMemorySize, WideForm::LDS); \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_gemm<EPI, CLS, Form64>, hipFuncAttributeMaxDynamicSharedMemorySize, Form64::LDS);     \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_gemm<EPI, CLS, Form128>, hipFuncAttributeMaxDynamicSharedMemorySize, Form128::LDS);
   HYP_GEMM_VARIANTS(X)
 #undef X
   return e;
@@ -670,13 +775,16 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
   if (rows == 0) return hipSuccess;
   GemmParams p = {};
   p.X = X; p.W = W; p.KT = K / 16; p.tok_blocks = rows / 32; p.feat_blocks = N / 32;
-  int tiles_t = (p.tok_blocks + XB - 1) / XB, tiles_n = p.feat_blocks / NBK;
+  constexpr int NST = WideForm::NST, XB = WideForm::XB, NBK = WideForm::NBK;
+  // up to 128 tokens: the weights' streaming time counts, not the products (see GemmForm)
+  const int form = p.tok_blocks <= Form64::XB ? 64 : p.tok_blocks <= Form128::XB ? 128 : 256;
+  int tiles_t = form < 256 ? 1 : (p.tok_blocks + XB - 1) / XB, tiles_n = p.feat_blocks / (form < 256 ? Form64::NBK : NBK);
   p.gm = tiles_t < 8 ? tiles_t : 8;
   p.n_tiles = tiles_t * tiles_n;
   p.out = out; p.out_K = out_K;
   p.Kc = ep.Kc; p.Vc = ep.Vc; p.geom = ep.geom; p.qd = ep.qd; p.kvd = ep.kvd;
   p.cos_tab = ep.cos_tab; p.sin_tab = ep.sin_tab; p.row_pos = ep.row_pos; p.row_req = ep.row_req;
-  p.rstd = ep.rstd; p.xres = ep.xres; p.gain = ep.gain; p.row_ext = ep.row_ext; p.ssq_part = ep.ssq_part;
+  p.rstd = ep.rstd; p.ssq_in = ep.ssq_in; p.ssq_groups = ep.ssq_in ? K / 64 : 0; p.inv_H = 1.0f / (float)K; p.eps = ep.eps; p.xres = ep.xres; p.gain = ep.gain; p.row_ext = ep.row_ext; p.ssq_part = ep.ssq_part;
   p.tiles_grid = (p.n_tiles + 7) / 8 * 8;
   // Few output tiles (short prompts): split the K loop over c workgroups per tile when a simple
   // model says it pays.  Rounds of 256 workgroups times the share of a tile's K loop each one
@@ -684,7 +792,33 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
   // at the ~3 TB/s write-through stores and the gather reach) plus the extra round trips.
   // Slices are whole numbers of stages, at least 2 NST of them each.
   p.ksplit = 1;
-  if (ep.split_ws && ep.split_counters && p.n_tiles <= kGemmSplitMaxTiles) {
+  if (form < 256) {
+    p.first = p.n_tiles;
+    if (ep.split_ws && ep.split_counters && p.n_tiles <= kGemmShortMaxTiles) {
+      // The short forms: the chip streams as much as its workgroups keep in flight over 2.9 us of loaded latency, 6 TB/s
+      // at best, a CU with one workgroup more than the others is waited for, and a split pays for its partial tiles as below.
+      const int nsteps = p.KT / KTS, nst = form == 64 ? Form64::NST : Form128::NST;
+      const double in_flight = (nst - 1) * (double)Form64::NBK * KTS * 1024, bytes = 2.0 * N * K;
+      double best = 1e30;
+      for (int c = 1; c == 1 || (c <= 32 && p.n_tiles * c <= kGemmSplitUnits); ++c) {
+        if (c > 1 && (nsteps % c != 0 || nsteps / c < 2 * nst)) continue;
+        const int units = p.n_tiles * c, per_cu = (units + kGemmSplitCus - 1) / kGemmSplitCus;
+        const double even = units <= kGemmSplitCus ? 1.0 : units / ((double)per_cu * kGemmSplitCus);
+        const double partial_mb = (double)units * p.tok_blocks * Form64::NBK * 4096.0 * 2 / 1e6;
+        const double t = bytes / (std::min(6.0e6, units * in_flight / 2.9) * even) + (c > 1 ? partial_mb / 3.0 + 5.0 : 0.0);
+        if (t < best) { best = t; p.ksplit = c; }
+      }
+      // More tiles than CUs, unsplit: the ones beyond the first 256 (24 of gate/up's 280) would double a few CUs' work.
+      // They are split so that they spread over all CUs beside the others.
+      const int rest = p.n_tiles - kGemmSplitCus;
+      if (p.ksplit == 1 && rest > 0)
+        for (int c = 16; c >= 2; --c)
+          if (nsteps % c == 0 && nsteps / c >= 2 * nst && rest * c <= kGemmSplitCus) {
+            p.first = kGemmSplitCus; p.ksplit2 = c;
+            break;
+          }
+    }
+  } else if (ep.split_ws && ep.split_counters && p.n_tiles <= kGemmSplitMaxTiles) {
     const int nsteps = p.KT / KTS;
     const double tile_us = K * 0.0267;  // 256 x 256 x K on one CU at the rate the big GEMMs run at
     const int live_blocks = p.tok_blocks < XB ? p.tok_blocks : XB;
@@ -710,10 +844,15 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
     p.pool_wgs = (2 * (p.n_tiles - p.n_static) + 7) / 8 * 8;
     p.tiles_grid = p.n_static + p.pool_wgs;
   }
-  int grid = p.tiles_grid * p.ksplit;
+  int grid = form < 256 ? p.first * p.ksplit + (p.n_tiles - p.first) * p.ksplit2 : p.tiles_grid * p.ksplit;
   bool launched = false;
 #define X(EPI, CLS) \
-  if (!launched && epi == EPI && cls == CLS) { k_gemm<EPI, CLS><<<grid, WF * WT * 64, GEMM_LDS, s>>>(p); launched = true; }
+  if (!launched && epi == EPI && cls == CLS) {                                                                       \
+    if (form == 64) k_gemm<EPI, CLS, Form64><<<grid, Form64::WF * Form64::WT * 64, Form64::LDS, s>>>(p);                      \
+    else if (form == 128) k_gemm<EPI, CLS, Form128><<<grid, Form128::WF * Form128::WT * 64, Form128::LDS, s>>>(p);             \
+    else k_gemm<EPI, CLS, WideForm><<<grid, WideForm::WF * WideForm::WT * 64, WideForm::LDS, s>>>(p);                           \
+    launched = true;                                                                                                 \
+  }
   HYP_GEMM_VARIANTS(X)
 #undef X
   if (!launched) return hipErrorInvalidValue;

@@ -213,7 +213,7 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
     L.attn_part = take(L.attn_part_bytes);
     L.counters_bytes = sizeof(unsigned) * (2 * I / 64 + (qd + 2 * kvd) / 64 + H / 32);
     L.counters = take(L.counters_bytes);
-    L.gemm_counters = take(sizeof(unsigned) * kGemmSplitMaxTiles);  // zeroed together with `counters`
+    L.gemm_counters = take(sizeof(unsigned) * (kGemmShortMaxTiles + 1));  // zeroed together with `counters`
     L.ssq = take(sizeof(float) * 32 * (H / 32));
     L.gemm_ws = take(mfma_gemm_split_ws_bytes());
     if (L.pages_per_req) L.page_table = take(sizeof(int) * (size_t)c.max_batch * L.pages_per_req);
@@ -416,6 +416,7 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
   float *rstd = at<float>(st, L.rstd), *ssq_part = at<float>(st, L.ssq_part);
   PROF(st, HYP_K_ADD_NORM, mfma_prefill_begin((const bf16_t *)hidden_in, xres, at<bf16_t>(st, L.layers[0].g1), y, rstd,
                                                row_ext, rows, d.H, d.eps, s));
+  const bool short_rows = rows <= kShortRows;
   GemmEpilogue split;  // scratch of GEMMs that split their K loop (short prompts leave few output tiles)
   split.split_ws = at<float>(st, L.gemm_ws); split.split_counters = at<unsigned>(st, L.gemm_counters);
   for (int l = 0; l < st->n_layers; ++l) {
@@ -427,7 +428,9 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
     e.geom = geom; e.qd = d.qd; e.kvd = d.kvd;
     e.cos_tab = at<float>(st, L.cos_tab); e.sin_tab = at<float>(st, L.sin_tab);
     e.row_pos = at<int>(st, L.row_pos); e.row_req = at<int>(st, L.row_req);
-    e.rstd = rstd;
+    // short prompts: the consumer adds up the sums of squares itself (the first block's come as factors)
+    if (short_rows && l > 0) { e.ssq_in = ssq_part; e.eps = d.eps; e.row_ext = row_ext; }
+    else e.rstd = rstd;
     PROF(st, HYP_K_GEMM_QKV, mfma_gemm(EPI_QKV, HYP_K_GEMM_QKV, y, at<bf16_t>(st, p.wqkv), rows, d.qd + 2 * d.kvd, d.H, q, d.qd, e, s));
     PROF(st, HYP_K_ATTN_PREFILL, mfma_attn_prefill(q, e.Kc, e.Vc, geom, attn, at<PrefillTile>(st, L.tiles), n_tiles,
                                   at<int>(st, L.req_len), d.nq, d.nkv, s));
@@ -436,14 +439,15 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
     r.xres = xres; r.row_ext = row_ext; r.ssq_part = ssq_part;
     r.gain = at<bf16_t>(st, p.g2);
     PROF(st, HYP_K_GEMM_O, mfma_gemm(EPI_RESID, HYP_K_GEMM_O, attn, at<bf16_t>(st, p.wo), rows, d.H, d.qd, y, d.H, r, s));
-    PROF(st, HYP_K_ADD_NORM, mfma_rstd(ssq_part, rstd, row_ext, rows, d.H, d.eps, s));
+    if (!short_rows) PROF(st, HYP_K_ADD_NORM, mfma_rstd(ssq_part, rstd, row_ext, rows, d.H, d.eps, s));
     GemmEpilogue g = split;
-    g.rstd = rstd;
+    if (short_rows) { g.ssq_in = ssq_part; g.eps = d.eps; g.row_ext = row_ext; }
+    else g.rstd = rstd;
     PROF(st, HYP_K_GEMM_GATEUP, mfma_gemm(EPI_SWIGLU, HYP_K_GEMM_GATEUP, y, at<bf16_t>(st, p.wgu), rows, 2 * d.I, d.H, m, d.I, g, s));
     if (!last) {
       r.gain = at<bf16_t>(st, L.layers[l + 1].g1);
       PROF(st, HYP_K_GEMM_DOWN, mfma_gemm(EPI_RESID, HYP_K_GEMM_DOWN, m, at<bf16_t>(st, p.wd), rows, d.H, d.I, y, d.H, r, s));
-      PROF(st, HYP_K_ADD_NORM, mfma_rstd(ssq_part, rstd, row_ext, rows, d.H, d.eps, s));
+      if (!short_rows) PROF(st, HYP_K_ADD_NORM, mfma_rstd(ssq_part, rstd, row_ext, rows, d.H, d.eps, s));
     } else {
       PROF(st, HYP_K_GEMM_DOWN, mfma_gemm(EPI_STORE, HYP_K_GEMM_DOWN, m, at<bf16_t>(st, p.wd), rows, d.H, d.I, delta, d.H, split, s));
       PROF(st, HYP_K_ADD_NORM, mfma_prefill_end(xres, delta, (bf16_t *)hidden_out, row_ext, rows, d.H, s));
