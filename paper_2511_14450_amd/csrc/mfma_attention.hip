@@ -66,7 +66,7 @@ __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(
 template <int G>
 __global__ void __launch_bounds__(128 * G) k_attn_prefill(const bf16_t *__restrict__ q,
                                                       const bf16_t *__restrict__ Kc,
-                                                      const bf16_t *__restrict__ Vc, CacheGeom geom,
+                                                      bf16_t *Vc, CacheGeom geom,
                                                       bf16_t *__restrict__ out,
                                                       const PrefillTile *__restrict__ tiles,
                                                       const int *__restrict__ req_len, int nq) {
@@ -85,6 +85,7 @@ __global__ void __launch_bounds__(128 * G) k_attn_prefill(const bf16_t *__restri
   const int n_kb = min(tile.qblk0 + 2, (len + 31) >> 5);  // 32-key blocks the tile needs
   const int n_st = (n_kb + 1) >> 1;                        // 64-key stages; every wave of the tile needs all of them
   const int rb = (tile.row0 >> 5) + tq;
+  const int orow = tile.out0 + tq * 32 + tl;  // row of out
   const float c = kLog2e * 0.08838834764831845f;  // log2(e) / sqrt(128)
   const int qpos = qblk * 32 + tl;
 
@@ -92,6 +93,13 @@ __global__ void __launch_bounds__(128 * G) k_attn_prefill(const bf16_t *__restri
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt)
     qf[dt] = *(const bf16x8_t *)(q + ((size_t)rb * (qd >> 4) + head * 8 + dt) * kTileElems + lane * 8);
+  // rows of q behind the request hold whatever an earlier call left: they count as zero (a wave moves its maxima together)
+  if (qpos >= len) {
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qf[dt][e] = (__bf16)0.f;
+  }
 
   f32x16_t o[4];
 #pragma unroll
@@ -153,13 +161,19 @@ __global__ void __launch_bounds__(128 * G) k_attn_prefill(const bf16_t *__restri
     }
   };
   // O^T += V^T P^T for the stage in `buf`
-  auto values = [&](int buf, const bf16x8_t *pf) {
+  // (the last stage's; key slots from `end` on, counted from the stage, hold anything and count as zero)
+  auto values = [&](int buf, const bf16x8_t *pf, int end) {
     const char *base = lds + buf * kKvStageBytes + lane * 16;
 #pragma unroll
     for (int h2 = 0; h2 < 4; ++h2)   // (key block, MFMA step) pairs
 #pragma unroll
       for (int db = 0; db < 4; ++db) {
         bf16x8_t vf = *(const bf16x8_t *)(base + (h2 >> 1) * 16384 + (8 + (h2 & 1) * 4 + db) * 1024);
+        if (end < kKvStageKeys) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (h2 * 16 + 8 * (e >> 2) + 4 * hh + (e & 3) >= end) vf[e] = (__bf16)0.f;
+        }
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[h2], o[db], 0, 0, 0);
       }
   };
@@ -271,14 +285,14 @@ __global__ void __launch_bounds__(128 * G) k_attn_prefill(const bf16_t *__restri
   // last stage: the only one that touches the diagonal (a block past the tile's need is fully
   // masked here: its keys lie after every row)
   {
-    const int kb0 = (n_st - 1) * 2;
+    const int kb0 = (n_st - 1) * 2, qlast = min(qpos, len - 1);
     float p[32];
     mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       int koff = 8 * (r >> 2) + 4 * hh + (r & 3);
-      p[r] = (kb0 * 32 + koff > qpos) ? -INFINITY : s0[r];
-      p[16 + r] = (kb0 * 32 + 32 + koff > qpos) ? -INFINITY : s1[r];
+      p[r] = (kb0 * 32 + koff > qlast) ? -INFINITY : s0[r];
+      p[16 + r] = (kb0 * 32 + 32 + koff > qlast) ? -INFINITY : s1[r];
       mx = fmaxf(mx, fmaxf(p[r], p[16 + r]));
     }
     follow_max(mx);
@@ -291,20 +305,33 @@ __global__ void __launch_bounds__(128 * G) k_attn_prefill(const bf16_t *__restri
     }
     l_run += rowsum;
     pf[0] = probs_operand(p, 0); pf[1] = probs_operand(p, 1); pf[2] = probs_operand(p + 16, 0); pf[3] = probs_operand(p + 16, 1);
-    values(buf, pf);
+    values(buf, pf, len - kb0 * 32);
   }
 
   // normalise and store into P(rows, qd): lane owns query tl, features 8g + 4hh + e of each d block
   float inv = 1.0f / xhalf_sum(l_run);
+  if (qpos < len) {
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < 4; ++db)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      int f0 = head * 128 + db * 32;
-      size_t off = ((size_t)rb * (qd >> 4) + ((f0 + 8 * g) >> 4)) * kTileElems + (((g & 1) << 5) + tl) * 8 + hh * 4;
-      *(bf16x4_t *)(out + off) = pack4(o[db][4 * g] * inv, o[db][4 * g + 1] * inv, o[db][4 * g + 2] * inv,
-                                       o[db][4 * g + 3] * inv);
+      for (int g = 0; g < 4; ++g) {
+        int f0 = head * 128 + db * 32;
+        size_t off = ((size_t)(orow >> 5) * (qd >> 4) + ((f0 + 8 * g) >> 4)) * kTileElems + (((g & 1) << 5) + (orow & 31)) * 8 + hh * 4;
+        *(bf16x4_t *)(out + off) = pack4(o[db][4 * g] * inv, o[db][4 * g + 1] * inv, o[db][4 * g + 2] * inv,
+                                         o[db][4 * g + 3] * inv);
+      }
+  }
+  // Decode steps multiply the slots behind the last key by probabilities of zero: the tile that ends the request clears
+  // them up to a multiple of 64 keys (no other workgroup reads that stage, and this one masks it above).
+  if ((tile.qblk0 + 2) * 32 >= len) {
+    const int pad = (-len) & 63;
+    for (int i = threadIdx.x; i < pad * 128; i += 128 * G) {
+      const int key = len + (i >> 7), d = i & 127;
+      int m, khh;
+      const int e = vtile_slot_of_key(key & 31, &m, &khh);
+      Vc[geom.off(tile.req, kvh, key >> 5) + (size_t)(m * 4 + (d >> 5)) * kTileElems + (khh * 32 + (d & 31)) * 8 + e] = 0;
     }
+  }
 }
 
 // ----------------------------------------------------------------------------
@@ -616,7 +643,7 @@ __global__ void __launch_bounds__(128) k_attn_decode_merge(const float *__restri
 
 }  // namespace
 
-hipError_t mfma_attn_prefill(const bf16_t *q, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
+hipError_t mfma_attn_prefill(const bf16_t *q, const bf16_t *Kc, bf16_t *Vc, CacheGeom geom,
                              bf16_t *out, const PrefillTile *tiles, int n_tiles, const int *req_len,
                              int nq, int nkv, hipStream_t s) {
   if (n_tiles == 0) return hipSuccess;

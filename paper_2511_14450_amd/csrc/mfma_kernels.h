@@ -16,7 +16,8 @@ struct GemmEpilogue {
   CacheGeom geom = {};
   int qd = 0, kvd = 0;
   const float *cos_tab = nullptr, *sin_tab = nullptr;  // [position][64]
-  const int *row_pos = nullptr, *row_req = nullptr;    // per internal row
+  const int *row_pos = nullptr, *row_req = nullptr;    // per internal row; row_req < 0: padding, nothing is written
+  const int *row_q = nullptr;                          // row of q that a row's queries go to
   // EPI_QKV, EPI_SWIGLU: RMS Norm factor of every input row (the rows carry the gain only)
   const float *rstd = nullptr;
   // up to kShortRows rows: the sums of squares (ssq_part of the GEMM before) instead, null where rstd is given; row_ext too
@@ -59,11 +60,12 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
                      int out_K, const GemmEpilogue &ep, hipStream_t s);
 
 // Causal GQA attention over the prompt (flash-style, scores never stored).
-//   q P(rows, nq*128) ; caches of the layer ; out P(rows, nq*128)
-//   work items: (request, first internal row, query blocks) per 64-row query tile
-struct PrefillTile { int req, row0, qblk0; };  // qblk0: index of the tile's first 32-row block in the request
+//   q P(rows of q, nq*128), requests padded to 64 rows ; caches of the layer ; out P(rows, nq*128), packed
+//   work items per 64-row query tile: request, first row of q, index of its first 32-row block in the request, first
+//   row of out.  The tile that ends a request clears the value slots behind it, up to a multiple of 64 keys.
+struct PrefillTile { int req, row0, qblk0, out0; };
 hipError_t mfma_attn_init();  // kernel attributes, once per process and device
-hipError_t mfma_attn_prefill(const bf16_t *q, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
+hipError_t mfma_attn_prefill(const bf16_t *q, const bf16_t *Kc, bf16_t *Vc, CacheGeom geom,
                              bf16_t *out, const PrefillTile *tiles, int n_tiles, const int *req_len,
                              int nq, int nkv, hipStream_t s);
 

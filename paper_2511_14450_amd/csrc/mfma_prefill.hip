@@ -197,7 +197,7 @@ struct GemmParams {
   CacheGeom geom;
   int qd, kvd;
   const float *cos_tab, *sin_tab;  // [pos][64]
-  const int *row_pos, *row_req;    // per internal row
+  const int *row_pos, *row_req, *row_q;  // per internal row
   const float *rstd;               // EPI_QKV / EPI_SWIGLU: RMS Norm factor of every row of X
   // EPI_RESID: residual stream A(T', N), gains of the next norm, padding map, statistics out
   float *xres;
@@ -638,14 +638,14 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
     const bool rotary = n0 < p.qd + p.kvd;
     // what the epilogue needs per token is requested up front (one round trip), the rotary table's entries - which
     // wait for the positions - one token half ahead of their use
-    int pos_all[TB][2], req_all[TB][2];
+    int pos_all[TB][2], req_all[TB][2], rq_all[TB][2];
     float rs_all[TB][2];
 #pragma unroll
     for (int j = 0; j < TB; ++j)
 #pragma unroll
       for (int th = 0; th < 2; ++th) {
         const int row = min(tb0 + wt * TB + j, p.tok_blocks - 1) * 32 + 16 * th + t16;
-        pos_all[j][th] = p.row_pos[row]; req_all[j][th] = p.row_req[row]; rs_all[j][th] = rstd[row - rstd0];
+        pos_all[j][th] = p.row_pos[row]; req_all[j][th] = p.row_req[row]; rq_all[j][th] = p.row_q[row]; rs_all[j][th] = rstd[row - rstd0];
       }
     f32x4_t cs[2][2][2];  // [parity of the token half][fh][cos, sin]
     auto fetch_cs = [&](int h) {  // h = 2 j + th
@@ -665,8 +665,9 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
       for (int th = 0; th < 2; ++th) {
         if (2 * j + th + 1 < 2 * TB) fetch_cs(2 * j + th + 1);
         if (tb >= p.tok_blocks) continue;
-        const int row = tb * 32 + 16 * th + t16;
+        const int row = rq_all[j][th];
         const int pos = pos_all[j][th], req = req_all[j][th];
+        if (req < 0) continue;  // padding behind the last request
         const float rs = rs_all[j][th];
         if (rotary) {
           // q or k: rotate the pair (d, d + 64) by the angle of this position; block 0 holds d, block 1 d + 64
@@ -783,7 +784,7 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
   p.n_tiles = tiles_t * tiles_n;
   p.out = out; p.out_K = out_K;
   p.Kc = ep.Kc; p.Vc = ep.Vc; p.geom = ep.geom; p.qd = ep.qd; p.kvd = ep.kvd;
-  p.cos_tab = ep.cos_tab; p.sin_tab = ep.sin_tab; p.row_pos = ep.row_pos; p.row_req = ep.row_req;
+  p.cos_tab = ep.cos_tab; p.sin_tab = ep.sin_tab; p.row_pos = ep.row_pos; p.row_req = ep.row_req; p.row_q = ep.row_q;
   p.rstd = ep.rstd; p.ssq_in = ep.ssq_in; p.ssq_groups = ep.ssq_in ? K / 64 : 0; p.inv_H = 1.0f / (float)K; p.eps = ep.eps; p.xres = ep.xres; p.gain = ep.gain; p.row_ext = ep.row_ext; p.ssq_part = ep.ssq_part;
   p.tiles_grid = (p.n_tiles + 7) / 8 * 8;
   // Few output tiles (short prompts): split the K loop over c workgroups per tile when a simple

@@ -69,7 +69,7 @@ struct Layout {
   int q_ld = 0, rows_pad = 0;
   PlainCache cache = {};
   // MFMA path only
-  size_t q = 0, delta = 0, row_ext = 0, row_pos = 0, row_req = 0, req_len = 0, row_ext_dec = 0, qdec = 0,
+  size_t q = 0, delta = 0, qdec = 0,
          partial = 0, attn_part = 0, counters = 0, gemm_counters = 0, rstd = 0, ssq_part = 0, gemm_ws = 0;
   size_t kv_bytes = 0;  // bytes of each of Kc, Vc over all layers
   int rows_cap = 0;     // internal rows the scratch holds
@@ -142,6 +142,11 @@ hyp_status_t check_config(const hyp_stage_config_t *c, int32_t l_start, int32_t 
   return HYP_OK;
 }
 
+// ints of a prefill's upload: lengths, four arrays of up to `rows` rows, tiles
+size_t prefill_upload_ints(int max_batch, int rows) {
+  return (size_t)max_batch + 4 * (size_t)rows + sizeof(PrefillTile) / sizeof(int) * ((size_t)rows / 64);
+}
+
 void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
   size_t es = elem_size(c);
   size_t H = c.hidden, qd = (size_t)c.n_q_heads * c.head_dim, kvd = (size_t)c.n_kv_heads * c.head_dim;
@@ -164,7 +169,7 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
     p.wd = take(operand(H, I));
   }
   if (mfma) {
-    // every request's rows are padded to a multiple of 64 (one query tile)
+    // queries keep every request's rows padded to a multiple of 64 (one query tile); everything else is packed
     L.rows_cap = round_up((int)c.max_prefill_tokens + 63 * c.max_batch, 64);
     if (L.rows_cap < 64) L.rows_cap = 64;
     R = L.rows_cap;
@@ -190,13 +195,8 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
     L.delta = take(es * R * H);
     L.rstd = take(sizeof(float) * R);
     L.ssq_part = take(sizeof(float) * R * (H / 64));
-    L.row_ext = take(sizeof(int) * R);
-    L.row_pos = take(sizeof(int) * R);
-    L.row_req = take(sizeof(int) * R);
-    L.tiles = take(sizeof(PrefillTile) * (R / 64));
-    L.req_len = take(sizeof(int) * c.max_batch);
-    L.lens = take(sizeof(int) * c.max_batch);
-    L.row_ext_dec = take(sizeof(int) * 32);
+    // what a prefill uploads in one piece: cached lengths, then the per-row arrays and query tiles of the call
+    L.lens = take(sizeof(int) * prefill_upload_ints(c.max_batch, L.rows_cap));
     L.qdec = take(es * (size_t)c.max_batch * c.n_kv_heads * 32 * 128);
     L.g_qkv = mfma_gemv_plan(HYP_K_GEMV_QKV, (int)(qd + 2 * kvd), (int)H, c.max_batch);
     L.g_o = mfma_gemv_plan(HYP_K_GEMV_O, (int)H, (int)qd, c.max_batch);
@@ -403,7 +403,7 @@ CacheGeom cache_geom(const hyp_stage *st) {
   return g;
 }
 
-// prefill through the MFMA kernels; `rows` internal rows (multiple of 64)
+// prefill through the MFMA kernels; `rows` internal rows (multiple of 32)
 hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden_out, int rows, int n_tiles) {
   const Dims &d = st->dm;
   hipStream_t s = st->stream;
@@ -411,7 +411,9 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
   float *xres = at<float>(st, L.xres);
   bf16_t *y = at<bf16_t>(st, L.y), *q = at<bf16_t>(st, L.q), *attn = at<bf16_t>(st, L.attn);
   bf16_t *m = at<bf16_t>(st, L.m), *delta = at<bf16_t>(st, L.delta);
-  const int *row_ext = at<int>(st, L.row_ext);
+  // the upload of this call (do_stage_prefill)
+  const int *row_ext = at<int>(st, L.lens) + st->cfg.max_batch, *row_pos = row_ext + rows, *row_req = row_pos + rows, *row_q = row_req + rows;
+  const PrefillTile *tiles = (const PrefillTile *)(row_q + rows);
   CacheGeom geom = cache_geom(st);
   float *rstd = at<float>(st, L.rstd), *ssq_part = at<float>(st, L.ssq_part);
   PROF(st, HYP_K_ADD_NORM, mfma_prefill_begin((const bf16_t *)hidden_in, xres, at<bf16_t>(st, L.layers[0].g1), y, rstd,
@@ -427,13 +429,13 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
     e.Vc = at<bf16_t>(st, L.Vc + L.kv_layer_stride * l);
     e.geom = geom; e.qd = d.qd; e.kvd = d.kvd;
     e.cos_tab = at<float>(st, L.cos_tab); e.sin_tab = at<float>(st, L.sin_tab);
-    e.row_pos = at<int>(st, L.row_pos); e.row_req = at<int>(st, L.row_req);
+    e.row_pos = row_pos; e.row_req = row_req; e.row_q = row_q;
     // short prompts: the consumer adds up the sums of squares itself (the first block's come as factors)
     if (short_rows && l > 0) { e.ssq_in = ssq_part; e.eps = d.eps; e.row_ext = row_ext; }
     else e.rstd = rstd;
     PROF(st, HYP_K_GEMM_QKV, mfma_gemm(EPI_QKV, HYP_K_GEMM_QKV, y, at<bf16_t>(st, p.wqkv), rows, d.qd + 2 * d.kvd, d.H, q, d.qd, e, s));
-    PROF(st, HYP_K_ATTN_PREFILL, mfma_attn_prefill(q, e.Kc, e.Vc, geom, attn, at<PrefillTile>(st, L.tiles), n_tiles,
-                                  at<int>(st, L.req_len), d.nq, d.nkv, s));
+    PROF(st, HYP_K_ATTN_PREFILL, mfma_attn_prefill(q, e.Kc, e.Vc, geom, attn, tiles, n_tiles,
+                                  at<int>(st, L.lens), d.nq, d.nkv, s));
     // residual add, the next norm's gain and its statistics all happen in the epilogue
     GemmEpilogue r = split;
     r.xres = xres; r.row_ext = row_ext; r.ssq_part = ssq_part;
@@ -705,7 +707,7 @@ hyp_status_t do_stage_create(const hyp_stage_config_t *cfg, int32_t l_start, int
     return code;
   };
 
-  st->h_stage_ints = st->mfma ? 3 * (size_t)st->L.rows_cap + 3 * ((size_t)st->L.rows_cap / 64) + 2 * (size_t)cfg->max_batch + 32
+  st->h_stage_ints = st->mfma ? prefill_upload_ints(cfg->max_batch, st->L.rows_cap)
                               : 2 * (size_t)max_rows(*cfg) + (size_t)cfg->max_batch + 4 * ((size_t)max_rows(*cfg) / 16 + cfg->max_batch);
   if (hipHostMalloc((void **)&st->h_stage, sizeof(int) * st->h_stage_ints, hipHostMallocDefault) != hipSuccess) {
     st->h_stage = nullptr; st->err = "hipHostMalloc failed";
@@ -819,42 +821,35 @@ hyp_status_t do_stage_prefill(hyp_stage_t *st, const void *hidden_in, const int3
   if (rc != HYP_OK) return rc;
   hipStream_t s = st->stream;
   if (st->mfma) {
-    // internal rows: every request starts at a multiple of 64 and is padded to one
+    // Internal rows: the requests one after the other as they come, the last block of 32 filled up.  Only the
+    // queries - whose 32-row blocks the attention kernel takes as they are - keep every request padded to a multiple
+    // of 64: row_q says where a row's query goes.
     const Layout &L = st->L;
-    int R = 0;
-    for (int b = 0; b < batch; ++b) R += round_up(seq_lens[b], 64);
-    int *h_ext = st->h_stage, *h_pos = h_ext + R, *h_req = h_pos + R;
-    PrefillTile *h_tiles = (PrefillTile *)(h_req + R);
-    int n_tiles = R / 64;
-    int *h_len = (int *)(h_tiles + n_tiles), *h_ext_dec = h_len + batch;
-    int row = 0, ext = 0, nt = 0;
+    const int R = round_up(rows, 32);
+    int *h_len = st->h_stage, *h_ext = h_len + st->cfg.max_batch, *h_pos = h_ext + R, *h_req = h_pos + R, *h_q = h_req + R;
+    PrefillTile *h_tiles = (PrefillTile *)(h_q + R);
+    int row = 0, row_q = 0, nt = 0;
+    for (int b = 0; b < st->cfg.max_batch; ++b) h_len[b] = b < batch ? seq_lens[b] : 0;
     for (int b = 0; b < batch; ++b) {
-      int padded = round_up(seq_lens[b], 64);
-      for (int p = 0; p < padded; ++p, ++row) {
-        h_ext[row] = p < seq_lens[b] ? ext + p : -1;
+      for (int qb = 0; qb * 32 < seq_lens[b]; qb += 2) h_tiles[nt++] = PrefillTile{b, row_q + qb * 32, qb, row + qb * 32};
+      for (int p = 0; p < seq_lens[b]; ++p, ++row) {
+        h_ext[row] = row;
         h_pos[row] = p;
         h_req[row] = b;
+        h_q[row] = row_q + p;
       }
-      for (int qb = 0; qb < padded / 32; qb += 2) h_tiles[nt++] = PrefillTile{b, row - padded + qb * 32, qb};
-      ext += seq_lens[b];
-      h_len[b] = seq_lens[b];
+      row_q += round_up(seq_lens[b], 64);
     }
+    for (; row < R; ++row) { h_ext[row] = -1; h_pos[row] = 0; h_req[row] = -1; h_q[row] = 0; }
     // causal attention work grows with a tile's position in its request: longest tiles first,
     // so that the launch ends on short ones
     std::sort(h_tiles, h_tiles + nt, [](const PrefillTile &a, const PrefillTile &b) {
       return a.qblk0 != b.qblk0 ? a.qblk0 > b.qblk0 : a.row0 < b.row0;  // total order, in place
     });
-    for (int i = 0; i < 32; ++i) h_ext_dec[i] = i < batch ? i : -1;
-    HIP_TRY(st, hipMemcpyAsync(st->ws + L.row_ext, h_ext, sizeof(int) * R, hipMemcpyHostToDevice, s));
-    HIP_TRY(st, hipMemcpyAsync(st->ws + L.row_pos, h_pos, sizeof(int) * R, hipMemcpyHostToDevice, s));
-    HIP_TRY(st, hipMemcpyAsync(st->ws + L.row_req, h_req, sizeof(int) * R, hipMemcpyHostToDevice, s));
-    HIP_TRY(st, hipMemcpyAsync(st->ws + L.tiles, h_tiles, sizeof(PrefillTile) * n_tiles, hipMemcpyHostToDevice, s));
-    HIP_TRY(st, hipMemcpyAsync(st->ws + L.req_len, h_len, sizeof(int) * batch, hipMemcpyHostToDevice, s));
-    HIP_TRY(st, hipMemcpyAsync(st->ws + L.lens, h_len, sizeof(int) * batch, hipMemcpyHostToDevice, s));
-    HIP_TRY(st, hipMemcpyAsync(st->ws + L.row_ext_dec, h_ext_dec, sizeof(int) * 32, hipMemcpyHostToDevice, s));
+    HIP_TRY(st, hipMemcpyAsync(st->ws + L.lens, st->h_stage, (char *)(h_tiles + nt) - (char *)st->h_stage, hipMemcpyHostToDevice, s));
     HIP_TRY(st, hipEventRecord(st->upload_done, s));
     st->upload_pending = true;
-    rc = run_prefill_mfma(st, hidden_in, hidden_out, R, n_tiles);
+    rc = run_prefill_mfma(st, hidden_in, hidden_out, R, nt);
   } else {
     int *h_req = st->h_stage, *h_pos = st->h_stage + rows, *h_len = st->h_stage + 2 * (size_t)rows;
     PlainTile *h_tiles = (PlainTile *)(h_len + batch);
