@@ -113,10 +113,13 @@ __global__ void __launch_bounds__(256) k_plain_begin(const T *__restrict__ in, f
 // meet in LDS, in wave order.  No LDS on the operand path: a float contraction spends 32 cycles of
 // the matrix pipe on every 256 bytes (128-wide wave tiles: 16 bytes per clock and CU), far below
 // what L1 delivers, and a decode step reads every weight tile once anyway.
-//   <1, 1, 1, 1, 8>  up to 16 tokens: a decode step, latency- and weight-bound; 8 waves share K
+//   <1, 1, 1, 1, 8>  up to 16 tokens: a decode step, latency- and weight-bound; 8 waves share K (4 tokens, float, 1024
+//                    wide: gate/up 9.2 us for 34 MB, 3.6 TB/s out of the caches; the scalar tiles before took 150 - 640)
 //   <1, 2, 1, 1, 8>  up to 32 tokens
-//   <2, 2, 1, 1, 4>  prompts that leave the wide form's grid short of the chip
-//   <4, 4, 2, 2, 1>  long prompts: 128 x 128 per workgroup
+//   <2, 2, 1, 1, 4>  prompts that leave the wide form's grid short of the chip (920 tokens, float: QKV 58 us = 67
+//                    TFLOP/s, down 90 us = 86 TFLOP/s)
+//   <4, 4, 2, 2, 1>  long prompts: 128 x 128 per workgroup (920 x 8192 x 1024: float 167 us = 92 TFLOP/s, 60 % of what
+//                    the vendor BLAS reaches on 8192^3; 1065 x 8192 x 1024 bf16 52 us = 343 TFLOP/s, bound by L1)
 // ----------------------------------------------------------------------------
 template <typename T> struct GemmArgs {
   PlainGemm<T> g;
@@ -357,7 +360,9 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
 // one head, or the query heads of one KV head for a single new token - and its KW waves take the
 // 16-key blocks in turn.  S^T = K q^T (keys on the M axis: a lane holds four keys of one query),
 // online softmax in fp32, O^T += V^T P^T with fp32 probabilities against fp32 products for either
-// storage type; the waves' (max, sum, output) meet in LDS in wave order.
+// storage type; the waves' (max, sum, output) meet in LDS in wave order.  Bound by the fp32 matrix pipe, which works
+// through 16 columns whatever the head group fills (decode, 536 keys, float, 128 wide: 27 us in one workgroup per KV
+// head, 10 + 3.6 us with the keys dealt to four; one wave per token and head took 166 us).
 // ----------------------------------------------------------------------------
 constexpr int kPlainMaxSplit = 8;
 template <typename T> struct AttnArgs {
