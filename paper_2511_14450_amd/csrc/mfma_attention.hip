@@ -489,8 +489,8 @@ __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ q
 // head), whose 8 waves take the 32-key blocks in turn (at most kShortKeys / 256 each, all
 // requested at once) and meet in LDS in wave order.  No partial results in memory and no merging
 // launch, which is what a short context costs: at 16 requests of up to 440 keys of a stage with
-// room for 4043 the chunked pair of kernels takes 15.2 + 5.3 us, at one request of 64 - 192 keys
-// 5.9 + 5.4 us.
+// room for 4043 the chunked pair of kernels takes 15.2 + 5.3 us, this one 8.3; at one request of
+// 64 - 192 keys 5.9 + 5.4 us against 5.4.
 // ----------------------------------------------------------------------------
 constexpr int kShortWaves = 8;
 

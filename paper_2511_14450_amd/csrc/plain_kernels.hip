@@ -114,11 +114,11 @@ __global__ void __launch_bounds__(256) k_plain_begin(const T *__restrict__ in, f
 // the matrix pipe on every 256 bytes (128-wide wave tiles: 16 bytes per clock and CU), far below
 // what L1 delivers, and a decode step reads every weight tile once anyway.
 //   <1, 1, 1, 1, 8>  up to 16 tokens: a decode step, latency- and weight-bound; 8 waves share K (4 tokens, float, 1024
-//                    wide: gate/up 9.2 us for 34 MB, 3.6 TB/s out of the caches; the scalar tiles before took 150 - 640)
+//                    wide: gate/up 10.4 us for 34 MB, 3.2 TB/s out of the caches; the scalar tiles before took 150 - 640)
 //   <1, 2, 1, 1, 8>  up to 32 tokens
-//   <2, 2, 1, 1, 4>  prompts that leave the wide form's grid short of the chip (920 tokens, float: QKV 58 us = 67
+//   <2, 2, 1, 1, 4>  prompts that leave the wide form's grid short of the chip (920 tokens, float: QKV 61 us = 64
 //                    TFLOP/s, down 90 us = 86 TFLOP/s)
-//   <4, 4, 2, 2, 1>  long prompts: 128 x 128 per workgroup (920 x 8192 x 1024: float 167 us = 92 TFLOP/s, 60 % of what
+//   <4, 4, 2, 2, 1>  long prompts: 128 x 128 per workgroup (920 x 8192 x 1024: float 170 us = 91 TFLOP/s, 60 % of what
 //                    the vendor BLAS reaches on 8192^3; 1065 x 8192 x 1024 bf16 52 us = 343 TFLOP/s, bound by L1)
 // ----------------------------------------------------------------------------
 template <typename T> struct GemmArgs {
