@@ -486,15 +486,15 @@ __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ q
 
 // ----------------------------------------------------------------------------
 // Decode attention while every context is short (kShortKeys): one workgroup per (request, KV
-// head), whose 8 waves take the 32-key blocks in turn (at most kShortKeys / 256 each, all
-// requested at once) and meet in LDS in wave order.  No partial results in memory and no merging
+// head), whose 8 waves take the 32-key blocks in turn (BLOCKS each, all requested at once, then
+// whatever is left one by one) and meet in LDS in wave order.  No partial results in memory and no merging
 // launch, which is what a short context costs: at 16 requests of up to 440 keys of a stage with
 // room for 4043 the chunked pair of kernels takes 15.2 + 5.3 us, this one 8.3; at one request of
 // 64 - 192 keys 5.9 + 5.4 us against 5.4.
 // ----------------------------------------------------------------------------
 constexpr int kShortWaves = 8;
 
-template <int BLOCKS>  // 32-key blocks per wave
+template <int BLOCKS>  // 32-key blocks per wave that are requested at once
 __global__ void __launch_bounds__(kShortWaves * 64) k_attn_decode_short(const bf16_t *__restrict__ qdec,
                                                     const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc,
                                                     CacheGeom geom, const int *__restrict__ lens,
@@ -517,26 +517,19 @@ __global__ void __launch_bounds__(kShortWaves * 64) k_attn_decode_short(const bf
     for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
   bf16x8_t kS[BLOCKS][8], vS[BLOCKS][8];
+  auto load = [&](int kb, bf16x8_t (&k)[8], bf16x8_t (&v)[8]) {
+    const size_t off = geom.off(req, kvh, kb) + lane * 8;
 #pragma unroll
-  for (int u = 0; u < BLOCKS; ++u) {
-    const int kb = wave + u * kShortWaves;
-    if (kb < n_kb) {
-      const size_t off = geom.off(req, kvh, kb) + lane * 8;
+    for (int t = 0; t < 8; ++t) k[t] = __builtin_nontemporal_load((const bf16x8_t *)(Kc + off + t * kTileElems));
 #pragma unroll
-      for (int t = 0; t < 8; ++t) kS[u][t] = __builtin_nontemporal_load((const bf16x8_t *)(Kc + off + t * kTileElems));
-#pragma unroll
-      for (int t = 0; t < 8; ++t) vS[u][t] = __builtin_nontemporal_load((const bf16x8_t *)(Vc + off + t * kTileElems));
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < BLOCKS; ++u) {
-    const int kb = wave + u * kShortWaves;
-    if (kb >= n_kb) continue;
+    for (int t = 0; t < 8; ++t) v[t] = __builtin_nontemporal_load((const bf16x8_t *)(Vc + off + t * kTileElems));
+  };
+  auto block = [&](int kb, const bf16x8_t (&kf)[8], const bf16x8_t (&vf)[8]) {
     f32x16_t s;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kS[u][dt], qf[dt], s, 0, 0, 0);
+    for (int dt = 0; dt < 8; ++dt) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[dt], qf[dt], s, 0, 0, 0);
     float p[16], mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -554,18 +547,29 @@ __global__ void __launch_bounds__(kShortWaves * 64) k_attn_decode_short(const bf
     }
     l_run = l_run * alpha + rowsum;
     m_run = m_new;
-    if (u > 0) {
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < 4; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-    }
+      for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
     const bf16x8_t pf0 = probs_operand(p, 0), pf1 = probs_operand(p, 1);
 #pragma unroll
     for (int db = 0; db < 4; ++db) {
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vS[u][db], pf0, o[db], 0, 0, 0);
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vS[u][4 + db], pf1, o[db], 0, 0, 0);
+      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], pf0, o[db], 0, 0, 0);
+      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 + db], pf1, o[db], 0, 0, 0);
     }
+  };
+#pragma unroll
+  for (int u = 0; u < BLOCKS; ++u)
+    if (wave + u * kShortWaves < n_kb) load(wave + u * kShortWaves, kS[u], vS[u]);
+#pragma unroll
+  for (int u = 0; u < BLOCKS; ++u)
+    if (wave + u * kShortWaves < n_kb) block(wave + u * kShortWaves, kS[u], vS[u]);
+  // Normally nothing is left.  The host chose BLOCKS from the lengths it knows; replays of a step that the caller
+  // recorded move the device's lengths alone, so a step launched after them may find more keys here.
+#pragma unroll 1
+  for (int kb = wave + BLOCKS * kShortWaves; kb < n_kb; kb += kShortWaves) {
+    load(kb, kS[0], vS[0]);
+    block(kb, kS[0], vS[0]);
   }
   const float l_tot = xhalf_sum(l_run);
   if (tl < G) {  // lanes tl < G hold real heads

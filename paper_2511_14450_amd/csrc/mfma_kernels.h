@@ -115,8 +115,8 @@ hipError_t mfma_dec_begin(const bf16_t *hidden_in, float *xres, const bf16_t *ga
 hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
                             int max_chunks, int chunk_keys, int short_blocks, hipStream_t s);
-// blocks of 32 keys per wave of the one-workgroup form, which serves steps whose longest context (the new token's
-// key included) is at most kShortKeys; 0: the chunked form
+// blocks of 32 keys that a wave of the one-workgroup form, made for steps whose longest context (the new token's key
+// included) is at most kShortKeys, requests at once; 0: the chunked form.  Either form is right at any context.
 constexpr int kShortKeys = 512;
 inline int mfma_decode_short_blocks(int longest) { return longest > kShortKeys ? 0 : longest > kShortKeys / 2 ? 2 : 1; }
 size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks);
