@@ -144,12 +144,22 @@ HYP_API hyp_status_t stage_prefill(hyp_stage_t *stage, const void *hidden_in, co
  * (KV-cached generation, Sec. V-A workload).
  *   hidden_in / hidden_out  device, [batch, hidden]; may alias.
  * Asynchronous on the stage's stream.
+ * A caller that records a step into a HIP graph of its own and replays it advances the cached
+ * lengths on the device alone: the checks here and stage_context_len() go on counting calls (the
+ * recorded one included), and the caller keeps its replays within max_seq.  A step called
+ * directly after replays works on the lengths that the device holds.
+ * Bits: every result is the same from run to run.  Where the MFMA kernels run, a request's decode
+ * step depends on its own inputs, cache and length, not on the other requests or on how the step
+ * is launched; a prefill's sums may also be grouped by the number of rows of the call.  The
+ * shape-generic kernels choose the grouping of their sums by the rows and the longest context of
+ * the call, so there the other requests of a batch can move a result by its rounding.
  * Errors: HYP_ESTATE (no prefill yet), HYP_ECAPACITY (some request already holds
  * max_seq tokens; nothing is changed), HYP_EINVAL, HYP_EDEVICE. */
 HYP_API hyp_status_t stage_decode_step(hyp_stage_t *stage, const void *hidden_in, void *hidden_out);
 
 /* stage_decode_step for callers that cannot allocate: code under HIP graph capture, tight
- * serving loops, harnesses that forbid allocation.  Same arguments, same result bit for bit, but
+ * serving loops, harnesses that forbid allocation.  Same arguments, same result bit for bit (also
+ * of a recorded step, at every context it is replayed at), but
  * the step's temporaries (partial sums and arrival counters of the split GEMVs, per-chunk
  * attention results, the block's activations of the <= 32 tokens) live in a 32 MiB array that is
  * part of the library's device image instead of the workspace, the kernels are launched one by

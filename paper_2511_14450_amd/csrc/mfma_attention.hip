@@ -343,115 +343,156 @@ __global__ void __launch_bounds__(128 * G) k_attn_prefill(const bf16_t *__restri
 // (request, KV head).  Every chunk
 // writes (max, sum, unnormalised output) and a second small kernel merges the
 // chunks of a head in index order, so the result does not depend on scheduling.
-// part layout: [request][head][chunk][130] = {m, l, o[128]}
+// Requests of at most short_keys keys are dealt to the first kShortWaves waves block by block instead, and merged
+// the same way.
+// part layout: [request][head][chunk < slots][130] = {m, l, o[128]}
 // ----------------------------------------------------------------------------
 constexpr int kPartStride = 130;
 
-template <int NSETS>
+struct DecodeAcc {
+  f32x16_t o[4];
+  float m, l;  // running maximum; sum of this lane's half of the keys
+};
+__device__ __forceinline__ void decode_clear(DecodeAcc &a) {
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) a.o[db][r] = 0.f;
+  a.m = -INFINITY;
+  a.l = 0.f;
+}
+__device__ __forceinline__ void decode_load(const bf16_t *Kc, const bf16_t *Vc, size_t off, bf16x8_t (&kf)[8], bf16x8_t (&vf)[8]) {
+#pragma unroll
+  for (int t = 0; t < 8; ++t) kf[t] = __builtin_nontemporal_load((const bf16x8_t *)(Kc + off + t * kTileElems));
+#pragma unroll
+  for (int t = 0; t < 8; ++t) vf[t] = __builtin_nontemporal_load((const bf16x8_t *)(Vc + off + t * kTileElems));
+}
+// one block of 32 keys, the first `nkeys` of the request visible; at least one of the block's is.  What is there already
+// is rescaled when some maximum of the wave has moved, always, or - the first block - never: the same bits, an unmoved
+// maximum's factor is 1.
+struct RegFrags {
+  const bf16x8_t *f;
+  __device__ __forceinline__ const bf16x8_t &operator()(int t) const { return f[t]; }
+};
+__device__ __forceinline__ RegFrags frags(const bf16x8_t (&f)[8]) { return RegFrags{f}; }
+enum { RESCALE_MOVED, RESCALE_ALWAYS, RESCALE_NEVER };
+// q(dt), k(dt), v(4 step + d block): the fragments.
+template <int RESCALE, typename Q, typename K, typename V>
+__device__ __forceinline__ void decode_block(DecodeAcc &a, int kb, int nkeys, int hh, Q q, K k, V v) {
+  const float c = kLog2e * 0.08838834764831845f;
+  f32x16_t s;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k(dt), q(dt), s, 0, 0, 0);
+  float p[16];
+  float mx = -INFINITY;
+  if ((kb + 1) * 32 > nkeys) {  // only the last block of a request can hold keys past the end
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      int kpos = kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
+      p[r] = kpos < nkeys ? s[r] : -INFINITY;
+      mx = fmaxf(mx, p[r]);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      p[r] = s[r];
+      mx = fmaxf(mx, p[r]);
+    }
+  }
+  mx = xhalf_max(mx);
+  float m_new = fmaxf(a.m, mx);  // finite: the first key of a block is visible
+  float mc = m_new * c, rowsum = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    p[r] = fast_exp2(p[r] * c - mc);
+    rowsum += p[r];
+  }
+  if (RESCALE == RESCALE_ALWAYS || (RESCALE == RESCALE_MOVED && __any(m_new > a.m))) {
+    float alpha = fast_exp2((a.m - m_new) * c);  // 0 on the first block
+    a.l *= alpha;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a.o[db][r] *= alpha;
+    a.m = m_new;
+  }
+  if (RESCALE == RESCALE_NEVER) a.m = m_new;
+  {
+#pragma clang fp contract(off)
+    a.l += rowsum;
+  }
+  bf16x8_t pf0 = probs_operand(p, 0), pf1 = probs_operand(p, 1);
+#pragma unroll
+  for (int db = 0; db < 4; ++db) {
+    a.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v(db), pf0, a.o[db], 0, 0, 0);
+    a.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v(4 + db), pf1, a.o[db], 0, 0, 0);
+  }
+}
+
+// A request of at most kShortKeys keys is dealt to kShortWaves waves, block by block, whichever kernel works on it.
+constexpr int kShortWaves = 8;
+// the operations of a merge, spelled out so that both kernels round alike
+__device__ __forceinline__ float merge_weight(float m_i, float m) { return fast_exp2((m_i - m) * (kLog2e * 0.08838834764831845f)); }
+__device__ __forceinline__ float merge_sum(float sum, float w, float l) {
+#pragma clang fp contract(off)
+  return sum + w * l;
+}
+__device__ __forceinline__ float merge_out(float acc, float w, float o) { return fmaf(w, o, acc); }
+static_assert(kShortWaves == kShortSlots, "room for the waves' partial results");
+
+template <int NSETS, bool MIXED>  // MIXED: short_keys > 0
 __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ qdec,
                                                     const bf16_t *__restrict__ Kc,
                                                     const bf16_t *__restrict__ Vc, CacheGeom geom,
                                                     const int *__restrict__ lens, float *__restrict__ part,
-                                                    int nq, int G, int max_chunks, int chunk_keys) {
+                                                    int nq, int G, int slots, int chunk_keys, int short_keys) {
   const int lane = threadIdx.x, hh = lane >> 5, tl = lane & 31;
   const int chunk = blockIdx.x, kvh = blockIdx.y, req = blockIdx.z;
   const int nkeys = lens[req] + 1;  // the new token's key is already in the cache
-  const int k0 = chunk * chunk_keys;
-  if (k0 >= nkeys) return;
-  const int kb_begin = k0 >> 5;
-  const int kb_end = min((k0 + chunk_keys) >> 5, (nkeys + 31) >> 5);
-  const float c = kLog2e * 0.08838834764831845f;
-  const int key_limit = nkeys;
+  const int n_kb = (nkeys + 31) >> 5;
+  // this wave's blocks: kb_begin, kb_begin + kb_step, ... below kb_end
+  const bool is_short = MIXED && nkeys <= short_keys;
+  const int kb_begin = is_short ? chunk : chunk * (chunk_keys >> 5), kb_step = is_short ? kShortWaves : 1;
+  const int kb_end = is_short ? n_kb : min(kb_begin + (chunk_keys >> 5), n_kb);
+  if (kb_begin >= kb_end || (is_short && chunk >= kShortWaves)) return;
 
   bf16x8_t qf[8];
   const bf16_t *qb = qdec + ((size_t)req * geom.nkv + kvh) * (32 * 128);
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) qf[dt] = *(const bf16x8_t *)(qb + dt * kTileElems + lane * 8);
 
-  f32x16_t o[4];
-#pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-
+  DecodeAcc acc;
+  decode_clear(acc);
   bf16x8_t kS[NSETS][8], vS[NSETS][8];
-  auto load_block = [&](int kb, bf16x8_t *kf, bf16x8_t *vf) {
-    const bf16_t *kblk = Kc + geom.off(req, kvh, kb) + lane * 8;
-    const bf16_t *vblk = Vc + geom.off(req, kvh, kb) + lane * 8;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) kf[t] = __builtin_nontemporal_load((const bf16x8_t *)(kblk + t * kTileElems));
-#pragma unroll
-    for (int t = 0; t < 8; ++t) vf[t] = __builtin_nontemporal_load((const bf16x8_t *)(vblk + t * kTileElems));
+  auto load_block = [&](int j, bf16x8_t (&kf)[8], bf16x8_t (&vf)[8]) {
+    decode_load(Kc, Vc, geom.off(req, kvh, kb_begin + j * kb_step) + lane * 8, kf, vf);
   };
-  auto compute_block = [&](int kb, const bf16x8_t *kf, const bf16x8_t *vf) {
-    f32x16_t s;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[dt], qf[dt], s, 0, 0, 0);
-    float p[16];
-    float mx = -INFINITY;
-    if ((kb + 1) * 32 > key_limit) {  // only the last block of a chunk can hold keys past the end
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        int kpos = kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
-        p[r] = kpos < key_limit ? s[r] : -INFINITY;
-        mx = fmaxf(mx, p[r]);
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        p[r] = s[r];
-        mx = fmaxf(mx, p[r]);
-      }
-    }
-    mx = xhalf_max(mx);
-    float m_new = fmaxf(m_run, mx);  // finite: the first key of a chunk is always valid and comes first
-    float mc = m_new * c, rowsum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      p[r] = fast_exp2(p[r] * c - mc);
-      rowsum += p[r];
-    }
-    if (__any(m_new > m_run)) {  // the accumulators are rescaled only when some maximum moved
-      float alpha = fast_exp2((m_run - m_new) * c);  // 0 on the first block
-      l_run *= alpha;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-      m_run = m_new;
-    }
-    l_run += rowsum;
-    bf16x8_t pf0 = probs_operand(p, 0), pf1 = probs_operand(p, 1);
-#pragma unroll
-    for (int db = 0; db < 4; ++db) {
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], pf0, o[db], 0, 0, 0);
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 + db], pf1, o[db], 0, 0, 0);
-    }
+  auto compute_block = [&](int j, const bf16x8_t (&kf)[8], const bf16x8_t (&vf)[8]) {
+    decode_block<RESCALE_MOVED>(acc, kb_begin + j * kb_step, nkeys, hh, frags(qf), frags(kf), frags(vf));
   };
   // NSETS register sets: the loads of the next NSETS - 1 blocks are in flight while one is used.
-  // Block kb_begin + j lives in set j % NSETS.  No load sits under a condition between two
+  // The j-th block lives in set j % NSETS.  No load sits under a condition between two
   // uses: the compiler counts outstanding loads per path, and a load that may or may not have
   // been issued makes it wait for everything.  So: a steady loop of whole groups of NSETS
   // blocks, then one of NSETS straight-line endings chosen by the number of loads still to issue.
-  const int n = kb_end - kb_begin;
+  const int n = is_short ? (kb_end - kb_begin + kShortWaves - 1) / kShortWaves : kb_end - kb_begin;
   if (n < NSETS - 1) {
     for (int j = 0; j < n; ++j) {
-      load_block(kb_begin + j, kS[0], vS[0]);
-      compute_block(kb_begin + j, kS[0], vS[0]);
+      load_block(j, kS[0], vS[0]);
+      compute_block(j, kS[0], vS[0]);
     }
   } else {
 #pragma unroll
-    for (int u = 0; u < NSETS - 1; ++u) load_block(kb_begin + u, kS[u], vS[u]);
+    for (int u = 0; u < NSETS - 1; ++u) load_block(u, kS[u], vS[u]);
     int i = 0;
     for (; i + 2 * NSETS - 1 <= n; i += NSETS) {
 #pragma unroll
       for (int u = 0; u < NSETS; ++u) {
-        load_block(kb_begin + i + u + NSETS - 1, kS[(u + NSETS - 1) % NSETS], vS[(u + NSETS - 1) % NSETS]);
+        load_block(i + u + NSETS - 1, kS[(u + NSETS - 1) % NSETS], vS[(u + NSETS - 1) % NSETS]);
         __builtin_amdgcn_sched_barrier(0);
-        compute_block(kb_begin + i + u, kS[u], vS[u]);
+        compute_block(i + u, kS[u], vS[u]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -460,9 +501,9 @@ __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ q
       constexpr int kR = decltype(R)::value;
 #pragma unroll
       for (int u = 0; u < kR + NSETS - 1; ++u) {
-        if (u < kR) load_block(kb_begin + i + u + NSETS - 1, kS[(u + NSETS - 1) % NSETS], vS[(u + NSETS - 1) % NSETS]);
+        if (u < kR) load_block(i + u + NSETS - 1, kS[(u + NSETS - 1) % NSETS], vS[(u + NSETS - 1) % NSETS]);
         __builtin_amdgcn_sched_barrier(0);
-        compute_block(kb_begin + i + u, kS[u % NSETS], vS[u % NSETS]);
+        compute_block(i + u, kS[u % NSETS], vS[u % NSETS]);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -472,30 +513,30 @@ __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ q
     else ending(std::integral_constant<int, NSETS < 4 ? 1 : 3>());
   }
   // lanes tl < G hold real heads
-  float l_tot = xhalf_sum(l_run);
+  float l_tot = xhalf_sum(acc.l);
   if (tl < G) {
     int head = kvh * G + tl;
-    float *dst = part + (((size_t)req * nq + head) * max_chunks + chunk) * kPartStride;
-    if (hh == 0) { dst[0] = m_run; dst[1] = l_tot; }
+    float *dst = part + (((size_t)req * nq + head) * slots + chunk) * kPartStride;
+    if (hh == 0) { dst[0] = acc.m; dst[1] = l_tot; }
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) dst[2 + db * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)] = o[db][r];
+      for (int r = 0; r < 16; ++r) dst[2 + db * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)] = acc.o[db][r];
   }
 }
 
 // ----------------------------------------------------------------------------
 // Decode attention while every context is short (kShortKeys): one workgroup per (request, KV
-// head), whose 8 waves take the 32-key blocks in turn (BLOCKS each, all requested at once, then
-// whatever is left one by one) and meet in LDS in wave order.  No partial results in memory and no merging
+// head), whose 8 waves take the 32-key blocks in turn (the first AHEAD requested at once, then
+// whatever is left one by one) and meet in LDS.  No partial results in memory and no merging
 // launch, which is what a short context costs: at 16 requests of up to 440 keys of a stage with
 // room for 4043 the chunked pair of kernels takes 15.2 + 5.3 us, this one 8.3; at one request of
 // 64 - 192 keys 5.9 + 5.4 us against 5.4.
+// A request's result has the bits that the chunked pair gives it where that deals it the same way
+// (short_keys): the waves' shares, their order and every operation of the merge are alike.
 // ----------------------------------------------------------------------------
-constexpr int kShortWaves = 8;
-
-template <int BLOCKS>  // 32-key blocks per wave that are requested at once
-__global__ void __launch_bounds__(kShortWaves * 64) k_attn_decode_short(const bf16_t *__restrict__ qdec,
+template <int AHEAD>  // blocks per wave that are requested at once
+__global__ void __launch_bounds__(kShortWaves * 64) __attribute__((amdgpu_waves_per_eu(AHEAD == 1 ? 4 : 2))) k_attn_decode_short(const bf16_t *__restrict__ qdec,
                                                     const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc,
                                                     CacheGeom geom, const int *__restrict__ lens,
                                                     bf16_t *__restrict__ out, int nq, int G) {
@@ -503,97 +544,59 @@ __global__ void __launch_bounds__(kShortWaves * 64) k_attn_decode_short(const bf
   __shared__ float o_s[kShortWaves][4][132];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hh = lane >> 5, tl = lane & 31;
   const int kvh = blockIdx.x, req = blockIdx.y;
-  const float c = kLog2e * 0.08838834764831845f;
   bf16x8_t qf[8];
   const bf16_t *qb = qdec + ((size_t)req * geom.nkv + kvh) * (32 * 128);
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) qf[dt] = *(const bf16x8_t *)(qb + dt * kTileElems + lane * 8);
   const int nkeys = lens[req] + 1;  // the new token's key is already in the cache
   const int n_kb = (nkeys + 31) >> 5;
-  f32x16_t o[4];
+  DecodeAcc acc;
+  decode_clear(acc);
+  bf16x8_t kS[AHEAD][8], vS[AHEAD][8];
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+  for (int u = 0; u < AHEAD; ++u)
+    if (wave + u * kShortWaves < n_kb) decode_load(Kc, Vc, geom.off(req, kvh, wave + u * kShortWaves) + lane * 8, kS[u], vS[u]);
+  if (wave < n_kb) decode_block<RESCALE_NEVER>(acc, wave, nkeys, hh, frags(qf), frags(kS[0]), frags(vS[0]));
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  bf16x8_t kS[BLOCKS][8], vS[BLOCKS][8];
-  auto load = [&](int kb, bf16x8_t (&k)[8], bf16x8_t (&v)[8]) {
-    const size_t off = geom.off(req, kvh, kb) + lane * 8;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) k[t] = __builtin_nontemporal_load((const bf16x8_t *)(Kc + off + t * kTileElems));
-#pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = __builtin_nontemporal_load((const bf16x8_t *)(Vc + off + t * kTileElems));
-  };
-  auto block = [&](int kb, const bf16x8_t (&kf)[8], const bf16x8_t (&vf)[8]) {
-    f32x16_t s;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[dt], qf[dt], s, 0, 0, 0);
-    float p[16], mx = -INFINITY;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int kpos = kb * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
-      p[r] = kpos < nkeys ? s[r] : -INFINITY;
-      mx = fmaxf(mx, p[r]);
-    }
-    const float m_new = fmaxf(m_run, xhalf_max(mx));  // finite: a block that is taken holds a key
-    const float mc = m_new * c, alpha = fast_exp2(m_run * c - mc);  // 0 on the first block
-    float rowsum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      p[r] = fast_exp2(p[r] * c - mc);
-      rowsum += p[r];
-    }
-    l_run = l_run * alpha + rowsum;
-    m_run = m_new;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-    const bf16x8_t pf0 = probs_operand(p, 0), pf1 = probs_operand(p, 1);
-#pragma unroll
-    for (int db = 0; db < 4; ++db) {
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db], pf0, o[db], 0, 0, 0);
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[4 + db], pf1, o[db], 0, 0, 0);
-    }
-  };
-#pragma unroll
-  for (int u = 0; u < BLOCKS; ++u)
-    if (wave + u * kShortWaves < n_kb) load(wave + u * kShortWaves, kS[u], vS[u]);
-#pragma unroll
-  for (int u = 0; u < BLOCKS; ++u)
-    if (wave + u * kShortWaves < n_kb) block(wave + u * kShortWaves, kS[u], vS[u]);
-  // Normally nothing is left.  The host chose BLOCKS from the lengths it knows; replays of a step that the caller
+  for (int u = 1; u < AHEAD; ++u)
+    if (wave + u * kShortWaves < n_kb) decode_block<RESCALE_ALWAYS>(acc, wave + u * kShortWaves, nkeys, hh, frags(qf), frags(kS[u]), frags(vS[u]));
+  // Normally nothing is left.  The host chose this kernel from the lengths it knows; replays of a step that the caller
   // recorded move the device's lengths alone, so a step launched after them may find more keys here.
 #pragma unroll 1
-  for (int kb = wave + BLOCKS * kShortWaves; kb < n_kb; kb += kShortWaves) {
-    load(kb, kS[0], vS[0]);
-    block(kb, kS[0], vS[0]);
+  for (int kb = wave + AHEAD * kShortWaves; kb < n_kb; kb += kShortWaves) {
+    const size_t off = geom.off(req, kvh, kb) + lane * 8;
+    auto from = [](const bf16_t *p) {
+      return [p](int t) {  // one after the other: read ahead they would cost every launch registers, and half its waves
+        __builtin_amdgcn_sched_barrier(0);
+        return *(const bf16x8_t *)(p + t * kTileElems);
+      };
+    };
+    decode_block<RESCALE_ALWAYS>(acc, kb, nkeys, hh, from(qb + lane * 8), from(Kc + off), from(Vc + off));
   }
-  const float l_tot = xhalf_sum(l_run);
+  const float l_tot = xhalf_sum(acc.l);
   if (tl < G) {  // lanes tl < G hold real heads
-    if (hh == 0) { m_s[wave][tl] = m_run; l_s[wave][tl] = l_tot; }
+    if (hh == 0) { m_s[wave][tl] = acc.m; l_s[wave][tl] = l_tot; }
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        *(f32x4_t *)&o_s[wave][tl][db * 32 + 8 * q + 4 * hh] = f32x4_t{o[db][4 * q], o[db][4 * q + 1], o[db][4 * q + 2], o[db][4 * q + 3]};
+        *(f32x4_t *)&o_s[wave][tl][db * 32 + 8 * q + 4 * hh] =
+            f32x4_t{acc.o[db][4 * q], acc.o[db][4 * q + 1], acc.o[db][4 * q + 2], acc.o[db][4 * q + 3]};
   }
   __syncthreads();
   const int g = threadIdx.x >> 7, d = threadIdx.x & 127;
   if (g >= G) return;
   float m = m_s[0][g];
 #pragma unroll
-  for (int w = 1; w < kShortWaves; ++w) m = fmaxf(m, m_s[w][g]);
-  float acc = 0.f, l = 0.f;
+  for (int w = 1; w < kShortWaves; ++w) m = fmaxf(m, m_s[w][g]);  // -inf: a wave without a block
+  float o = 0.f, l = 0.f;
 #pragma unroll
   for (int w = 0; w < kShortWaves; ++w) {
-    const float wgt = w < n_kb ? fast_exp2((m_s[w][g] - m) * c) : 0.f;  // waves without a block hold zeros
-    l += wgt * l_s[w][g];
-    acc += wgt * o_s[w][g][d];
+    const float wgt = w < n_kb ? merge_weight(m_s[w][g], m) : 0.f;  // waves without a block hold zeros
+    l = merge_sum(l, wgt, l_s[w][g]);
+    o = merge_out(o, wgt, o_s[w][g][d]);
   }
-  out[frag_offset(req, (kvh * G + g) * 128 + d, nq * 128)] = f2bf_dev(acc / l);
+  out[frag_offset(req, (kvh * G + g) * 128 + d, nq * 128)] = f2bf_dev(o / l);
 }
 
 // One 128-thread block per (request, query head): combine its chunks in chunk
@@ -602,29 +605,30 @@ __global__ void __launch_bounds__(kShortWaves * 64) k_attn_decode_short(const bf
 __global__ void __launch_bounds__(128) k_attn_decode_merge(const float *__restrict__ part,
                                                            const int *__restrict__ lens,
                                                            bf16_t *__restrict__ out, int nq,
-                                                           int max_chunks, int chunk_keys) {
+                                                           int slots, int chunk_keys, int short_keys) {
   __shared__ float wgt[64];
   __shared__ float lsum;
   const int head = blockIdx.x, req = blockIdx.y, d = threadIdx.x;
-  const int n_chunks = (lens[req] + 1 + chunk_keys - 1) / chunk_keys;  // <= 64 by the host's choice of chunk_keys
-  const float c = kLog2e * 0.08838834764831845f;
-  const float *src = part + ((size_t)req * nq + head) * max_chunks * kPartStride;
+  const int nkeys = lens[req] + 1;
+  const int n_chunks = nkeys <= short_keys ? min((nkeys + 31) >> 5, kShortWaves)
+                                           : (nkeys + chunk_keys - 1) / chunk_keys;  // <= 64 by the host's choice of chunk_keys
+  const float *src = part + ((size_t)req * nq + head) * slots * kPartStride;
   // One round trip: the first 16 chunks' outputs, the maxima and the sums are requested for every
   // chunk slot the buffer has, without waiting for the request's length; slots past n_chunks hold
   // whatever an earlier step left there and are dropped below without entering any arithmetic.
   float v0[16];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) v0[u] = u < max_chunks ? src[u * kPartStride + 2 + d] : 0.f;
+  for (int u = 0; u < 16; ++u) v0[u] = u < slots ? src[u * kPartStride + 2 + d] : 0.f;
   float mi_raw = 0.f, li_raw = 0.f;
-  if (d < 64 && d < max_chunks) { mi_raw = src[d * kPartStride]; li_raw = src[d * kPartStride + 1]; }
+  if (d < 64 && d < slots) { mi_raw = src[d * kPartStride]; li_raw = src[d * kPartStride + 1]; }
   if (d < 64) {
     float mi = d < n_chunks ? mi_raw : -INFINITY;
     float li = d < n_chunks ? li_raw : 0.f;
     float m = mi;
     for (int o2 = 32; o2 > 0; o2 >>= 1) m = fmaxf(m, __shfl_xor(m, o2, 64));
-    float w = d < n_chunks ? exp2f((mi - m) * c) : 0.f;
+    float w = d < n_chunks ? merge_weight(mi, m) : 0.f;
     wgt[d] = w;
-    float wl = w * li, tot = 0.f;
+    float wl = merge_sum(0.f, w, li), tot = 0.f;
     for (int i = 0; i < n_chunks; ++i) tot += __shfl(wl, i, 64);  // chunk order
     if (d == 0) lsum = tot;
   }
@@ -632,16 +636,16 @@ __global__ void __launch_bounds__(128) k_attn_decode_merge(const float *__restri
   float acc = 0.f;
 #pragma unroll
   for (int u = 0; u < 16; ++u)
-    if (u < n_chunks) acc += wgt[u] * v0[u];
+    if (u < n_chunks) acc = merge_out(acc, wgt[u], v0[u]);
   int i = 16;
   for (; i + 8 <= n_chunks; i += 8) {
     float v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) v[u] = src[(i + u) * kPartStride + 2 + d];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc += wgt[i + u] * v[u];
+    for (int u = 0; u < 8; ++u) acc = merge_out(acc, wgt[i + u], v[u]);
   }
-  for (; i < n_chunks; ++i) acc += wgt[i] * src[i * kPartStride + 2 + d];
+  for (; i < n_chunks; ++i) acc = merge_out(acc, wgt[i], src[i * kPartStride + 2 + d]);
   out[frag_offset(req, head * 128 + d, nq * 128)] = f2bf_dev(acc / lsum);
 }
 
@@ -671,23 +675,23 @@ hipError_t mfma_attn_init() {
   return e;
 }
 
-size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks) {
-  return (size_t)batch * nq * max_chunks * kPartStride;
-}
+size_t mfma_attn_decode_part_floats(int nq, int batch, int slots) { return (size_t)batch * nq * slots * kPartStride; }
 
 hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
-                            int max_chunks, int chunk_keys, int short_blocks, hipStream_t s) {
+                            int max_chunks, int chunk_keys, int form, hipStream_t s) {
   int G = nq / nkv;
-  if (short_blocks) {
-    if (short_blocks == 1) k_attn_decode_short<1><<<dim3(nkv, batch), kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G);
+  if (form == DEC_ATTN_SHORT || form == DEC_ATTN_SHORT2) {
+    if (form == DEC_ATTN_SHORT) k_attn_decode_short<1><<<dim3(nkv, batch), kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G);
     else k_attn_decode_short<2><<<dim3(nkv, batch), kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G);
     return hipGetLastError();
   }
-  k_attn_decode<2><<<dim3(max_chunks, nkv, batch), 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, max_chunks, chunk_keys);
+  const int short_keys = form == DEC_ATTN_MIXED ? kShortKeys : 0, slots = form == DEC_ATTN_MIXED ? mfma_decode_mixed_slots(max_chunks) : max_chunks;
+  if (short_keys) k_attn_decode<2, true><<<dim3(slots, nkv, batch), 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, slots, chunk_keys, short_keys);
+  else k_attn_decode<2, false><<<dim3(slots, nkv, batch), 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, slots, chunk_keys, short_keys);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_attn_decode_merge<<<dim3(nq, batch), 128, 0, s>>>(part, lens, out, nq, max_chunks, chunk_keys);
+  k_attn_decode_merge<<<dim3(nq, batch), 128, 0, s>>>(part, lens, out, nq, slots, chunk_keys, short_keys);
   return hipGetLastError();
 }
 

@@ -111,15 +111,26 @@ hipError_t mfma_gemv_init();  // kernel attributes, once per process and device
 hipError_t mfma_dec_begin(const bf16_t *hidden_in, float *xres, const bf16_t *gain, bf16_t *y_out, float *ssq_out,
                           int H, int batch, hipStream_t s);
 
-// split-KV decode attention + fixed-order merge; out row b of P(32, nq*128)
+// Decode attention; out row b of P(32, nq*128).  Every form is right at any context; they differ in speed, and the first
+// in bits:
+//   DEC_ATTN_CHUNKED  split-KV over chunks of chunk_keys keys + fixed-order merge, for every request
+//   DEC_ATTN_SHORT    one workgroup per (request, KV head), made for contexts of at most kShortKeys keys (the new token's
+//   DEC_ATTN_SHORT2   included); the second requests two blocks per wave at once instead of one
+//   DEC_ATTN_MIXED    the chunked pair of kernels, in which a request of at most kShortKeys keys gets the bits that the
+//                     short forms give it: for batches with contexts on both sides, and for steps that are replayed at
+//                     contexts the host does not see
+// part: mfma_attn_decode_part_floats(nq, batch, slots) floats, slots = max_chunks, for MIXED mfma_decode_mixed_slots()
+enum { DEC_ATTN_CHUNKED = 0, DEC_ATTN_SHORT = 1, DEC_ATTN_SHORT2 = 2, DEC_ATTN_MIXED = 3 };
+constexpr int kShortKeys = 512, kShortSlots = 8;
+// One block per wave is all there is up to 256 keys, and half the registers let two workgroups share a CU (32 x 10 heads,
+// 240 keys: 15.0 against 16.6 us; 8 x 10 heads 9.2 against 9.3); beyond, two save a round trip (8 x 10 heads, 300 keys:
+// 10.1 against 13.9).
+inline int mfma_decode_short_form(int longest) { return longest <= kShortKeys / 2 ? DEC_ATTN_SHORT : DEC_ATTN_SHORT2; }
+inline int mfma_decode_mixed_slots(int max_chunks) { return max_chunks > kShortSlots ? max_chunks : kShortSlots; }
 hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
-                            int max_chunks, int chunk_keys, int short_blocks, hipStream_t s);
-// blocks of 32 keys that a wave of the one-workgroup form, made for steps whose longest context (the new token's key
-// included) is at most kShortKeys, requests at once; 0: the chunked form.  Either form is right at any context.
-constexpr int kShortKeys = 512;
-inline int mfma_decode_short_blocks(int longest) { return longest > kShortKeys ? 0 : longest > kShortKeys / 2 ? 2 : 1; }
-size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks);
+                            int max_chunks, int chunk_keys, int form, hipStream_t s);
+size_t mfma_attn_decode_part_floats(int nq, int batch, int slots);
 // keys per decode-attention chunk (one wave each, one wave per SIMD): the largest power-of-two
 // multiple of 128 up to 1024 that still gives the longest context about 512 waves over all
 // (request, KV head) pairs - chunks of 256 for 8 x 10 pairs at 2K keys, 1024 for 32 x 10

@@ -97,3 +97,53 @@ def test_recorded_steps_replayed_past_the_short_form_and_direct_steps_after_them
                 if prompt + s >= max(keys, prompt) + 20:
                     assert err_without_late_keys(ost, xd, ref, keys) > 4 * TOL, (s, keys)
     st.destroy()
+
+
+def test_a_recorded_step_gives_the_bits_of_a_direct_one():
+    import torch
+    shape = synth.BlockShape(hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=512, dtype="bf16")
+    layers = [synth.layer_weights(shape, 0, 42_100, sigma=0.05)]
+    lens, cap = [508, 40, 250, 700], 900
+    x = to_dev(synth.hidden_states(sum(lens), shape, 42_101), "bf16")
+    xd = [to_dev(synth.hidden_states(4, shape, 42_102 + s), "bf16") for s in range(12)]
+    for some in ([0, 1, 2, 3], [1, 2]):  # contexts on both sides of the change of form; short ones alone
+        ln = [lens[r] for r in some]
+        at = [sum(lens[:r]) for r in some]
+        xs = torch.cat([x[a:a + n] for a, n in zip(at, ln)])
+        direct = make_gpu_stage(shape, layers, 4, cap, sum(lens))
+        direct.prefill(xs, ln)
+        want = [direct.decode_step(d[some].contiguous()).clone() for d in xd]
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            rec = make_gpu_stage(shape, layers, 4, cap, sum(lens))
+            rec.prefill(xs, ln)
+            hid, out = xd[0][some].contiguous(), torch.empty_like(xd[0][some])
+            stream.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                rec.decode_step_noalloc(hid, out)
+            for s, d in enumerate(xd):
+                hid.copy_(d[some])
+                graph.replay()
+                stream.synchronize()
+                assert torch.equal(out, want[s]), (some, s)
+        direct.destroy(); rec.destroy()
+
+
+def test_a_request_decodes_to_the_same_bits_beside_longer_ones():
+    # every contraction is 256 deep and every prefill has more than 128 rows, so that no projection of a prompt is split
+    import torch
+    shape = synth.BlockShape(hidden=256, n_q_heads=2, n_kv_heads=2, head_dim=128, ffn_dim=256, dtype="bf16")
+    layers = [synth.layer_weights(shape, l, 42_200, sigma=0.05) for l in range(2)]
+    x = to_dev(synth.hidden_states(1250, shape, 42_201), "bf16")
+    xd = [to_dev(synth.hidden_states(3, shape, 42_202 + s), "bf16") for s in range(6)]
+    results = []
+    for lens in ([150], [150, 400], [150, 400, 700]):
+        st = make_gpu_stage(shape, layers, 3, 1000, 1250)
+        got = [st.prefill(x[:sum(lens)].contiguous(), lens)[:150].clone()]
+        got += [st.decode_step(d[:len(lens)].contiguous())[:1].clone() for d in xd]
+        results.append(got)
+        st.destroy()
+    for other in results[1:]:
+        for s, (a, b) in enumerate(zip(results[0], other)):
+            assert torch.equal(a, b), s - 1
