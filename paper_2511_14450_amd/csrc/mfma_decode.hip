@@ -363,10 +363,26 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
         }
       } else {
         bf16_t *dst = p.Vc + p.geom.off(b, head - p.nq - p.nkv, pos >> 5);
+        // The feature's 32 slots are four runs of 8: MFMA steps m, lane halves khh.  The token that opens a block clears the
+        // rest of it: decode attention multiplies the slots behind the last key by probabilities of zero, and whatever an
+        // earlier request left there need not be finite (prefill does the same behind a prompt's last key).
         int m, khh;
-        int e = vtile_slot_of_key(pos & 31, &m, &khh);
-        dst[(size_t)(m * 4 + (d0 >> 5)) * kTileElems + (khh * 32 + (d0 & 31)) * 8 + e] = f2bf_dev(a);
-        dst[(size_t)(m * 4 + (d1 >> 5)) * kTileElems + (khh * 32 + (d1 & 31)) * 8 + e] = f2bf_dev(c);
+        const int e = vtile_slot_of_key(pos & 31, &m, &khh);
+        auto put = [&](int d, float v) {
+          bf16_t *row = dst + (size_t)(d >> 5) * kTileElems + (d & 31) * 8;
+          if ((pos & 31) == 0) {
+            u16x8_t run = {};
+            *(u16x8_t *)(row + 32 * 8) = run;
+            *(u16x8_t *)(row + 4 * kTileElems) = run;
+            *(u16x8_t *)(row + 4 * kTileElems + 32 * 8) = run;
+            run.v[0] = f2bf_dev(v);
+            *(u16x8_t *)row = run;
+          } else {
+            row[(size_t)m * 4 * kTileElems + khh * 32 * 8 + e] = f2bf_dev(v);
+          }
+        };
+        put(d0, a);
+        put(d1, c);
       }
     }
   } else if (EPI == DEC_SWIGLU) {

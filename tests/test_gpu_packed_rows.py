@@ -33,18 +33,26 @@ def test_ragged_batches_against_oracle(lens, paged, G):
     gst.destroy()
 
 
-def test_what_an_earlier_prefill_left_stays_out():
+# (prompts after the longer one, decode steps): inside the last 64 keys of a prompt; a prompt that ends on their edge, so that
+# the first step opens a block; steps across it; contexts of the chunked form (its last block, over two edges), alone and mixed
+@pytest.mark.parametrize("lens,steps", [([31, 40], 4), ([64, 1], 2), ([31, 62], 40), ([640, 574], 70), ([600, 64], 3)])
+@pytest.mark.parametrize("paged", [False, True])
+def test_what_an_earlier_prefill_left_stays_out(lens, steps, paged):
     import torch
+    from paper_2511_14450_amd import binding
     shape = synth.BlockShape(hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=512, dtype="bf16")
     layers = [synth.layer_weights(shape, l, 45_000, sigma=0.05) for l in range(2)]
-    x = synth.hidden_states(200, shape, 45_001)
+    longer, cap = [max(lens) + 120] * 2, max(lens) + 121
+    x = synth.hidden_states(sum(longer), shape, 45_001)
     bad = x.copy()
     bad[30:] = np.nan
-    used, fresh = make_gpu_stage(shape, layers, 2, 130, 200), make_gpu_stage(shape, layers, 2, 130, 200)
-    used.prefill(to_dev(bad, "bf16"), [100, 100])  # the caches hold NaN from key 30 on, and so does every scratch row
-    a, b = used.prefill(to_dev(x[:71], "bf16"), [31, 40]), fresh.prefill(to_dev(x[:71], "bf16"), [31, 40])
+    flags = binding.HYP_FLAG_PAGED_KV if paged else 0
+    used, fresh = (make_gpu_stage(shape, layers, 2, cap, sum(longer), flags=flags) for _ in range(2))
+    used.prefill(to_dev(bad, "bf16"), longer)  # the caches hold NaN from key 30 on, and so does every scratch row
+    xs = to_dev(x[:sum(lens)], "bf16")
+    a, b = used.prefill(xs, lens), fresh.prefill(xs, lens)
     assert torch.equal(a, b) and bool(torch.isfinite(a).all())
-    for s in range(4):
+    for s in range(steps):
         d = to_dev(synth.hidden_states(2, shape, 45_002 + s), "bf16")
         a, b = used.decode_step(d), fresh.decode_step(d)
         assert torch.equal(a, b) and bool(torch.isfinite(a).all()), s
