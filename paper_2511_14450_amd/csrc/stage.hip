@@ -534,6 +534,8 @@ void drop_decode_graph(hyp_stage::DecGraph &g) {
   g.graph = nullptr;
 }
 
+constexpr size_t kDecGraphs = 16;
+
 // The launches of a decode step are latency-bound next to ~0.1 ms of streaming
 // per block, so the step is recorded into a HIP graph (kernel nodes only) the
 // first time a (batch, output buffer, attention form) is seen and replayed afterwards;
@@ -550,12 +552,13 @@ hyp_status_t run_decode_mfma(hyp_stage *st, const void *hidden_in, void *hidden_
   // new input address every step does not force a new graph
   hyp_status_t rc0 = decode_step_mfma(st, s, st->dec_ws, hidden_in, hidden_out, attn, true, false);
   if (rc0 != HYP_OK) return rc0;
-  // a few recorded graphs, keyed by what is baked into their kernel arguments
+  // a few recorded graphs, keyed by what is baked into them: room for four output buffers in each of the four forms
+  // of attention that a generation passes through as its contexts grow
   hyp_stage::DecGraph *g = nullptr;
   for (auto &c : st->dec_graphs)
     if (c.batch == st->batch && c.out == hidden_out && c.attn == attn) g = &c;
   if (!g) {
-    if (st->dec_graphs.size() >= 4) {
+    if (st->dec_graphs.size() >= kDecGraphs) {
       drop_decode_graph(st->dec_graphs.front());
       st->dec_graphs.erase(st->dec_graphs.begin());
     }
