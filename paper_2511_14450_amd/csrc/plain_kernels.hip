@@ -488,7 +488,7 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
 #pragma unroll
         for (int f = 0; f < NF; ++f)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) odd |= f < nf && !(fabsf(vf[f][i]) < INFINITY);
+          for (int i = 0; i < 4; ++i) odd |= f * 16 + tl < d && !(fabsf(vf[f][i]) < INFINITY);  // features past d hold anything
         shared = !__any(odd);
         if (!shared) {
 #pragma unroll 1

@@ -95,3 +95,25 @@ def test_values_that_are_not_finite_stay_behind_earlier_queries(bad):
     assert np.array_equal(short, to_host(fresh.prefill(to_dev(x[:19], "f32"), [19])))
     assert np.array_equal(step, to_host(fresh.decode_step(to_dev(x[40:41], "f32"))))
     st.destroy(); fresh.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_the_workspace_may_hold_anything_at_the_start(dtype):
+    # 18-wide heads leave 14 padding features in the last value tile; products must not depend on what lies there, and
+    # neither must the order they are added in (a diagonal block whose values are not finite is added key by key)
+    import torch
+    import paper_2511_14450_amd as hyp
+    from paper_2511_14450_amd import binding
+    shp = synth.BlockShape(dtype=dtype, **SHAPES["group20"])
+    lens, cap = [33, 5, 70], 74
+    layers = [{k: to_dev(v, dtype) for k, v in synth.layer_weights(shp, l, 34_000, sigma=0.05).items()} for l in range(2)]
+    cfg = hyp.stage_config(shp, len(lens), cap, sum(lens), binding.HYP_FLAG_PLAIN_KERNELS)
+    need, results = hyp.stage_workspace_bytes(cfg, 0, 2), []
+    for fill in (0, 255):  # 255: every float and bf16 a NaN
+        st = hyp.stage_create(cfg, 0, 2, layers, workspace=torch.full((need,), fill, dtype=torch.uint8, device="cuda"))
+        got = [st.prefill(to_dev(synth.hidden_states(sum(lens), shp, 34_001), dtype), lens)]
+        got += [st.decode_step(to_dev(synth.hidden_states(len(lens), shp, 34_002 + s), dtype)) for s in range(2)]
+        results.append(got)
+        st.destroy()
+    for a, b in zip(*results):
+        assert bool(torch.isfinite(a).all()) and torch.equal(a, b)
