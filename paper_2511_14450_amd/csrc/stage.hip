@@ -72,7 +72,7 @@ struct Layout {
   size_t q = 0, delta = 0, qdec = 0,
          partial = 0, attn_part = 0, counters = 0, gemm_counters = 0, rstd = 0, ssq_part = 0, gemm_ws = 0;
   size_t kv_bytes = 0;  // bytes of each of Kc, Vc over all layers
-  int rows_cap = 0;     // internal rows the scratch holds
+  int rows_cap = 0, q_rows_cap = 0;  // internal rows, and rows of the queries, the scratch holds
   int key_blocks = 0;   // 32-key blocks per (request, kv head)
   int max_chunks = 0;   // decode attention chunks per head
   int chunk_keys = 128; // keys per chunk
@@ -143,9 +143,9 @@ hyp_status_t check_config(const hyp_stage_config_t *c, int32_t l_start, int32_t 
   return HYP_OK;
 }
 
-// ints of a prefill's upload: lengths, four arrays of up to `rows` rows, tiles
-size_t prefill_upload_ints(int max_batch, int rows) {
-  return (size_t)max_batch + 4 * (size_t)rows + sizeof(PrefillTile) / sizeof(int) * ((size_t)rows / 64);
+// ints of a prefill's upload: lengths, four arrays of up to `rows` rows, a tile for every 64 of up to `q_rows` query rows
+size_t prefill_upload_ints(int max_batch, int rows, int q_rows) {
+  return (size_t)max_batch + 4 * (size_t)rows + sizeof(PrefillTile) / sizeof(int) * ((size_t)q_rows / 64);
 }
 
 void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
@@ -170,9 +170,10 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
     p.wd = take(operand(H, I));
   }
   if (mfma) {
-    // queries keep every request's rows padded to a multiple of 64 (one query tile); everything else is packed
-    L.rows_cap = round_up((int)c.max_prefill_tokens + 63 * c.max_batch, 64);
-    if (L.rows_cap < 64) L.rows_cap = 64;
+    // rows are packed, whole blocks of 32 (one at least: a decode step's tokens); only the queries keep every request's
+    // rows padded to a multiple of 64 (one query tile)
+    L.rows_cap = round_up((int)c.max_prefill_tokens, 32);
+    L.q_rows_cap = round_up((int)c.max_prefill_tokens + 63 * c.max_batch, 64);
     R = L.rows_cap;
     L.key_blocks = round_up(c.max_seq, 64) / 32;
     if (c.flags & HYP_FLAG_PAGED_KV) {
@@ -190,14 +191,14 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
     L.sin_tab = take(tab);
     L.xres = take(sizeof(float) * R * H);
     L.y = take(es * R * H);
-    L.q = take(es * R * qd);
+    L.q = take(es * L.q_rows_cap * qd);
     L.attn = take(es * R * qd);
     L.m = take(es * R * I);
     L.delta = take(es * R * H);
     L.rstd = take(sizeof(float) * R);
     L.ssq_part = take(sizeof(float) * R * (H / 64));
     // what a prefill uploads in one piece: cached lengths, then the per-row arrays and query tiles of the call
-    L.lens = take(sizeof(int) * prefill_upload_ints(c.max_batch, L.rows_cap));
+    L.lens = take(sizeof(int) * prefill_upload_ints(c.max_batch, L.rows_cap, L.q_rows_cap));
     L.qdec = take(es * (size_t)c.max_batch * c.n_kv_heads * 32 * 128);
     L.g_qkv = mfma_gemv_plan(HYP_K_GEMV_QKV, (int)(qd + 2 * kvd), (int)H, c.max_batch);
     L.g_o = mfma_gemv_plan(HYP_K_GEMV_O, (int)H, (int)qd, c.max_batch);
@@ -716,7 +717,7 @@ hyp_status_t do_stage_create(const hyp_stage_config_t *cfg, int32_t l_start, int
     return code;
   };
 
-  st->h_stage_ints = st->mfma ? prefill_upload_ints(cfg->max_batch, st->L.rows_cap)
+  st->h_stage_ints = st->mfma ? prefill_upload_ints(cfg->max_batch, st->L.rows_cap, st->L.q_rows_cap)
                               : 2 * (size_t)max_rows(*cfg) + (size_t)cfg->max_batch + 4 * ((size_t)max_rows(*cfg) / 16 + cfg->max_batch);
   if (hipHostMalloc((void **)&st->h_stage, sizeof(int) * st->h_stage_ints, hipHostMallocDefault) != hipSuccess) {
     st->h_stage = nullptr; st->err = "hipHostMalloc failed";

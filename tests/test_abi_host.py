@@ -46,6 +46,17 @@ def test_workspace_bytes_scales_and_rejects():
     assert "n_kv_heads" in hyp.stage_last_error(None)
 
 
+def test_prefill_scratch_does_not_grow_with_the_batch():
+    # rows of the activations are packed: 32 requests may bring 64 tokens between them.  A wider FFN adds its weights, those
+    # rows of the activation and at most 2 x 4 B a (token, feature) of decode partial sums, not 63 padding rows a request.
+    def bytes_of(ffn):
+        shape = synth.BlockShape(hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=ffn, dtype="bf16")
+        return hyp.stage_workspace_bytes(make_config(shape, 32, 128, 64), 0, 1)
+    more = 65536
+    weights, rows, partial = 3 * 256 * 2 * more, 64 * 2 * more, 2 * 32 * 4 * more
+    assert bytes_of(1024 + more) - bytes_of(1024) < weights + rows + partial + (1 << 20)
+
+
 def test_phi3_stage_fits_hbm():
     cfg = make_config(synth.PHI3_MEDIUM, 8, 8192 + 1024, 8 * 8192)
     need = hyp.stage_workspace_bytes(cfg, 0, 20)
