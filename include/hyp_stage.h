@@ -147,12 +147,13 @@ HYP_API hyp_status_t stage_prefill(hyp_stage_t *stage, const void *hidden_in, co
  * A caller that records a step into a HIP graph of its own and replays it advances the cached
  * lengths on the device alone: the checks here and stage_context_len() go on counting calls (the
  * recorded one included), and the caller keeps its replays within max_seq.  A step called
- * directly after replays works on the lengths that the device holds.
- * Bits: every result is the same from run to run.  Where the MFMA kernels run, a request's decode
- * step depends on its own inputs, cache and length, not on the other requests or on how the step
- * is launched; a prefill's sums may also be grouped by the number of rows of the call.  The
- * shape-generic kernels choose the grouping of their sums by the rows and the longest context of
- * the call, so there the other requests of a batch can move a result by its rounding.
+ * directly after replays works on the lengths that the device holds (its sums grouped for the
+ * lengths that the host counts).
+ * Bits: every result is the same from run to run, of a call and of a replay.  Sums are
+ * grouped by the size of the call, so the other requests of a batch can move a request's result
+ * by its rounding: a prefill by the number of rows; a decode step by whether the longest context
+ * of the batch passes 512 keys and, on the shape-generic kernels, by the number of requests and
+ * the longest context.
  * Errors: HYP_ESTATE (no prefill yet), HYP_ECAPACITY (some request already holds
  * max_seq tokens; nothing is changed), HYP_EINVAL, HYP_EDEVICE. */
 HYP_API hyp_status_t stage_decode_step(hyp_stage_t *stage, const void *hidden_in, void *hidden_out);

@@ -343,9 +343,7 @@ __global__ void __launch_bounds__(128 * G) k_attn_prefill(const bf16_t *__restri
 // (request, KV head).  Every chunk
 // writes (max, sum, unnormalised output) and a second small kernel merges the
 // chunks of a head in index order, so the result does not depend on scheduling.
-// Requests of at most short_keys keys are dealt to the first kShortWaves waves block by block instead, and merged
-// the same way.
-// part layout: [request][head][chunk < slots][130] = {m, l, o[128]}
+// part layout: [request][head][chunk][130] = {m, l, o[128]}
 // ----------------------------------------------------------------------------
 constexpr int kPartStride = 130;
 
@@ -367,14 +365,22 @@ __device__ __forceinline__ void decode_load(const bf16_t *Kc, const bf16_t *Vc, 
 #pragma unroll
   for (int t = 0; t < 8; ++t) vf[t] = __builtin_nontemporal_load((const bf16x8_t *)(Vc + off + t * kTileElems));
 }
-// one block of 32 keys, the first `nkeys` of the request visible; at least one of the block's is.  What is there already
-// is rescaled when some maximum of the wave has moved, always, or - the first block - never: the same bits, an unmoved
-// maximum's factor is 1.
+// fragments of a block, in registers or fetched as they are used (read ahead they would cost every launch registers, and
+// half its waves)
 struct RegFrags {
   const bf16x8_t *f;
   __device__ __forceinline__ const bf16x8_t &operator()(int t) const { return f[t]; }
 };
-__device__ __forceinline__ RegFrags frags(const bf16x8_t (&f)[8]) { return RegFrags{f}; }
+struct MemFrags {
+  const bf16_t *p;
+  __device__ __forceinline__ bf16x8_t operator()(int t) const {
+    __builtin_amdgcn_sched_barrier(0);
+    return *(const bf16x8_t *)(p + t * kTileElems);
+  }
+};
+// one block of 32 keys, the first `nkeys` of the request visible; at least one of the block's is.  What is there already
+// is rescaled when some maximum of the wave has moved, always, or - the first block - never: the same bits, an unmoved
+// maximum's factor is 1.
 enum { RESCALE_MOVED, RESCALE_ALWAYS, RESCALE_NEVER };
 // q(dt), k(dt), v(4 step + d block): the fragments.
 template <int RESCALE, typename Q, typename K, typename V>
@@ -431,32 +437,39 @@ __device__ __forceinline__ void decode_block(DecodeAcc &a, int kb, int nkeys, in
   }
 }
 
-// A request of at most kShortKeys keys is dealt to kShortWaves waves, block by block, whichever kernel works on it.
-constexpr int kShortWaves = 8;
-// the operations of a merge, spelled out so that both kernels round alike
-__device__ __forceinline__ float merge_weight(float m_i, float m) { return fast_exp2((m_i - m) * (kLog2e * 0.08838834764831845f)); }
+// A batch whose contexts are all short runs another form (k_attn_decode_short).  The host chooses by the lengths it knows;
+// in a step that the caller records, the kernels choose by the lengths they find.
+// A wave looks at all of them: lane b holds the length of request b.
+__device__ __forceinline__ int batch_len(const int *lens, int batch, int lane) { return lane < batch ? lens[lane] : 0; }  // batch <= 32
+__device__ __forceinline__ bool all_short(int batch_len) { return !__any(batch_len + 1 > kShortKeys); }
+// the operations of a merge, spelled out so that every kernel that merges rounds alike
 __device__ __forceinline__ float merge_sum(float sum, float w, float l) {
 #pragma clang fp contract(off)
   return sum + w * l;
 }
 __device__ __forceinline__ float merge_out(float acc, float w, float o) { return fmaf(w, o, acc); }
-static_assert(kShortWaves == kShortSlots, "room for the waves' partial results");
 
-template <int NSETS, bool MIXED>  // MIXED: short_keys > 0
+template <int NSETS, bool RECORDED>
 __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ qdec,
                                                     const bf16_t *__restrict__ Kc,
                                                     const bf16_t *__restrict__ Vc, CacheGeom geom,
                                                     const int *__restrict__ lens, float *__restrict__ part,
-                                                    int nq, int G, int slots, int chunk_keys, int short_keys) {
+                                                    int nq, int G, int max_chunks, int chunk_keys) {
   const int lane = threadIdx.x, hh = lane >> 5, tl = lane & 31;
   const int chunk = blockIdx.x, kvh = blockIdx.y, req = blockIdx.z;
-  const int nkeys = lens[req] + 1;  // the new token's key is already in the cache
-  const int n_kb = (nkeys + 31) >> 5;
-  // this wave's blocks: kb_begin, kb_begin + kb_step, ... below kb_end
-  const bool is_short = MIXED && nkeys <= short_keys;
-  const int kb_begin = is_short ? chunk : chunk * (chunk_keys >> 5), kb_step = is_short ? kShortWaves : 1;
-  const int kb_end = is_short ? n_kb : min(kb_begin + (chunk_keys >> 5), n_kb);
-  if (kb_begin >= kb_end || (is_short && chunk >= kShortWaves)) return;
+  int len;
+  if (RECORDED) {
+    const int mine = batch_len(lens, gridDim.z, lane);
+    if (all_short(mine)) return;
+    len = __builtin_amdgcn_readlane(mine, req);
+  } else {
+    len = lens[req];
+  }
+  const int nkeys = len + 1;  // the new token's key is already in the cache
+  const int k0 = chunk * chunk_keys;
+  if (k0 >= nkeys) return;
+  const int kb_begin = k0 >> 5;
+  const int kb_end = min((k0 + chunk_keys) >> 5, (nkeys + 31) >> 5);
 
   bf16x8_t qf[8];
   const bf16_t *qb = qdec + ((size_t)req * geom.nkv + kvh) * (32 * 128);
@@ -467,17 +480,17 @@ __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ q
   decode_clear(acc);
   bf16x8_t kS[NSETS][8], vS[NSETS][8];
   auto load_block = [&](int j, bf16x8_t (&kf)[8], bf16x8_t (&vf)[8]) {
-    decode_load(Kc, Vc, geom.off(req, kvh, kb_begin + j * kb_step) + lane * 8, kf, vf);
+    decode_load(Kc, Vc, geom.off(req, kvh, kb_begin + j) + lane * 8, kf, vf);
   };
   auto compute_block = [&](int j, const bf16x8_t (&kf)[8], const bf16x8_t (&vf)[8]) {
-    decode_block<RESCALE_MOVED>(acc, kb_begin + j * kb_step, nkeys, hh, frags(qf), frags(kf), frags(vf));
+    decode_block<RESCALE_MOVED>(acc, kb_begin + j, nkeys, hh, RegFrags{qf}, RegFrags{kf}, RegFrags{vf});
   };
   // NSETS register sets: the loads of the next NSETS - 1 blocks are in flight while one is used.
   // The j-th block lives in set j % NSETS.  No load sits under a condition between two
   // uses: the compiler counts outstanding loads per path, and a load that may or may not have
   // been issued makes it wait for everything.  So: a steady loop of whole groups of NSETS
   // blocks, then one of NSETS straight-line endings chosen by the number of loads still to issue.
-  const int n = is_short ? (kb_end - kb_begin + kShortWaves - 1) / kShortWaves : kb_end - kb_begin;
+  const int n = kb_end - kb_begin;
   if (n < NSETS - 1) {
     for (int j = 0; j < n; ++j) {
       load_block(j, kS[0], vS[0]);
@@ -516,7 +529,7 @@ __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ q
   float l_tot = xhalf_sum(acc.l);
   if (tl < G) {
     int head = kvh * G + tl;
-    float *dst = part + (((size_t)req * nq + head) * slots + chunk) * kPartStride;
+    float *dst = part + (((size_t)req * nq + head) * max_chunks + chunk) * kPartStride;
     if (hh == 0) { dst[0] = acc.m; dst[1] = l_tot; }
 #pragma unroll
     for (int db = 0; db < 4; ++db)
@@ -528,22 +541,20 @@ __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ q
 // ----------------------------------------------------------------------------
 // Decode attention while every context is short (kShortKeys): one workgroup per (request, KV
 // head), whose 8 waves take the 32-key blocks in turn (the first AHEAD requested at once, then
-// whatever is left one by one) and meet in LDS.  No partial results in memory and no merging
-// launch, which is what a short context costs: at 16 requests of up to 440 keys of a stage with
-// room for 4043 the chunked pair of kernels takes 15.2 + 5.3 us, this one 8.3; at one request of
-// 64 - 192 keys 5.9 + 5.4 us against 5.4.
-// A request's result has the bits that the chunked pair gives it where that deals it the same way
-// (short_keys): the waves' shares, their order and every operation of the merge are alike.
+// whatever is left one by one) and meet in LDS in wave order.  No partial results in memory and no
+// merging launch, which is what a short context costs: at 16 requests of up to 440 keys of a stage
+// with room for 4043 the chunked pair of kernels takes 15.2 + 5.3 us, this one 8.3; at one request
+// of 64 - 192 keys 5.9 + 5.4 us against 5.4.
 // ----------------------------------------------------------------------------
+constexpr int kShortWaves = 8;
+struct ShortLds {
+  float m[kShortWaves][4], l[kShortWaves][4], o[kShortWaves][4][132];
+};
+
 template <int AHEAD>  // blocks per wave that are requested at once
-__global__ void __launch_bounds__(kShortWaves * 64) __attribute__((amdgpu_waves_per_eu(AHEAD == 1 ? 4 : 2))) k_attn_decode_short(const bf16_t *__restrict__ qdec,
-                                                    const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc,
-                                                    CacheGeom geom, const int *__restrict__ lens,
-                                                    bf16_t *__restrict__ out, int nq, int G) {
-  __shared__ float m_s[kShortWaves][4], l_s[kShortWaves][4];
-  __shared__ float o_s[kShortWaves][4][132];
+__device__ __forceinline__ void decode_short(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, const CacheGeom &geom, const int *lens,
+                                             bf16_t *out, int nq, int G, int kvh, int req, ShortLds &lds) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, hh = lane >> 5, tl = lane & 31;
-  const int kvh = blockIdx.x, req = blockIdx.y;
   bf16x8_t qf[8];
   const bf16_t *qb = qdec + ((size_t)req * geom.nkv + kvh) * (32 * 128);
 #pragma unroll
@@ -556,87 +567,95 @@ __global__ void __launch_bounds__(kShortWaves * 64) __attribute__((amdgpu_waves_
 #pragma unroll
   for (int u = 0; u < AHEAD; ++u)
     if (wave + u * kShortWaves < n_kb) decode_load(Kc, Vc, geom.off(req, kvh, wave + u * kShortWaves) + lane * 8, kS[u], vS[u]);
-  if (wave < n_kb) decode_block<RESCALE_NEVER>(acc, wave, nkeys, hh, frags(qf), frags(kS[0]), frags(vS[0]));
+  if (wave < n_kb) decode_block<RESCALE_NEVER>(acc, wave, nkeys, hh, RegFrags{qf}, RegFrags{kS[0]}, RegFrags{vS[0]});
 #pragma unroll
   for (int u = 1; u < AHEAD; ++u)
-    if (wave + u * kShortWaves < n_kb) decode_block<RESCALE_ALWAYS>(acc, wave + u * kShortWaves, nkeys, hh, frags(qf), frags(kS[u]), frags(vS[u]));
-  // Normally nothing is left.  The host chose this kernel from the lengths it knows; replays of a step that the caller
-  // recorded move the device's lengths alone, so a step launched after them may find more keys here.
+    if (wave + u * kShortWaves < n_kb)
+      decode_block<RESCALE_ALWAYS>(acc, wave + u * kShortWaves, nkeys, hh, RegFrags{qf}, RegFrags{kS[u]}, RegFrags{vS[u]});
+  // In a step launched by the host nothing is left, normally: it chose AHEAD, and this form, from the lengths it knows.
+  // Replays of a step that the caller recorded move the device's lengths alone, so a step launched after them may find
+  // more keys here, as a recorded step does between 256 and 512 keys.
 #pragma unroll 1
   for (int kb = wave + AHEAD * kShortWaves; kb < n_kb; kb += kShortWaves) {
     const size_t off = geom.off(req, kvh, kb) + lane * 8;
-    auto from = [](const bf16_t *p) {
-      return [p](int t) {  // one after the other: read ahead they would cost every launch registers, and half its waves
-        __builtin_amdgcn_sched_barrier(0);
-        return *(const bf16x8_t *)(p + t * kTileElems);
-      };
-    };
-    decode_block<RESCALE_ALWAYS>(acc, kb, nkeys, hh, from(qb + lane * 8), from(Kc + off), from(Vc + off));
+    const bf16_t *qp = qb + lane * 8;
+    asm volatile("" : "+v"(qp));  // or the query's fragments are fetched ahead of the loop into registers of their own
+    decode_block<RESCALE_ALWAYS>(acc, kb, nkeys, hh, MemFrags{qp}, MemFrags{Kc + off}, MemFrags{Vc + off});
   }
   const float l_tot = xhalf_sum(acc.l);
   if (tl < G) {  // lanes tl < G hold real heads
-    if (hh == 0) { m_s[wave][tl] = acc.m; l_s[wave][tl] = l_tot; }
+    if (hh == 0) { lds.m[wave][tl] = acc.m; lds.l[wave][tl] = l_tot; }
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        *(f32x4_t *)&o_s[wave][tl][db * 32 + 8 * q + 4 * hh] =
+        *(f32x4_t *)&lds.o[wave][tl][db * 32 + 8 * q + 4 * hh] =
             f32x4_t{acc.o[db][4 * q], acc.o[db][4 * q + 1], acc.o[db][4 * q + 2], acc.o[db][4 * q + 3]};
   }
   __syncthreads();
   const int g = threadIdx.x >> 7, d = threadIdx.x & 127;
   if (g >= G) return;
-  float m = m_s[0][g];
+  const float c = kLog2e * 0.08838834764831845f;
+  float m = lds.m[0][g];
 #pragma unroll
-  for (int w = 1; w < kShortWaves; ++w) m = fmaxf(m, m_s[w][g]);  // -inf: a wave without a block
+  for (int w = 1; w < kShortWaves; ++w) m = fmaxf(m, lds.m[w][g]);  // -inf: a wave without a block
   float o = 0.f, l = 0.f;
 #pragma unroll
   for (int w = 0; w < kShortWaves; ++w) {
-    const float wgt = w < n_kb ? merge_weight(m_s[w][g], m) : 0.f;  // waves without a block hold zeros
-    l = merge_sum(l, wgt, l_s[w][g]);
-    o = merge_out(o, wgt, o_s[w][g][d]);
+    const float wgt = w < n_kb ? fast_exp2((lds.m[w][g] - m) * c) : 0.f;  // waves without a block hold zeros
+    l = merge_sum(l, wgt, lds.l[w][g]);
+    o = merge_out(o, wgt, lds.o[w][g][d]);
   }
   out[frag_offset(req, (kvh * G + g) * 128 + d, nq * 128)] = f2bf_dev(o / l);
 }
 
-// One 128-thread block per (request, query head): combine its chunks in chunk
-// order.  Lane i of the first wave takes chunk i (max, sum -> weight); then thread
-// d accumulates output feature d over all chunks, eight loads in flight at a time.
-__global__ void __launch_bounds__(128) k_attn_decode_merge(const float *__restrict__ part,
-                                                           const int *__restrict__ lens,
-                                                           bf16_t *__restrict__ out, int nq,
-                                                           int slots, int chunk_keys, int short_keys) {
-  __shared__ float wgt[64];
-  __shared__ float lsum;
-  const int head = blockIdx.x, req = blockIdx.y, d = threadIdx.x;
-  const int nkeys = lens[req] + 1;
-  const int n_chunks = nkeys <= short_keys ? min((nkeys + 31) >> 5, kShortWaves)
-                                           : (nkeys + chunk_keys - 1) / chunk_keys;  // <= 64 by the host's choice of chunk_keys
-  const float *src = part + ((size_t)req * nq + head) * slots * kPartStride;
-  // One round trip: the first 16 chunks' outputs, the maxima and the sums are requested for every
-  // chunk slot the buffer has, without waiting for the request's length; slots past n_chunks hold
-  // whatever an earlier step left there and are dropped below without entering any arithmetic.
-  float v0[16];
+template <int AHEAD>
+__global__ void __launch_bounds__(kShortWaves * 64) __attribute__((amdgpu_waves_per_eu(AHEAD == 1 ? 4 : 2)))
+k_attn_decode_short(const bf16_t *__restrict__ qdec, const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc, CacheGeom geom,
+                    const int *__restrict__ lens, bf16_t *__restrict__ out, int nq, int G) {
+  __shared__ ShortLds lds;
+  decode_short<AHEAD>(qdec, Kc, Vc, geom, lens, out, nq, G, blockIdx.x, blockIdx.y, lds);
+}
+
+// 128 threads (d) combine the chunks of one (request, query head) in chunk order.  Lane i of their first wave takes
+// chunk i (max, sum -> weight); then thread d accumulates output feature d over all chunks, eight loads in flight at a
+// time.  Threads that are not `live` only meet the barrier.
+// One round trip: the first 16 chunks' outputs, the maxima and the sums are requested for every chunk slot the buffer
+// has, without waiting for the request's length; slots past n_chunks hold whatever an earlier step left there and are
+// dropped below without entering any arithmetic.
+struct MergeLoads {
+  const float *src;
+  float v0[16], m, l;
+  __device__ __forceinline__ MergeLoads(const float *part, int nq, int max_chunks, int head, int req, int d, bool live) {
+    src = part + ((size_t)req * nq + head) * max_chunks * kPartStride;
 #pragma unroll
-  for (int u = 0; u < 16; ++u) v0[u] = u < slots ? src[u * kPartStride + 2 + d] : 0.f;
-  float mi_raw = 0.f, li_raw = 0.f;
-  if (d < 64 && d < slots) { mi_raw = src[d * kPartStride]; li_raw = src[d * kPartStride + 1]; }
-  if (d < 64) {
-    float mi = d < n_chunks ? mi_raw : -INFINITY;
-    float li = d < n_chunks ? li_raw : 0.f;
+    for (int u = 0; u < 16; ++u) v0[u] = live && u < max_chunks ? src[u * kPartStride + 2 + d] : 0.f;
+    m = l = 0.f;
+    if (live && d < 64 && d < max_chunks) { m = src[d * kPartStride]; l = src[d * kPartStride + 1]; }
+  }
+};
+__device__ __forceinline__ void merge_chunks(const MergeLoads &in, int len, bf16_t *out, int nq, int chunk_keys, int head, int req, int d,
+                                             bool live, float *wgt /*64*/, float *lsum) {
+  const int n_chunks = (len + 1 + chunk_keys - 1) / chunk_keys;  // <= 64 by the host's choice of chunk_keys
+  const float c = kLog2e * 0.08838834764831845f;
+  const float *src = in.src;
+  if (live && d < 64) {
+    float mi = d < n_chunks ? in.m : -INFINITY;
+    float li = d < n_chunks ? in.l : 0.f;
     float m = mi;
     for (int o2 = 32; o2 > 0; o2 >>= 1) m = fmaxf(m, __shfl_xor(m, o2, 64));
-    float w = d < n_chunks ? merge_weight(mi, m) : 0.f;
+    float w = d < n_chunks ? exp2f((mi - m) * c) : 0.f;
     wgt[d] = w;
     float wl = merge_sum(0.f, w, li), tot = 0.f;
     for (int i = 0; i < n_chunks; ++i) tot += __shfl(wl, i, 64);  // chunk order
-    if (d == 0) lsum = tot;
+    if (d == 0) *lsum = tot;
   }
   __syncthreads();
+  if (!live) return;
   float acc = 0.f;
 #pragma unroll
   for (int u = 0; u < 16; ++u)
-    if (u < n_chunks) acc = merge_out(acc, wgt[u], v0[u]);
+    if (u < n_chunks) acc = merge_out(acc, wgt[u], in.v0[u]);
   int i = 16;
   for (; i + 8 <= n_chunks; i += 8) {
     float v[8];
@@ -646,7 +665,36 @@ __global__ void __launch_bounds__(128) k_attn_decode_merge(const float *__restri
     for (int u = 0; u < 8; ++u) acc = merge_out(acc, wgt[i + u], v[u]);
   }
   for (; i < n_chunks; ++i) acc = merge_out(acc, wgt[i], src[i * kPartStride + 2 + d]);
-  out[frag_offset(req, head * 128 + d, nq * 128)] = f2bf_dev(acc / lsum);
+  out[frag_offset(req, head * 128 + d, nq * 128)] = f2bf_dev(acc / *lsum);
+}
+
+// one workgroup per (request, query head)
+__global__ void __launch_bounds__(128) k_attn_decode_merge(const float *__restrict__ part,
+                                                           const int *__restrict__ lens,
+                                                           bf16_t *__restrict__ out, int nq,
+                                                           int max_chunks, int chunk_keys) {
+  __shared__ float wgt[64];
+  __shared__ float lsum;
+  const MergeLoads in(part, nq, max_chunks, blockIdx.x, blockIdx.y, threadIdx.x, true);
+  merge_chunks(in, lens[blockIdx.y], out, nq, chunk_keys, blockIdx.x, blockIdx.y, threadIdx.x, true, wgt, &lsum);
+}
+
+// The second kernel of a recorded step, one workgroup per (request, KV head): the merge, or the whole of a short batch's
+// attention, whose first kernel returned at once.  (A step that the caller replays must give what a direct call gives at
+// the same context, and the two forms add up in different orders.)
+__global__ void __launch_bounds__(kShortWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
+k_attn_decode_recorded_end(const bf16_t *__restrict__ qdec, const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc, CacheGeom geom,
+                           const int *__restrict__ lens, const float *__restrict__ part, bf16_t *__restrict__ out, int nq, int G,
+                           int max_chunks, int chunk_keys) {
+  static_assert(kShortWaves * 64 == 4 * 128, "128 threads for each of up to 4 query heads");
+  __shared__ ShortLds lds;
+  __shared__ float wgt[4][64], lsum[4];
+  const int kvh = blockIdx.x, req = blockIdx.y, g = threadIdx.x >> 7, head = kvh * G + min(g, G - 1), d = threadIdx.x & 127;
+  const int mine = batch_len(lens, gridDim.y, threadIdx.x & 63);
+  const MergeLoads in(part, nq, max_chunks, head, req, d, g < G);  // on their way while the lengths arrive
+  asm volatile("" ::: "memory");
+  if (all_short(mine)) decode_short<1>(qdec, Kc, Vc, geom, lens, out, nq, G, kvh, req, lds);
+  else merge_chunks(in, __builtin_amdgcn_readlane(mine, req), out, nq, chunk_keys, head, req, d, g < G, wgt[g], &lsum[g]);
 }
 
 }  // namespace
@@ -675,23 +723,31 @@ hipError_t mfma_attn_init() {
   return e;
 }
 
-size_t mfma_attn_decode_part_floats(int nq, int batch, int slots) { return (size_t)batch * nq * slots * kPartStride; }
+size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks) {
+  return (size_t)batch * nq * max_chunks * kPartStride;
+}
 
 hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
                             int max_chunks, int chunk_keys, int form, hipStream_t s) {
   int G = nq / nkv;
-  if (form == DEC_ATTN_SHORT || form == DEC_ATTN_SHORT2) {
-    if (form == DEC_ATTN_SHORT) k_attn_decode_short<1><<<dim3(nkv, batch), kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G);
-    else k_attn_decode_short<2><<<dim3(nkv, batch), kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G);
-    return hipGetLastError();
+  const dim3 chunks(max_chunks, nkv, batch), heads(nkv, batch);
+  hipError_t e = hipSuccess;
+  switch (form) {
+    case DEC_ATTN_SHORT: k_attn_decode_short<1><<<heads, kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G); break;
+    case DEC_ATTN_SHORT2: k_attn_decode_short<2><<<heads, kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G); break;
+    case DEC_ATTN_CHUNKED:
+      k_attn_decode<2, false><<<chunks, 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, max_chunks, chunk_keys);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      k_attn_decode_merge<<<dim3(nq, batch), 128, 0, s>>>(part, lens, out, nq, max_chunks, chunk_keys);
+      break;
+    case DEC_ATTN_RECORDED:
+      k_attn_decode<2, true><<<chunks, 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, max_chunks, chunk_keys);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      k_attn_decode_recorded_end<<<heads, kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, out, nq, G, max_chunks, chunk_keys);
+      break;
+    default: return hipErrorInvalidValue;
   }
-  const int short_keys = form == DEC_ATTN_MIXED ? kShortKeys : 0, slots = form == DEC_ATTN_MIXED ? mfma_decode_mixed_slots(max_chunks) : max_chunks;
-  if (short_keys) k_attn_decode<2, true><<<dim3(slots, nkv, batch), 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, slots, chunk_keys, short_keys);
-  else k_attn_decode<2, false><<<dim3(slots, nkv, batch), 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, slots, chunk_keys, short_keys);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_attn_decode_merge<<<dim3(nq, batch), 128, 0, s>>>(part, lens, out, nq, slots, chunk_keys, short_keys);
   return hipGetLastError();
 }
 

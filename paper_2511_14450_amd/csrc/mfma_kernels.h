@@ -111,26 +111,26 @@ hipError_t mfma_gemv_init();  // kernel attributes, once per process and device
 hipError_t mfma_dec_begin(const bf16_t *hidden_in, float *xres, const bf16_t *gain, bf16_t *y_out, float *ssq_out,
                           int H, int batch, hipStream_t s);
 
-// Decode attention; out row b of P(32, nq*128).  Every form is right at any context; they differ in speed, and the first
-// in bits:
-//   DEC_ATTN_CHUNKED  split-KV over chunks of chunk_keys keys + fixed-order merge, for every request
-//   DEC_ATTN_SHORT    one workgroup per (request, KV head), made for contexts of at most kShortKeys keys (the new token's
-//   DEC_ATTN_SHORT2   included); the second requests two blocks per wave at once instead of one
-//   DEC_ATTN_MIXED    the chunked pair of kernels, in which a request of at most kShortKeys keys gets the bits that the
-//                     short forms give it: for batches with contexts on both sides, and for steps that are replayed at
-//                     contexts the host does not see
-// part: mfma_attn_decode_part_floats(nq, batch, slots) floats, slots = max_chunks, for MIXED mfma_decode_mixed_slots()
-enum { DEC_ATTN_CHUNKED = 0, DEC_ATTN_SHORT = 1, DEC_ATTN_SHORT2 = 2, DEC_ATTN_MIXED = 3 };
-constexpr int kShortKeys = 512, kShortSlots = 8;
+// Decode attention; out row b of P(32, nq*128).  Every form is right at any context; they differ in speed and in the order
+// of their sums:
+//   DEC_ATTN_CHUNKED   split-KV over chunks of chunk_keys keys + fixed-order merge
+//   DEC_ATTN_SHORT     one workgroup per (request, KV head), made for batches whose longest context is at most kShortKeys
+//   DEC_ATTN_SHORT2    keys (the new token's included); the second requests two blocks per wave at once instead of one
+//   DEC_ATTN_RECORDED  for steps that are replayed at contexts the host does not see: a batch whose longest context is at
+//                      most kShortKeys keys gets the bits of the short forms, any other the chunked form's
+// part: mfma_attn_decode_part_floats() floats
+enum { DEC_ATTN_CHUNKED = 0, DEC_ATTN_SHORT = 1, DEC_ATTN_SHORT2 = 2, DEC_ATTN_RECORDED = 3 };
+constexpr int kShortKeys = 512;
 // One block per wave is all there is up to 256 keys, and half the registers let two workgroups share a CU (32 x 10 heads,
 // 240 keys: 15.0 against 16.6 us; 8 x 10 heads 9.2 against 9.3); beyond, two save a round trip (8 x 10 heads, 300 keys:
 // 10.1 against 13.9).
-inline int mfma_decode_short_form(int longest) { return longest <= kShortKeys / 2 ? DEC_ATTN_SHORT : DEC_ATTN_SHORT2; }
-inline int mfma_decode_mixed_slots(int max_chunks) { return max_chunks > kShortSlots ? max_chunks : kShortSlots; }
+inline int mfma_decode_attn_form(int longest) {
+  return longest <= kShortKeys / 2 ? DEC_ATTN_SHORT : longest <= kShortKeys ? DEC_ATTN_SHORT2 : DEC_ATTN_CHUNKED;
+}
 hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
                             int max_chunks, int chunk_keys, int form, hipStream_t s);
-size_t mfma_attn_decode_part_floats(int nq, int batch, int slots);
+size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks);
 // keys per decode-attention chunk (one wave each, one wave per SIMD): the largest power-of-two
 // multiple of 128 up to 1024 that still gives the longest context about 512 waves over all
 // (request, KV head) pairs - chunks of 256 for 8 x 10 pairs at 2K keys, 1024 for 32 x 10

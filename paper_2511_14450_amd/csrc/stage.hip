@@ -76,7 +76,6 @@ struct Layout {
   int key_blocks = 0;   // 32-key blocks per (request, kv head)
   int max_chunks = 0;   // decode attention chunks per head
   int chunk_keys = 128; // keys per chunk
-  bool short_forms = true;  // decode attention may take the forms for short contexts
   GemvPlan g_qkv, g_o, g_gu, g_d;  // how the four skinny GEMMs of a decode step are cut into workgroups
   size_t partial_bytes = 0, attn_part_bytes = 0, counters_bytes = 0;
   // paged KV cache (HYP_FLAG_PAGED_KV): pages per layer of the pool, table entries per request
@@ -211,8 +210,7 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
     L.partial = take(L.partial_bytes);
     L.chunk_keys = mfma_decode_chunk_keys(c.max_seq, c.max_batch * c.n_kv_heads);
     L.max_chunks = (c.max_seq + L.chunk_keys - 1) / L.chunk_keys;
-    // a stage of at most kShortKeys keys a request runs the form that leaves no partial results
-    L.attn_part_bytes = sizeof(float) * mfma_attn_decode_part_floats(c.n_q_heads, c.max_batch, c.max_seq > kShortKeys ? mfma_decode_mixed_slots(L.max_chunks) : L.max_chunks);
+    L.attn_part_bytes = sizeof(float) * mfma_attn_decode_part_floats(c.n_q_heads, c.max_batch, L.max_chunks);
     L.attn_part = take(L.attn_part_bytes);
     L.counters_bytes = sizeof(unsigned) * (2 * I / 64 + (qd + 2 * kvd) / 64 + H / 32);
     L.counters = take(L.counters_bytes);
@@ -461,16 +459,13 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
   return HYP_OK;
 }
 
-// The form of decode attention that this step's contexts get.  A request's bits follow from its own length: at most
-// kShortKeys keys or more.  A step that the caller records is replayed at contexts the host does not see: it gets the form
-// that finds out on the device.
+// The form of decode attention that this step's contexts get.  A step that the caller records is replayed at contexts the
+// host does not see: where the stage has room for both kinds, the form that finds out on the device.
 int decode_attn_form(const hyp_stage *st, bool recorded_by_caller) {
-  const int capacity = st->cfg.max_seq;
-  if (!st->L.short_forms) return DEC_ATTN_CHUNKED;
-  if (recorded_by_caller) return capacity <= kShortKeys ? mfma_decode_short_form(capacity) : DEC_ATTN_MIXED;
-  int longest = 0, shortest = capacity;
-  for (int b = 0; b < st->batch; ++b) { longest = std::max(longest, st->lens[b] + 1); shortest = std::min(shortest, st->lens[b] + 1); }
-  return longest <= kShortKeys ? mfma_decode_short_form(longest) : shortest > kShortKeys ? DEC_ATTN_CHUNKED : DEC_ATTN_MIXED;
+  if (recorded_by_caller) return st->cfg.max_seq > kShortKeys ? (int)DEC_ATTN_RECORDED : mfma_decode_attn_form(st->cfg.max_seq);
+  int longest = 0;
+  for (int b = 0; b < st->batch; ++b) longest = std::max(longest, st->lens[b] + 1);
+  return mfma_decode_attn_form(longest);
 }
 
 // One decode step through the MFMA kernels (a single block of 32 token rows):
@@ -535,7 +530,7 @@ void drop_decode_graph(hyp_stage::DecGraph &g) {
   g.graph = nullptr;
 }
 
-constexpr size_t kDecGraphs = 16;
+constexpr size_t kDecGraphs = 12;
 
 // The launches of a decode step are latency-bound next to ~0.1 ms of streaming
 // per block, so the step is recorded into a HIP graph (kernel nodes only) the
@@ -553,7 +548,7 @@ hyp_status_t run_decode_mfma(hyp_stage *st, const void *hidden_in, void *hidden_
   // new input address every step does not force a new graph
   hyp_status_t rc0 = decode_step_mfma(st, s, st->dec_ws, hidden_in, hidden_out, attn, true, false);
   if (rc0 != HYP_OK) return rc0;
-  // a few recorded graphs, keyed by what is baked into them: room for four output buffers in each of the four forms
+  // a few recorded graphs, keyed by what is baked into them: room for four output buffers in each of the three forms
   // of attention that a generation passes through as its contexts grow
   hyp_stage::DecGraph *g = nullptr;
   for (auto &c : st->dec_graphs)
@@ -743,28 +738,22 @@ hyp_status_t do_stage_create(const hyp_stage_config_t *cfg, int32_t l_start, int
     void *sbase = nullptr;
     e = static_scratch_of_current_device(&sbase);
     if (e != hipSuccess) { st->err = std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e); return bail(HYP_EDEVICE); }
-    auto place = [&](size_t attn_part_bytes, char *b, DecScratch &t) {
+    {
       const size_t es = 2, H = d.H;
       size_t off = 0;
-      auto take = [&](size_t bytes) { char *p = b + off; off = align_up(off + bytes); return p; };
-      t.counters = (unsigned *)take(L.counters_bytes);
-      t.xres = (float *)take(sizeof(float) * 32 * H);
-      t.ssq = (float *)take(sizeof(float) * 32 * (H / 32));
-      t.y = (bf16_t *)take(es * 32 * H);
-      t.attn = (bf16_t *)take(es * 32 * (size_t)d.qd);
-      t.m = (bf16_t *)take(es * 32 * (size_t)d.I);
-      t.qdec = (bf16_t *)take(es * (size_t)d.max_batch * d.nkv * 32 * 128);
-      t.partial = (float *)take(L.partial_bytes);
-      t.attn_part = (float *)take(attn_part_bytes);
-      return off;
-    };
-    st->static_bytes = place(L.attn_part_bytes, (char *)sbase, st->dec_static);
-    if (st->static_bytes > kNoAllocScratchBytes) {
-      // without the slots that only the forms for short contexts need it may fit: such a stage runs the chunked form throughout
-      DecScratch t;
-      const size_t bytes = place(sizeof(float) * mfma_attn_decode_part_floats(d.nq, d.max_batch, L.max_chunks), (char *)sbase, t);
-      if (bytes <= kNoAllocScratchBytes) { st->L.short_forms = false; st->static_bytes = bytes; }
-      st->dec_static = bytes <= kNoAllocScratchBytes ? t : DecScratch();
+      auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
+      const size_t o_cnt = take(L.counters_bytes), o_xres = take(sizeof(float) * 32 * H), o_ssq = take(sizeof(float) * 32 * (H / 32)),
+                   o_y = take(es * 32 * H), o_attn = take(es * 32 * (size_t)d.qd), o_m = take(es * 32 * (size_t)d.I),
+                   o_q = take(es * (size_t)d.max_batch * d.nkv * 32 * 128), o_part = take(L.partial_bytes),
+                   o_ap = take(L.attn_part_bytes);
+      st->static_bytes = off;
+      if (off <= kNoAllocScratchBytes) {
+        char *b = (char *)sbase;
+        DecScratch &t = st->dec_static;
+        t.counters = (unsigned *)(b + o_cnt); t.xres = (float *)(b + o_xres); t.ssq = (float *)(b + o_ssq);
+        t.y = (bf16_t *)(b + o_y); t.attn = (bf16_t *)(b + o_attn); t.m = (bf16_t *)(b + o_m); t.qdec = (bf16_t *)(b + o_q);
+        t.partial = (float *)(b + o_part); t.attn_part = (float *)(b + o_ap);
+      }
     }
     rc = pack_weights_mfma(st, layers);
     if (rc == HYP_OK && st->L.pages_per_req) {

@@ -77,21 +77,3 @@ def test_noalloc_decode_refuses_what_does_not_fit_or_does_not_apply():
         tiny.decode_step_noalloc(xt[:1].contiguous(), torch.empty_like(xt[:1]))
     assert e.value.status == binding.HYP_ESHAPE
     tiny.destroy()
-
-
-def test_noalloc_decode_of_a_stage_that_fits_without_the_short_forms_of_attention():
-    # 32 requests of 128 query heads: 22 MB of temporaries, 37 MB with the eight partial results a head that contexts of
-    # at most 512 keys take; such a stage keeps the chunked form for every context, in either entry point
-    import torch
-    wide = synth.BlockShape(hidden=256, n_q_heads=128, n_kv_heads=32, head_dim=128, ffn_dim=32768, dtype="bf16")
-    layers = [synth.layer_weights(wide, 0, 8400, sigma=0.02)]
-    st = [make_gpu_stage(wide, layers, 32, 700, 1000) for _ in range(2)]
-    lens = [5, 100, 600]
-    x = to_dev(synth.hidden_states(sum(lens), wide, 8401), "bf16")
-    for t in st:
-        t.prefill(x, lens)
-    for s in range(2):
-        xd = to_dev(synth.hidden_states(3, wide, 8402 + s), "bf16")
-        assert torch.equal(st[0].decode_step(xd), st[1].decode_step_noalloc(xd, torch.empty_like(xd))), s
-    for t in st:
-        t.destroy()
