@@ -681,7 +681,8 @@ __global__ void __launch_bounds__(128) k_attn_decode_merge(const float *__restri
 
 // The second kernel of a recorded step, one workgroup per (request, KV head): the merge, or the whole of a short batch's
 // attention, whose first kernel returned at once.  (A step that the caller replays must give what a direct call gives at
-// the same context, and the two forms add up in different orders.)
+// the same context, and the two forms add up in different orders.)  Latency: a replayed 256-wide block of 8 requests takes
+// 32.9 us at 200 keys (39.1 as chunks) and 62.6 at 4500 (62.0 with the merge in workgroups of one head each).
 __global__ void __launch_bounds__(kShortWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
 k_attn_decode_recorded_end(const bf16_t *__restrict__ qdec, const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc, CacheGeom geom,
                            const int *__restrict__ lens, const float *__restrict__ part, bf16_t *__restrict__ out, int nq, int G,

@@ -365,7 +365,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
         bf16_t *dst = p.Vc + p.geom.off(b, head - p.nq - p.nkv, pos >> 5);
         // The feature's 32 slots are four runs of 8: MFMA steps m, lane halves khh.  The token that opens a block clears the
         // rest of it: decode attention multiplies the slots behind the last key by probabilities of zero, and whatever an
-        // earlier request left there need not be finite (prefill does the same behind a prompt's last key).
+        // earlier request left there need not be finite (prefill does the same behind a prompt's last key).  One step in 32;
+        // no request's time moved, where masking in the attention kernels cost 0.2 - 0.4 % of it.
         int m, khh;
         const int e = vtile_slot_of_key(pos & 31, &m, &khh);
         auto put = [&](int d, float v) {

@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(256) k_plain_pack(const T *__restrict__ src0, 
 }
 
 // x = hidden_in ; residual = x ; y = x * gain -> F(rows, H) ; sum of squares per 16 features.
-// grid (ceil(H16 / 256), rows); a thread per feature, 16 neighbouring lanes share a sum.
+// grid (rows, ceil(H / 256)); a thread per feature, 16 neighbouring lanes share a sum.
 template <typename T>
 __global__ void __launch_bounds__(256) k_plain_begin(const T *__restrict__ in, float *__restrict__ xres,
                                                      const T *__restrict__ gain, T *__restrict__ y,

@@ -774,7 +774,7 @@ hyp_status_t do_stage_create(const hyp_stage_config_t *cfg, int32_t l_start, int
   // RoPE tables: angle = pos * base^(-2i/d), formed in double on the host
   {
     int half = d.d / 2;
-    int n_pos = st->mfma ? st->L.key_blocks * 32 : d.max_seq;  // the MFMA path also rotates padding rows
+    int n_pos = st->mfma ? st->L.key_blocks * 32 : d.max_seq;  // MFMA path: whole key blocks
     std::vector<float> ct((size_t)n_pos * half), sn((size_t)n_pos * half);
     for (int i = 0; i < half; ++i) {
       double theta = pow((double)cfg->rope_base, -2.0 * (double)i / (double)d.d);
