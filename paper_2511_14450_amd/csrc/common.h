@@ -123,7 +123,7 @@ hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T 
 template <typename T>
 hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch, int longest,
                              float *part, const PlainCache &cache, const Dims &dm, hipStream_t s);
-size_t plain_attn_part_floats(int nq, int batch, int d);
+size_t plain_attn_part_floats(int nq, int nkv, int batch, int d);
 hipError_t plain_init();  // kernel attributes
 template <typename T>
 hipError_t plain_export_kv(const T *Kc, const T *Vc, T *k_out, T *v_out, int request, int len,

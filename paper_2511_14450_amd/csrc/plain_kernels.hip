@@ -2,6 +2,7 @@
 // contractions with fp32 accumulation on float or bf16 storage for any width, head size up to 256
 // and batch.  They are the whole fp32 path and serve bf16 stages whose shape the large bf16
 // kernels do not cover.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -365,6 +366,7 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
 // head, 10 + 3.6 us with the keys dealt to four; one wave per token and head took 166 us).
 // ----------------------------------------------------------------------------
 constexpr int kPlainMaxSplit = 8;
+constexpr size_t kPlainSplitGroups = 512;  // workgroups that a split may make of a decode step
 template <typename T> struct AttnArgs {
   const T *q, *Kc, *Vc;
   T *out;
@@ -712,7 +714,11 @@ hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T 
   return launch_attn<T, false>(a, dim3(n_tiles, dm.nq), s);
 }
 
-size_t plain_attn_part_floats(int nq, int batch, int d) { return (size_t)batch * nq * kPlainMaxSplit * (2 + d); }
+// a split of c needs batch * heads in flight * c <= kPlainSplitGroups: so many shares of all requests together
+size_t plain_attn_part_floats(int nq, int nkv, int batch, int d) {
+  const size_t per_request = (size_t)nkv * ((nq / nkv + 15) / 16);
+  return std::min((size_t)batch * kPlainMaxSplit, kPlainSplitGroups / per_request) * nq * (2 + d);
+}
 
 template <typename T>
 hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch, int longest,
@@ -728,7 +734,7 @@ hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *
   const int blocks = longest / 16 + 1, kw = 8;
   a.split = 1;
   double best = (blocks + kw - 1) / kw * round_us;
-  for (int c = 2; c <= kPlainMaxSplit && (size_t)batch * dm.nkv * groups * c <= 512; c *= 2) {
+  for (int c = 2; c <= kPlainMaxSplit && (size_t)batch * dm.nkv * groups * c <= kPlainSplitGroups; c *= 2) {
     const double t = (blocks + kw * c - 1) / (kw * c) * round_us + 5.0;
     if (t < best) { best = t; a.split = c; }
   }

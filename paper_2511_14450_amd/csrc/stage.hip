@@ -239,7 +239,7 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
   L.m = take(operand(R, I));
   L.act_end = off;
   L.ssq = take(sizeof(float) * (size_t)L.rows_pad * ((H + 15) / 16));
-  L.attn_part = take(sizeof(float) * plain_attn_part_floats(c.n_q_heads, c.max_batch, c.head_dim));
+  L.attn_part = take(sizeof(float) * plain_attn_part_floats(c.n_q_heads, c.n_kv_heads, c.max_batch, c.head_dim));
   L.tok_req = take(sizeof(int) * R);
   L.tok_pos = take(sizeof(int) * R);
   L.tiles = take(sizeof(PlainTile) * (R / 16 + c.max_batch));

@@ -57,6 +57,16 @@ def test_prefill_scratch_does_not_grow_with_the_batch():
     assert bytes_of(1024 + more) - bytes_of(1024) < weights + rows + partial + (1 << 20)
 
 
+def test_generic_decode_scratch_is_bounded_in_the_batch():
+    # decode attention's partial results serve batches too small to fill the chip; a large batch needs none.  A request adds
+    # its cache (2 x 16 keys x 64 floats), its row of the activations, tables - and nothing of the size of its 64 heads' partials
+    shape = synth.BlockShape(hidden=64, n_q_heads=64, n_kv_heads=1, head_dim=64, ffn_dim=64, dtype="f32")
+    def bytes_of(batch):
+        return hyp.stage_workspace_bytes(make_config(shape, batch, 16, 16), 0, 1)
+    cache, rows = 2 * 16 * 64 * 4, 4 * (64 + 64 + 2 * 64 * 64 + 64 + 4)
+    assert bytes_of(8192) - bytes_of(4096) < 4096 * (cache + rows + 256)
+
+
 def test_phi3_stage_fits_hbm():
     cfg = make_config(synth.PHI3_MEDIUM, 8, 8192 + 1024, 8 * 8192)
     need = hyp.stage_workspace_bytes(cfg, 0, 20)

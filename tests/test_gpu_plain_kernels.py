@@ -94,13 +94,14 @@ def test_decode_attention_with_its_keys_dealt_to_several_workgroups(dtype):
     from paper_2511_14450_amd import binding
     shp = synth.BlockShape(hidden=64, n_q_heads=2, n_kv_heads=1, head_dim=128, ffn_dim=64, dtype=dtype)
     layers = [synth.layer_weights(shp, 0, 33_000, sigma=0.05)]
-    for lens in ([3, 1530], [250, 700], [14, 15]):
+    for lens in ([3, 1530], [250, 700], [14, 15], [40] * 63 + [1200]):  # the last: as many pairs as may be split eightfold
+        B = len(lens)
         x = synth.hidden_states(sum(lens), shp, 33_001) / 8
-        ost = orc.Stage(shp, layers, 2, max(lens) + 3, "f32")
-        gst = make_gpu_stage(shp, layers, 2, max(lens) + 3, sum(lens), flags=binding.HYP_FLAG_PLAIN_KERNELS)
+        ost = orc.Stage(shp, layers, B, max(lens) + 3, "f32")
+        gst = make_gpu_stage(shp, layers, B, max(lens) + 3, sum(lens), flags=binding.HYP_FLAG_PLAIN_KERNELS)
         check(to_host(gst.prefill(to_dev(x, dtype), lens)), ost.prefill(x, lens), x, dtype, (lens, "prefill"))
         for s in range(3):
-            xd = synth.hidden_states(2, shp, 33_002 + s) / 8
+            xd = synth.hidden_states(B, shp, 33_002 + s) / 8
             check(to_host(gst.decode_step(to_dev(xd, dtype))), ost.decode_step(xd), xd, dtype, (lens, s))
         gst.destroy()
 
