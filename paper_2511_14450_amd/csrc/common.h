@@ -20,12 +20,16 @@ __host__ __device__ inline float bf16_to_f32(bf16_t v) {
 }
 
 __host__ __device__ inline bf16_t f32_to_bf16(float f) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_bit_cast(bf16_t, (__bf16)f);  // v_cvt_pk_bf16_f32: the bits of the steps below for all 2^32 inputs
+#else
   union { uint32_t u; float f; } c;
   c.f = f;
   uint32_t u = c.u;
   if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40u);  // NaN stays NaN
   u += 0x7fffu + ((u >> 16) & 1u);
   return (bf16_t)(u >> 16);
+#endif
 }
 
 template <typename T> __device__ inline float load_f32(const T *p);
@@ -86,8 +90,9 @@ template <typename T> struct PlainGemm {
   int ssq_parts = 0, rows_pad = 0;
   float eps = 0.f;
   // PLAIN_QKV: rotary position, cache append, queries row-major [rows][nq][q_ld]
-  const int *tok_req = nullptr, *tok_pos = nullptr;
-  const float *cos_tab = nullptr, *sin_tab = nullptr;
+  const int *tok_req = nullptr, *tok_pos = nullptr;  // no tok_req: row r is request r
+  const float *cos_tab = nullptr, *sin_tab = nullptr;  // [position][d / 2], or [row][d / 2] with tab_by_row
+  bool tab_by_row = false;
   T *q = nullptr, *Kc = nullptr, *Vc = nullptr;
   int q_ld = 0;
   PlainCache cache = {};
@@ -110,11 +115,20 @@ enum { PLAIN_ROWS = 0, PLAIN_PAIRS_QKV = 1, PLAIN_PAIRS_GATEUP = 2 };
 template <typename T>
 hipError_t plain_pack_weight(const T *src0, const T *src1, const T *src2, int rows0, int rows1, T *dst, int N, int K,
                              int mode, int head_dim, int qk_rows, hipStream_t s);
+// decode: positions of the rows, and their rotary angles out of the tables into [row][half]; pos null: none
+struct PlainAngles {
+  const int *pos = nullptr;
+  const float *cos_tab = nullptr, *sin_tab = nullptr;
+  float *cos_row = nullptr, *sin_row = nullptr;
+  int half = 0;
+};
 // x = hidden_in ; xres = x ; y = x * gain -> F(rows, H) ; sums of squares per 16 features
 template <typename T>
 hipError_t plain_begin(const T *hidden_in, float *xres, const T *gain, T *y, float *ssq_out, int rows, int rows_pad, int H,
-                       hipStream_t s);
+                       const PlainAngles &ang, hipStream_t s);
 template <typename T> hipError_t plain_gemm(int epi, const PlainGemm<T> &g, hipStream_t s);
+constexpr int kPlainGemvRows = 32;  // up to so many rows plain_gemm is
+template <typename T> hipError_t plain_gemv(int epi, const PlainGemm<T> &g, hipStream_t s);
 // prompt: tiles of up to 16 tokens; out F(rows, nq d)
 template <typename T>
 hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const PlainTile *tiles, int n_tiles,
@@ -123,7 +137,8 @@ hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T 
 template <typename T>
 hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch, int longest,
                              float *part, const PlainCache &cache, const Dims &dm, hipStream_t s);
-size_t plain_attn_part_floats(int nq, int nkv, int batch, int d);
+size_t plain_attn_part_floats(const Dims &dm, int batch);
+hipError_t plain_decode_init();
 hipError_t plain_init();  // kernel attributes
 template <typename T>
 hipError_t plain_export_kv(const T *Kc, const T *Vc, T *k_out, T *v_out, int request, int len,

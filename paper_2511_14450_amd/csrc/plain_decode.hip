@@ -1,0 +1,489 @@
+// Shape-generic kernels of a decode step (Sec. III-A of the paper): contractions of up to 32 token rows and attention of one
+// new token per request over the cache.  A step is a chain of short dependent kernels, so what counts in each of them is the
+// number of memory round trips one behind the other: everything that does not depend on another load is requested at the start.
+#include "plain_common.h"
+
+namespace hyp {
+
+namespace {
+
+// The sum over the wave's four rows of 16 lanes of four registers: row rho of the result holds register quad_reg(rho).
+// v_permlane32_swap / v_permlane16_swap exchange halves (odd and even rows) of two registers, so three exchanges and three
+// additions do what eight shuffles would, and no lane repeats another.
+__device__ __forceinline__ int quad_reg(int rho) { return (rho >> 1) | ((rho & 1) << 1); }
+__device__ __forceinline__ float rows_sum4(f32x4 v) {
+  auto add32 = [](float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
+  const float lo = add32(v[0], v[1]), hi = add32(v[2], v[3]);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// ----------------------------------------------------------------------------
+// out^T[N, rows] = W[N, K] X[rows, K]^T for up to TB token columns, the epilogues as for prompts (plain_epilogue).
+//
+// A workgroup owns 16 features; its KW waves take the tiles along K in turn, up to U of them requested at once, and meet in
+// LDS, in wave order.  Behind the first tiles follow the sums of squares (a KW-th of them per wave, combined in LDS with the
+// products) and what the epilogue needs, so that a workgroup waits for memory once.  (When every wave added up all the sums
+// of squares behind its K loop, that took 2.2 - 3.6 of the kernel's 4.8 - 5.6 us, 64 sums, 1024 wide.)
+//
+// Up to 8 tokens are staged through LDS, each chunk requested once per workgroup: fetched by the lanes of each wave as an MFMA
+// operand the four live rows of sixteen, or four copies of them, cost as many requests as the weights (float, 4 tokens, QKV
+// of 1024 x 2048: 6.1 -> 5.3 us).
+//
+// 4 tokens, 1024 wide, FFN 4096, two blocks (traced; before: one form of the prompt's kernel): QKV 7.7 -> 5.3 us float, 6.4 ->
+// 4.7 bf16; O 5.3 -> 4.1, 4.1 -> 3.8; gate/up 9.9 -> 8.2 (4.1 TB/s), 7.5 -> 5.6; down 10.3 -> 6.7, 5.6 -> 5.0.
+//
+// Float with up to 8 tokens multiplies with v_mfma_f32_4x4x1_16b_f32, whose sixteen blocks are (4 rows of the tile) x (K
+// group of the lane): the tile is its operand as it stands and four token columns replace sixteen, of which batch 4 would
+// fill a quarter (32 against 128 cycles of the matrix pipe per KiB of weights).
+// ----------------------------------------------------------------------------
+constexpr int kStage = 8;  // 16-byte chunks of the tokens that a thread stages at most
+
+template <typename T, int EPI, int TB, int KW>
+__global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(4))) k_plain_gemv(GemmArgs<T> a) {
+  constexpr bool kStaged = TB <= 8, kQuads = kStaged && sizeof(T) == 4;
+  constexpr int NB = kStaged ? 1 : TB / 16;   // 16-token blocks
+  constexpr int NX = kQuads ? TB / 4 : NB;    // token operands: quads, or 16-token blocks
+  constexpr int NA = kQuads ? 2 : 1;          // accumulator chains of an operand
+  constexpr int U = NB == 1 ? 8 : 4, kSsq = 4;  // registers: four waves per SIMD
+  extern __shared__ __attribute__((aligned(16))) u32x4 x_s[];  // staged tokens: [tile][4][TB]
+  const PlainGemm<T> &g = a.g;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, tl = lane & 15, row = lane >> 4;
+  const int ft = blockIdx.x;
+  const bool finisher = wave < NB;  // this wave runs the epilogue of token block `wave`
+  PlainAhead<T> pf;
+
+  const int chunks = a.tiles * 4 * TB, n_stage = (chunks + KW * 64 - 1) / (KW * 64);
+  u32x4 st[kStaged ? kStage : 1];
+  if constexpr (kStaged) {
+#pragma unroll
+    for (int i = 0; i < kStage; ++i)
+      if (i < n_stage) {
+        const int c = min((int)threadIdx.x + i * KW * 64, chunks - 1);
+        st[i] = ((const u32x4 *)g.X)[(c / TB) * 16 + c % TB];
+      }
+  }
+  const int tile0 = min(wave, a.tiles - 1);  // a wave without a tile rereads the last one and uses nothing
+  const u32x4 *wp = (const u32x4 *)g.W + ((size_t)ft * a.tiles + tile0) * 64 + lane;
+  const u32x4 *xp[NX];
+#pragma unroll
+  for (int j = 0; j < NX; ++j)
+    xp[j] = kStaged ? x_s + (wave * 4 + row) * TB + (kQuads ? (lane & 3) + 4 * j : tl % TB)
+                    : (const u32x4 *)g.X + ((size_t)min(j, a.tt - 1) * a.tiles + tile0) * 64 +
+                          (j * 16 + tl < g.rows ? lane : lane & 48);  // no token: the block's first again
+  constexpr int kXStep = KW * (kStaged ? 4 * TB : 64);
+  u32x4 wf[U], xf[kStaged ? 1 : NX][kStaged ? 1 : U];
+  f32x4 acc[NX][NA];
+#pragma unroll
+  for (int j = 0; j < NX; ++j)
+#pragma unroll
+    for (int c = 0; c < NA; ++c) acc[j][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto load = [&](int u, int i) {
+    wf[u] = wp[(size_t)i * KW * 64];
+    if constexpr (!kStaged)
+#pragma unroll
+      for (int j = 0; j < NX; ++j) xf[j][u] = xp[j][(size_t)i * kXStep];
+  };
+  auto use = [&](int u, int i) {
+    u32x4 x[NX];
+#pragma unroll
+    for (int j = 0; j < NX; ++j)
+      if constexpr (kStaged) x[j] = xp[j][i * kXStep];
+      else x[j] = xf[j][u];
+#pragma unroll
+    for (int e = 0; e < kMmaSteps<T>; ++e)
+#pragma unroll
+      for (int j = 0; j < NX; ++j) {
+        if constexpr (kQuads)
+          acc[j][e % NA] = __builtin_amdgcn_mfma_f32_4x4x1f32(__uint_as_float(wf[u][e]), __uint_as_float(x[j][e]), acc[j][e % NA], 0, 0, 0);
+        else acc[j][0] = mma<T>(wf[u], x[j], acc[j][0], e);
+      }
+  };
+  // sums of squares of this wave's share of the parts, lane = (token, part modulo 4)
+  constexpr bool kNorm = EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU;
+  float sq[NB][kSsq];
+  const float *ssq = g.ssq_in + (size_t)(wave * 4 + row) * g.rows_pad + tl;
+  // what follows the first tiles' requests
+  auto early = [&] {
+    if constexpr (kNorm) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int i = 0; i < kSsq; ++i)
+          sq[j][i] = wave * 4 + row + i * 4 * KW < g.ssq_parts ? ssq[(size_t)i * 4 * KW * g.rows_pad + min(j, a.tt - 1) * 16] : 0.f;
+    }
+    if (finisher) plain_fetch<T, EPI>(pf, g, wave * 16 + tl, ft * 16 + row * 4);
+    if constexpr (kStaged) {
+#pragma unroll
+      for (int i = 0; i < kStage; ++i)
+        if (i < n_stage) x_s[threadIdx.x + i * KW * 64] = st[i];
+      __syncthreads();
+    }
+  };
+  const int n = (a.tiles - wave + KW - 1) / KW;  // this wave's tiles: wave, wave + KW, ...
+  // Full windows: a tile's registers are refilled as soon as it has gone through the MFMAs.  The first window is requested
+  // without a condition (past the end: the first tile again), so that each wait is for one tile only.
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (U == 4 || u < 4) load(u, u < n ? u : 0);
+    else if (u < n) load(u, u);
+  early();
+  int t = 0;
+  for (; t + 2 * U <= n; t += U)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      use(u, t + u);
+      load(u, t + U + u);
+    }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (t + u < n) {
+      use(u, t + u);
+      if (t + U + u < n) load(u, t + U + u);
+    }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (t + U + u < n) use(u, t + U + u);
+
+  // [wave][operand]: 16 features x 16 tokens as the epilogue's lanes hold them, or x 4 tokens
+  __shared__ float red[KW][NX][kQuads ? 64 : 256];
+  __shared__ float sq_s[KW][NB][16];
+#pragma unroll
+  for (int j = 0; j < NX; ++j) {
+    if constexpr (kQuads) {
+      f32x4 s = acc[j][0];
+#pragma unroll
+      for (int c = 1; c < NA; ++c) s += acc[j][c];
+      red[wave][j][tl * 4 + quad_reg(row)] = rows_sum4(s);  // rows 4 (tl / 4) .. + 3 of token tl % 4
+    } else {
+      *(f32x4 *)&red[wave][j][lane * 4] = acc[j][0];
+    }
+  }
+  if constexpr (kNorm) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      float s = (sq[j][0] + sq[j][1]) + (sq[j][2] + sq[j][3]);
+      for (int p = wave * 4 + row + kSsq * 4 * KW; p < g.ssq_parts; p += 4 * KW) s += g.ssq_in[(size_t)p * g.rows_pad + min(j, a.tt - 1) * 16 + tl];
+      s += __shfl_xor(s, 16, 64);
+      s += __shfl_xor(s, 32, 64);
+      if (lane < 16) sq_s[wave][j][lane] = s;
+    }
+  }
+  __syncthreads();
+  if (finisher) {
+    const float *src = kQuads ? &red[0][NX == 1 ? 0 : (tl >> 2) & 1][(row * 4 + (tl & 3)) * 4] : &red[0][wave][lane * 4];
+    constexpr int kStride = NX * (kQuads ? 64 : 256);
+    f32x4 sum = *(const f32x4 *)src;
+#pragma unroll
+    for (int w = 1; w < KW; ++w) sum += *(const f32x4 *)(src + w * kStride);
+    float rs = 1.f;
+    if constexpr (kNorm) {
+      float s = sq_s[0][wave][tl];
+#pragma unroll
+      for (int w = 1; w < KW; ++w) s += sq_s[w][wave][tl];
+      rs = 1.0f / sqrtf(s * a.inv_K + g.eps);
+    }
+    plain_epilogue<T, EPI, true>(g, a.out_tiles, ft, wave * 16 + tl, row * 4, sum, rs, pf);
+  }
+  if (EPI == PLAIN_FINAL && g.lens_advance && blockIdx.x == 0 && (int)threadIdx.x < g.rows) g.lens_advance[threadIdx.x] += 1;
+}
+
+// ----------------------------------------------------------------------------
+// Attention of one new token per request.  A workgroup owns four query heads of a KV head (or a share of their keys); its KW
+// waves take the 16-key blocks in turn.  Four heads are the columns of v_mfma_f32_4x4x1_16b_f32, whose sixteen blocks are
+// (4 keys or features of a tile) x (16-byte chunk of the lane), so key and value tiles are operands as they lie in the cache
+// and no column is padding for a group of four; sixteen columns, of which a group of two fills an eighth, kept the matrix
+// pipe busy for 4 times as long and bounded the kernel (4 requests x 4 KV heads of 2 x 128 features in float, 536 keys: 9.8 us
+// and a merging launch of 2.9, now 10.7 without one; bf16, 64 features: 9.4 -> 6.8).  bf16 scores take v_mfma_f32_16x16x32_bf16 with the four heads repeated over its sixteen columns.  Online
+// softmax, probabilities and their products with the values in fp32 for either storage type; the waves' (max, sum, output)
+// meet in LDS, in wave order.
+// ----------------------------------------------------------------------------
+// NF: 16-feature blocks the registers hold, a multiple of what d needs
+// FULL: the head size fills them, so that no access is under a condition
+template <typename T, int NF, int KW, bool FULL>
+__global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
+  constexpr int NC = NF * (int)sizeof(T) / 4;  // K tiles: 16 floats or 32 bf16 each
+  constexpr int kSets = NF <= 8 ? 2 : 1;       // blocks of a wave in flight or in use
+  extern __shared__ __attribute__((aligned(16))) f32x4 o_s[];  // [KW][nf][64]
+  __shared__ float m_s[KW][4], l_s[KW][4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, row = lane >> 4, g4 = row * 4;
+  const int d = FULL ? NF * 16 : a.cache.d, nf = (d + 15) / 16, nc = plain_tiles(d, sizeof(T));
+  const int req = blockIdx.x / a.split, share = blockIdx.x % a.split, kvh = blockIdx.y;
+  const int col = blockIdx.z * 4 + (lane & 3), head = kvh * a.G + min(col, a.G - 1);  // this lane's column
+  const int last = a.lens[req];
+  const u32x4 *kp = (const u32x4 *)(a.Kc + ((size_t)req * a.cache.nkv + kvh) * a.cache.k_elems(sizeof(T))) + lane;
+  const T *vp = a.Vc + ((size_t)req * a.cache.nkv + kvh) * a.cache.v_elems() + lane * 4;
+  const u32x4 *qp = (const u32x4 *)(a.q + ((size_t)req * a.nq + head) * a.q_ld) + row;
+  const int first = share * KW + wave, step = a.split * KW;
+  u32x4 kS[kSets][NC], qf[NC];
+  typename VRaw<T>::V vS[kSets][NF];
+  auto load = [&](u32x4 (&k)[NC], typename VRaw<T>::V (&v)[NF], int kb) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (c < nc) k[c] = kp[((size_t)kb * nc + c) * 64];
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+      if (f < nf) v[f] = *(const typename VRaw<T>::V *)(vp + ((size_t)kb * nf + f) * 256);
+  };
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    if (c < nc) qf[c] = qp[c * 4];
+  // before the context's length is known: the request's room bounds what may be read
+  load(kS[0], vS[0], min(first, a.cache.key_blocks - 1));
+  f32x4 o[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) o[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;
+  const int n_kb = (last >> 4) + 1;
+  auto block = [&](u32x4 (&kf)[NC], typename VRaw<T>::V (&v)[NF], int kb) {
+    f32x4 s = {0.f, 0.f, 0.f, 0.f}, s1 = s;  // two chains
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (c < nc)
+#pragma unroll
+        for (int e = 0; e < kMmaSteps<T>; ++e) {
+          f32x4 &to = (c * kMmaSteps<T> + e) & 1 ? s1 : s;
+          if constexpr (sizeof(T) == 4) to = __builtin_amdgcn_mfma_f32_4x4x1f32(__uint_as_float(kf[c][e]), __uint_as_float(qf[c][e]), to, 0, 0, 0);
+          else to = mma<T>(kf[c], qf[c], to, e);
+        }
+    s += s1;
+    f32x4 vf[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+      if (f < nf) vf[f] = widen_v4<T>(v[f]);
+    const bool edge = kb == n_kb - 1;  // the only block with slots past the last key
+    float p[4], mx = -INFINITY;
+    if constexpr (sizeof(T) == 4) {
+      // a lane's score is that of one key: 4 ((lane / 4) % 4) + quad_reg(row)
+      p[0] = rows_sum4(s) * a.scale;
+      if (edge && kb * 16 + (lane & 12) + quad_reg(row) > last) p[0] = -INFINITY;
+      mx = fmaxf(p[0], __shfl_xor(p[0], 4, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 8, 64));
+    } else {
+      // a lane's scores are those of keys 4 row .. + 3
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        p[i] = s[i] * a.scale;
+        if (edge && kb * 16 + g4 + i > last) p[i] = -INFINITY;
+        mx = fmaxf(mx, p[i]);
+      }
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);
+    const float ref = m_new == -INFINITY ? 0.f : m_new;
+    const float corr = expf(m_run - ref);
+    m_run = m_new;
+    if constexpr (sizeof(T) == 4) {
+      const float w = expf(p[0] - ref);
+      l_run = l_run * corr + w;
+      // keys 4 row .. + 3 of this lane's head
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = __shfl(w, (((i >> 1) | ((i & 1) << 1)) << 4) | g4 | (lane & 3), 64);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = expf(p[i] - ref);
+      l_run = l_run * corr + ((p[0] + p[1]) + (p[2] + p[3]));
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) o[f] *= corr;
+    if (edge)
+      // slots past the last cached key hold anything: no product may meet them
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (f < nf && kb * 16 + g4 + i > last) vf[f][i] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+        if (f < nf) o[f] = __builtin_amdgcn_mfma_f32_4x4x1f32(vf[f][i], p[i], o[f], 0, 0, 0);
+  };
+  if constexpr (kSets == 2) {
+    load(kS[1], vS[1], min(first + step, n_kb - 1));  // past the end: the last block again, not used
+    for (int kb = first; kb < n_kb; kb += 2 * step) {
+      block(kS[0], vS[0], kb);
+      if (kb + step >= n_kb) break;
+      load(kS[0], vS[0], min(kb + 2 * step, n_kb - 1));
+      block(kS[1], vS[1], kb + step);
+      load(kS[1], vS[1], min(kb + 3 * step, n_kb - 1));
+    }
+  } else {
+    for (int kb = first; kb < n_kb; kb += step) {
+      block(kS[0], vS[0], kb);
+      load(kS[0], vS[0], min(kb + step, n_kb - 1));
+    }
+  }
+  // sum of the probabilities over the lanes that hold different keys
+  if constexpr (sizeof(T) == 4) {
+    l_run += __shfl_xor(l_run, 4, 64);
+    l_run += __shfl_xor(l_run, 8, 64);
+  }
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (lane < 4) { m_s[wave][lane] = m_run; l_s[wave][lane] = l_run; }
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+    if (f < nf) o_s[(wave * nf + f) * 64 + lane] = o[f];
+  __syncthreads();
+  const int c = lane & 3;
+  float m = m_s[0][c];  // -inf: a share without a key, whose weights and sums are 0
+#pragma unroll
+  for (int w = 1; w < KW; ++w) m = fmaxf(m, m_s[w][c]);
+  float wgt[KW], l = 0.f;
+#pragma unroll
+  for (int w = 0; w < KW; ++w) {
+    wgt[w] = m_s[w][c] == -INFINITY ? 0.f : expf(m_s[w][c] - m);
+    l += wgt[w] * l_s[w][c];
+  }
+  for (int f = wave; f < nf; f += KW) {
+    f32x4 r = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < KW; ++w)
+      r += o_s[(w * nf + f) * 64 + lane] * wgt[w];  // zeros of a share without a key
+    const float v = rows_sum4(r);  // the rows hold the sums over different keys
+    const int feat = f * 16 + (lane & 12) + quad_reg(row);
+    if (col >= a.G || feat >= d) continue;
+    if (a.split > 1) {
+      float *dst = a.part + (((size_t)req * a.nq + head) * a.split + share) * (2 + d);
+      if (feat == 0) { dst[0] = m; dst[1] = l; }
+      dst[2 + feat] = v;
+    } else {
+      store_f32(a.out + plain_offset<T>(req, head * d + feat, a.out_tiles), v / l);
+    }
+  }
+}
+
+// one workgroup per (head, request): the shares of a split decode attention in order
+// (a thread per feature; everything is requested before the first value is used)
+template <typename T> __global__ void __launch_bounds__(256) k_plain_attn_merge(AttnArgs<T> a) {
+  const int head = blockIdx.x, req = blockIdx.y, d = a.cache.d, f = min((int)threadIdx.x, d - 1);
+  const float *src = a.part + ((size_t)req * a.nq + head) * a.split * (2 + d);
+  float ms[kPlainMaxSplit], ls[kPlainMaxSplit], os[kPlainMaxSplit];
+#pragma unroll
+  for (int s = 0; s < kPlainMaxSplit; ++s) {
+    const float *p = src + min(s, a.split - 1) * (2 + d);
+    ms[s] = p[0]; ls[s] = p[1]; os[s] = p[2 + f];
+  }
+  float m = ms[0];
+#pragma unroll
+  for (int s = 1; s < kPlainMaxSplit; ++s) m = fmaxf(m, ms[s]);  // slots past the last repeat it
+  float l = 0.f, o = 0.f;
+#pragma unroll
+  for (int s = 0; s < kPlainMaxSplit; ++s) {
+    const float w = s >= a.split || ms[s] == -INFINITY ? 0.f : expf(ms[s] - m);
+    if (s < a.split) { l += w * ls[s]; o += w * os[s]; }
+  }
+  if ((int)threadIdx.x < d) store_f32(a.out + plain_offset<T>(req, head * d + f, a.out_tiles), o / l);
+}
+
+}  // namespace
+
+// groups of four query heads per KV head
+static int column_groups(const Dims &dm) { return (dm.nq / dm.nkv + 3) / 4; }
+
+template <typename T, int EPI>
+static hipError_t launch_gemv(const PlainGemm<T> &g, hipStream_t s) {
+  GemmArgs<T> a = gemm_args<T, EPI>(g);
+  // Where every CU holds one workgroup at most and eight waves would take more than one round of loads, sixteen share K.
+  const bool deep = a.ft <= 256 && a.tiles > 64;
+  // Up to 8 rows, as long as their copy in LDS is at most 128 KiB and kStage chunks a thread; written by whole waves.
+  const int threads = deep ? 1024 : 512;
+  auto staged = [&](int tb) { return g.rows <= tb && a.tiles * 4 * tb <= std::min(kStage * threads, 8192); };
+  auto lds = [&](int tb) { return (size_t)(a.tiles * 4 * tb + threads - 1) / threads * threads * 16; };
+#define X(TB, LDS)                                                           \
+  {                                                                          \
+    if (deep) k_plain_gemv<T, EPI, TB, 16><<<a.ft, 1024, LDS, s>>>(a);       \
+    else k_plain_gemv<T, EPI, TB, 8><<<a.ft, 512, LDS, s>>>(a);              \
+    return hipGetLastError();                                                \
+  }
+  if (staged(4)) X(4, lds(4))
+  if (staged(8)) X(8, lds(8))
+  if (g.rows <= 16) X(16, 0)
+  X(32, 0)
+#undef X
+}
+
+template <typename T> hipError_t plain_gemv(int epi, const PlainGemm<T> &g, hipStream_t s) {
+  if (g.rows == 0) return hipSuccess;
+  if (g.rows > kPlainGemvRows) return hipErrorInvalidValue;
+  switch (epi) {
+    case PLAIN_QKV: return launch_gemv<T, PLAIN_QKV>(g, s);
+    case PLAIN_SWIGLU: return launch_gemv<T, PLAIN_SWIGLU>(g, s);
+    case PLAIN_RESID: return launch_gemv<T, PLAIN_RESID>(g, s);
+    case PLAIN_FINAL: return launch_gemv<T, PLAIN_FINAL>(g, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+// (register blocks, waves): enough for d features; the waves' outputs pass 64 KiB of LDS at 8 waves of 128 features and more
+#define HYP_PLAIN_ATTN(X) X(4, 8, true) X(8, 8, true) X(4, 8, false) X(8, 8, false) X(16, 4, false)
+
+hipError_t plain_decode_init() {
+  hipError_t e = hipSuccess;
+#define X(T, EPI, TB, KW) \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_gemv<T, EPI, TB, KW>, hipFuncAttributeMaxDynamicSharedMemorySize, 8192 * 16);
+#define Y(T, TB, KW) X(T, PLAIN_QKV, TB, KW) X(T, PLAIN_SWIGLU, TB, KW) X(T, PLAIN_RESID, TB, KW) X(T, PLAIN_FINAL, TB, KW)
+  Y(float, 4, 8) Y(float, 4, 16) Y(float, 8, 8) Y(float, 8, 16) Y(bf16_t, 4, 8) Y(bf16_t, 4, 16) Y(bf16_t, 8, 8) Y(bf16_t, 8, 16)
+#undef Y
+#undef X
+#define X(NF, KW, FULL)                                                                                                              \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_dec_attn<float, NF, KW, FULL>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);  \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_dec_attn<bf16_t, NF, KW, FULL>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);
+  HYP_PLAIN_ATTN(X)
+#undef X
+  return e;
+}
+
+// a split of c needs batch * heads in flight * c <= kPlainSplitGroups: so many shares of all requests together
+size_t plain_attn_part_floats(const Dims &dm, int batch) {
+  const size_t per_request = (size_t)dm.nkv * column_groups(dm);
+  return std::min((size_t)batch * kPlainMaxSplit, kPlainSplitGroups / per_request) * dm.nq * (2 + dm.d);
+}
+
+template <typename T>
+hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch, int longest,
+                             float *part, const PlainCache &cache, const Dims &dm, hipStream_t s) {
+  if (batch == 0) return hipSuccess;
+  AttnArgs<T> a = attn_args<T>(q, q_ld, Kc, Vc, out, cache, dm);
+  a.lens = lens; a.part = part;
+  const int groups = column_groups(dm), nf = (dm.d + 15) / 16, nc = plain_tiles(dm.d, sizeof(T));
+  // Few (request, KV head) pairs leave most CUs idle: the keys of a head are dealt to `split` workgroups where the rounds of
+  // blocks that this saves (their MFMAs at two waves per SIMD, 2.4 GHz, plus 0.5 us of softmax and latency each) pay for
+  // the merging launch (5 us).
+  const double round_us = (nc * kMmaSteps<T> + nf * 4) * 16.0 / 2400.0 + 0.5;
+  const int blocks = longest / 16 + 1, kw = 8;
+  a.split = 1;
+  double best = (blocks + kw - 1) / kw * round_us;
+  for (int c = 2; c <= kPlainMaxSplit && (size_t)batch * dm.nkv * groups * c <= kPlainSplitGroups; c *= 2) {
+    const double t = (blocks + kw * c - 1) / (kw * c) * round_us + 5.0;
+    if (t < best) { best = t; a.split = c; }
+  }
+  const dim3 grid(batch * a.split, dm.nkv, groups);
+  const int nf_tiles = nc * 4 / (int)sizeof(T);
+  hipError_t e = hipErrorInvalidValue;
+#define X(NF, KW, FULL)                                                                    \
+  if (e == hipErrorInvalidValue && (FULL ? dm.d == NF * 16 : nf_tiles <= NF)) {      \
+    k_plain_dec_attn<T, NF, KW, FULL><<<grid, KW * 64, (size_t)KW * nf * 1024, s>>>(a); \
+    e = hipGetLastError();                                                           \
+    if (e != hipSuccess) return e;                                                   \
+  }
+  HYP_PLAIN_ATTN(X)
+#undef X
+  if (e != hipSuccess || a.split == 1) return e;
+  k_plain_attn_merge<T><<<dim3(dm.nq, batch), (dm.d + 63) / 64 * 64, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+#define HYP_INSTANTIATE(T)                                                                                            \
+  template hipError_t plain_gemv<T>(int, const PlainGemm<T> &, hipStream_t);                                          \
+  template hipError_t plain_attn_decode<T>(const T *, int, const T *, const T *, T *, const int *, int, int, float *,  \
+                                           const PlainCache &, const Dims &, hipStream_t);
+HYP_INSTANTIATE(float)
+HYP_INSTANTIATE(bf16_t)
+
+}  // namespace hyp

@@ -2,46 +2,11 @@
 // contractions with fp32 accumulation on float or bf16 storage for any width, head size up to 256
 // and batch.  They are the whole fp32 path and serve bf16 stages whose shape the large bf16
 // kernels do not cover.
-#include <algorithm>
-#include <type_traits>
-
-#include "common.h"
+#include "plain_common.h"
 
 namespace hyp {
 
 namespace {
-
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-
-// MFMA steps that the 64 bytes of K of one fragment pair take, and the i-th of them: acc += A B
-template <typename T> constexpr int kMmaSteps = 1;
-template <> constexpr int kMmaSteps<float> = 4;
-template <typename T> __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 acc, int i);
-template <> __device__ __forceinline__ f32x4 mma<float>(u32x4 a, u32x4 b, f32x4 acc, int i) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[i]), __uint_as_float(b[i]), acc, 0, 0, 0);
-}
-template <> __device__ __forceinline__ f32x4 mma<bf16_t>(u32x4 a, u32x4 b, f32x4 acc, int) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-}
-
-// four consecutive elements: one wide access where `vec` says the address allows it
-template <typename T> struct Four;
-template <> struct Four<float> { typedef f32x4 V; };
-template <> struct Four<bf16_t> { typedef uint2 V; };
-template <typename T> __device__ __forceinline__ void put4(T *p, const float *v, int n, bool vec) {
-  if (vec && n == 4) {
-    union { T e[4]; typename Four<T>::V v; } u;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) store_f32(&u.e[i], v[i]);
-    *(typename Four<T>::V *)p = u.v;
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (i < n) store_f32(p + i, v[i]);
-  }
-}
 
 // packed row -> row of the stacked matrices.  Rows an epilogue combines sit next to each other:
 // the rotary partners i, i + d/2 of every query and key head; gate and up of an FFN feature.
@@ -80,14 +45,21 @@ __global__ void __launch_bounds__(256) k_plain_pack(const T *__restrict__ src0, 
 }
 
 // x = hidden_in ; residual = x ; y = x * gain -> F(rows, H) ; sum of squares per 16 features.
-// grid (rows, ceil(H / 256)); a thread per feature, 16 neighbouring lanes share a sum.
+// grid (rows, ceil(max(H, half) / 256)); a thread per feature, 16 neighbouring lanes share a sum.  A decode step also copies
+// its tokens' rotary angles next to each other: the contractions of all blocks then find them without looking at the lengths
+// first (one round trip less in each).
 template <typename T>
 __global__ void __launch_bounds__(256) k_plain_begin(const T *__restrict__ in, float *__restrict__ xres,
                                                      const T *__restrict__ gain, T *__restrict__ y,
-                                                     float *__restrict__ ssq, int H, int rows_pad, int tiles) {
+                                                     float *__restrict__ ssq, int H, int rows_pad, int tiles, PlainAngles ang) {
   const int f = blockIdx.y * 256 + threadIdx.x;
   const size_t row = blockIdx.x;
   float x = 0.f;
+  if (ang.pos && f < ang.half) {
+    const size_t from = (size_t)ang.pos[row] * ang.half + f, to = row * ang.half + f;
+    ang.cos_row[to] = ang.cos_tab[from];
+    ang.sin_row[to] = ang.sin_tab[from];
+  }
   if (f < H) {
     x = load_f32(in + row * H + f);
     xres[row * H + f] = x;
@@ -113,23 +85,12 @@ __global__ void __launch_bounds__(256) k_plain_begin(const T *__restrict__ in, f
 // ahead of their use; FW x TW waves of a workgroup lie side by side, KW waves share the K loop and
 // meet in LDS, in wave order.  No LDS on the operand path: a float contraction spends 32 cycles of
 // the matrix pipe on every 256 bytes (128-wide wave tiles: 16 bytes per clock and CU), far below
-// what L1 delivers, and a decode step reads every weight tile once anyway.
-//   <1, 1, 1, 1, 8>  up to 16 tokens: a decode step, latency- and weight-bound; 8 waves share K (4 tokens, float, 1024
-//                    wide: gate/up 10.4 us for 34 MB, 3.2 TB/s out of the caches; the scalar tiles before took 150 - 640)
-//   <1, 2, 1, 1, 8>  up to 32 tokens
+// what L1 delivers.  More than kPlainGemvRows rows (fewer: plain_gemv).
 //   <2, 2, 1, 1, 4>  prompts that leave the wide form's grid short of the chip (920 tokens, float: QKV 61 us = 64
 //                    TFLOP/s, down 90 us = 86 TFLOP/s)
 //   <4, 4, 2, 2, 1>  long prompts: 128 x 128 per workgroup (920 x 8192 x 1024: float 170 us = 91 TFLOP/s, 60 % of what
 //                    the vendor BLAS reaches on 8192^3; 1065 x 8192 x 1024 bf16 52 us = 343 TFLOP/s, bound by L1)
 // ----------------------------------------------------------------------------
-template <typename T> struct GemmArgs {
-  PlainGemm<T> g;
-  int tiles;      // tiles along K
-  int ft, tt;     // 16-row tiles of features, of tokens
-  int out_tiles;  // tiles along K of the output matrix in fragment order
-  float inv_K;
-};
-
 template <typename T, int EPI, int WM, int WN, int FW, int TW, int KW>
 __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a) {
   constexpr int U = WM * WN >= 16 ? 2 : WM * WN >= 4 ? 2 : 4;
@@ -185,32 +146,11 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
   // What the epilogue of the small forms (registers) needs from memory is requested under the first
   // tiles: positions, rotary angles, residual and gain of the blocks this wave finishes.
   constexpr bool kAhead = KW >= WM * WN;  // at most one block per wave: kw / WN, kw % WN
-  int pf_req = 0, pf_pos = 0;
-  float pf_c[2] = {0.f, 0.f}, pf_s[2] = {0.f, 0.f};
-  f32x4 pf_x = {0.f, 0.f, 0.f, 0.f}, pf_g = {0.f, 0.f, 0.f, 0.f};
+  PlainAhead<T> pf;
   if constexpr (kAhead) {
-    const int f0 = (ft0 + kw / WN) * 16 + q4, tok = (tt0 + kw % WN) * 16 + tl;
-    if (kw < WM * WN && tok < g.rows && f0 < g.N) {
-      if (EPI == PLAIN_QKV) {
-        pf_req = g.tok_req[tok]; pf_pos = g.tok_pos[tok];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          if (f0 + 2 * h < g.dm.qd + g.dm.kvd) {
-            const size_t at = (size_t)pf_pos * (g.dm.d >> 1) + ((f0 + 2 * h) % g.dm.d >> 1);
-            pf_c[h] = g.cos_tab[at]; pf_s[h] = g.sin_tab[at];
-          }
-      } else if (EPI == PLAIN_RESID || EPI == PLAIN_FINAL) {
-        const float *xr = g.xres + (size_t)tok * g.N + f0;
-        if (g.N % 4 == 0) pf_x = *(const f32x4 *)xr;
-        else
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (f0 + e < g.N) pf_x[e] = xr[e];
-        if (EPI == PLAIN_RESID)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (f0 + e < g.N) pf_g[e] = load_f32(g.gain + f0 + e);
-      }
+    if (kw < WM * WN) {
+      const int tok = (tt0 + kw % WN) * 16 + tl;
+      plain_fetch<T, EPI>(pf, g, tok, (ft0 + kw / WN) * 16 + q4);
     }
   }
   // pairs of whole groups, then what is left (checked tile by tile)
@@ -270,150 +210,32 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
       if (KW > 1 && (i * WN + j) % KW != kw) continue;
-      const int ft = ft0 + i, tok = (tt0 + j) * 16 + tl, f0 = ft * 16 + q4;
-      if (ft >= a.ft || tt0 + j >= a.tt) continue;  // uniform over the wave
-      const bool live = tok < g.rows;
-      if (EPI == PLAIN_QKV) {
-        if (!live || f0 >= g.N) continue;
-        const int d = g.dm.d, half = d >> 1, qk = g.dm.qd + g.dm.kvd;
-        const int req = kAhead ? pf_req : g.tok_req[tok], pos = kAhead ? pf_pos : g.tok_pos[tok];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int r = f0 + 2 * h;  // a pair of packed rows: every boundary between heads and matrices is even
-          if (r >= g.N) break;
-          float v0 = acc[i][j][2 * h] * rs[j], v1 = acc[i][j][2 * h + 1] * rs[j];
-          if (r < qk) {
-            const int head = r / d, e = (r % d) >> 1;
-            const float c = kAhead ? pf_c[h] : g.cos_tab[(size_t)pos * half + e], s = kAhead ? pf_s[h] : g.sin_tab[(size_t)pos * half + e];
-            const float lo = v0 * c - v1 * s, hi = v1 * c + v0 * s;
-            if (head < g.dm.nq) {
-              T *dst = g.q + ((size_t)tok * g.dm.nq + head) * g.q_ld;
-              store_f32(dst + e, lo);
-              store_f32(dst + e + half, hi);
-            } else {
-              const int tk = plain_tiles(d, sizeof(T));
-              T *dst = g.Kc + ((size_t)req * g.dm.nkv + head - g.dm.nq) * g.cache.k_elems(sizeof(T));
-              store_f32(dst + plain_offset<T>(pos, e, tk), lo);
-              store_f32(dst + plain_offset<T>(pos, e + half, tk), hi);
-            }
-          } else {
-            const int head = (r - qk) / d, e = (r - qk) % d;
-            T *dst = g.Vc + ((size_t)req * g.dm.nkv + head) * g.cache.v_elems();
-            store_f32(dst + g.cache.v_offset(pos, e), v0);
-            store_f32(dst + g.cache.v_offset(pos, e + 1), v1);
-          }
-        }
-      } else if (EPI == PLAIN_SWIGLU) {
-        if (!live || f0 >= g.N) continue;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if (f0 + 2 * h >= g.N) break;
-          const float gt = acc[i][j][2 * h] * rs[j], up = acc[i][j][2 * h + 1] * rs[j];
-          store_f32(g.m + plain_offset<T>(tok, (f0 >> 1) + h, a.out_tiles), gt / (1.0f + expf(-gt)) * up);
-        }
-      } else {
-        const int n = min(4, g.N - f0);
-        const bool vec = g.N % 4 == 0;
-        float x[4] = {0.f, 0.f, 0.f, 0.f};
-        if (live && n > 0) {
-          float *xr = g.xres + (size_t)tok * g.N + f0;
-          if (kAhead) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (e < n) x[e] = pf_x[e] + acc[i][j][e];
-          } else if (vec) {
-            const f32x4 old = *(const f32x4 *)xr;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = old[e] + acc[i][j][e];
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (e < n) x[e] = xr[e] + acc[i][j][e];
-          }
-          if (EPI == PLAIN_RESID) {
-            put4(xr, x, n, vec);
-            float y[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = e < n ? x[e] * (kAhead ? pf_g[e] : load_f32(g.gain + f0 + e)) : 0.f;
-            put4(g.y + plain_offset<T>(tok, f0, a.out_tiles), y, n, true);
-          } else {
-            put4(g.hidden_out + (size_t)tok * g.N + f0, x, n, false);
-          }
-        }
-        if (EPI == PLAIN_RESID) {
-          float s;
-          {
-#pragma clang fp contract(off)
-            s = (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
-          }
-          s += __shfl_xor(s, 16, 64);
-          s += __shfl_xor(s, 32, 64);
-          if (lane < 16 && live) g.ssq_out[(size_t)ft * g.rows_pad + tok] = s;
-        }
-      }
+      if (ft0 + i >= a.ft || tt0 + j >= a.tt) continue;  // uniform over the wave
+      plain_epilogue<T, EPI, kAhead>(g, a.out_tiles, ft0 + i, (tt0 + j) * 16 + tl, q4, acc[i][j],
+                                     EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU ? rs[j] : 1.f, pf);
     }
   if (EPI == PLAIN_FINAL && g.lens_advance && blockIdx.x == 0)
     for (int b = threadIdx.x; b < g.rows; b += FW * TW * KW * 64) g.lens_advance[b] += 1;
 }
 
 // ----------------------------------------------------------------------------
-// Attention over the cache.  A workgroup owns 16 query columns - 16 consecutive prompt tokens of
-// one head, or the query heads of one KV head for a single new token - and its KW waves take the
+// Attention of a prompt over the cache.  A workgroup owns 16 consecutive prompt tokens of one head and its KW waves take the
 // 16-key blocks in turn.  S^T = K q^T (keys on the M axis: a lane holds four keys of one query),
 // online softmax in fp32, O^T += V^T P^T with fp32 probabilities against fp32 products for either
-// storage type; the waves' (max, sum, output) meet in LDS in wave order.  Bound by the fp32 matrix pipe, which works
-// through 16 columns whatever the head group fills (decode, 536 keys, float, 128 wide: 27 us in one workgroup per KV
-// head, 10 + 3.6 us with the keys dealt to four; one wave per token and head took 166 us).
+// storage type; the waves' (max, sum, output) meet in LDS in wave order.  Bound by the fp32 matrix pipe.
 // ----------------------------------------------------------------------------
-constexpr int kPlainMaxSplit = 8;
-constexpr size_t kPlainSplitGroups = 512;  // workgroups that a split may make of a decode step
-template <typename T> struct AttnArgs {
-  const T *q, *Kc, *Vc;
-  T *out;
-  const PlainTile *tiles;
-  const int *lens;
-  PlainCache cache;
-  int nq, G, q_ld, out_tiles;
-  float scale;
-  int split;    // decode: workgroups that share the keys of a (request, head group)
-  float *part;  // split > 1: [request][head][split][2 + d] = max, sum, unnormalised output
-};
-
-template <typename T> struct VRaw;
-template <> struct VRaw<float> { typedef f32x4 V; };
-template <> struct VRaw<bf16_t> { typedef uint2 V; };
-template <typename T> __device__ __forceinline__ f32x4 widen_v4(typename VRaw<T>::V u);
-template <> __device__ __forceinline__ f32x4 widen_v4<float>(f32x4 u) { return u; }
-template <> __device__ __forceinline__ f32x4 widen_v4<bf16_t>(uint2 u) {
-  return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
-}
-
 // NF: 16-feature blocks the registers hold, a multiple of what d needs
-template <typename T, int NF, int KW, bool DECODE>
+template <typename T, int NF, int KW>
 __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
   constexpr int NC = NF * (int)sizeof(T) / 4;  // K tiles: 16 floats or 32 bf16 each
   extern __shared__ __attribute__((aligned(16))) f32x4 o_s[];  // [KW][nf][64]
   __shared__ float m_s[KW][16], l_s[KW][16];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, tl = lane & 15, g4 = (lane >> 4) * 4;
   const int d = a.cache.d, nf = (d + 15) / 16, nc = plain_tiles(d, sizeof(T));
-  int req, kvh, row, head, qpos, last;
-  bool live;
-  if (DECODE) {
-    req = blockIdx.x / a.split; kvh = blockIdx.y;
-    const int c = blockIdx.z * 16 + tl;
-    live = c < a.G;
-    head = kvh * a.G + min(c, a.G - 1);
-    row = req;
-    qpos = last = a.lens[req];
-  } else {
-    const PlainTile t = a.tiles[blockIdx.x];
-    head = blockIdx.y;
-    kvh = head / a.G; req = t.req;
-    live = tl < t.n;
-    row = t.row0 + min(tl, t.n - 1);
-    qpos = t.pos0 + min(tl, t.n - 1);
-    last = t.pos0 + t.n - 1;
-  }
+  const PlainTile t = a.tiles[blockIdx.x];
+  const int head = blockIdx.y, kvh = head / a.G, req = t.req, row = t.row0 + min(tl, t.n - 1), qpos = t.pos0 + min(tl, t.n - 1);
+  const int last = t.pos0 + t.n - 1;
+  const bool live = tl < t.n;
   const u32x4 *kp = (const u32x4 *)(a.Kc + ((size_t)req * a.cache.nkv + kvh) * a.cache.k_elems(sizeof(T))) + lane;
   const T *vp = a.Vc + ((size_t)req * a.cache.nkv + kvh) * a.cache.v_elems() + lane * 4;
   const u32x4 *qp = (const u32x4 *)(a.q + ((size_t)row * a.nq + head) * a.q_ld) + (lane >> 4);
@@ -426,8 +248,6 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
   for (int f = 0; f < NF; ++f) o[f] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
   const int n_kb = (last >> 4) + 1;
-  // this wave's blocks: every step-th from `first` on
-  const int share = DECODE ? (int)(blockIdx.x % a.split) : 0, first = share * KW + wave, step = DECODE ? a.split * KW : KW;
   // a wave's next block is requested before the current one is used, where the registers allow it
   constexpr int kSets = NF * (int)sizeof(T) <= 16 ? 2 : 1;
   u32x4 kS[kSets][NC];
@@ -483,7 +303,7 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (f < nf && kb * 16 + g4 + i > last) vf[f][i] = 0.f;
-      if (!DECODE) {
+      {
         // a value that is not finite must not reach the queries in front of it (0 * inf): such a
         // block - no ordinary one - is added key by key
         bool odd = false;
@@ -518,16 +338,16 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
           if (f < nf) o[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[f][i], p[i], o[f], 0, 0, 0);
   };
   if constexpr (kSets == 2) {
-    if (first < n_kb) load(kS[0], vS[0], first);
-    for (int kb = first; kb < n_kb; kb += 2 * step) {
-      load(kS[1], vS[1], min(kb + step, n_kb - 1));  // past the end: the last block again, not used
+    if (wave < n_kb) load(kS[0], vS[0], wave);
+    for (int kb = wave; kb < n_kb; kb += 2 * KW) {
+      load(kS[1], vS[1], min(kb + KW, n_kb - 1));  // past the end: the last block again, not used
       block(kS[0], vS[0], kb);
-      if (kb + step >= n_kb) break;
-      load(kS[0], vS[0], min(kb + 2 * step, n_kb - 1));
-      block(kS[1], vS[1], kb + step);
+      if (kb + KW >= n_kb) break;
+      load(kS[0], vS[0], min(kb + 2 * KW, n_kb - 1));
+      block(kS[1], vS[1], kb + KW);
     }
   } else {
-    for (int kb = first; kb < n_kb; kb += step) {
+    for (int kb = wave; kb < n_kb; kb += KW) {
       load(kS[0], vS[0], kb);
       block(kS[0], vS[0], kb);
     }
@@ -552,45 +372,16 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
     f32x4 r = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < KW; ++w)
-      if (share * KW + w < n_kb) r += o_s[(w * nf + f) * 64 + lane] * wgt[w];
+      if (w < n_kb) r += o_s[(w * nf + f) * 64 + lane] * wgt[w];
     float v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[i] = r[i] / l;
     const int f0 = f * 16 + g4, n = min(4, d - f0), k = head * d + f0;
     if (!live || n <= 0) continue;
-    if (DECODE && a.split > 1) {
-      float *dst = a.part + (((size_t)req * a.nq + head) * a.split + share) * (2 + d);
-      if (f0 == 0) { dst[0] = m; dst[1] = l; }
-      for (int i = 0; i < n; ++i) dst[2 + f0 + i] = r[i];
-      continue;
-    }
     if (d % 4 == 0) put4(a.out + plain_offset<T>(row, k, a.out_tiles), v, n, true);
     else
       for (int i = 0; i < n; ++i) store_f32(a.out + plain_offset<T>(row, k + i, a.out_tiles), v[i]);
   }
-}
-
-// one workgroup per (head, request): the shares of a split decode attention in order
-// (a thread per feature; everything is requested before the first value is used)
-template <typename T> __global__ void __launch_bounds__(256) k_plain_attn_merge(AttnArgs<T> a) {
-  const int head = blockIdx.x, req = blockIdx.y, d = a.cache.d, f = min((int)threadIdx.x, d - 1);
-  const float *src = a.part + ((size_t)req * a.nq + head) * a.split * (2 + d);
-  float ms[kPlainMaxSplit], ls[kPlainMaxSplit], os[kPlainMaxSplit];
-#pragma unroll
-  for (int s = 0; s < kPlainMaxSplit; ++s) {
-    const float *p = src + min(s, a.split - 1) * (2 + d);
-    ms[s] = p[0]; ls[s] = p[1]; os[s] = p[2 + f];
-  }
-  float m = ms[0];
-#pragma unroll
-  for (int s = 1; s < kPlainMaxSplit; ++s) m = fmaxf(m, ms[s]);  // slots past the last repeat it
-  float l = 0.f, o = 0.f;
-#pragma unroll
-  for (int s = 0; s < kPlainMaxSplit; ++s) {
-    const float w = s >= a.split || ms[s] == -INFINITY ? 0.f : expf(ms[s] - m);
-    if (s < a.split) { l += w * ls[s]; o += w * os[s]; }
-  }
-  if ((int)threadIdx.x < d) store_f32(a.out + plain_offset<T>(req, head * d + f, a.out_tiles), o / l);
 }
 
 template <typename T>
@@ -631,34 +422,28 @@ hipError_t plain_pack_weight(const T *src0, const T *src1, const T *src2, int ro
 
 template <typename T>
 hipError_t plain_begin(const T *hidden_in, float *xres, const T *gain, T *y, float *ssq_out, int rows, int rows_pad, int H,
-                       hipStream_t s) {
+                       const PlainAngles &ang, hipStream_t s) {
   if (rows == 0) return hipSuccess;
   // grid.x carries the row (up to 2^31 - 1)
-  k_plain_begin<T><<<dim3(rows, (H + 255) / 256), 256, 0, s>>>(hidden_in, xres, gain, y, ssq_out, H, rows_pad, plain_tiles(H, sizeof(T)));
+  k_plain_begin<T><<<dim3(rows, (std::max(H, ang.pos ? ang.half : 0) + 255) / 256), 256, 0, s>>>(hidden_in, xres, gain, y, ssq_out, H, rows_pad,
+                                                                                                 plain_tiles(H, sizeof(T)), ang);
   return hipGetLastError();
 }
 
 template <typename T, int EPI>
 static hipError_t launch_gemm(const PlainGemm<T> &g, hipStream_t s) {
-  GemmArgs<T> a;
-  a.g = g;
-  a.tiles = plain_tiles(g.K, sizeof(T));
-  a.ft = (g.N + 15) / 16; a.tt = (g.rows + 15) / 16;
-  a.out_tiles = plain_tiles(EPI == PLAIN_SWIGLU ? g.N / 2 : g.N, sizeof(T));
-  a.inv_K = 1.0f / (float)g.K;
+  GemmArgs<T> a = gemm_args<T, EPI>(g);
   auto groups = [](int n, int per) { return (unsigned)((n + per - 1) / per); };
   // The widest form whose workgroups still fill the chip twice over; below that latency counts, and
   // more, smaller workgroups with their K loop shared by the waves win.
   const size_t wide = (size_t)groups(a.ft, 8) * groups(a.tt, 8);
-  if (a.tt == 1) k_plain_gemm<T, EPI, 1, 1, 1, 1, 8><<<a.ft, 512, 0, s>>>(a);
-  else if (a.tt == 2) k_plain_gemm<T, EPI, 1, 2, 1, 1, 8><<<a.ft, 512, 0, s>>>(a);
-  else if (wide >= 512) k_plain_gemm<T, EPI, 4, 4, 2, 2, 1><<<groups(a.ft, 8) * groups(a.tt, 8), 256, 0, s>>>(a);
+  if (wide >= 512) k_plain_gemm<T, EPI, 4, 4, 2, 2, 1><<<groups(a.ft, 8) * groups(a.tt, 8), 256, 0, s>>>(a);
   else k_plain_gemm<T, EPI, 2, 2, 1, 1, 4><<<groups(a.ft, 2) * groups(a.tt, 2), 256, 0, s>>>(a);
   return hipGetLastError();
 }
 
 template <typename T> hipError_t plain_gemm(int epi, const PlainGemm<T> &g, hipStream_t s) {
-  if (g.rows == 0) return hipSuccess;
+  if (g.rows <= kPlainGemvRows) return plain_gemv<T>(epi, g, s);
   switch (epi) {
     case PLAIN_QKV: return launch_gemm<T, PLAIN_QKV>(g, s);
     case PLAIN_SWIGLU: return launch_gemm<T, PLAIN_SWIGLU>(g, s);
@@ -671,12 +456,12 @@ template <typename T> hipError_t plain_gemm(int epi, const PlainGemm<T> &g, hipS
 // (register blocks, waves): enough for d features; the waves' outputs pass 64 KiB of LDS at 8 waves of 128 features and more
 #define HYP_PLAIN_ATTN(X) X(4, 8) X(8, 8) X(16, 4)
 
-template <typename T, bool DECODE>
+template <typename T>
 static hipError_t launch_attn(const AttnArgs<T> &a, dim3 grid, hipStream_t s) {
   const int nf = (a.cache.d + 15) / 16, nf_tiles = plain_tiles(a.cache.d, sizeof(T)) * 4 / (int)sizeof(T);
 #define X(NF, KW)                                                                              \
   if (nf_tiles <= NF) {                                                                         \
-    k_plain_attn<T, NF, KW, DECODE><<<grid, KW * 64, (size_t)KW * nf * 1024, s>>>(a);           \
+    k_plain_attn<T, NF, KW><<<grid, KW * 64, (size_t)KW * nf * 1024, s>>>(a);           \
     return hipGetLastError();                                                                  \
   }
   HYP_PLAIN_ATTN(X)
@@ -685,24 +470,13 @@ static hipError_t launch_attn(const AttnArgs<T> &a, dim3 grid, hipStream_t s) {
 }
 
 hipError_t plain_init() {
-  hipError_t e = hipSuccess;
+  hipError_t e = plain_decode_init();
 #define X(NF, KW)                                                                                                              \
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<float, NF, KW, false>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);  \
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<float, NF, KW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);   \
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<bf16_t, NF, KW, false>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024); \
-  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<bf16_t, NF, KW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<float, NF, KW>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);  \
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<bf16_t, NF, KW>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024); \
   HYP_PLAIN_ATTN(X)
 #undef X
   return e;
-}
-
-template <typename T>
-static AttnArgs<T> attn_args(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const PlainCache &cache, const Dims &dm) {
-  AttnArgs<T> a = {};
-  a.q = q; a.Kc = Kc; a.Vc = Vc; a.out = out; a.cache = cache;
-  a.nq = dm.nq; a.G = dm.nq / dm.nkv; a.q_ld = q_ld; a.out_tiles = plain_tiles(dm.qd, sizeof(T));
-  a.scale = 1.0f / sqrtf((float)dm.d);
-  return a;
 }
 
 template <typename T>
@@ -711,37 +485,7 @@ hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T 
   if (n_tiles == 0) return hipSuccess;
   AttnArgs<T> a = attn_args<T>(q, q_ld, Kc, Vc, out, cache, dm);
   a.tiles = tiles;
-  return launch_attn<T, false>(a, dim3(n_tiles, dm.nq), s);
-}
-
-// a split of c needs batch * heads in flight * c <= kPlainSplitGroups: so many shares of all requests together
-size_t plain_attn_part_floats(int nq, int nkv, int batch, int d) {
-  const size_t per_request = (size_t)nkv * ((nq / nkv + 15) / 16);
-  return std::min((size_t)batch * kPlainMaxSplit, kPlainSplitGroups / per_request) * nq * (2 + d);
-}
-
-template <typename T>
-hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const int *lens, int batch, int longest,
-                             float *part, const PlainCache &cache, const Dims &dm, hipStream_t s) {
-  if (batch == 0) return hipSuccess;
-  AttnArgs<T> a = attn_args<T>(q, q_ld, Kc, Vc, out, cache, dm);
-  a.lens = lens; a.part = part;
-  const int groups = (a.G + 15) / 16, nf = (dm.d + 15) / 16, nc = plain_tiles(dm.d, sizeof(T));
-  // Few (request, KV head) pairs leave most CUs idle while one CU's matrix pipes work through 16 query columns of
-  // which the group fills a few: its keys are dealt to `split` workgroups where the rounds of blocks that this saves
-  // (their MFMAs at two waves per SIMD, 2.4 GHz, plus 0.6 us of latency each) pay for the merging launch (5 us).
-  const double round_us = (nc * kMmaSteps<T> + nf * 4) * 64.0 / 2400.0 + 0.6;
-  const int blocks = longest / 16 + 1, kw = 8;
-  a.split = 1;
-  double best = (blocks + kw - 1) / kw * round_us;
-  for (int c = 2; c <= kPlainMaxSplit && (size_t)batch * dm.nkv * groups * c <= kPlainSplitGroups; c *= 2) {
-    const double t = (blocks + kw * c - 1) / (kw * c) * round_us + 5.0;
-    if (t < best) { best = t; a.split = c; }
-  }
-  hipError_t e = launch_attn<T, true>(a, dim3(batch * a.split, dm.nkv, groups), s);
-  if (e != hipSuccess || a.split == 1) return e;
-  k_plain_attn_merge<T><<<dim3(dm.nq, batch), (dm.d + 63) / 64 * 64, 0, s>>>(a);
-  return hipGetLastError();
+  return launch_attn<T>(a, dim3(n_tiles, dm.nq), s);
 }
 
 template <typename T>
@@ -760,12 +504,10 @@ hipError_t plain_fill_zero(void *p, size_t bytes, hipStream_t s) {
 
 #define HYP_INSTANTIATE(T)                                                                                                   \
   template hipError_t plain_pack_weight<T>(const T *, const T *, const T *, int, int, T *, int, int, int, int, int, hipStream_t); \
-  template hipError_t plain_begin<T>(const T *, float *, const T *, T *, float *, int, int, int, hipStream_t);               \
+  template hipError_t plain_begin<T>(const T *, float *, const T *, T *, float *, int, int, int, const PlainAngles &, hipStream_t); \
   template hipError_t plain_gemm<T>(int, const PlainGemm<T> &, hipStream_t);                                                 \
   template hipError_t plain_attn_prefill<T>(const T *, int, const T *, const T *, T *, const PlainTile *, int,               \
                                             const PlainCache &, const Dims &, hipStream_t);                                  \
-  template hipError_t plain_attn_decode<T>(const T *, int, const T *, const T *, T *, const int *, int, int, float *,         \
-                                           const PlainCache &, const Dims &, hipStream_t);                                   \
   template hipError_t plain_export_kv<T>(const T *, const T *, T *, T *, int, int, const PlainCache &, hipStream_t);
 HYP_INSTANTIATE(float)
 HYP_INSTANTIATE(bf16_t)

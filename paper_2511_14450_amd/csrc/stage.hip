@@ -61,9 +61,9 @@ struct LayerPtrs {
 struct Layout {
   std::vector<LayerPtrs> layers;
   size_t Kc = 0, Vc = 0, kv_layer_stride = 0;  // per-layer stride in bytes (plain path: of Kc)
-  size_t cos_tab = 0, sin_tab = 0;
+  size_t cos_tab = 0, sin_tab = 0, cos_row = 0, sin_row = 0;
   size_t xres = 0, y = 0, attn = 0, m = 0, tiles = 0, ssq = 0;
-  size_t tok_req = 0, tok_pos = 0, lens = 0, iota = 0;
+  size_t tok_req = 0, tok_pos = 0, lens = 0;
   // plain path only: stride of Vc, row length of a query head, rows in whole 16-row tiles, end of the padded activations
   size_t v_layer_stride = 0, act_end = 0;
   int q_ld = 0, rows_pad = 0;
@@ -105,6 +105,14 @@ bool mfma_applies(const hyp_stage_config_t &c) {
   if (c.hidden % 256 || c.ffn_dim % 256) return false;
   if (c.max_batch > 32) return false;
   return true;
+}
+
+Dims dims_of(const hyp_stage_config_t &c) {
+  Dims d;
+  d.H = c.hidden; d.nq = c.n_q_heads; d.nkv = c.n_kv_heads; d.d = c.head_dim;
+  d.I = c.ffn_dim; d.qd = d.nq * d.d; d.kvd = d.nkv * d.d;
+  d.max_batch = c.max_batch; d.max_seq = c.max_seq; d.eps = c.rms_eps;
+  return d;
 }
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
@@ -239,12 +247,13 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
   L.m = take(operand(R, I));
   L.act_end = off;
   L.ssq = take(sizeof(float) * (size_t)L.rows_pad * ((H + 15) / 16));
-  L.attn_part = take(sizeof(float) * plain_attn_part_floats(c.n_q_heads, c.n_kv_heads, c.max_batch, c.head_dim));
+  L.attn_part = take(sizeof(float) * plain_attn_part_floats(dims_of(c), c.max_batch));
+  L.cos_row = take(sizeof(float) * (size_t)c.max_batch * (c.head_dim / 2));
+  L.sin_row = take(sizeof(float) * (size_t)c.max_batch * (c.head_dim / 2));
   L.tok_req = take(sizeof(int) * R);
   L.tok_pos = take(sizeof(int) * R);
   L.tiles = take(sizeof(PlainTile) * (R / 16 + c.max_batch));
   L.lens = take(sizeof(int) * c.max_batch);
-  L.iota = take(sizeof(int) * c.max_batch);
   L.total = off;
 }
 
@@ -589,7 +598,13 @@ hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, i
   float *xres = at<float>(st, L.xres), *ssq = at<float>(st, L.ssq);
   T *y = at<T>(st, L.y), *q = at<T>(st, L.q), *attn = at<T>(st, L.attn), *m = at<T>(st, L.m);
   int *lens = at<int>(st, L.lens);
-  HIP_TRY(st, plain_begin<T>((const T *)hidden_in, xres, at<T>(st, L.layers[0].g1), y, ssq, rows, L.rows_pad, d.H, s));
+  PlainAngles ang;
+  if (decode) {
+    ang.pos = lens; ang.half = d.d / 2;
+    ang.cos_tab = at<float>(st, L.cos_tab); ang.sin_tab = at<float>(st, L.sin_tab);
+    ang.cos_row = at<float>(st, L.cos_row); ang.sin_row = at<float>(st, L.sin_row);
+  }
+  HIP_TRY(st, plain_begin<T>((const T *)hidden_in, xres, at<T>(st, L.layers[0].g1), y, ssq, rows, L.rows_pad, d.H, ang, s));
   PlainGemm<T> base;
   base.rows = rows; base.rows_pad = L.rows_pad; base.eps = d.eps; base.dm = d; base.xres = xres;
   for (int l = 0; l < st->n_layers; ++l) {
@@ -598,8 +613,9 @@ hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, i
     PlainGemm<T> a = base;
     a.W = at<T>(st, p.wqkv); a.X = y; a.N = d.qd + 2 * d.kvd; a.K = d.H;
     a.ssq_in = ssq; a.ssq_parts = (d.H + 15) / 16;
-    a.tok_req = at<int>(st, decode ? L.iota : L.tok_req); a.tok_pos = decode ? lens : at<int>(st, L.tok_pos);
-    a.cos_tab = at<float>(st, L.cos_tab); a.sin_tab = at<float>(st, L.sin_tab);
+    a.tok_req = decode ? nullptr : at<int>(st, L.tok_req); a.tok_pos = decode ? lens : at<int>(st, L.tok_pos);
+    a.cos_tab = at<float>(st, decode ? L.cos_row : L.cos_tab); a.sin_tab = at<float>(st, decode ? L.sin_row : L.sin_tab);
+    a.tab_by_row = decode;
     a.q = q; a.q_ld = L.q_ld; a.Kc = Kc; a.Vc = Vc; a.cache = L.cache;
     HIP_TRY(st, plain_gemm<T>(PLAIN_QKV, a, s));
     if (decode) HIP_TRY(st, plain_attn_decode<T>(q, L.q_ld, Kc, Vc, attn, lens, rows, longest, at<float>(st, L.attn_part), L.cache, d, s));
@@ -693,10 +709,8 @@ hyp_status_t do_stage_create(const hyp_stage_config_t *cfg, int32_t l_start, int
   st->ws = (char *)workspace;
   st->h_stage = nullptr; st->upload_done = nullptr; st->upload_pending = false;
   st->batch = 0; st->prefilled = false;
-  Dims &d = st->dm;
-  d.H = cfg->hidden; d.nq = cfg->n_q_heads; d.nkv = cfg->n_kv_heads; d.d = cfg->head_dim;
-  d.I = cfg->ffn_dim; d.qd = d.nq * d.d; d.kvd = d.nkv * d.d;
-  d.max_batch = cfg->max_batch; d.max_seq = cfg->max_seq; d.eps = cfg->rms_eps;
+  st->dm = dims_of(*cfg);
+  const Dims &d = st->dm;
   make_layout(*cfg, st->n_layers, st->L);
   if (workspace_bytes < st->L.total) {
     std::string m = "workspace too small: need " + std::to_string(st->L.total) + " bytes";
@@ -787,10 +801,6 @@ hyp_status_t do_stage_create(const hyp_stage_config_t *cfg, int32_t l_start, int
     hipError_t e = hipMemcpyAsync(st->ws + st->L.cos_tab, ct.data(), sizeof(float) * ct.size(), hipMemcpyHostToDevice, st->stream);
     if (e == hipSuccess)
       e = hipMemcpyAsync(st->ws + st->L.sin_tab, sn.data(), sizeof(float) * sn.size(), hipMemcpyHostToDevice, st->stream);
-    std::vector<int> iota(cfg->max_batch);
-    for (int i = 0; i < cfg->max_batch; ++i) iota[i] = i;
-    if (e == hipSuccess && !st->mfma)
-      e = hipMemcpyAsync(st->ws + st->L.iota, iota.data(), sizeof(int) * iota.size(), hipMemcpyHostToDevice, st->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(st->stream);  // host vectors die here
     if (e != hipSuccess) { st->err = std::string("table upload: ") + hipGetErrorString(e); return bail(HYP_EDEVICE); }
   }

@@ -1,0 +1,43 @@
+"""Shape-generic decode kernels at the sizes where they can go wrong: token counts around the 4, 8, 16 and 32 columns that
+choose a form, K lengths around the window of tiles a wave requests at once, groups of query heads around the four columns of
+decode attention, head sizes that fill its registers and others, contexts around its rounds of 16-key blocks."""
+import pytest
+
+from oracle import hyp_oracle as orc
+from workloads import synth
+from tests.helpers import make_gpu_stage, rel_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+TOL = {"f32": 1e-4, "bf16": 2e-2}
+
+# hidden, query heads, KV heads, head size, FFN width.  Tiles of 64 bytes along K: eight waves with one tile or none,
+# one window and a rest, several windows, sixteen waves.
+SHAPES = {
+    "short_k": (48, 2, 2, 16, 72),
+    "full64": (528, 6, 2, 64, 1040),
+    "full128": (256, 4, 1, 128, 2320),
+    "group5": (160, 10, 2, 40, 4160),
+    "group9": (64, 9, 1, 128, 96),
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("batch", [1, 4, 5, 8, 9, 17, 33])
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_decode_against_oracle(shape, batch, dtype):
+    from paper_2511_14450_amd import binding
+    hidden, nq, nkv, d, ffn = SHAPES[shape]
+    shp = synth.BlockShape(hidden, nq, nkv, d, ffn, dtype=dtype)
+    lens = [1 + (b * 37) % 50 for b in range(batch)]
+    if batch <= 5:
+        lens[0] = 1 + 16 * 16 * 2 - 2  # the steps pass from two whole rounds of eight blocks into the next
+    layers = [synth.layer_weights(shp, l, 47_000, sigma=0.05) for l in range(2)]
+    x = synth.hidden_states(sum(lens), shp, 47_001)
+    cap = max(lens) + 4
+    ost = orc.Stage(shp, layers, batch, cap, "f32")
+    gst = make_gpu_stage(shp, layers, batch, cap, sum(lens), flags=binding.HYP_FLAG_PLAIN_KERNELS)
+    assert rel_err(to_host(gst.prefill(to_dev(x, dtype), lens)), ost.prefill(x, lens)) <= TOL[dtype]
+    for s in range(3):
+        xd = synth.hidden_states(batch, shp, 47_002 + s)
+        assert rel_err(to_host(gst.decode_step(to_dev(xd, dtype))), ost.decode_step(xd)) <= TOL[dtype], f"step {s}"
+    gst.destroy()
