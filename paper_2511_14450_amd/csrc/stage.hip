@@ -248,8 +248,9 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
   L.act_end = off;
   L.ssq = take(sizeof(float) * (size_t)L.rows_pad * ((H + 15) / 16));
   L.attn_part = take(sizeof(float) * plain_attn_part_floats(dims_of(c), c.max_batch));
-  L.cos_row = take(sizeof(float) * (size_t)c.max_batch * (c.head_dim / 2));
-  L.sin_row = take(sizeof(float) * (size_t)c.max_batch * (c.head_dim / 2));
+  const size_t angles = (size_t)std::min((int)c.max_batch, kPlainGemvRows) * (c.head_dim / 2);
+  L.cos_row = take(sizeof(float) * angles);
+  L.sin_row = take(sizeof(float) * angles);
   L.tok_req = take(sizeof(int) * R);
   L.tok_pos = take(sizeof(int) * R);
   L.tiles = take(sizeof(PlainTile) * (R / 16 + c.max_batch));
@@ -591,7 +592,7 @@ hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, i
   const Dims &d = st->dm;
   const Layout &L = st->L;
   hipStream_t s = st->stream;
-  const bool decode = n_tiles == 0;
+  const bool decode = n_tiles == 0, by_row = decode && rows <= kPlainGemvRows;  // by_row: the latency-bound forms
   int longest = 0;
   if (decode)
     for (int b = 0; b < rows; ++b) longest = std::max(longest, st->lens[b]);
@@ -599,7 +600,7 @@ hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, i
   T *y = at<T>(st, L.y), *q = at<T>(st, L.q), *attn = at<T>(st, L.attn), *m = at<T>(st, L.m);
   int *lens = at<int>(st, L.lens);
   PlainAngles ang;
-  if (decode) {
+  if (by_row) {
     ang.pos = lens; ang.half = d.d / 2;
     ang.cos_tab = at<float>(st, L.cos_tab); ang.sin_tab = at<float>(st, L.sin_tab);
     ang.cos_row = at<float>(st, L.cos_row); ang.sin_row = at<float>(st, L.sin_row);
@@ -614,8 +615,8 @@ hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, i
     a.W = at<T>(st, p.wqkv); a.X = y; a.N = d.qd + 2 * d.kvd; a.K = d.H;
     a.ssq_in = ssq; a.ssq_parts = (d.H + 15) / 16;
     a.tok_req = decode ? nullptr : at<int>(st, L.tok_req); a.tok_pos = decode ? lens : at<int>(st, L.tok_pos);
-    a.cos_tab = at<float>(st, decode ? L.cos_row : L.cos_tab); a.sin_tab = at<float>(st, decode ? L.sin_row : L.sin_tab);
-    a.tab_by_row = decode;
+    a.cos_tab = at<float>(st, by_row ? L.cos_row : L.cos_tab); a.sin_tab = at<float>(st, by_row ? L.sin_row : L.sin_tab);
+    a.tab_by_row = by_row;
     a.q = q; a.q_ld = L.q_ld; a.Kc = Kc; a.Vc = Vc; a.cache = L.cache;
     HIP_TRY(st, plain_gemm<T>(PLAIN_QKV, a, s));
     if (decode) HIP_TRY(st, plain_attn_decode<T>(q, L.q_ld, Kc, Vc, attn, lens, rows, longest, at<float>(st, L.attn_part), L.cache, d, s));
