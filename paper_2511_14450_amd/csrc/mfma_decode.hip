@@ -177,6 +177,49 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
 #pragma unroll
   for (int u = 0; u < UNROLL; ++u)
     if (u < rem) use_tile(u);
+  const int n_pairs = p.batch * kGroupRows;
+  // What the epilogue needs from memory besides the sums, requested at once: rotary angles, residual stream and next norm's
+  // gain, the sums of squares behind the RMS Norm factor (16 row groups per thread).
+  float cos_pf[kPf] = {0.f, 0.f}, sin_pf[kPf] = {0.f, 0.f};
+  constexpr int kPfR = 4;  // (token, row) pairs per thread fetched ahead: 16 tokens' worth
+  float xres_pf[kPfR], gain_pf[kPfR];
+  float ssq_v[16];
+  const int ssq_tkn = threadIdx.x & 31, ssq_part_id = threadIdx.x >> 5;
+  auto fetch = [&] {
+    if (EPI == DEC_QKV) {
+#pragma unroll
+      for (int j = 0; j < kPf; ++j) {
+        int idx = threadIdx.x + j * NW * 64;
+        if (idx < p.batch * 32) {
+          int d0 = ((fb0 >> 1) & 1) * 32 + (idx & 31);
+          cos_pf[j] = p.cos_tab[(size_t)pos_pf[j] * 64 + d0];
+          sin_pf[j] = p.sin_tab[(size_t)pos_pf[j] * 64 + d0];
+        }
+      }
+    }
+    if (EPI == DEC_RESID || EPI == DEC_FINAL) {
+#pragma unroll
+      for (int j = 0; j < kPfR; ++j) {
+        int idx = threadIdx.x + j * NW * 64;
+        xres_pf[j] = 0.f; gain_pf[j] = 0.f;
+        if (idx < n_pairs) {
+          int f = idx % kGroupRows, b = idx / kGroupRows;
+          xres_pf[j] = p.xres[(size_t)b * p.H + fb0 * 32 + f];
+          if (EPI == DEC_RESID) gain_pf[j] = bf16_to_f32(p.gain[fb0 * 32 + f]);
+        }
+      }
+    }
+    if (EPI == DEC_QKV || EPI == DEC_SWIGLU) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        int g = ssq_part_id + kSsqParts * u;
+        ssq_v[u] = g < p.n_ssq && ssq_tkn < p.batch ? p.ssq_in[g * 32 + ssq_tkn] : 0.f;
+      }
+    }
+  };
+  // An unsplit workgroup finishes for sure: the requests go out ahead of the waves' meeting (512-wide blocks: 1.1 of 4.4 us
+  // of QKV and gate/up were this round trip, with the epilogue's turn through LDS); a slice waits to know that it is the last.
+  if (ksplit == 1) fetch();
   // accumulator register r of lane l of block i is packed row 32 i + 8 (r/4) + 4 (l/32) + r%4 of
   // token l % 32: four consecutive rows per 16-byte store; token columns beyond the batch stay home
   if ((lane & 31) < p.batch) {
@@ -189,31 +232,24 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
       }
   }
   __syncthreads();
-  // sums of the 64 rows of this group, at most 8 (token, row) pairs per thread
-  const int n_pairs = p.batch * kGroupRows;
-  float mine[8];
+  // a row's sum over the waves, in wave order
+  auto wave_sum = [&](int token, int f) {
+    float s = 0.f;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    int idx = threadIdx.x + j * NW * 64;
-    mine[j] = 0.f;
-    if (idx < n_pairs) {
-      int f = idx % kGroupRows, token = idx / kGroupRows;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) mine[j] += red[w * p.batch + token][f];
-    }
-  }
-  __syncthreads();  // `red` is free from here on
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    int idx = threadIdx.x + j * NW * 64;
-    if (idx < n_pairs) {
-      int f = idx % kGroupRows, token = idx / kGroupRows;
-      if (ksplit > 1)  // write-through store: visible to the other XCDs once it has completed
-        __hip_atomic_store(&part[((size_t)ks * 32 + token) * part_n + part_r0 + f], mine[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else fin[token][f] = mine[j];
-    }
-  }
+    for (int w = 0; w < NW; ++w) s += red[w * p.batch + token][f];
+    return s;
+  };
   if (ksplit > 1) {
+    // at most 8 (token, row) pairs per thread
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      int idx = threadIdx.x + j * NW * 64;
+      if (idx < n_pairs) {
+        int f = idx % kGroupRows, token = idx / kGroupRows;
+        // write-through store: visible to the other XCDs once it has completed
+        __hip_atomic_store(&part[((size_t)ks * 32 + token) * part_n + part_r0 + f], wave_sum(token, f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
     __builtin_amdgcn_s_waitcnt(0);  // this thread's partial sums have completed ...
     __syncthreads();
     if (threadIdx.x == 0) {  // ... before it is counted
@@ -221,51 +257,12 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
       is_last = (old == (unsigned)ksplit - 1) ? 1u : 0u;
       if (is_last) p.counters[group] = 0;  // ready for the next launch
     }
-    __syncthreads();
+    __syncthreads();  // `red` is free from here on
     if (!is_last) return;
-  }
-  // The finishing workgroup.  Its loads are issued together so that their round trips
-  // overlap: first the sums of squares behind the RMS Norm factor (16 row groups per
-  // thread at once), then the partial sums.
-  // what the epilogues need from memory besides the partial sums is requested first, so that
-  // all of a finisher's loads share one round trip
-  float cos_pf[kPf] = {0.f, 0.f}, sin_pf[kPf] = {0.f, 0.f};
-  if (EPI == DEC_QKV) {
-#pragma unroll
-    for (int j = 0; j < kPf; ++j) {
-      int idx = threadIdx.x + j * NW * 64;
-      if (idx < p.batch * 32) {
-        int d0 = ((fb0 >> 1) & 1) * 32 + (idx & 31);
-        cos_pf[j] = p.cos_tab[(size_t)pos_pf[j] * 64 + d0];
-        sin_pf[j] = p.sin_tab[(size_t)pos_pf[j] * 64 + d0];
-      }
-    }
-  }
-  constexpr int kPfR = 4;  // (token, row) pairs per thread fetched ahead: 16 tokens' worth
-  float xres_pf[kPfR], gain_pf[kPfR];  // residual stream and next norm's gain
-  if (EPI == DEC_RESID || EPI == DEC_FINAL) {
-#pragma unroll
-    for (int j = 0; j < kPfR; ++j) {
-      int idx = threadIdx.x + j * NW * 64;
-      xres_pf[j] = 0.f; gain_pf[j] = 0.f;
-      if (idx < n_pairs) {
-        int f = idx % kGroupRows, b = idx / kGroupRows;
-        xres_pf[j] = p.xres[(size_t)b * p.H + fb0 * 32 + f];
-        if (EPI == DEC_RESID) gain_pf[j] = bf16_to_f32(p.gain[fb0 * 32 + f]);
-      }
-    }
-  }
-  float ssq_v[16];
-  const int ssq_tkn = threadIdx.x & 31, ssq_part_id = threadIdx.x >> 5;
-  if (EPI == DEC_QKV || EPI == DEC_SWIGLU) {
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      int g = ssq_part_id + kSsqParts * u;
-      ssq_v[u] = g < p.n_ssq ? p.ssq_in[g * 32 + ssq_tkn] : 0.f;
-    }
+    fetch();
   }
   if (ksplit > 1) {
-    // Plain loads are enough here: every 256-byte run of `partial` has exactly one
+    // The finishing workgroup.  Plain loads are enough here: every 256-byte run of `partial` has exactly one
     // writer in this launch, this XCD's L2 was invalidated when the launch began,
     // and nothing in this launch read these lines before, so a line is either
     // absent (fetched from memory, where the writer's store has completed) or was
@@ -335,6 +332,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
     }
   }
   __syncthreads();
+  auto total = [&](int token, int f) { return ksplit > 1 ? fin[token][f] : wave_sum(token, f); };
 
   if (EPI == DEC_QKV) {
     const int r0 = fb0 * 32;
@@ -344,7 +342,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
       int idx = threadIdx.x + j * NW * 64;
       if (idx >= p.batch * 32) break;
       int x = idx & 31, b = idx >> 5;
-      float a = fin[b][x] * rstd_s[b], c = fin[b][32 + x] * rstd_s[b];
+      float a = total(b, x) * rstd_s[b], c = total(b, 32 + x) * rstd_s[b];
       int d0 = w * 32 + x, d1 = d0 + 64;
       int pos = j < kPf ? pos_pf[j] : p.lens[b];
       if (head < p.nq + p.nkv) {
@@ -390,7 +388,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
     const int f0 = (fb0 >> 3) * 128 + ((fb0 >> 1) & 3) * 32;
     for (int idx = threadIdx.x; idx < p.batch * 32; idx += NW * 64) {
       int x = idx & 31, b = idx >> 5;
-      float g = fin[b][x] * rstd_s[b], u = fin[b][32 + x] * rstd_s[b];
+      float g = total(b, x) * rstd_s[b], u = total(b, 32 + x) * rstd_s[b];
       p.m_out[frag_offset(b, f0 + x, p.I)] = f2bf_dev(g / (1.0f + __expf(-g)) * u);
     }
   } else {
@@ -400,24 +398,19 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
       int idx = threadIdx.x + j * NW * 64;
       if (idx >= n_pairs) break;
       int f = idx % kGroupRows, b = idx / kGroupRows;
-      float xn = (j < kPfR ? xres_pf[j] : p.xres[(size_t)b * p.H + n0 + f]) + fin[b][f];
+      float xn = (j < kPfR ? xres_pf[j] : p.xres[(size_t)b * p.H + n0 + f]) + total(b, f);
       if (EPI == DEC_RESID) {
         p.xres[(size_t)b * p.H + n0 + f] = xn;
         p.y_out[frag_offset(b, n0 + f, p.H)] = f2bf_dev(xn * (j < kPfR ? gain_pf[j] : bf16_to_f32(p.gain[n0 + f])));
-        fin[b][f] = xn * xn;
+        float ss = xn * xn;  // over the lanes of the token: kGroupRows of them
+#pragma unroll
+        for (int o = kGroupRows / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+        if (f == 0) p.ssq_out[group * 32 + b] = ss;
       } else {
         p.hidden_out[(size_t)b * p.H + n0 + f] = f2bf_dev(xn);
       }
     }
     if (EPI == DEC_FINAL && group == 0 && p.lens_advance && threadIdx.x < p.batch) p.lens_advance[threadIdx.x] += 1;
-    if (EPI == DEC_RESID) {
-      __syncthreads();
-      if (threadIdx.x < p.batch) {
-        float ss = 0.f;
-        for (int f = 0; f < kGroupRows; ++f) ss += fin[threadIdx.x][f];
-        p.ssq_out[group * 32 + threadIdx.x] = ss;
-      }
-    }
   }
 }
 
