@@ -179,6 +179,7 @@ template <int WF_, int WT_, int TB_, int NST_> struct GemmForm {
   static constexpr int STAGE_BYTES = (XB + NBK) * KTS * 1024;
   static constexpr int LPW = (XB + NBK) * KTS / (WF * WT);          // wave loads per wave and stage
   static constexpr int LDS = STAGE_BYTES * NST;
+  static constexpr int ACC = FB * 2 * TB * 2 * 4;                   // accumulator registers of a lane: 128 in the wide form
   static_assert(LPW * WF * WT == (XB + NBK) * KTS, "every wave issues the same number of loads");
 };
 typedef GemmForm<4, 2, 4, 4> WideForm;
@@ -210,6 +211,7 @@ struct GemmParams {
   // K loop split over `ksplit` workgroups per tile (GEMMs with few tiles): fp32 partial tiles and arrival counters
   int ksplit, tiles_grid;
   int first, ksplit2;              // short forms: tiles from `first` on are split over ksplit2 workgroups each
+  bool finish;                     // the slices' sums are added up by k_gemm_finish
   const float *ssq_in;             // short forms: sums of squares [ssq_groups][T'] instead of rstd
   int ssq_groups;
   float inv_H, eps;
@@ -231,6 +233,14 @@ __device__ __forceinline__ void store4(bf16_t *out, int out_K, int row, int f0, 
   typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2_t;
   const bf16x4_t pk = pack4(v[0], v[1], v[2], v[3]);
   __builtin_nontemporal_store(__builtin_bit_cast(u32x2_t, pk), (u32x2_t *)(out + frag_offset(row, f0, out_K)));
+}
+
+// feature and token tile of tile q: bands of gm token tiles, all feature tiles of a band before the next
+template <typename F> __device__ __forceinline__ void tile_of(const GemmParams &p, int q, int &tile_n, int &tile_t) {
+  const int tiles_n = p.feat_blocks / F::NBK, tiles_t = (p.tok_blocks + F::XB - 1) / F::XB;
+  const int band = q / (p.gm * tiles_n), in_band = q - band * p.gm * tiles_n, rows_in_band = min(p.gm, tiles_t - band * p.gm);
+  tile_n = in_band / rows_in_band;
+  tile_t = band * p.gm + in_band % rows_in_band;
 }
 
 // CLS (a hyp_kernel_class_t) does not change the code: it gives each GEMM of a block a kernel name of its
@@ -273,12 +283,8 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
     q = p.n_static + (int)split_last;
   }
   if (q >= p.n_tiles) return;
-  const int tiles_n = p.feat_blocks / NBK;
-  const int tiles_t = (p.tok_blocks + XB - 1) / XB;
-  int band = q / (p.gm * tiles_n);
-  int in_band = q - band * p.gm * tiles_n;
-  int rows_in_band = min(p.gm, tiles_t - band * p.gm);
-  int tile_n = in_band / rows_in_band, tile_t = band * p.gm + in_band % rows_in_band;
+  int tile_n, tile_t;
+  tile_of<F>(p, q, tile_n, tile_t);
   const int tb0 = tile_t * XB, nb0 = tile_n * NBK;
   const int KT = p.KT;
 
@@ -441,12 +447,30 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // drain the tail refills before the wave ends
 
-  constexpr int kAccRegs = FB * 2 * TB * 2 * 4;  // 128 in the wide form
+  constexpr int kAccRegs = F::ACC;
   const float *rstd = p.rstd;
   int rstd0 = 0;  // row that rstd[0] belongs to
-  // ------------------------------------------------------------------ split K: the last workgroup of a tile adds up
+  // ------------------------------------------------------------------ split K
+  if (p.finish) {
+    // every tile is split: its slices leave their sums for k_gemm_finish
+    float *mine = p.split_ws + (((size_t)q * ksplit + slice) * (WF * WT) + wave) * (kAccRegs * 64) + lane * 4;
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      if (tb0 + wt * TB + j >= p.tok_blocks) continue;
+#pragma unroll
+      for (int th = 0; th < 2; ++th)
+#pragma unroll
+        for (int i = 0; i < FB; ++i)
+#pragma unroll
+          for (int fh = 0; fh < 2; ++fh) *(f32x4_t *)(mine + (((j * 2 + th) * FB + i) * 2 + fh) * 256) = acc[i][fh][j][th];
+    }
+    return;
+  }
+  if constexpr (!kWide)
   if (ksplit > 1) {
-    const size_t unit0 = kWide || q < p.first ? (size_t)q * ksplit : (size_t)p.first * p.ksplit + (size_t)(q - p.first) * ksplit;
+    const size_t unit0 = (size_t)(q - p.first) * ksplit;
+    // The few tiles beyond a round of unsplit ones: the last of a tile's workgroups to arrive adds up while the others of
+    // the launch still stream.
     // Every workgroup of a tile leaves its fp32 accumulators of the live token blocks in the
     // scratch area (write-through stores, completed before its arrival is counted); the one
     // that arrives last reads all slices back in slice order - so the sum does not depend on
@@ -717,6 +741,158 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
   }
 }
 
+// ----------------------------------------------------------------------------
+// The second half of a GEMM whose K loop is split: adds up the slices of a tile, in slice order, and runs the epilogue.  A
+// wave takes 16 tokens x 64 features (a lane's accumulators of one token half), so the reading - which bounds it - goes to
+// every CU.  Left to the workgroup of a tile that arrived last, adding up and the epilogue took longer than the products
+// (Phi-3 block, O projection: 13 of 26 us at 64 rows, 25 of 42 at 128, 41 of 62 at 256).
+// ----------------------------------------------------------------------------
+template <int EPI, typename F> __global__ void __launch_bounds__(256) k_gemm_finish(GemmParams p) {
+  constexpr int WF = F::WF, WT = F::WT, TB = F::TB, XB = F::XB, NBK = F::NBK, kWaves = WF * WT;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, q4 = (lane >> 4) * 4, t16 = lane & 15;
+  const int unit = blockIdx.x * 4 + wave, th = unit & 1, j = unit / 2 % TB, w = unit / (2 * TB) % kWaves, q = unit / (2 * TB * kWaves);
+  if (q >= p.n_tiles) return;
+  int tile_n, tile_t;
+  tile_of<F>(p, q, tile_n, tile_t);
+  const int wf = w / WT, tb = tile_t * XB + w % WT * TB + j, fb0 = tile_n * NBK + wf * FB;
+  if (tb >= p.tok_blocks) return;
+  const int rows = p.tok_blocks * 32, row = tb * 32 + 16 * th + t16;
+  // what the epilogue needs besides the sums is requested first
+  const bool live = EPI == EPI_STORE || p.row_ext == nullptr || p.row_ext[row] >= 0;
+  float rs = 1.f, sq = 0.f;
+  int pos = 0, req = 0, rq = 0;
+  f32x4_t old[FB][2];
+  bf16x4_t gg[FB][2];
+  auto xres_at = [&](int i, int fh) { return p.xres + (((size_t)tb * p.feat_blocks + fb0 + i) * 4 + fh * 2 + th) * 256 + lane * 4; };
+  if (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
+    if (p.rstd) rs = p.rstd[row];
+    else
+      for (int g0 = lane >> 4; g0 < p.ssq_groups; g0 += 64) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = g0 + 4 * u < p.ssq_groups ? p.ssq_in[(size_t)(g0 + 4 * u) * rows + row] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sq += v[u];
+      }
+  }
+  if (EPI == EPI_QKV) { pos = p.row_pos[row]; req = p.row_req[row]; rq = p.row_q[row]; }
+  if (EPI == EPI_RESID) {
+#pragma unroll
+    for (int i = 0; i < FB; ++i)
+#pragma unroll
+      for (int fh = 0; fh < 2; ++fh) {
+        old[i][fh] = *(const f32x4_t *)xres_at(i, fh);
+        gg[i][fh] = *(const bf16x4_t *)(p.gain + (fb0 + i) * 32 + 16 * fh + q4);
+      }
+  }
+  const float *src = p.split_ws + ((size_t)q * p.ksplit * kWaves + w) * (F::ACC * 64) + (j * 2 + th) * (FB * 2 * 256) + lane * 4;
+  const size_t stride = (size_t)kWaves * (F::ACC * 64);
+  f32x4_t acc[FB][2];
+#pragma unroll
+  for (int i = 0; i < FB; ++i)
+#pragma unroll
+    for (int fh = 0; fh < 2; ++fh) acc[i][fh] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  constexpr int kAhead = 8;  // slices in flight
+  for (int s0 = 0; s0 < p.ksplit; s0 += kAhead) {
+    f32x4_t v[kAhead][FB][2];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+      for (int i = 0; i < FB; ++i)
+#pragma unroll
+        for (int fh = 0; fh < 2; ++fh)  // past the end: the last slice again, not used
+          v[u][i][fh] = *(const f32x4_t *)(src + (size_t)min(s0 + u, p.ksplit - 1) * stride + (i * 2 + fh) * 256);
+    asm volatile("" ::: "memory");  // or the compiler moves a slice's loads behind the sums of the one before
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      if (s0 + u < p.ksplit)
+#pragma unroll
+        for (int i = 0; i < FB; ++i)
+#pragma unroll
+          for (int fh = 0; fh < 2; ++fh) acc[i][fh] += v[u][i][fh];
+  }
+  if ((EPI == EPI_QKV || EPI == EPI_SWIGLU) && !p.rstd) {
+    sq += __shfl_xor(sq, 16, 64);
+    sq += __shfl_xor(sq, 32, 64);
+    rs = live ? 1.0f / sqrtf(sq * p.inv_H + p.eps) : 0.f;  // a padding row's sum is 0: no 1/0 when eps == 0
+  }
+  if (EPI == EPI_STORE) {
+#pragma unroll
+    for (int i = 0; i < FB; ++i)
+#pragma unroll
+      for (int fh = 0; fh < 2; ++fh) store4(p.out, p.out_K, row, (fb0 + i) * 32 + 16 * fh + q4, acc[i][fh]);
+  } else if (EPI == EPI_SWIGLU) {
+#pragma unroll
+    for (int fh = 0; fh < 2; ++fh) {
+      f32x4_t v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float g = acc[0][fh][e] * rs, u = acc[1][fh][e] * rs;
+        v[e] = g / (1.0f + __expf(-g)) * u;
+      }
+      store4(p.out, p.out_K, row, (tile_n * WF + wf) * 32 + 16 * fh + q4, v);
+    }
+  } else if (EPI == EPI_RESID) {
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < FB; ++i)
+#pragma unroll
+      for (int fh = 0; fh < 2; ++fh) {
+        f32x4_t nw, v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float xn = live ? old[i][fh][e] + acc[i][fh][e] : 0.f;
+          nw[e] = xn;
+          ss += xn * xn;
+          v[e] = xn * bf16_to_f32(gg[i][fh].v[e]);
+        }
+        *(f32x4_t *)xres_at(i, fh) = nw;
+        store4(p.out, p.out_K, row, (fb0 + i) * 32 + 16 * fh + q4, v);
+      }
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    if (lane < 16) p.ssq_part[(size_t)(fb0 >> 1) * rows + row] = ss;
+  } else {  // EPI_QKV
+    if (req < 0) return;  // padding behind the last request
+    const int r0 = fb0 * 32, ib = r0 & 32 * FB ? 32 : 0;  // the wave's 64 packed rows: the lower or the upper pairs of a head
+    if (r0 < p.qd + p.kvd) {
+#pragma unroll
+      for (int fh = 0; fh < 2; ++fh) {
+        const int d0 = ib + 16 * fh + q4;
+        const f32x4_t c4 = *(const f32x4_t *)(p.cos_tab + (size_t)pos * 64 + d0), s4 = *(const f32x4_t *)(p.sin_tab + (size_t)pos * 64 + d0);
+        f32x4_t lo, hi;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a = acc[0][fh][e] * rs, b = acc[1][fh][e] * rs;
+          lo[e] = a * c4[e] - b * s4[e];
+          hi[e] = b * c4[e] + a * s4[e];
+        }
+        if (r0 < p.qd) {
+          store4(p.out, p.out_K, rq, (r0 >> 7) * 128 + d0, lo);
+          store4(p.out, p.out_K, rq, (r0 >> 7) * 128 + 64 + d0, hi);
+        } else {
+          bf16_t *kb = p.Kc + p.geom.off(req, (r0 - p.qd) >> 7, pos >> 5);
+          *(bf16x4_t *)(kb + frag_offset(pos & 31, d0, 128)) = pack4(lo[0], lo[1], lo[2], lo[3]);
+          *(bf16x4_t *)(kb + frag_offset(pos & 31, 64 + d0, 128)) = pack4(hi[0], hi[1], hi[2], hi[3]);
+        }
+      }
+    } else {
+      bf16_t *vb = p.Vc + p.geom.off(req, (r0 - p.qd - p.kvd) >> 7, pos >> 5);
+      int m, khh;
+      const int e = vtile_slot_of_key(pos & 31, &m, &khh);
+#pragma unroll
+      for (int i = 0; i < FB; ++i)
+#pragma unroll
+        for (int fh = 0; fh < 2; ++fh)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int d = ib + i * 64 + 16 * fh + q4 + r;
+            vb[(size_t)(m * 4 + (d >> 5)) * kTileElems + (khh * 32 + (d & 31)) * 8 + e] = f2bf_dev(acc[i][fh][r] * rs);
+          }
+    }
+  }
+}
+
 }  // namespace
 
 // ----------------------------------------------------------------------------
@@ -848,17 +1024,24 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
     p.pool_wgs = (2 * (p.n_tiles - p.n_static) + 7) / 8 * 8;
     p.tiles_grid = p.n_static + p.pool_wgs;
   }
+  p.finish = p.ksplit > 1;
   int grid = form < 256 ? p.first * p.ksplit + (p.n_tiles - p.first) * p.ksplit2 : p.tiles_grid * p.ksplit;
   bool launched = false;
-#define X(EPI, CLS) \
-  if (!launched && epi == EPI && cls == CLS) {                                                                       \
-    if (form == 64) k_gemm<EPI, CLS, Form64><<<grid, Form64::WF * Form64::WT * 64, Form64::LDS, s>>>(p);                      \
-    else if (form == 128) k_gemm<EPI, CLS, Form128><<<grid, Form128::WF * Form128::WT * 64, Form128::LDS, s>>>(p);             \
-    else k_gemm<EPI, CLS, WideForm><<<grid, WideForm::WF * WideForm::WT * 64, WideForm::LDS, s>>>(p);                           \
-    launched = true;                                                                                                 \
+#define Y(EPI, CLS, F)                                                                                              \
+  {                                                                                                                 \
+    k_gemm<EPI, CLS, F><<<grid, F::WF * F::WT * 64, F::LDS, s>>>(p);                                                 \
+    if (p.finish) k_gemm_finish<EPI, F><<<p.n_tiles * F::WF * F::WT * F::TB * 2 / 4, 256, 0, s>>>(p);                \
+  }
+#define X(EPI, CLS)                                                                                                 \
+  if (!launched && epi == EPI && cls == CLS) {                                                                      \
+    if (form == 64) Y(EPI, CLS, Form64)                                                                             \
+    else if (form == 128) Y(EPI, CLS, Form128)                                                                      \
+    else Y(EPI, CLS, WideForm)                                                                                      \
+    launched = true;                                                                                                \
   }
   HYP_GEMM_VARIANTS(X)
 #undef X
+#undef Y
   if (!launched) return hipErrorInvalidValue;
   return hipGetLastError();
 }
