@@ -35,7 +35,10 @@ struct GemmEpilogue {
 };
 
 constexpr int kShortRows = 128;          // prompts of up to so many internal rows run the GEMM's short forms
-constexpr int kGemmSplitMaxTiles = 255;  // wide GEMMs with at least a round of output tiles are never split
+// Wide GEMMs of two and a half rounds of 256 tiles or more are never split: a request that fills them alone then has the same
+// bits in any batch, and what splitting the last, partial round saves falls with the number of rounds (Phi-3 block: gate/up 210
+// -> 155 us at 384 rows = 280 tiles, 325 -> 292 at 1024 = 560).
+constexpr int kGemmSplitMaxTiles = 639;
 constexpr int kGemmShortMaxTiles = 511;  // short forms: tiles that may be split, and counters
 size_t mfma_gemm_split_ws_bytes();
 

@@ -208,10 +208,11 @@ struct GemmParams {
   const bf16_t *gain;
   const int *row_ext;
   float *ssq_part;                 // [N / 64][T']
-  // K loop split over `ksplit` workgroups per tile (GEMMs with few tiles): fp32 partial tiles and arrival counters
-  int ksplit, tiles_grid;
-  int first, ksplit2;              // short forms: tiles from `first` on are split over ksplit2 workgroups each
-  bool finish;                     // the slices' sums are added up by k_gemm_finish
+  // Tiles from `first` on have their K loop split over `ksplit` workgroups each: fp32 partial tiles, and arrival counters
+  // where the last to arrive adds up instead of k_gemm_finish.  Workgroups: first_grid for the others, then rest_grid (a
+  // multiple of 8; with the tiles rounded up instead, 20 tiles in 11 slices left an XCD idle and took 98 us, not 69 as in 10).
+  int first, ksplit, first_grid, rest_grid;
+  bool finish;
   const float *ssq_in;             // short forms: sums of squares [ssq_groups][T'] instead of rstd
   int ssq_groups;
   float inv_H, eps;
@@ -254,18 +255,18 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
   const int wf = wave / WT, wt = wave % WT;
   // tile of this workgroup
   __shared__ unsigned split_last;
-  const int nwg = p.tiles_grid, id = blockIdx.x % p.tiles_grid;
-  int slice = blockIdx.x / p.tiles_grid, ksplit = p.ksplit, q;
-  if constexpr (!kWide) {
-    const int in_first = p.first * p.ksplit, b = blockIdx.x;
-    if (b < in_first) {
-      q = b % p.first; slice = b / p.first;
-    } else {
-      const int rest = p.n_tiles - p.first;
-      q = p.first + (b - in_first) % rest; slice = (b - in_first) / rest; ksplit = p.ksplit2;
-    }
-  } else if (p.pool_wgs == 0) {
-    q = (id % 8) * (nwg / 8) + id / 8;
+  // Tiles from p.first on are split: `ksplit` workgroups of a tile take a slice of its K loop each.
+  int slice = 0, ksplit = 1, q;
+  const int id = blockIdx.x;
+  if (id >= p.first_grid) {
+    // an XCD (id % 8) takes neighbouring tiles of the same slice, which share their operand panels; all take equally many
+    const int rest = p.n_tiles - p.first, at = id - p.first_grid, v = (at % 8) * (p.rest_grid / 8) + at / 8;
+    if (v >= rest * p.ksplit) return;
+    slice = v / rest; ksplit = p.ksplit;
+    q = p.first + v % rest;
+  } else if (!kWide || p.pool_wgs == 0) {
+    q = (id % 8) * (p.first_grid / 8) + id / 8;
+    if (q >= p.first) return;
   } else if (id < p.n_static) {
     // a large unsplit GEMM: most tiles belong to an XCD by position, as above ...
     q = (id % 8) * (p.n_static / 8) + id / 8;
@@ -281,8 +282,8 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
     }
     __syncthreads();
     q = p.n_static + (int)split_last;
+    if (q >= p.n_tiles) return;
   }
-  if (q >= p.n_tiles) return;
   int tile_n, tile_t;
   tile_of<F>(p, q, tile_n, tile_t);
   const int tb0 = tile_t * XB, nb0 = tile_n * NBK;
@@ -300,8 +301,9 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[i][fh][j][th][e] = 0.f;
 
-  const int nsteps = KT / KTS / ksplit;  // stages of this workgroup's K slice, >= NST guaranteed by the host
-  const size_t k_first = (size_t)slice * nsteps * KTS * kTileElems;
+  // this workgroup's stages: its slice of the K loop, >= NST of them guaranteed by the host
+  const int stages = KT / KTS, stage0 = slice * stages / ksplit, nsteps = (slice + 1) * stages / ksplit - stage0;
+  const size_t k_first = (size_t)stage0 * KTS * kTileElems;
   const bf16_t *src[LPW];
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
@@ -451,9 +453,9 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
   const float *rstd = p.rstd;
   int rstd0 = 0;  // row that rstd[0] belongs to
   // ------------------------------------------------------------------ split K
-  if (p.finish) {
-    // every tile is split: its slices leave their sums for k_gemm_finish
-    float *mine = p.split_ws + (((size_t)q * ksplit + slice) * (WF * WT) + wave) * (kAccRegs * 64) + lane * 4;
+  if (p.finish && ksplit > 1) {
+    // the slices leave their sums for k_gemm_finish
+    float *mine = p.split_ws + (((size_t)(q - p.first) * ksplit + slice) * (WF * WT) + wave) * (kAccRegs * 64) + lane * 4;
 #pragma unroll
     for (int j = 0; j < TB; ++j) {
       if (tb0 + wt * TB + j >= p.tok_blocks) continue;
@@ -750,7 +752,7 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
 template <int EPI, typename F> __global__ void __launch_bounds__(256) k_gemm_finish(GemmParams p) {
   constexpr int WF = F::WF, WT = F::WT, TB = F::TB, XB = F::XB, NBK = F::NBK, kWaves = WF * WT;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, q4 = (lane >> 4) * 4, t16 = lane & 15;
-  const int unit = blockIdx.x * 4 + wave, th = unit & 1, j = unit / 2 % TB, w = unit / (2 * TB) % kWaves, q = unit / (2 * TB * kWaves);
+  const int unit = blockIdx.x * 4 + wave, th = unit & 1, j = unit / 2 % TB, w = unit / (2 * TB) % kWaves, q = p.first + unit / (2 * TB * kWaves);
   if (q >= p.n_tiles) return;
   int tile_n, tile_t;
   tile_of<F>(p, q, tile_n, tile_t);
@@ -785,7 +787,7 @@ template <int EPI, typename F> __global__ void __launch_bounds__(256) k_gemm_fin
         gg[i][fh] = *(const bf16x4_t *)(p.gain + (fb0 + i) * 32 + 16 * fh + q4);
       }
   }
-  const float *src = p.split_ws + ((size_t)q * p.ksplit * kWaves + w) * (F::ACC * 64) + (j * 2 + th) * (FB * 2 * 256) + lane * 4;
+  const float *src = p.split_ws + ((size_t)(q - p.first) * p.ksplit * kWaves + w) * (F::ACC * 64) + (j * 2 + th) * (FB * 2 * 256) + lane * 4;
   const size_t stride = (size_t)kWaves * (F::ACC * 64);
   f32x4_t acc[FB][2];
 #pragma unroll
@@ -965,72 +967,72 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
   p.Kc = ep.Kc; p.Vc = ep.Vc; p.geom = ep.geom; p.qd = ep.qd; p.kvd = ep.kvd;
   p.cos_tab = ep.cos_tab; p.sin_tab = ep.sin_tab; p.row_pos = ep.row_pos; p.row_req = ep.row_req; p.row_q = ep.row_q;
   p.rstd = ep.rstd; p.ssq_in = ep.ssq_in; p.ssq_groups = ep.ssq_in ? K / 64 : 0; p.inv_H = 1.0f / (float)K; p.eps = ep.eps; p.xres = ep.xres; p.gain = ep.gain; p.row_ext = ep.row_ext; p.ssq_part = ep.ssq_part;
-  p.tiles_grid = (p.n_tiles + 7) / 8 * 8;
-  // Few output tiles (short prompts): split the K loop over c workgroups per tile when a simple
-  // model says it pays.  Rounds of 256 workgroups times the share of a tile's K loop each one
-  // runs, against what the slices then write and read back (the token blocks that exist, fp32,
-  // at the ~3 TB/s write-through stores and the gather reach) plus the extra round trips.
-  // Slices are whole numbers of stages, at least 2 NST of them each.
-  p.ksplit = 1;
+  const int stages = p.KT / KTS;
+  p.first = p.n_tiles; p.ksplit = 1; p.finish = true;
+  p.split_ws = ep.split_ws; p.split_counters = ep.split_counters;
+  // Few output tiles, or a few more than fill the chip's rounds: their K loop is split over c workgroups per tile when a
+  // simple model says it pays.  Slices are whole numbers of stages, at least two rounds through the LDS buffers.  They cost
+  // their partial tiles, written and read at 5 TB/s together, and the launch that adds them up.
+  const auto slice_cost = [&](int tiles, int c, int tok, int feat) { return c == 1 ? 0.0 : (double)tiles * c * tok * feat * 4096.0 / 2.5e6 + 5.0; };
   if (form < 256) {
-    p.first = p.n_tiles;
     if (ep.split_ws && ep.split_counters && p.n_tiles <= kGemmShortMaxTiles) {
-      // The short forms: the chip streams as much as its workgroups keep in flight over 2.9 us of loaded latency, 6 TB/s
-      // at best, a CU with one workgroup more than the others is waited for, and a split pays for its partial tiles as below.
-      const int nsteps = p.KT / KTS, nst = form == 64 ? Form64::NST : Form128::NST;
+      // The short forms: the chip streams as much as its workgroups keep in flight over 1.5 us of latency, 6 TB/s at best,
+      // and a CU with one workgroup more than the others is waited for.  (64 rows, slices 10 -> 5: down 51 -> 43 us, O 25 ->
+      // 21; QKV 8 -> 4: 30 -> 26.)
+      const int nst = form == 64 ? Form64::NST : Form128::NST;
       const double in_flight = (nst - 1) * (double)Form64::NBK * KTS * 1024, bytes = 2.0 * N * K;
       double best = 1e30;
       for (int c = 1; c == 1 || (c <= 32 && p.n_tiles * c <= kGemmSplitUnits); ++c) {
-        if (c > 1 && (nsteps % c != 0 || nsteps / c < 2 * nst)) continue;
+        if (c > 1 && stages / c < 2 * nst) continue;
         const int units = p.n_tiles * c, per_cu = (units + kGemmSplitCus - 1) / kGemmSplitCus;
         const double even = units <= kGemmSplitCus ? 1.0 : units / ((double)per_cu * kGemmSplitCus);
-        const double partial_mb = (double)units * p.tok_blocks * Form64::NBK * 4096.0 * 2 / 1e6;
-        const double t = bytes / (std::min(6.0e6, units * in_flight / 2.9) * even) + (c > 1 ? partial_mb / 3.0 + 5.0 : 0.0);
-        if (t < best) { best = t; p.ksplit = c; }
+        const double t = bytes / (std::min(6.0e6, units * in_flight / 1.5) * even) + slice_cost(p.n_tiles, c, p.tok_blocks, Form64::NBK);
+        if (t < best) { best = t; p.ksplit = c; p.first = c > 1 ? 0 : p.n_tiles; }
       }
       // More tiles than CUs, unsplit: the ones beyond the first 256 (24 of gate/up's 280) would double a few CUs' work.
-      // They are split so that they spread over all CUs beside the others.
+      // They are split so that they spread over all CUs beside the others, and added up there.
       const int rest = p.n_tiles - kGemmSplitCus;
       if (p.ksplit == 1 && rest > 0)
         for (int c = 16; c >= 2; --c)
-          if (nsteps % c == 0 && nsteps / c >= 2 * nst && rest * c <= kGemmSplitCus) {
-            p.first = kGemmSplitCus; p.ksplit2 = c;
+          if (stages / c >= 2 * nst && rest * c <= kGemmSplitCus) {
+            p.first = kGemmSplitCus; p.ksplit = c; p.finish = false;
             break;
           }
     }
-  } else if (ep.split_ws && ep.split_counters && p.n_tiles <= kGemmSplitMaxTiles) {
-    const int nsteps = p.KT / KTS;
-    const double tile_us = K * 0.0267;  // 256 x 256 x K on one CU at the rate the big GEMMs run at
-    const int live_blocks = p.tok_blocks < XB ? p.tok_blocks : XB;
-    double best = 0.9 * (double)((p.n_tiles + kGemmSplitCus - 1) / kGemmSplitCus) * tile_us;  // a split has to win clearly
-    for (int c = 2; c <= 32 && p.n_tiles * c <= kGemmSplitUnits; ++c) {
-      if (nsteps % c != 0 || nsteps / c < 2 * NST) continue;
-      double rounds = (double)((p.n_tiles * c + kGemmSplitCus - 1) / kGemmSplitCus);
-      double partial_mb = (double)p.n_tiles * c * live_blocks * NBK * 4096.0 * 2 / 1e6;
-      double t = rounds * tile_us / c + partial_mb / 3.0 + 5.0;
-      if (t < best) { best = t; p.ksplit = c; }
+  } else if (ep.split_ws && p.n_tiles <= kGemmSplitMaxTiles) {
+    // The wide form: whole rounds of one tile per CU, then the rest, in as many rounds as its slices take.
+    const int rest = p.n_tiles % kGemmSplitCus, live = std::min(p.tok_blocks, XB);
+    const double tile_us = K * 0.020, start_us = 4.0;  // a 256 x 256 tile on one CU, whatever the others do (K = 5120: 105 us)
+    double best = 0.95 * (tile_us + start_us);         // a split has to win clearly
+    for (int c = 2; c <= 32 && rest * c <= kGemmSplitUnits && rest > 0; ++c) {
+      if (stages / c < 2 * NST) break;
+      const int rounds = (rest * c + kGemmSplitCus - 1) / kGemmSplitCus;
+      const double t = rounds * (tile_us / c + start_us) + slice_cost(rest, c, live, NBK);
+      if (t < best) { best = t; p.ksplit = c; p.first = p.n_tiles - rest; }
     }
   }
-  p.split_ws = ep.split_ws; p.split_counters = ep.split_counters;
+  p.first_grid = (p.first + 7) / 8 * 8;
+  p.rest_grid = ((p.n_tiles - p.first) * p.ksplit + 7) / 8 * 8;
   // 64 rounds of 256 tiles or more: the last sixteenth of the rounds is drawn from a counter by twice as many
   // workgroups as it has tiles, so that an XCD can take up to a quarter of it.  (Gate/up at 64 K tokens, 140 rounds:
   // 2.3 % faster.  With 20 - 30 rounds the drawn tiles' lost L2 neighbourhood and the tile granularity cost more than
   // the balance brings: down projection 1.7 % slower.)
   p.n_static = 0; p.pool_wgs = 0;
-  if (p.ksplit == 1 && ep.split_counters && p.n_tiles >= 64 * kGemmSplitCus) {
+  if (ep.split_counters && p.n_tiles >= 64 * kGemmSplitCus) {
     const int rounds = p.n_tiles / kGemmSplitCus;
     const int pool_rounds = (rounds + 8) / 16;
+    p.first = p.n_tiles; p.ksplit = 1; p.rest_grid = 0;
     p.n_static = (rounds - pool_rounds) * kGemmSplitCus;
     p.pool_wgs = (2 * (p.n_tiles - p.n_static) + 7) / 8 * 8;
-    p.tiles_grid = p.n_static + p.pool_wgs;
+    p.first_grid = p.n_static + p.pool_wgs;
   }
-  p.finish = p.ksplit > 1;
-  int grid = form < 256 ? p.first * p.ksplit + (p.n_tiles - p.first) * p.ksplit2 : p.tiles_grid * p.ksplit;
+  const int grid = p.first_grid + p.rest_grid;
   bool launched = false;
 #define Y(EPI, CLS, F)                                                                                              \
   {                                                                                                                 \
     k_gemm<EPI, CLS, F><<<grid, F::WF * F::WT * 64, F::LDS, s>>>(p);                                                 \
-    if (p.finish) k_gemm_finish<EPI, F><<<p.n_tiles * F::WF * F::WT * F::TB * 2 / 4, 256, 0, s>>>(p);                \
+    if (p.finish && p.first < p.n_tiles)                                                                             \
+      k_gemm_finish<EPI, F><<<(p.n_tiles - p.first) * F::WF * F::WT * F::TB * 2 / 4, 256, 0, s>>>(p);                \
   }
 #define X(EPI, CLS)                                                                                                 \
   if (!launched && epi == EPI && cls == CLS) {                                                                      \
