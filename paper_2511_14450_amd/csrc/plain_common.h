@@ -176,11 +176,21 @@ __device__ __forceinline__ void plain_epilogue(const PlainGemm<T> &g, int out_ti
     }
   } else if (EPI == PLAIN_SWIGLU) {
     if (!live || f0 >= g.N) return;
+    // FFN features f0 / 2 and f0 / 2 + 1 lie side by side (f0 / 2 is even)
+    T *dst = g.m + plain_offset<T>(tok, f0 >> 1, out_tiles);
+    float v[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      if (f0 + 2 * h >= g.N) break;
       const float gt = acc[2 * h] * rs, up = acc[2 * h + 1] * rs;
-      store_f32(g.m + plain_offset<T>(tok, (f0 >> 1) + h, out_tiles), gt / (1.0f + expf(-gt)) * up);
+      v[h] = gt / (1.0f + expf(-gt)) * up;
+    }
+    if (f0 + 2 < g.N) {
+      struct __attribute__((aligned(2 * sizeof(T)))) Two { T e[2]; } two;
+      store_f32(&two.e[0], v[0]);
+      store_f32(&two.e[1], v[1]);
+      *(Two *)dst = two;
+    } else {
+      store_f32(dst, v[0]);
     }
   } else {
     const int n = min(4, g.N - f0);

@@ -153,6 +153,21 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
       plain_fetch<T, EPI>(pf, g, tok, (ft0 + kw / WN) * 16 + q4);
     }
   }
+  // RMS Norm factors: the sums of squares of this wave's tokens, added up by lane groups (four parts at a time).  Waves that
+  // share the K loop share them too and request theirs here, under the first tiles; a wave on its own adds them up behind the
+  // loop, where registers are free, 32 parts of a token requested at once.  (Pairs of parts one after the other took 4 of 14
+  // us in a form of 32 x 32, 8 of 36 in the wide one: bf16, 1065 rows, 64 parts.)
+  constexpr bool kNorm = EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU;
+  constexpr int kSsq = 4;
+  const int row = lane >> 4;
+  float sq[WN][kSsq];
+  auto part = [&](int p, int j) { return p < g.ssq_parts ? g.ssq_in[(size_t)p * g.rows_pad + min(tt0 + j, a.tt - 1) * 16 + tl] : 0.f; };
+  if constexpr (kNorm && KW > 1) {
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int i = 0; i < kSsq; ++i) sq[j][i] = part((i * KW + kw) * 4 + row, j);
+  }
   // pairs of whole groups, then what is left (checked tile by tile)
   int t = kw;
   for (; t + 2 * kStep - KW < a.tiles; t += 2 * kStep) {
@@ -165,23 +180,33 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
   if (!kLate) load(wf[1], xf[1], t + kStep);
   use(std::false_type(), wf[0], xf[0], t);
   use(std::false_type(), wf[1], xf[1], t + kStep);
-  // RMS Norm factor of this wave's tokens from the sums of squares
   float rs[WN];
-  if (EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU) {
+  if constexpr (kNorm) {
+#pragma unroll
+    for (int j = 0; j < WN; ++j) rs[j] = 0.f;
+    if constexpr (KW > 1) {
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        rs[j] = (sq[j][0] + sq[j][1]) + (sq[j][2] + sq[j][3]);
+        for (int p = (kSsq * KW + kw) * 4 + row; p < g.ssq_parts; p += 4 * KW) rs[j] += part(p, j);
+      }
+    } else {
+      for (int p0 = 0; p0 < g.ssq_parts; p0 += 32) {
+        float v[WN][8];
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) v[j][i] = part(p0 + i * 4 + row, j);
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) rs[j] += v[j][i];
+      }
+    }
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
-      const int tok = min(tt0 + j, a.tt - 1) * 16 + tl;
-      float s0 = 0.f, s1 = 0.f;  // parts of four lane groups, two chains
-      int p = lane >> 4;
-      for (; p + 4 < g.ssq_parts; p += 8) {
-        s0 += g.ssq_in[(size_t)p * g.rows_pad + tok];
-        s1 += g.ssq_in[(size_t)(p + 4) * g.rows_pad + tok];
-      }
-      if (p < g.ssq_parts) s0 += g.ssq_in[(size_t)p * g.rows_pad + tok];
-      float s = s0 + s1;
-      s += __shfl_xor(s, 16, 64);
-      s += __shfl_xor(s, 32, 64);
-      rs[j] = 1.0f / sqrtf(s * a.inv_K + g.eps);
+      rs[j] += __shfl_xor(rs[j], 16, 64);
+      rs[j] += __shfl_xor(rs[j], 32, 64);
     }
   }
 
@@ -192,7 +217,18 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
     for (int i = 0; i < WM; ++i)
 #pragma unroll
       for (int j = 0; j < WN; ++j) red[kw][slot][i * WN + j][lane] = acc[i][j];
+    __shared__ float sq_s[KW][FW * TW][WN][16];
+    if (kNorm && lane < 16)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) sq_s[kw][slot][j][lane] = rs[j];
     __syncthreads();
+    if constexpr (kNorm)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        rs[j] = sq_s[0][slot][j][tl];
+#pragma unroll
+        for (int w = 1; w < KW; ++w) rs[j] += sq_s[w][slot][j][tl];
+      }
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -204,6 +240,10 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
         acc[i][j] = s;
       }
   }
+
+  if constexpr (kNorm)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) rs[j] = 1.0f / sqrtf(rs[j] * a.inv_K + g.eps);
 
 #pragma unroll
   for (int i = 0; i < WM; ++i)
