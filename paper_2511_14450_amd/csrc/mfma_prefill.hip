@@ -958,25 +958,50 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
   GemmParams p = {};
   p.X = X; p.W = W; p.KT = K / 16; p.tok_blocks = rows / 32; p.feat_blocks = N / 32;
   constexpr int NST = WideForm::NST, XB = WideForm::XB, NBK = WideForm::NBK;
-  // up to 128 tokens: the weights' streaming time counts, not the products (see GemmForm)
-  const int form = p.tok_blocks <= Form64::XB ? 64 : p.tok_blocks <= Form128::XB ? 128 : 256;
-  int tiles_t = form < 256 ? 1 : (p.tok_blocks + XB - 1) / XB, tiles_n = p.feat_blocks / (form < 256 ? Form64::NBK : NBK);
+  const int stages = p.KT / KTS;
+  // A K loop in slices costs their partial tiles, written and read at 5 TB/s together, and the launch that adds them up.
+  const auto slice_cost = [](int tiles, int c, int tok, int feat) { return c == 1 ? 0.0 : (double)tiles * c * tok * feat * 4096.0 / 2.5e6 + 5.0; };
+  // The wide form: whole rounds of one tile per CU, then the rest, in as many rounds as its slices take.  Slices are whole
+  // numbers of stages, at least two rounds through the LDS buffers.
+  const int wide_tiles = (p.tok_blocks + XB - 1) / XB * (p.feat_blocks / NBK), wide_rest = wide_tiles % kGemmSplitCus;
+  const double tile_us = K * 0.020, start_us = 4.0;  // a 256 x 256 tile on one CU, whatever the others do (K = 5120: 105 us)
+  int wide_split = 1;
+  double wide_us = wide_rest ? tile_us + start_us : 0.0;
+  if (ep.split_ws && wide_tiles <= kGemmSplitMaxTiles) {
+    double best = 0.95 * wide_us;  // a split has to win clearly
+    for (int c = 2; c <= 32 && wide_rest * c <= kGemmSplitUnits && wide_rest > 0 && stages / c >= 2 * NST; ++c) {
+      const int rounds = (wide_rest * c + kGemmSplitCus - 1) / kGemmSplitCus;
+      const double t = rounds * (tile_us / c + start_us) + slice_cost(wide_rest, c, std::min(p.tok_blocks, XB), NBK);
+      if (t < best) { best = wide_us = t; wide_split = c; }
+    }
+  }
+  wide_us += wide_tiles / kGemmSplitCus * (tile_us + start_us) + 6.0;  // and the epilogue
+  // Which form?  Up to 128 tokens the weights' streaming time counts, not the products (see GemmForm): one token tile.  A GEMM
+  // of few tiles is bound by the latency of a stage (0.24 us with 64 tokens a tile, alone on its CU, 0.53 in the wide form) and
+  // by its epilogue, so narrow layers take tiles of 128 features x 64 tokens as long as those fit the chip in a round or two
+  // (two to a CU: 0.40 us, and 0.45 for every 512 more).  512 wide, 553 rows: QKV 26.7 -> 12.3 us, O 17.7 -> 14.7, gate/up 18.8
+  // -> 10.9, down 16.6 -> 12.5; 1024 wide, FFN 2048: gate/up 1024 rows 27 -> 20, but 2000 rows 28 against 33.
+  int form = 256;
+  if (p.tok_blocks <= Form128::XB) {
+    form = p.tok_blocks <= Form64::XB || 2.0 * N * K <= 16e6 ? 64 : 128;
+  } else {
+    const int tiles = (p.tok_blocks + Form64::XB - 1) / Form64::XB * (p.feat_blocks / Form64::NBK);
+    const double per = 0.24 + 0.16 * std::max(0, std::min(tiles, 512) - 256) / 256.0 + 0.45 * std::max(0, tiles - 512) / 512.0;
+    if (7.5 + stages * per < 0.9 * wide_us) form = 64;
+  }
+  const int tok_tile = form == 64 ? Form64::XB : form == 128 ? Form128::XB : XB;
+  const int tiles_t = (p.tok_blocks + tok_tile - 1) / tok_tile, tiles_n = p.feat_blocks / (form < 256 ? Form64::NBK : NBK);
   p.gm = tiles_t < 8 ? tiles_t : 8;
   p.n_tiles = tiles_t * tiles_n;
   p.out = out; p.out_K = out_K;
   p.Kc = ep.Kc; p.Vc = ep.Vc; p.geom = ep.geom; p.qd = ep.qd; p.kvd = ep.kvd;
   p.cos_tab = ep.cos_tab; p.sin_tab = ep.sin_tab; p.row_pos = ep.row_pos; p.row_req = ep.row_req; p.row_q = ep.row_q;
   p.rstd = ep.rstd; p.ssq_in = ep.ssq_in; p.ssq_groups = ep.ssq_in ? K / 64 : 0; p.inv_H = 1.0f / (float)K; p.eps = ep.eps; p.xres = ep.xres; p.gain = ep.gain; p.row_ext = ep.row_ext; p.ssq_part = ep.ssq_part;
-  const int stages = p.KT / KTS;
   p.first = p.n_tiles; p.ksplit = 1; p.finish = true;
   p.split_ws = ep.split_ws; p.split_counters = ep.split_counters;
-  // Few output tiles, or a few more than fill the chip's rounds: their K loop is split over c workgroups per tile when a
-  // simple model says it pays.  Slices are whole numbers of stages, at least two rounds through the LDS buffers.  They cost
-  // their partial tiles, written and read at 5 TB/s together, and the launch that adds them up.
-  const auto slice_cost = [&](int tiles, int c, int tok, int feat) { return c == 1 ? 0.0 : (double)tiles * c * tok * feat * 4096.0 / 2.5e6 + 5.0; };
   if (form < 256) {
     if (ep.split_ws && ep.split_counters && p.n_tiles <= kGemmShortMaxTiles) {
-      // The short forms: the chip streams as much as its workgroups keep in flight over 1.5 us of latency, 6 TB/s at best,
+      // The short forms, few tiles: the chip streams as much as its workgroups keep in flight over 1.5 us of latency, 6 TB/s at best,
       // and a CU with one workgroup more than the others is waited for.  (64 rows, slices 10 -> 5: down 51 -> 43 us, O 25 ->
       // 21; QKV 8 -> 4: 30 -> 26.)
       const int nst = form == 64 ? Form64::NST : Form128::NST;
@@ -992,24 +1017,15 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
       // More tiles than CUs, unsplit: the ones beyond the first 256 (24 of gate/up's 280) would double a few CUs' work.
       // They are split so that they spread over all CUs beside the others, and added up there.
       const int rest = p.n_tiles - kGemmSplitCus;
-      if (p.ksplit == 1 && rest > 0)
+      if (p.ksplit == 1 && rest > 0 && tiles_t == 1)
         for (int c = 16; c >= 2; --c)
           if (stages / c >= 2 * nst && rest * c <= kGemmSplitCus) {
             p.first = kGemmSplitCus; p.ksplit = c; p.finish = false;
             break;
           }
     }
-  } else if (ep.split_ws && p.n_tiles <= kGemmSplitMaxTiles) {
-    // The wide form: whole rounds of one tile per CU, then the rest, in as many rounds as its slices take.
-    const int rest = p.n_tiles % kGemmSplitCus, live = std::min(p.tok_blocks, XB);
-    const double tile_us = K * 0.020, start_us = 4.0;  // a 256 x 256 tile on one CU, whatever the others do (K = 5120: 105 us)
-    double best = 0.95 * (tile_us + start_us);         // a split has to win clearly
-    for (int c = 2; c <= 32 && rest * c <= kGemmSplitUnits && rest > 0; ++c) {
-      if (stages / c < 2 * NST) break;
-      const int rounds = (rest * c + kGemmSplitCus - 1) / kGemmSplitCus;
-      const double t = rounds * (tile_us / c + start_us) + slice_cost(rest, c, live, NBK);
-      if (t < best) { best = t; p.ksplit = c; p.first = p.n_tiles - rest; }
-    }
+  } else if (wide_split > 1) {
+    p.ksplit = wide_split; p.first = p.n_tiles - wide_rest;
   }
   p.first_grid = (p.first + 7) / 8 * 8;
   p.rest_grid = ((p.n_tiles - p.first) * p.ksplit + 7) / 8 * 8;
