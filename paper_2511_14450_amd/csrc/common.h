@@ -93,6 +93,9 @@ template <typename T> struct PlainGemm {
   const int *tok_req = nullptr, *tok_pos = nullptr;  // no tok_req: row r is request r
   const float *cos_tab = nullptr, *sin_tab = nullptr;  // [position][d / 2], or [row][d / 2] with tab_by_row
   bool tab_by_row = false;
+  float *cos_row = nullptr, *sin_row = nullptr;  // where given: the rows' angles are left here, [row][d / 2]
+  // plain_gemv_opens(): the rows as the stage gets them, [rows][K], and the norm's gain, instead of X and ssq_in
+  const T *first_in = nullptr, *first_gain = nullptr;
   T *q = nullptr, *Kc = nullptr, *Vc = nullptr;
   int q_ld = 0;
   PlainCache cache = {};
@@ -101,6 +104,7 @@ template <typename T> struct PlainGemm {
   T *m = nullptr;
   // PLAIN_RESID: residual [rows][N], gain of the next norm, y = x * gain -> F(rows, N), sums of squares per 16 features
   float *xres = nullptr;
+  const T *res_in = nullptr;  // the residual as the stage gets it, instead of xres (which is written)
   const T *gain = nullptr;
   T *y = nullptr;
   float *ssq_out = nullptr;
@@ -129,6 +133,8 @@ hipError_t plain_begin(const T *hidden_in, float *xres, const T *gain, T *y, flo
 template <typename T> hipError_t plain_gemm(int epi, const PlainGemm<T> &g, hipStream_t s);
 constexpr int kPlainGemvRows = 32;  // up to so many rows plain_gemm is
 template <typename T> hipError_t plain_gemv(int epi, const PlainGemm<T> &g, hipStream_t s);
+// whether a step of so many rows can open with its QKV contraction: what plain_begin does happens in its staging
+template <typename T> bool plain_gemv_opens(const T *hidden_in, int rows, int N, int K);
 // prompt: tiles of up to 16 tokens; out F(rows, nq d)
 template <typename T>
 hipError_t plain_attn_prefill(const T *q, int q_ld, const T *Kc, const T *Vc, T *out, const PlainTile *tiles, int n_tiles,

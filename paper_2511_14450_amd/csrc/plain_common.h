@@ -137,7 +137,11 @@ template <typename T, int EPI> __device__ __forceinline__ void plain_fetch(Plain
       if (f0 + 2 * h < g.N) pf.dst[h] = plain_qkv_dst(g, tok, req, pos, f0 + 2 * h, &pf.second[h]);
   } else if (EPI == PLAIN_RESID || EPI == PLAIN_FINAL) {
     const float *xr = g.xres + (size_t)tok * g.N + f0;
-    if (g.N % 4 == 0) pf.x = *(const f32x4 *)xr;
+    if (EPI == PLAIN_RESID && g.res_in) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (f0 + e < g.N) pf.x[e] = load_f32(g.res_in + (size_t)tok * g.N + f0 + e);
+    } else if (g.N % 4 == 0) pf.x = *(const f32x4 *)xr;
     else
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -168,6 +172,10 @@ __device__ __forceinline__ void plain_epilogue(const PlainGemm<T> &g, int out_ti
       if (r < g.dm.qd + g.dm.kvd) {
         const size_t at = AHEAD ? 0 : plain_angle(g, tok, pos, r);
         const float c = AHEAD ? pf.c[h] : g.cos_tab[at], s = AHEAD ? pf.s[h] : g.sin_tab[at];
+        if (AHEAD && g.cos_row && r < g.dm.d) {  // the first query head: every angle once
+          g.cos_row[(size_t)tok * (g.dm.d >> 1) + (r >> 1)] = c;
+          g.sin_row[(size_t)tok * (g.dm.d >> 1) + (r >> 1)] = s;
+        }
         const float lo = v0 * c - v1 * s, hi = v1 * c + v0 * s;
         v0 = lo; v1 = hi;
       }

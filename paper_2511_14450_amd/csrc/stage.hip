@@ -599,24 +599,28 @@ hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, i
   float *xres = at<float>(st, L.xres), *ssq = at<float>(st, L.ssq);
   T *y = at<T>(st, L.y), *q = at<T>(st, L.q), *attn = at<T>(st, L.attn), *m = at<T>(st, L.m);
   int *lens = at<int>(st, L.lens);
+  const int n_qkv = d.qd + 2 * d.kvd;
+  const bool opens = by_row && plain_gemv_opens<T>((const T *)hidden_in, rows, n_qkv, d.H);  // no opening kernel
   PlainAngles ang;
   if (by_row) {
     ang.pos = lens; ang.half = d.d / 2;
     ang.cos_tab = at<float>(st, L.cos_tab); ang.sin_tab = at<float>(st, L.sin_tab);
     ang.cos_row = at<float>(st, L.cos_row); ang.sin_row = at<float>(st, L.sin_row);
   }
-  HIP_TRY(st, plain_begin<T>((const T *)hidden_in, xres, at<T>(st, L.layers[0].g1), y, ssq, rows, L.rows_pad, d.H, ang, s));
+  if (!opens) HIP_TRY(st, plain_begin<T>((const T *)hidden_in, xres, at<T>(st, L.layers[0].g1), y, ssq, rows, L.rows_pad, d.H, ang, s));
   PlainGemm<T> base;
   base.rows = rows; base.rows_pad = L.rows_pad; base.eps = d.eps; base.dm = d; base.xres = xres;
   for (int l = 0; l < st->n_layers; ++l) {
     const LayerPtrs &p = L.layers[l];
     T *Kc = at<T>(st, L.Kc + L.kv_layer_stride * l), *Vc = at<T>(st, L.Vc + L.v_layer_stride * l);
     PlainGemm<T> a = base;
-    a.W = at<T>(st, p.wqkv); a.X = y; a.N = d.qd + 2 * d.kvd; a.K = d.H;
+    const bool first = opens && l == 0;
+    a.W = at<T>(st, p.wqkv); a.X = y; a.N = n_qkv; a.K = d.H;
     a.ssq_in = ssq; a.ssq_parts = (d.H + 15) / 16;
+    if (first) { a.first_in = (const T *)hidden_in; a.first_gain = at<T>(st, p.g1); a.cos_row = ang.cos_row; a.sin_row = ang.sin_row; }
     a.tok_req = decode ? nullptr : at<int>(st, L.tok_req); a.tok_pos = decode ? lens : at<int>(st, L.tok_pos);
-    a.cos_tab = at<float>(st, by_row ? L.cos_row : L.cos_tab); a.sin_tab = at<float>(st, by_row ? L.sin_row : L.sin_tab);
-    a.tab_by_row = by_row;
+    a.tab_by_row = by_row && !first;
+    a.cos_tab = at<float>(st, a.tab_by_row ? L.cos_row : L.cos_tab); a.sin_tab = at<float>(st, a.tab_by_row ? L.sin_row : L.sin_tab);
     a.q = q; a.q_ld = L.q_ld; a.Kc = Kc; a.Vc = Vc; a.cache = L.cache;
     HIP_TRY(st, plain_gemm<T>(PLAIN_QKV, a, s));
     if (decode) HIP_TRY(st, plain_attn_decode<T>(q, L.q_ld, Kc, Vc, attn, lens, rows, longest, at<float>(st, L.attn_part), L.cache, d, s));
@@ -624,6 +628,7 @@ hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, i
     PlainGemm<T> o = base;
     o.W = at<T>(st, p.wo); o.X = attn; o.N = d.H; o.K = d.qd;
     o.gain = at<T>(st, p.g2); o.y = y; o.ssq_out = ssq;
+    if (first) o.res_in = (const T *)hidden_in;
     HIP_TRY(st, plain_gemm<T>(PLAIN_RESID, o, s));
     PlainGemm<T> g = base;
     g.W = at<T>(st, p.wgu); g.X = y; g.N = 2 * d.I; g.K = d.H;

@@ -41,3 +41,29 @@ def test_decode_against_oracle(shape, batch, dtype):
         xd = synth.hidden_states(batch, shp, 47_002 + s)
         assert rel_err(to_host(gst.decode_step(to_dev(xd, dtype))), ost.decode_step(xd)) <= TOL[dtype], f"step {s}"
     gst.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,batch", [("full64", 3), ("full64", 7), ("short_k", 4), ("group5", 8)])
+def test_a_step_opens_alike_whatever_the_alignment(shape, batch, dtype):
+    """Rows that are not aligned to 16 bytes go through the opening kernel, others straight into the first contraction: the
+    sums of squares are added in the same order, so the bits are the same."""
+    import torch
+    from paper_2511_14450_amd import binding
+    hidden, nq, nkv, d, ffn = SHAPES[shape]
+    shp = synth.BlockShape(hidden, nq, nkv, d, ffn, dtype=dtype)
+    layers = [synth.layer_weights(shp, l, 47_100, sigma=0.05) for l in range(2)]
+    x = to_dev(synth.hidden_states(batch * 3, shp, 47_101), dtype)
+    out = []
+    for shift in (0, 1):
+        gst = make_gpu_stage(shp, layers, batch, 8, batch * 3, flags=binding.HYP_FLAG_PLAIN_KERNELS)
+        gst.prefill(x, [3] * batch)
+        for s in range(2):
+            xd = to_dev(synth.hidden_states(batch, shp, 47_102 + s), dtype)
+            room = torch.zeros(xd.numel() + 8, dtype=xd.dtype, device="cuda")
+            rows = room[shift:shift + xd.numel()].view(batch, hidden)
+            rows.copy_(xd)
+            assert (rows.data_ptr() % 16 != 0) == bool(shift)
+            out.append(gst.decode_step(rows))
+        gst.destroy()
+    assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
