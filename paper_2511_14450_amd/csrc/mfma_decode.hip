@@ -529,6 +529,12 @@ size_t mfma_gemv_partial_floats(const GemvPlan &g, int N, int K) {
   return (size_t)g.ksplit * 32 * N + (size_t)g.ksplit * tail * 32 * fine_rows;
 }
 
+bool mfma_gemv_counts(const GemvPlan &g, int N, int K) {
+  int groups1, tail;
+  gemv_cut(g, N, K, &groups1, &tail);
+  return g.ksplit > 1 || tail > 1;
+}
+
 // the (epilogue, blocks per workgroup, waves per workgroup, class) combinations a plan may ask for
 #define HYP_GEMV_VARIANTS(X, NW)                                                                         \
   X(DEC_QKV, 2, NW, HYP_K_GEMV_QKV) X(DEC_SWIGLU, 2, NW, HYP_K_GEMV_GATEUP)                              \

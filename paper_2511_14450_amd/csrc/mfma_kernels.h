@@ -109,6 +109,7 @@ struct DecGemv {
 hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s);  // cls: as for mfma_gemm
 GemvPlan mfma_gemv_plan(int cls, int N, int K, int batch);  // cls: HYP_K_GEMV_*
 size_t mfma_gemv_partial_floats(const GemvPlan &plan, int N, int K);
+bool mfma_gemv_counts(const GemvPlan &plan, int N, int K);  // whether the GEMM uses its arrival counters
 hipError_t mfma_gemv_init();  // kernel attributes, once per process and device
 // x = hidden_in ; xres = x ; y' = x * gain -> P(32, H) ; ssq_out[H/64][32]
 hipError_t mfma_dec_begin(const bf16_t *hidden_in, float *xres, const bf16_t *gain, bf16_t *y_out, float *ssq_out,

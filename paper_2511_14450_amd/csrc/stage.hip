@@ -940,9 +940,12 @@ hyp_status_t do_stage_decode_step_noalloc(hyp_stage_t *st, const void *hidden_in
                                        " bytes of temporaries; the static array holds " + std::to_string(kNoAllocScratchBytes));
   hyp_status_t rc = check_decode_args(st, hidden_in, hidden_out);
   if (rc != HYP_OK) return rc;
-  // the array keeps whatever the last call on this GPU left: the arrival counters must start at zero
-  // (a fill kernel, not a memset node, so that the call can be captured into a graph)
-  HIP_TRY(st, mfma_fill_zero(st->dec_static.counters, align_up(st->L.counters_bytes), st->stream));
+  // the array keeps whatever the last call on this GPU left: the arrival counters must start at zero, where a GEMM of the step
+  // has any (a fill kernel, not a memset node, so that the call can be captured into a graph; a launch takes 2.5 us)
+  const Layout &L = st->L;
+  const int H = st->dm.H, qkv = st->dm.qd + 2 * st->dm.kvd, I = st->dm.I;
+  if (mfma_gemv_counts(L.g_qkv, qkv, H) || mfma_gemv_counts(L.g_o, H, st->dm.qd) || mfma_gemv_counts(L.g_gu, 2 * I, H) || mfma_gemv_counts(L.g_d, H, I))
+    HIP_TRY(st, mfma_fill_zero(st->dec_static.counters, align_up(st->L.counters_bytes), st->stream));
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   HIP_TRY(st, hipStreamIsCapturing(st->stream, &cap));
   st->prof_off = true;
