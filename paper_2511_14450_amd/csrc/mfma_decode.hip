@@ -28,6 +28,9 @@ namespace {
 // partial sums are written with device-scope (write-through) stores that have
 // completed before the counter is bumped, which keeps cache write-backs and
 // invalidations out of the protocol.  Epilogues:
+//   DEC_QKV_OPEN the same for the first block of a stage: x is hidden_in as the caller gives it, and gain, rounding and sums of
+//              squares of the norm happen on the way to the MFMAs (30 vector instructions per KiB of weights, hidden under
+//              them); every workgroup sees all of K.  Also leaves the residual stream
 //   DEC_QKV    scale by the RMS Norm factor, RoPE at position lens[b], write q
 //              to the decode query buffer and k, v into the cache
 //   DEC_SWIGLU scale, m = silu(gate) * up -> P(32, I)
@@ -70,8 +73,8 @@ struct DecGemvParams {
   int *lens_advance;  // DEC_FINAL: cached lengths to bump once the step's last kernel finishes
 };
 
-// FBW row blocks of 32 per workgroup: 2 where an epilogue pairs rows of two blocks (RoPE partners,
-// gate and up) and for long K; 1 for the residual epilogues at short K, where 32-row workgroups with
+// FBW row blocks of 32 per workgroup: 2 where the epilogue pairs rows of two blocks (gate and up) and for long K; 1 for QKV,
+// whose RoPE partners lie in one block, and for the residual epilogues at short K, where 32-row workgroups with
 // a 10-tile window give as many waves with as much in flight as two slices of 64-row workgroups
 // would, without partial sums, counter and gather at the end.
 // CLS (a hyp_kernel_class_t) only gives each GEMM of a block its own kernel name in a trace.
@@ -79,7 +82,8 @@ struct DecGemvParams {
 // fewer K slices across workgroups (fewer partial sums in memory, or none) for the same number of
 // waves in flight.
 template <int EPI, int FBW, int NW, int CLS>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) k_dec_gemv(DecGemvParams p) {
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EPI == DEC_QKV_OPEN ? 2 : 4))) k_dec_gemv(DecGemvParams p) {
+  constexpr bool kOpen = EPI == DEC_QKV_OPEN, kQkv = EPI == DEC_QKV || kOpen, kSsqIn = EPI == DEC_QKV || EPI == DEC_SWIGLU;
   constexpr int UNROLL = FBW == 1 ? 10 : 5;
   constexpr int kGroupRows = FBW * 32;
   constexpr int kRedStride = kGroupRows + 4;  // keeps 16-byte alignment, spreads tokens over banks
@@ -112,13 +116,13 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
   const int part_r0 = fine ? (group - p.groups1) * kGroupRows : fb0 * 32;       // this group's first row
   // positions of the step's tokens (the QKV epilogue's rotary angles depend on them): fetched under the streaming loop
   // (ahead of time for the first kPf * 8 tokens, which covers the usual batch; the rest is loaded in place)
-  constexpr int kPf = 2;
+  constexpr int kPf = 2, kPairs = FBW * 16;
   int pos_pf[kPf] = {0, 0};
-  if (EPI == DEC_QKV) {
+  if (kQkv) {
 #pragma unroll
     for (int j = 0; j < kPf; ++j) {
       int idx = threadIdx.x + j * NW * 64;
-      if (idx < p.batch * 32) pos_pf[j] = p.lens[idx >> 5];
+      if (idx < p.batch * kPairs) pos_pf[j] = p.lens[idx / kPairs];
     }
   }
   // the workgroup's NW waves take the k-tiles of its slice in turn, so that each step of
@@ -133,7 +137,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
     for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
   // token columns beyond the batch feed output columns nobody reads: their lanes all read
   // token 0's chunk, so the x tile costs one cache line more instead of a whole tile
-  const bf16_t *xp = p.x + (size_t)kt0 * kTileElems + ((lane & 31) < p.batch ? lane : (lane & 32)) * 8;
+  const bf16_t *xp = kOpen ? p.x + (size_t)((lane & 31) < p.batch ? lane & 31 : 0) * p.H + kt0 * 16 + (lane >> 5) * 8
+                           : p.x + (size_t)kt0 * kTileElems + ((lane & 31) < p.batch ? lane : (lane & 32)) * 8;
   const bf16_t *wp[FBW];
 #pragma unroll
   for (int i = 0; i < FBW; ++i) wp[i] = p.W + ((size_t)(fb0 + i) * p.KT + kt0) * kTileElems + lane * 8;
@@ -144,9 +149,37 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
   auto load_tile = [&](int u, int tile) {
 #pragma unroll
     for (int i = 0; i < FBW; ++i) wf[i][u] = __builtin_nontemporal_load((const bf16x8_t *)(wp[i] + (size_t)tile * kStep));
-    xf[u] = *(const bf16x8_t *)(xp + (size_t)tile * kStep);
+    xf[u] = *(const bf16x8_t *)(xp + (size_t)tile * (kOpen ? NW * 16 : kStep));
   };
-  auto use_tile = [&](int u) {
+  // DEC_QKV_OPEN: gain and rounding of the norm on the way to the MFMA, and the tokens' sums of squares of this wave's k-tiles
+  bf16_t *const gain_s = (bf16_t *)(red_raw + NW * p.batch * kRedStride);  // behind the waves' sums
+  float sq = 0.f;
+  auto open_tile = [&](int u, int tile) {
+    const bf16x8_t g = *(const bf16x8_t *)(gain_s + (kt0 + tile * NW) * 16 + (lane >> 5) * 8);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float x = (float)xf[u][e];
+      sq += x * x;
+      xf[u][e] = (__bf16)(x * (float)g[e]);
+    }
+  };
+  auto open = [&] {
+    if constexpr (kOpen) {
+      for (int c = threadIdx.x; c < p.H / 8; c += NW * 64) *(u16x8_t *)(gain_s + c * 8) = *(const u16x8_t *)(p.gain + c * 8);
+      // the residual stream: 64 features of every token per workgroup
+      if (blockIdx.x < (unsigned)p.H / 64)
+        for (int c = threadIdx.x; c < p.batch * 8; c += NW * 64) {
+          const size_t at = (size_t)(c >> 3) * p.H + blockIdx.x * 64 + (c & 7) * 8;
+          const u16x8_t h = *(const u16x8_t *)(p.x + at);
+#pragma unroll
+          for (int e = 0; e < 8; e += 4)
+            *(f32x4_t *)(p.xres + at + e) = f32x4_t{bf16_to_f32(h.v[e]), bf16_to_f32(h.v[e + 1]), bf16_to_f32(h.v[e + 2]), bf16_to_f32(h.v[e + 3])};
+        }
+      __syncthreads();
+    }
+  };
+  auto use_tile = [&](int u, int tile) {
+    if constexpr (kOpen) open_tile(u, tile);
 #pragma unroll
     for (int i = 0; i < FBW; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i][u], xf[u], acc[i], 0, 0, 0);
   };
@@ -155,10 +188,11 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
     int t = 0;
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) load_tile(u, u);
+    open();
     for (int wi = 1; wi < n_win; ++wi, t += UNROLL) {
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) {
-        use_tile(u);
+        use_tile(u, t + u);
         load_tile(u, t + UNROLL + u);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -166,17 +200,18 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
     // last full window; the rem (< UNROLL) tiles left over move into its registers as they free up
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      use_tile(u);
+      use_tile(u, t + u);
       if (u < rem) load_tile(u, t + UNROLL + u);
     }
   } else {
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u)
       if (u < rem) load_tile(u, u);
+    open();
   }
 #pragma unroll
   for (int u = 0; u < UNROLL; ++u)
-    if (u < rem) use_tile(u);
+    if (u < rem) use_tile(u, n_win * UNROLL + u);
   const int n_pairs = p.batch * kGroupRows;
   // What the epilogue needs from memory besides the sums, requested at once: rotary angles, residual stream and next norm's
   // gain, the sums of squares behind the RMS Norm factor (16 row groups per thread).
@@ -186,12 +221,12 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
   float ssq_v[16];
   const int ssq_tkn = threadIdx.x & 31, ssq_part_id = threadIdx.x >> 5;
   auto fetch = [&] {
-    if (EPI == DEC_QKV) {
+    if (kQkv) {
 #pragma unroll
       for (int j = 0; j < kPf; ++j) {
         int idx = threadIdx.x + j * NW * 64;
-        if (idx < p.batch * 32) {
-          int d0 = ((fb0 >> 1) & 1) * 32 + (idx & 31);
+        if (idx < p.batch * kPairs) {
+          int d0 = (fb0 & 3) * 16 + idx % kPairs;
           cos_pf[j] = p.cos_tab[(size_t)pos_pf[j] * 64 + d0];
           sin_pf[j] = p.sin_tab[(size_t)pos_pf[j] * 64 + d0];
         }
@@ -209,7 +244,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
         }
       }
     }
-    if (EPI == DEC_QKV || EPI == DEC_SWIGLU) {
+    if (kSsqIn) {
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         int g = ssq_part_id + kSsqParts * u;
@@ -313,11 +348,13 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
       }
     }
   }
-  if (EPI == DEC_QKV || EPI == DEC_SWIGLU) {
+  if (kQkv || EPI == DEC_SWIGLU) {
     // RMS Norm factor of every token: the row groups' sums of squares, added in a
     // fixed order (kSsqParts interleaved partial sums, then those in order)
     __shared__ float ssq_part[kSsqParts][32];
-    {
+    if constexpr (kOpen) {
+      ssq_part[ssq_part_id][ssq_tkn] = sq;  // a wave's two halves of its k-tiles
+    } else {
       float ss = 0.f;
 #pragma unroll
       for (int u = 0; u < 16; ++u) ss += ssq_v[u];
@@ -334,16 +371,15 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
   __syncthreads();
   auto total = [&](int token, int f) { return ksplit > 1 ? fin[token][f] : wave_sum(token, f); };
 
-  if (EPI == DEC_QKV) {
-    const int r0 = fb0 * 32;
-    const int head = r0 >> 7, w = (r0 >> 6) & 1;
+  if (kQkv) {
+    const int head = fb0 >> 2;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       int idx = threadIdx.x + j * NW * 64;
-      if (idx >= p.batch * 32) break;
-      int x = idx & 31, b = idx >> 5;
-      float a = total(b, x) * rstd_s[b], c = total(b, 32 + x) * rstd_s[b];
-      int d0 = w * 32 + x, d1 = d0 + 64;
+      if (idx >= p.batch * kPairs) break;
+      int x = idx % kPairs, b = idx / kPairs, f = (x >> 4) * 32 + (x & 15);
+      float a = total(b, f) * rstd_s[b], c = total(b, f + 16) * rstd_s[b];
+      int d0 = (fb0 & 3) * 16 + x, d1 = d0 + 64;
       int pos = j < kPf ? pos_pf[j] : p.lens[b];
       if (head < p.nq + p.nkv) {
         float cs = j < kPf ? cos_pf[j] : p.cos_tab[(size_t)pos * 64 + d0];
@@ -414,7 +450,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4)
   }
 }
 
-// first kernel of a decode step: x = hidden_in ; xres = x ; y' = x * gain ; ssq
+// first kernel of a decode step whose rows are not aligned to 16 bytes (else DEC_QKV_OPEN): x = hidden_in ; xres = x ; y' = x * gain ; ssq
 // grid H / 64, 512 threads: a wave per token, a lane per feature, the sum of squares over the wave's lanes.  (Added
 // thread by thread through LDS a request of 16 chat prompts took 0.4 % longer; in a trace the kernel sits at the launch
 // floor, 4.7 us, either way.)
@@ -471,21 +507,27 @@ __global__ void k_fill_zero(uint4 *p, size_t n16) {
 }  // namespace
 
 // How one skinny GEMM of a decode step is cut into workgroups.
-//   fbw     32-row blocks per workgroup: 2 where the epilogue pairs rows of two blocks (RoPE partners,
-//           gate and up) and for long K; 1 for the residual GEMMs at short K, which then run as
-//           unsplit 4-wave workgroups with a 10-tile window
+//   fbw     32-row blocks per workgroup: 2 where the epilogue pairs rows of two blocks (gate and up) and
+//           for long K; 1 for QKV and the residual GEMMs at short K, which then run as unsplit 4-wave
+//           workgroups with a 10-tile window
 //   nw      waves per workgroup; they share the k-tiles of the workgroup's K slice.  8 for the
 //           64-row workgroups: the same waves in flight with half the K slices of 4-wave workgroups
 //   ksplit  K slices across workgroups (partial sums in memory, the last to arrive adds them up):
 //           the fewest that put a wave on every slot of the chip (16 per CU), as long as a wave
 //           keeps at least 20 k-tiles (four windows of the streaming loop) and the fp32 partial sums
 //           (written and read once per slice and token) stay a few percent of the weight bytes.
-//           Phi-3-medium shapes: gate/up unsplit (560 workgroups), QKV 2 slices, down 7 slices;
+//           Phi-3-medium shapes: gate/up unsplit (560 workgroups), down 7 slices;
 //           measured against every other admissible cut of each GEMM at batch 8 and 32, this rule's
 //           choices were the fastest or within 1 % of it.
 GemvPlan mfma_gemv_plan(int cls, int N, int K, int batch) {
   GemvPlan g;
   const int KT = K / 16;
+  // QKV: a workgroup per 32 rows, which hold whole RoPE pairs; no partial sums, counter and gather.  (Two blocks of 32 in two
+  // slices before: Phi-3 16.2 -> 14.7 us at batch 1, Llama3-8B 16.2 -> 15.0 at batch 8.  8 waves: 0.0 - 1.3 % of a block slower.)
+  if (cls == HYP_K_GEMV_QKV) {
+    g.fbw = 1; g.nw = 4; g.ksplit = 1;
+    return g;
+  }
   if ((cls == HYP_K_GEMV_O || cls == HYP_K_GEMV_DOWN) && KT / 4 <= 112 && KT % 4 == 0) {
     g.fbw = 1; g.nw = 4; g.ksplit = 1;
     return g;
@@ -529,6 +571,12 @@ size_t mfma_gemv_partial_floats(const GemvPlan &g, int N, int K) {
   return (size_t)g.ksplit * 32 * N + (size_t)g.ksplit * tail * 32 * fine_rows;
 }
 
+// LDS of the gain beside 64 KiB and less of sums
+constexpr int kMaxGainBytes = 65536;
+bool mfma_dec_opens(const bf16_t *hidden_in, int H, int N) {
+  return (uintptr_t)hidden_in % 16 == 0 && sizeof(bf16_t) * H <= (size_t)kMaxGainBytes && N / 32 >= H / 64;  // a workgroup per 64 features
+}
+
 bool mfma_gemv_counts(const GemvPlan &g, int N, int K) {
   int groups1, tail;
   gemv_cut(g, N, K, &groups1, &tail);
@@ -537,7 +585,7 @@ bool mfma_gemv_counts(const GemvPlan &g, int N, int K) {
 
 // the (epilogue, blocks per workgroup, waves per workgroup, class) combinations a plan may ask for
 #define HYP_GEMV_VARIANTS(X, NW)                                                                         \
-  X(DEC_QKV, 2, NW, HYP_K_GEMV_QKV) X(DEC_SWIGLU, 2, NW, HYP_K_GEMV_GATEUP)                              \
+  X(DEC_QKV, 1, NW, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 1, NW, HYP_K_GEMV_QKV) X(DEC_SWIGLU, 2, NW, HYP_K_GEMV_GATEUP)                              \
   X(DEC_RESID, 1, NW, HYP_K_GEMV_O) X(DEC_RESID, 2, NW, HYP_K_GEMV_O)                                    \
   X(DEC_RESID, 1, NW, HYP_K_GEMV_DOWN) X(DEC_RESID, 2, NW, HYP_K_GEMV_DOWN)                              \
   X(DEC_FINAL, 1, NW, HYP_K_GEMV_DOWN) X(DEC_FINAL, 2, NW, HYP_K_GEMV_DOWN)
@@ -548,7 +596,7 @@ hipError_t mfma_gemv_init() {
 #define X(EPI, FBW, NW, CLS)                                                                                     \
   if (e == hipSuccess)                                                                                           \
     e = hipFuncSetAttribute((const void *)k_dec_gemv<EPI, FBW, NW, CLS>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                            (int)(sizeof(float) * NW * 32 * (FBW * 32 + 4)));
+                            (int)(sizeof(float) * NW * 32 * (FBW * 32 + 4)) + (EPI == DEC_QKV_OPEN ? kMaxGainBytes : 0));
   HYP_GEMV_VARIANTS(X, 8)
   HYP_GEMV_VARIANTS(X, 16)
 #undef X
@@ -561,7 +609,7 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
   p.W = a.W; p.x = a.x; p.partial = a.partial; p.counters = a.counters;
   p.N = a.N; p.KT = a.K / 16; p.ksplit = ksplit; p.tiles_per_wave = p.KT / (ksplit * nw); p.batch = a.batch;
   if (p.tiles_per_wave * ksplit * nw != p.KT || a.N % (fbw * 32) != 0 || kWavesPerCu % nw != 0) return hipErrorInvalidValue;
-  p.ssq_in = a.ssq_in; p.n_ssq = a.n_ssq; p.inv_H = a.n_ssq ? 1.0f / (float)a.K : 0.f; p.eps = a.eps;
+  p.ssq_in = a.ssq_in; p.n_ssq = a.n_ssq; p.inv_H = a.n_ssq || epi == DEC_QKV_OPEN ? 1.0f / (float)a.K : 0.f; p.eps = a.eps;
   p.lens = a.lens; p.cos_tab = a.cos_tab; p.sin_tab = a.sin_tab; p.qdec = a.qdec; p.Kc = a.Kc; p.Vc = a.Vc;
   p.geom = a.geom; p.nq = a.nq; p.nkv = a.nkv; p.m_out = a.m_out; p.I = a.I; p.xres = a.xres; p.gain = a.gain;
   p.y_out = a.y_out; p.ssq_out = a.ssq_out; p.hidden_out = a.hidden_out; p.H = a.H; p.lens_advance = a.lens_advance;
@@ -571,7 +619,9 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
   gemv_cut(a.plan, a.N, a.K, &p.groups1, &p.tail);
   if (mfma_gemv_partial_floats(a.plan, a.N, a.K) > a.partial_floats) return hipErrorInvalidValue;
   dim3 grid(p.groups1 * ksplit + (groups - p.groups1) * p.tail * ksplit);
-  const size_t lds = sizeof(float) * nw * a.batch * (fbw * 32 + 4);  // the waves' sums of the live tokens
+  // the waves' sums of the live tokens, and the norm's gain
+  const size_t lds = sizeof(float) * nw * a.batch * (fbw * 32 + 4) + (epi == DEC_QKV_OPEN ? sizeof(bf16_t) * a.H : 0);
+  if (epi == DEC_QKV_OPEN && (ksplit != 1 || fbw != 1 || a.K != a.H || !mfma_dec_opens(a.x, a.H, a.N))) return hipErrorInvalidValue;
   bool launched = false;
 #define X(EPI, FBW, NW, CLS)                                                 \
   if (!launched && epi == EPI && fbw == FBW && nw == NW && cls == CLS) {      \

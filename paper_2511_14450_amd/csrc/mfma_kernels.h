@@ -73,7 +73,7 @@ hipError_t mfma_attn_prefill(const bf16_t *q, const bf16_t *Kc, bf16_t *Vc, Cach
                              int nq, int nkv, hipStream_t s);
 
 // ------------------------------------------------------------------ decode
-enum { DEC_QKV = 0, DEC_SWIGLU = 1, DEC_RESID = 2, DEC_FINAL = 3 };
+enum { DEC_QKV = 0, DEC_SWIGLU = 1, DEC_RESID = 2, DEC_FINAL = 3, DEC_QKV_OPEN = 4 };
 
 // One skinny GEMM of a decode step, sum[token, n] = W[n, :] . x[token, :], with
 // its consumer fused in (see k_dec_gemv).  Fields a given epilogue does not use
@@ -111,6 +111,8 @@ GemvPlan mfma_gemv_plan(int cls, int N, int K, int batch);  // cls: HYP_K_GEMV_*
 size_t mfma_gemv_partial_floats(const GemvPlan &plan, int N, int K);
 bool mfma_gemv_counts(const GemvPlan &plan, int N, int K);  // whether the GEMM uses its arrival counters
 hipError_t mfma_gemv_init();  // kernel attributes, once per process and device
+// whether DEC_QKV_OPEN takes these rows (x = hidden_in, gain, xres, H set) instead of mfma_dec_begin and DEC_QKV
+bool mfma_dec_opens(const bf16_t *hidden_in, int H, int N);
 // x = hidden_in ; xres = x ; y' = x * gain -> P(32, H) ; ssq_out[H/64][32]
 hipError_t mfma_dec_begin(const bf16_t *hidden_in, float *xres, const bf16_t *gain, bf16_t *y_out, float *ssq_out,
                           int H, int batch, hipStream_t s);

@@ -14,14 +14,14 @@ namespace {
 // ----------------------------------------------------------------------------
 // Row permutations applied when a weight matrix is repacked, chosen so that the
 // two values an epilogue has to combine land in the same lane and register of
-// two accumulator blocks of one wave (a wave owns 64 packed rows = 2 blocks):
-//   QKV:     inside every head, block 0 of a wave holds d in [ib, ib+32) and
-//            block 1 holds d + 64 -> the RoPE partner (i, i + 64);
+// a wave's accumulators (a wave owns 64 packed rows = 2 blocks):
+//   QKV:     a block of 32 rows holds 16 features d of a head and their RoPE partners d + 64 behind
+//            them -> the two halves of one block (a decode step's workgroups then need one block only);
 //   gate/up: block 0 holds gate rows f..f+31, block 1 the up rows of the same f.
 // ----------------------------------------------------------------------------
 __device__ inline int src_row_qkv(int r) {  // packed row -> row of [wq; wk; wv]
-  int head = r >> 7, w = (r >> 6) & 1, i = (r >> 5) & 1, x = r & 31;
-  return head * 128 + w * 32 + i * 64 + x;
+  int head = r >> 7, block = (r >> 5) & 3, half = (r >> 4) & 1, x = r & 15;
+  return head * 128 + block * 16 + half * 64 + x;
 }
 __device__ inline int src_row_gateup(int r, int I) {  // packed row -> row of [gate; up]
   int tile = r >> 8, w = (r >> 6) & 3, i = (r >> 5) & 1, x = r & 31;
@@ -676,14 +676,14 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
         const int row = min(tb0 + wt * TB + j, p.tok_blocks - 1) * 32 + 16 * th + t16;
         pos_all[j][th] = p.row_pos[row]; req_all[j][th] = p.row_req[row]; rq_all[j][th] = p.row_q[row]; rs_all[j][th] = rstd[row - rstd0];
       }
-    f32x4_t cs[2][2][2];  // [parity of the token half][fh][cos, sin]
+    f32x4_t cs[2][FB][2];  // [parity of the token half][i][cos, sin]
     auto fetch_cs = [&](int h) {  // h = 2 j + th
       if (!rotary) return;
 #pragma unroll
-      for (int fh = 0; fh < 2; ++fh) {
-        const size_t at = (size_t)pos_all[h >> 1][h & 1] * 64 + ib + 16 * fh + q4;
-        cs[h & 1][fh][0] = *(const f32x4_t *)(p.cos_tab + at);
-        cs[h & 1][fh][1] = *(const f32x4_t *)(p.sin_tab + at);
+      for (int i = 0; i < FB; ++i) {
+        const size_t at = (size_t)pos_all[h >> 1][h & 1] * 64 + ib + 16 * i + q4;
+        cs[h & 1][i][0] = *(const f32x4_t *)(p.cos_tab + at);
+        cs[h & 1][i][1] = *(const f32x4_t *)(p.sin_tab + at);
       }
     };
     fetch_cs(0);
@@ -699,15 +699,15 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
         if (req < 0) continue;  // padding behind the last request
         const float rs = rs_all[j][th];
         if (rotary) {
-          // q or k: rotate the pair (d, d + 64) by the angle of this position; block 0 holds d, block 1 d + 64
+          // q or k: rotate the pair (d, d + 64) by the angle of this position; a block's lower half holds d, its upper d + 64
 #pragma unroll
-          for (int fh = 0; fh < 2; ++fh) {
-            const int d0 = ib + 16 * fh + q4;  // d0 .. d0 + 3 and their partners d0 + 64 ..
-            const f32x4_t c4 = cs[(2 * j + th) & 1][fh][0], s4 = cs[(2 * j + th) & 1][fh][1];
+          for (int i = 0; i < FB; ++i) {
+            const int d0 = ib + 16 * i + q4;  // d0 .. d0 + 3 and their partners d0 + 64 ..
+            const f32x4_t c4 = cs[(2 * j + th) & 1][i][0], s4 = cs[(2 * j + th) & 1][i][1];
             f32x4_t lo, hi;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              float a = acc[0][fh][j][th][e] * rs, b = acc[1][fh][j][th][e] * rs;
+              float a = acc[i][0][j][th][e] * rs, b = acc[i][1][j][th][e] * rs;
               lo[e] = a * c4[e] - b * s4[e];
               hi[e] = b * c4[e] + a * s4[e];
             }
@@ -734,7 +734,7 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
             for (int fh = 0; fh < 2; ++fh)
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
-                const int d = ib + i * 64 + 16 * fh + q4 + r;
+                const int d = ib + 16 * i + 64 * fh + q4 + r;
                 vb[(size_t)(m * 4 + (d >> 5)) * kTileElems + (khh * 32 + (d & 31)) * 8 + e] = f2bf_dev(acc[i][fh][j][th][r] * rs);
               }
         }
@@ -856,16 +856,16 @@ template <int EPI, typename F> __global__ void __launch_bounds__(256) k_gemm_fin
     if (lane < 16) p.ssq_part[(size_t)(fb0 >> 1) * rows + row] = ss;
   } else {  // EPI_QKV
     if (req < 0) return;  // padding behind the last request
-    const int r0 = fb0 * 32, ib = r0 & 32 * FB ? 32 : 0;  // the wave's 64 packed rows: the lower or the upper pairs of a head
+    const int r0 = fb0 * 32, ib = r0 & 32 * FB ? 32 : 0;  // the wave's 64 packed rows: the lower or the upper 32 pairs of a head
     if (r0 < p.qd + p.kvd) {
 #pragma unroll
-      for (int fh = 0; fh < 2; ++fh) {
-        const int d0 = ib + 16 * fh + q4;
+      for (int i = 0; i < FB; ++i) {
+        const int d0 = ib + 16 * i + q4;
         const f32x4_t c4 = *(const f32x4_t *)(p.cos_tab + (size_t)pos * 64 + d0), s4 = *(const f32x4_t *)(p.sin_tab + (size_t)pos * 64 + d0);
         f32x4_t lo, hi;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float a = acc[0][fh][e] * rs, b = acc[1][fh][e] * rs;
+          const float a = acc[i][0][e] * rs, b = acc[i][1][e] * rs;
           lo[e] = a * c4[e] - b * s4[e];
           hi[e] = b * c4[e] + a * s4[e];
         }
@@ -888,7 +888,7 @@ template <int EPI, typename F> __global__ void __launch_bounds__(256) k_gemm_fin
         for (int fh = 0; fh < 2; ++fh)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const int d = ib + i * 64 + 16 * fh + q4 + r;
+            const int d = ib + 16 * i + 64 * fh + q4 + r;
             vb[(size_t)(m * 4 + (d >> 5)) * kTileElems + (khh * 32 + (d & 31)) * 8 + e] = f2bf_dev(acc[i][fh][r] * rs);
           }
     }

@@ -496,19 +496,29 @@ hyp_status_t decode_step_mfma(hyp_stage *st, hipStream_t s, const DecScratch &sc
   float *ssq = sc.ssq;
   bf16_t *y = sc.y, *attn = sc.attn, *m = sc.m;
   CacheGeom geom = cache_geom(st);
-  if (begin)
-    PROF(st, HYP_K_ADD_NORM, mfma_dec_begin((const bf16_t *)hidden_in, base.xres, at<bf16_t>(st, L.layers[0].g1), y, ssq,
-                                             d.H, st->batch, s));
-  for (int l = 0; layers && l < st->n_layers; ++l) {
-    const LayerPtrs &p = L.layers[l];
-    bf16_t *Kc = at<bf16_t>(st, L.Kc + L.kv_layer_stride * l), *Vc = at<bf16_t>(st, L.Vc + L.kv_layer_stride * l);
+  auto qkv = [&](int l) {
     DecGemv a = base;
-    a.W = at<bf16_t>(st, p.wqkv); a.x = y; a.N = d.qd + 2 * d.kvd; a.K = d.H; a.plan = L.g_qkv;
+    a.W = at<bf16_t>(st, L.layers[l].wqkv); a.x = y; a.N = d.qd + 2 * d.kvd; a.K = d.H; a.plan = L.g_qkv;
     a.ssq_in = ssq; a.n_ssq = d.H / (l == 0 ? 64 : 32 * L.g_d.fbw);  // written by the opening kernel / the previous down GEMM
     a.lens = at<int>(st, L.lens); a.cos_tab = at<float>(st, L.cos_tab); a.sin_tab = at<float>(st, L.sin_tab);
-    a.qdec = sc.qdec; a.Kc = Kc; a.Vc = Vc; a.geom = geom; a.nq = d.nq; a.nkv = d.nkv;
-    PROF(st, HYP_K_GEMV_QKV, mfma_dec_gemv(DEC_QKV, HYP_K_GEMV_QKV, a, s));
-    PROF(st, HYP_K_ATTN_DECODE, mfma_attn_decode(a.qdec, Kc, Vc, geom, a.lens, sc.attn_part,
+    a.qdec = sc.qdec; a.Kc = at<bf16_t>(st, L.Kc + L.kv_layer_stride * l); a.Vc = at<bf16_t>(st, L.Vc + L.kv_layer_stride * l);
+    a.geom = geom; a.nq = d.nq; a.nkv = d.nkv;
+    return a;
+  };
+  // what reads the caller's rows: the first block's QKV contraction, behind a kernel of its own where they are not aligned
+  if (begin) {
+    DecGemv a = qkv(0);
+    const bool opens = mfma_dec_opens((const bf16_t *)hidden_in, d.H, a.N);
+    if (opens) { a.x = (const bf16_t *)hidden_in; a.gain = at<bf16_t>(st, L.layers[0].g1); a.ssq_in = nullptr; a.n_ssq = 0; }
+    else
+      PROF(st, HYP_K_ADD_NORM, mfma_dec_begin((const bf16_t *)hidden_in, base.xres, at<bf16_t>(st, L.layers[0].g1), y, ssq, d.H, st->batch, s));
+    PROF(st, HYP_K_GEMV_QKV, mfma_dec_gemv(opens ? DEC_QKV_OPEN : DEC_QKV, HYP_K_GEMV_QKV, a, s));
+  }
+  for (int l = 0; layers && l < st->n_layers; ++l) {
+    const LayerPtrs &p = L.layers[l];
+    const DecGemv a = qkv(l);
+    if (l > 0) PROF(st, HYP_K_GEMV_QKV, mfma_dec_gemv(DEC_QKV, HYP_K_GEMV_QKV, a, s));
+    PROF(st, HYP_K_ATTN_DECODE, mfma_attn_decode(a.qdec, a.Kc, a.Vc, geom, a.lens, sc.attn_part,
                                                  attn, d.nq, d.nkv, st->batch,
                                                  L.max_chunks, L.chunk_keys, attn_form, s));
     DecGemv o = base;
@@ -554,8 +564,7 @@ hyp_status_t run_decode_mfma(hyp_stage *st, const void *hidden_in, void *hidden_
   bool use_graph = st->prof_mask == 0 && cap == hipStreamCaptureStatusNone && !(st->cfg.flags & HYP_FLAG_NO_GRAPH);
   const int attn = decode_attn_form(st, cap != hipStreamCaptureStatusNone);
   if (!use_graph) return decode_step_mfma(st, s, st->dec_ws, hidden_in, hidden_out, attn, true, true);
-  // the first kernel reads the caller's input and stays outside the recording, so a
-  // new input address every step does not force a new graph
+  // what reads the caller's input stays outside the recording, so a new input address every step does not force a new graph
   hyp_status_t rc0 = decode_step_mfma(st, s, st->dec_ws, hidden_in, hidden_out, attn, true, false);
   if (rc0 != HYP_OK) return rc0;
   // a few recorded graphs, keyed by what is baked into them: room for four output buffers in each of the three forms
