@@ -16,6 +16,7 @@ queue model `hypsched_simulate` predicts from the measured service time.
 from __future__ import annotations
 
 import argparse
+import itertools
 import json
 import time
 from typing import Callable, Dict, List, Optional, Sequence
@@ -62,6 +63,7 @@ class Tier:
         del layers
         torch.cuda.synchronize()
         self.queues: List[List[_Task]] = [[] for _ in range(n_nodes)]
+        self.rows: List[Dict[int, tuple]] = [{} for _ in range(n_nodes)]  # a step's output buffers by batch
         self.decisions: List[dict] = []  # what the scheduler saw and chose, task by task
 
     def node_state(self, now: float):
@@ -96,11 +98,18 @@ class Tier:
         with torch.cuda.stream(stream):
             out = binding.stage_prefill(stage, hidden, seq_lens)
             if decode_steps:
-                ends = torch.cumsum(torch.tensor(list(seq_lens)), 0) - 1
-                h = out[ends.to(out.device)].contiguous()
-                for _ in range(decode_steps):
-                    h = binding.stage_decode_step(stage, h)
-                out = h
+                # the requests' last rows by slices: indices in a tensor would be copied to the device behind the prefill, and
+                # the host would wait for it there
+                ends = list(itertools.accumulate(seq_lens))
+                h = torch.cat([out[e - 1:e] for e in ends])
+                # two buffers a node, used in turn by all its tasks (its stream orders them): a recorded step belongs to its
+                # output buffer, and fresh ones had every step recorded anew
+                rows = self.rows[k].get(len(ends))
+                if rows is None:
+                    rows = self.rows[k][len(ends)] = (torch.empty_like(h), torch.empty_like(h))
+                for i in range(decode_steps):
+                    h = binding.stage_decode_step(stage, h, rows[i % 2])
+                out = h.clone()
             done = torch.cuda.Event()
             done.record(stream)
         hidden.record_stream(stream)
@@ -112,7 +121,7 @@ class Tier:
         torch.cuda.synchronize()
         for st in self.stages:
             st.destroy()
-        self.stages = []
+        self.stages, self.rows = [], []
 
 
 def main():
