@@ -108,6 +108,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     }
   }
   const int fb0 = group * FBW;
+  const bool split = !kQkv && ksplit > 1;  // QKV is never split
   // partial sums [slice][32 tokens][rows]: the finely cut last groups have a narrow array of their own behind the
   // main one (rows of those groups only), so their extra slices do not cost room over all N rows
   const bool fine = group >= p.groups1;
@@ -254,7 +255,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
   };
   // An unsplit workgroup finishes for sure: the requests go out ahead of the waves' meeting (512-wide blocks: 1.1 of 4.4 us
   // of QKV and gate/up were this round trip, with the epilogue's turn through LDS); a slice waits to know that it is the last.
-  if (ksplit == 1) fetch();
+  if (!split) fetch();
   // accumulator register r of lane l of block i is packed row 32 i + 8 (r/4) + 4 (l/32) + r%4 of
   // token l % 32: four consecutive rows per 16-byte store; token columns beyond the batch stay home
   if ((lane & 31) < p.batch) {
@@ -274,7 +275,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     for (int w = 0; w < NW; ++w) s += red[w * p.batch + token][f];
     return s;
   };
-  if (ksplit > 1) {
+  if (split) {
     // at most 8 (token, row) pairs per thread
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -296,7 +297,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     if (!is_last) return;
     fetch();
   }
-  if (ksplit > 1) {
+  if (split) {
     // The finishing workgroup.  Plain loads are enough here: every 256-byte run of `partial` has exactly one
     // writer in this launch, this XCD's L2 was invalidated when the launch began,
     // and nothing in this launch read these lines before, so a line is either
@@ -304,7 +305,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     // put there by a writer on this very XCD.  With more than four slices, two (token, row)
     // pairs per thread and GW slices of each are in flight at once; slices beyond ksplit are masked
     // rather than peeled, so the gather costs ceil(ksplit / GW) round trips.
-    constexpr int GW = EPI == DEC_QKV ? 8 : 16;
+    constexpr int GW = 16;
     if (ksplit <= 4) {
       // few slices: four of the thread's pairs at once (16 tokens' worth per round trip)
       for (int j0 = 0; j0 * NW * 64 < n_pairs; j0 += 4) {
@@ -369,7 +370,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     }
   }
   __syncthreads();
-  auto total = [&](int token, int f) { return ksplit > 1 ? fin[token][f] : wave_sum(token, f); };
+  auto total = [&](int token, int f) { return split ? fin[token][f] : wave_sum(token, f); };
 
   if (kQkv) {
     const int head = fb0 >> 2;
@@ -584,8 +585,9 @@ bool mfma_gemv_counts(const GemvPlan &g, int N, int K) {
 }
 
 // the (epilogue, blocks per workgroup, waves per workgroup, class) combinations a plan may ask for
+#define HYP_GEMV_QKV(X) X(DEC_QKV, 1, 4, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 1, 4, HYP_K_GEMV_QKV)
 #define HYP_GEMV_VARIANTS(X, NW)                                                                         \
-  X(DEC_QKV, 1, NW, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 1, NW, HYP_K_GEMV_QKV) X(DEC_SWIGLU, 2, NW, HYP_K_GEMV_GATEUP)                              \
+  X(DEC_SWIGLU, 2, NW, HYP_K_GEMV_GATEUP)                                                                \
   X(DEC_RESID, 1, NW, HYP_K_GEMV_O) X(DEC_RESID, 2, NW, HYP_K_GEMV_O)                                    \
   X(DEC_RESID, 1, NW, HYP_K_GEMV_DOWN) X(DEC_RESID, 2, NW, HYP_K_GEMV_DOWN)                              \
   X(DEC_FINAL, 1, NW, HYP_K_GEMV_DOWN) X(DEC_FINAL, 2, NW, HYP_K_GEMV_DOWN)
@@ -597,6 +599,7 @@ hipError_t mfma_gemv_init() {
   if (e == hipSuccess)                                                                                           \
     e = hipFuncSetAttribute((const void *)k_dec_gemv<EPI, FBW, NW, CLS>, hipFuncAttributeMaxDynamicSharedMemorySize, \
                             (int)(sizeof(float) * NW * 32 * (FBW * 32 + 4)) + (EPI == DEC_QKV_OPEN ? kMaxGainBytes : 0));
+  HYP_GEMV_QKV(X)
   HYP_GEMV_VARIANTS(X, 8)
   HYP_GEMV_VARIANTS(X, 16)
 #undef X
@@ -608,6 +611,7 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
   const int fbw = a.plan.fbw, nw = a.plan.nw, ksplit = a.plan.ksplit;
   p.W = a.W; p.x = a.x; p.partial = a.partial; p.counters = a.counters;
   p.N = a.N; p.KT = a.K / 16; p.ksplit = ksplit; p.tiles_per_wave = p.KT / (ksplit * nw); p.batch = a.batch;
+  if ((epi == DEC_QKV || epi == DEC_QKV_OPEN) && ksplit != 1) return hipErrorInvalidValue;
   if (p.tiles_per_wave * ksplit * nw != p.KT || a.N % (fbw * 32) != 0 || kWavesPerCu % nw != 0) return hipErrorInvalidValue;
   p.ssq_in = a.ssq_in; p.n_ssq = a.n_ssq; p.inv_H = a.n_ssq || epi == DEC_QKV_OPEN ? 1.0f / (float)a.K : 0.f; p.eps = a.eps;
   p.lens = a.lens; p.cos_tab = a.cos_tab; p.sin_tab = a.sin_tab; p.qdec = a.qdec; p.Kc = a.Kc; p.Vc = a.Vc;
@@ -621,13 +625,14 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
   dim3 grid(p.groups1 * ksplit + (groups - p.groups1) * p.tail * ksplit);
   // the waves' sums of the live tokens, and the norm's gain
   const size_t lds = sizeof(float) * nw * a.batch * (fbw * 32 + 4) + (epi == DEC_QKV_OPEN ? sizeof(bf16_t) * a.H : 0);
-  if (epi == DEC_QKV_OPEN && (ksplit != 1 || fbw != 1 || a.K != a.H || !mfma_dec_opens(a.x, a.H, a.N))) return hipErrorInvalidValue;
+  if (epi == DEC_QKV_OPEN && (fbw != 1 || a.K != a.H || !mfma_dec_opens(a.x, a.H, a.N))) return hipErrorInvalidValue;
   bool launched = false;
 #define X(EPI, FBW, NW, CLS)                                                 \
   if (!launched && epi == EPI && fbw == FBW && nw == NW && cls == CLS) {      \
     k_dec_gemv<EPI, FBW, NW, CLS><<<grid, NW * 64, lds, s>>>(p);             \
     launched = true;                                                         \
   }
+  HYP_GEMV_QKV(X)
   HYP_GEMV_VARIANTS(X, 4)
   HYP_GEMV_VARIANTS(X, 8)
   HYP_GEMV_VARIANTS(X, 16)
