@@ -20,7 +20,7 @@ struct GemmEpilogue {
   const int *row_q = nullptr;                          // row of q that a row's queries go to
   // EPI_QKV, EPI_SWIGLU: RMS Norm factor of every input row (the rows carry the gain only)
   const float *rstd = nullptr;
-  // up to kShortRows rows: the sums of squares (ssq_part of the GEMM before) instead, null where rstd is given; row_ext too
+  // where mfma_gemm_adds_sums(): the sums of squares (ssq_part of the GEMM before) instead, null where rstd is given; row_ext too
   const float *ssq_in = nullptr;
   float eps = 0.f;
   // EPI_RESID: residual stream A(T', N), gains of the following norm, padding map,
@@ -29,12 +29,11 @@ struct GemmEpilogue {
   const bf16_t *gain = nullptr;
   const int *row_ext = nullptr;
   float *ssq_part = nullptr;
-  // any epilogue: scratch for GEMMs whose K loop is split across workgroups (few output tiles)
+  // every epilogue: scratch for GEMMs whose K loop is split across workgroups (few output tiles)
   float *split_ws = nullptr;          // mfma_gemm_split_ws_bytes()
   unsigned *split_counters = nullptr;  // kGemmShortMaxTiles + 1, zero between launches
 };
 
-constexpr int kShortRows = 128;          // prompts of up to so many internal rows run the GEMM's short forms
 // Wide GEMMs of two and a half rounds of 256 tiles or more are never split: a request that fills them alone then has the same
 // bits in any batch, and what splitting the last, partial round saves falls with the number of rounds (Phi-3 block: gate/up 210
 // -> 155 us at 384 rows = 280 tiles, 325 -> 292 at 1024 = 560).
@@ -55,6 +54,9 @@ hipError_t mfma_prefill_end(const float *xres, const bf16_t *delta_bf, bf16_t *h
 // rstd[row] from the per-group sums of squares of EPI_RESID
 hipError_t mfma_rstd(const float *ssq_part, float *rstd, const int *row_ext, int rows, int H, float eps, hipStream_t s);
 
+// whether a QKV or gate/up GEMM adds up the sums of squares of its rows itself (the short forms, and k_gemm_finish where all tiles
+// are split): the launch of mfma_rstd, 4 - 5 us, is saved
+bool mfma_gemm_adds_sums(int rows, int N, int K);
 hipError_t mfma_gemm_init();
 // out^T[N, rows] = W[N,K] X[rows,K]^T with the epilogue `epi`; rows % 32 == 0,
 // N % 256 == 0, K % 32 == 0, K >= 128

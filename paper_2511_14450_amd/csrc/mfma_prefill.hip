@@ -952,26 +952,26 @@ hipError_t mfma_gemm_init() {
   return e;
 }
 
-hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int rows, int N, int K, bf16_t *out,
-                     int out_K, const GemmEpilogue &ep, hipStream_t s) {
-  if (rows == 0) return hipSuccess;
-  GemmParams p = {};
-  p.X = X; p.W = W; p.KT = K / 16; p.tok_blocks = rows / 32; p.feat_blocks = N / 32;
+// How a GEMM is cut: its form (tokens of a tile: 64, 128, 256), and for the wide form the slices of the tiles beyond whole rounds
+struct GemmCut { int form, wide_split, wide_rest, wide_tiles; };
+
+// A K loop in slices costs their partial tiles, written and read at 5 TB/s together, and the launch that adds them up.
+static double slice_cost(int tiles, int c, int tok, int feat) { return c == 1 ? 0.0 : (double)tiles * c * tok * feat * 4096.0 / 2.5e6 + 5.0; }
+
+static GemmCut gemm_cut(int rows, int N, int K) {
   constexpr int NST = WideForm::NST, XB = WideForm::XB, NBK = WideForm::NBK;
-  const int stages = p.KT / KTS;
-  // A K loop in slices costs their partial tiles, written and read at 5 TB/s together, and the launch that adds them up.
-  const auto slice_cost = [](int tiles, int c, int tok, int feat) { return c == 1 ? 0.0 : (double)tiles * c * tok * feat * 4096.0 / 2.5e6 + 5.0; };
+  const int tok_blocks = rows / 32, feat_blocks = N / 32, stages = K / 16 / KTS;
   // The wide form: whole rounds of one tile per CU, then the rest, in as many rounds as its slices take.  Slices are whole
   // numbers of stages, at least two rounds through the LDS buffers.
-  const int wide_tiles = (p.tok_blocks + XB - 1) / XB * (p.feat_blocks / NBK), wide_rest = wide_tiles % kGemmSplitCus;
+  const int wide_tiles = (tok_blocks + XB - 1) / XB * (feat_blocks / NBK), wide_rest = wide_tiles % kGemmSplitCus;
   const double tile_us = K * 0.020, start_us = 4.0;  // a 256 x 256 tile on one CU, whatever the others do (K = 5120: 105 us)
   int wide_split = 1;
   double wide_us = wide_rest ? tile_us + start_us : 0.0;
-  if (ep.split_ws && wide_tiles <= kGemmSplitMaxTiles) {
+  if (wide_tiles <= kGemmSplitMaxTiles) {
     double best = 0.95 * wide_us;  // a split has to win clearly
     for (int c = 2; c <= 32 && wide_rest * c <= kGemmSplitUnits && wide_rest > 0 && stages / c >= 2 * NST; ++c) {
       const int rounds = (wide_rest * c + kGemmSplitCus - 1) / kGemmSplitCus;
-      const double t = rounds * (tile_us / c + start_us) + slice_cost(wide_rest, c, std::min(p.tok_blocks, XB), NBK);
+      const double t = rounds * (tile_us / c + start_us) + slice_cost(wide_rest, c, std::min(tok_blocks, XB), NBK);
       if (t < best) { best = wide_us = t; wide_split = c; }
     }
   }
@@ -982,13 +982,31 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
   // (two to a CU: 0.40 us, and 0.45 for every 512 more).  512 wide, 553 rows: QKV 26.7 -> 12.3 us, O 17.7 -> 14.7, gate/up 18.8
   // -> 10.9, down 16.6 -> 12.5; 1024 wide, FFN 2048: gate/up 1024 rows 27 -> 20, but 2000 rows 28 against 33.
   int form = 256;
-  if (p.tok_blocks <= Form128::XB) {
-    form = p.tok_blocks <= Form64::XB || 2.0 * N * K <= 16e6 ? 64 : 128;
+  if (tok_blocks <= Form128::XB) {
+    form = tok_blocks <= Form64::XB || 2.0 * N * K <= 16e6 ? 64 : 128;
   } else {
-    const int tiles = (p.tok_blocks + Form64::XB - 1) / Form64::XB * (p.feat_blocks / Form64::NBK);
+    const int tiles = (tok_blocks + Form64::XB - 1) / Form64::XB * (feat_blocks / Form64::NBK);
     const double per = 0.24 + 0.16 * std::max(0, std::min(tiles, 512) - 256) / 256.0 + 0.45 * std::max(0, tiles - 512) / 512.0;
     if (7.5 + stages * per < 0.9 * wide_us) form = 64;
   }
+  return {form, wide_split, wide_rest, wide_tiles};
+}
+
+bool mfma_gemm_adds_sums(int rows, int N, int K) {
+  const GemmCut cut = gemm_cut(rows, N, K);
+  return cut.form < 256 || (cut.wide_split > 1 && cut.wide_rest == cut.wide_tiles);
+}
+
+hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int rows, int N, int K, bf16_t *out,
+                     int out_K, const GemmEpilogue &ep, hipStream_t s) {
+  if (rows == 0) return hipSuccess;
+  if (!ep.split_ws || !ep.split_counters || (!ep.rstd && ep.ssq_in && !mfma_gemm_adds_sums(rows, N, K))) return hipErrorInvalidValue;
+  GemmParams p = {};
+  p.X = X; p.W = W; p.KT = K / 16; p.tok_blocks = rows / 32; p.feat_blocks = N / 32;
+  constexpr int XB = WideForm::XB, NBK = WideForm::NBK;
+  const int stages = p.KT / KTS;
+  const GemmCut cut = gemm_cut(rows, N, K);
+  const int form = cut.form;
   const int tok_tile = form == 64 ? Form64::XB : form == 128 ? Form128::XB : XB;
   const int tiles_t = (p.tok_blocks + tok_tile - 1) / tok_tile, tiles_n = p.feat_blocks / (form < 256 ? Form64::NBK : NBK);
   p.gm = tiles_t < 8 ? tiles_t : 8;
@@ -1000,7 +1018,7 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
   p.first = p.n_tiles; p.ksplit = 1; p.finish = true;
   p.split_ws = ep.split_ws; p.split_counters = ep.split_counters;
   if (form < 256) {
-    if (ep.split_ws && ep.split_counters && p.n_tiles <= kGemmShortMaxTiles) {
+    if (p.n_tiles <= kGemmShortMaxTiles) {
       // The short forms, few tiles: the chip streams as much as its workgroups keep in flight over 1.5 us of latency, 6 TB/s at best,
       // and a CU with one workgroup more than the others is waited for.  (64 rows, slices 10 -> 5: down 51 -> 43 us, O 25 ->
       // 21; QKV 8 -> 4: 30 -> 26.)
@@ -1024,8 +1042,8 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
             break;
           }
     }
-  } else if (wide_split > 1) {
-    p.ksplit = wide_split; p.first = p.n_tiles - wide_rest;
+  } else if (cut.wide_split > 1) {
+    p.ksplit = cut.wide_split; p.first = p.n_tiles - cut.wide_rest;
   }
   p.first_grid = (p.first + 7) / 8 * 8;
   p.rest_grid = ((p.n_tiles - p.first) * p.ksplit + 7) / 8 * 8;
@@ -1034,7 +1052,7 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
   // 2.3 % faster.  With 20 - 30 rounds the drawn tiles' lost L2 neighbourhood and the tile granularity cost more than
   // the balance brings: down projection 1.7 % slower.)
   p.n_static = 0; p.pool_wgs = 0;
-  if (ep.split_counters && p.n_tiles >= 64 * kGemmSplitCus) {
+  if (form == 256 && p.n_tiles >= 64 * kGemmSplitCus) {
     const int rounds = p.n_tiles / kGemmSplitCus;
     const int pool_rounds = (rounds + 8) / 16;
     p.first = p.n_tiles; p.ksplit = 1; p.rest_grid = 0;

@@ -429,7 +429,8 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
   float *rstd = at<float>(st, L.rstd), *ssq_part = at<float>(st, L.ssq_part);
   PROF(st, HYP_K_ADD_NORM, mfma_prefill_begin((const bf16_t *)hidden_in, xres, at<bf16_t>(st, L.layers[0].g1), y, rstd,
                                                row_ext, rows, d.H, d.eps, s));
-  const bool short_rows = rows <= kShortRows;
+  // the consumer of a residual GEMM adds up the sums of squares itself, or finds them as factors (the first block's always are)
+  const bool qkv_adds = mfma_gemm_adds_sums(rows, d.qd + 2 * d.kvd, d.H), gu_adds = mfma_gemm_adds_sums(rows, 2 * d.I, d.H);
   GemmEpilogue split;  // scratch of GEMMs that split their K loop (short prompts leave few output tiles)
   split.split_ws = at<float>(st, L.gemm_ws); split.split_counters = at<unsigned>(st, L.gemm_counters);
   for (int l = 0; l < st->n_layers; ++l) {
@@ -441,8 +442,7 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
     e.geom = geom; e.qd = d.qd; e.kvd = d.kvd;
     e.cos_tab = at<float>(st, L.cos_tab); e.sin_tab = at<float>(st, L.sin_tab);
     e.row_pos = row_pos; e.row_req = row_req; e.row_q = row_q;
-    // short prompts: the consumer adds up the sums of squares itself (the first block's come as factors)
-    if (short_rows && l > 0) { e.ssq_in = ssq_part; e.eps = d.eps; e.row_ext = row_ext; }
+    if (qkv_adds && l > 0) { e.ssq_in = ssq_part; e.eps = d.eps; e.row_ext = row_ext; }
     else e.rstd = rstd;
     PROF(st, HYP_K_GEMM_QKV, mfma_gemm(EPI_QKV, HYP_K_GEMM_QKV, y, at<bf16_t>(st, p.wqkv), rows, d.qd + 2 * d.kvd, d.H, q, d.qd, e, s));
     PROF(st, HYP_K_ATTN_PREFILL, mfma_attn_prefill(q, e.Kc, e.Vc, geom, attn, tiles, n_tiles,
@@ -452,15 +452,15 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
     r.xres = xres; r.row_ext = row_ext; r.ssq_part = ssq_part;
     r.gain = at<bf16_t>(st, p.g2);
     PROF(st, HYP_K_GEMM_O, mfma_gemm(EPI_RESID, HYP_K_GEMM_O, attn, at<bf16_t>(st, p.wo), rows, d.H, d.qd, y, d.H, r, s));
-    if (!short_rows) PROF(st, HYP_K_ADD_NORM, mfma_rstd(ssq_part, rstd, row_ext, rows, d.H, d.eps, s));
+    if (!gu_adds) PROF(st, HYP_K_ADD_NORM, mfma_rstd(ssq_part, rstd, row_ext, rows, d.H, d.eps, s));
     GemmEpilogue g = split;
-    if (short_rows) { g.ssq_in = ssq_part; g.eps = d.eps; g.row_ext = row_ext; }
+    if (gu_adds) { g.ssq_in = ssq_part; g.eps = d.eps; g.row_ext = row_ext; }
     else g.rstd = rstd;
     PROF(st, HYP_K_GEMM_GATEUP, mfma_gemm(EPI_SWIGLU, HYP_K_GEMM_GATEUP, y, at<bf16_t>(st, p.wgu), rows, 2 * d.I, d.H, m, d.I, g, s));
     if (!last) {
       r.gain = at<bf16_t>(st, L.layers[l + 1].g1);
       PROF(st, HYP_K_GEMM_DOWN, mfma_gemm(EPI_RESID, HYP_K_GEMM_DOWN, m, at<bf16_t>(st, p.wd), rows, d.H, d.I, y, d.H, r, s));
-      if (!short_rows) PROF(st, HYP_K_ADD_NORM, mfma_rstd(ssq_part, rstd, row_ext, rows, d.H, d.eps, s));
+      if (!qkv_adds) PROF(st, HYP_K_ADD_NORM, mfma_rstd(ssq_part, rstd, row_ext, rows, d.H, d.eps, s));
     } else {
       PROF(st, HYP_K_GEMM_DOWN, mfma_gemm(EPI_STORE, HYP_K_GEMM_DOWN, m, at<bf16_t>(st, p.wd), rows, d.H, d.I, delta, d.H, split, s));
       PROF(st, HYP_K_ADD_NORM, mfma_prefill_end(xres, delta, (bf16_t *)hidden_out, row_ext, rows, d.H, s));
