@@ -165,13 +165,14 @@ constexpr int FB = 2, KTS = 2;
 // How a workgroup is laid out: WF waves along the features (FB blocks of 32 each) times WT along the tokens (TB
 // blocks each), NST stages in LDS.
 //   <4, 2, 4, 4>  256 features x 256 tokens: the form described above
-//   <2, 2, 1, 6>  128 features x 64 tokens: a short prompt.  It is bound by the weights' way out of HBM, and the wide
+//   <2, 2, 1, 6>  128 features x 64 tokens: a short prompt, or a narrow layer at any number of rows (gemm_cut).  A short
+//                 prompt is bound by the weights' way out of HBM, and the wide
 //                 form multiplies three tokens of padding for every live one on top (gate/up of 64 tokens: 94 GFLOP,
 //                 100 us, for 367 MB).  Twice as many tiles as 256 features would give put a workgroup on every CU
 //                 (two fit) with fewer K slices; each keeps five stages of 12 KiB on their way.
 //   <2, 2, 2, 4>  128 features x 128 tokens: the same, stages of 16 KiB
-// Measured per Phi-3-sized block: 64 tokens gate/up 101 -> 78 us, down 69 -> 52, QKV 47 -> 33, O 44 -> 28; the whole block
-// of 128 tokens 405 -> 295 us.  128 features x 256 tokens in three stages for 129 - 256 tokens lost (379 -> 540 us):
+// Measured per Phi-3-sized block against the wide form: 64 tokens gate/up 101 -> 78 us, down 69 -> 42 (with k_gemm_finish), QKV 47
+// -> 27, O 44 -> 20; the whole block of 128 tokens 405 -> 230 us.  128 features x 256 tokens in three stages for 129 - 256 tokens lost (379 -> 540 us):
 // without the wide form's read-ahead the loop waits for LDS at every stage.
 template <int WF_, int WT_, int TB_, int NST_> struct GemmForm {
   static constexpr int WF = WF_, WT = WT_, TB = TB_, NST = NST_;

@@ -479,8 +479,8 @@ int decode_attn_form(const hyp_stage *st, bool recorded_by_caller) {
 }
 
 // One decode step through the MFMA kernels (a single block of 32 token rows):
-// 1 + 5 launches per block, every reduction finished inside the kernel that
-// produced it.
+// 5 launches per block (and one in front where the rows are not aligned), every
+// reduction finished inside the kernel that produced it.
 hyp_status_t decode_step_mfma(hyp_stage *st, hipStream_t s, const DecScratch &sc, const void *hidden_in, void *hidden_out,
                               int attn_form, bool begin, bool layers) {
   const Dims &d = st->dm;
@@ -595,7 +595,8 @@ hyp_status_t run_decode_mfma(hyp_stage *st, const void *hidden_in, void *hidden_
 }
 
 // rows tokens through every block with the shape-generic kernels: a prompt in `n_tiles` query tiles, or
-// (n_tiles == 0) one token of every resident request.  1 + 5 launches per block.
+// (n_tiles == 0) one token of every resident request.  5 launches per block and one in front, which a step of
+// few requests does without (plain_gemv_opens).
 template <typename T>
 hyp_status_t run_plain(hyp_stage *st, const void *hidden_in, void *hidden_out, int rows, int n_tiles) {
   const Dims &d = st->dm;
