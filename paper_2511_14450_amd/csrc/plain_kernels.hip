@@ -155,10 +155,12 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
   }
   // RMS Norm factors: the sums of squares of this wave's tokens, added up by lane groups (four parts at a time).  Waves that
   // share the K loop share them too and request theirs here, under the first tiles; a wave on its own adds them up behind the
-  // loop, where registers are free, 32 parts of a token requested at once.  (Pairs of parts one after the other took 4 of 14
-  // us in a form of 32 x 32, 8 of 36 in the wide one: bf16, 1065 rows, 64 parts.)
+  // loop.  (Pairs of parts one after the other took 4 of 14 us in a form of 32 x 32, 8 of 36 in the wide one: bf16, 1065 rows, 64
+  // parts.)  It requests 32 parts of a token at once in float, whose accumulators and operands leave one wave a SIMD either way,
+  // and 16 in bf16: 32 took the wide form from 240 to 280 registers and so from two waves to one (a block of 5120 wide, 20 / 4
+  // heads, FFN 8960, 4000 rows: 2991 us against 3479; 1024 wide, FFN 4096, 1065 rows: 168 against 180).
   constexpr bool kNorm = EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU;
-  constexpr int kSsq = 4;
+  constexpr int kSsq = 4, kTogether = sizeof(T) == 2 ? 4 : 8;
   const int row = lane >> 4;
   float sq[WN][kSsq];
   auto part = [&](int p, int j) { return p < g.ssq_parts ? g.ssq_in[(size_t)p * g.rows_pad + min(tt0 + j, a.tt - 1) * 16 + tl] : 0.f; };
@@ -191,16 +193,16 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
         for (int p = (kSsq * KW + kw) * 4 + row; p < g.ssq_parts; p += 4 * KW) rs[j] += part(p, j);
       }
     } else {
-      for (int p0 = 0; p0 < g.ssq_parts; p0 += 32) {
-        float v[WN][8];
+      for (int p0 = 0; p0 < g.ssq_parts; p0 += 4 * kTogether) {
+        float v[WN][kTogether];
 #pragma unroll
         for (int j = 0; j < WN; ++j)
 #pragma unroll
-          for (int i = 0; i < 8; ++i) v[j][i] = part(p0 + i * 4 + row, j);
+          for (int i = 0; i < kTogether; ++i) v[j][i] = part(p0 + i * 4 + row, j);
 #pragma unroll
         for (int j = 0; j < WN; ++j)
 #pragma unroll
-          for (int i = 0; i < 8; ++i) rs[j] += v[j][i];
+          for (int i = 0; i < kTogether; ++i) rs[j] += v[j][i];
       }
     }
 #pragma unroll
