@@ -635,7 +635,11 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
       if (tb >= p.tok_blocks) continue;
 #pragma unroll
       for (int th = 0; th < 2; ++th) {
-        const int row = tb * 32 + 16 * th + t16;
+        // The lane's places come from an opaque copy: worked out once for all token halves and kept, they took the wide form to 256
+        // registers, four of them spilled.  242 now (Phi-3, 2048 rows: O projection 126 -> 122 us; 65536 rows: down 8458 -> 8427).
+        int at = lane;
+        asm volatile("" : "+v"(at));
+        const int q4 = (at >> 4) * 4, row = tb * 32 + 16 * th + (at & 15);
         const bool live = p.row_ext[row] >= 0;
         float ss = 0.f;
 #pragma unroll

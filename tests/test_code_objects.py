@@ -50,3 +50,9 @@ def test_wide_bf16_generic_gemms_keep_two_waves_a_simd(kernels):
     # four epilogues; registers of a wave, accumulators among them: 512 / 2
     for name, k in pick(kernels, r"12k_plain_gemmItLi\dELi4ELi4ELi2ELi2ELi1E", 4).items():
         assert k["vgprs"] <= 256 and k["scratch"] == 0, (name, k)
+
+
+def test_prefill_gemms_do_not_spill(kernels):
+    # five pairs of epilogue and class in three forms; the wide one (waves 4 x 2, four token blocks each) keeps 8 waves a CU
+    for name, k in pick(kernels, r"6k_gemmILi\dELi\dENS0_8GemmForm", 15).items():
+        assert k["vgprs"] <= 256 and k["spilled"] == 0 and k["scratch"] == 0, (name, k)
