@@ -61,13 +61,16 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(FI
   PlainAhead<T> pf;
 
   const int chunks = a.tiles * 4 * TB, n_stage = (chunks + KW * 64 - 1) / (KW * 64);
-  u32x4 st[kStaged ? kStage : 1], st_gain[FIRST ? kStage : 1];
+  // sixteen waves have 128 registers each: rows and gain of all eight chunks of a thread would not fit beside the tiles (18
+  // spilled in bf16), so the second four, which only more than 4096 chunks need, are requested behind the first
+  constexpr int kHeld = FIRST && KW == 16 ? kStage / 2 : kStage;
+  u32x4 st[kStaged ? kHeld : 1], st_gain[FIRST ? kHeld : 1];
   constexpr int E = plain_chunk<T>();
-  if constexpr (kStaged) {
+  auto request = [&](int i0) {
 #pragma unroll
-    for (int i = 0; i < kStage; ++i)
-      if (i < n_stage) {
-        const int c = min((int)threadIdx.x + i * KW * 64, chunks - 1);
+    for (int i = 0; i < kHeld; ++i)
+      if (i0 + i < n_stage) {
+        const int c = min((int)threadIdx.x + (i0 + i) * KW * 64, chunks - 1);
         if constexpr (FIRST) {
           const int k = c / TB * E, r = c % TB;
           st[i] = st_gain[i] = u32x4{0, 0, 0, 0};  // no such row, or padding along K
@@ -79,7 +82,8 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(FI
           st[i] = ((const u32x4 *)g.X)[(c / TB) * 16 + c % TB];
         }
       }
-  }
+  };
+  if constexpr (kStaged) request(0);
   const int tile0 = min(wave, a.tiles - 1);  // a wave without a tile rereads the last one and uses nothing
   const u32x4 *wp = (const u32x4 *)g.W + ((size_t)ft * a.tiles + tile0) * 64 + lane;
   const u32x4 *xp[NX];
@@ -132,35 +136,43 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(FI
     }
     if (finisher) plain_fetch<T, EPI>(pf, g, wave * 16 + tl, ft * 16 + row * 4);
     if constexpr (kStaged) {
+      auto stage = [&](int i0) {
 #pragma unroll
-      for (int i = 0; i < kStage; ++i)
-        if (i < n_stage) {
-          if constexpr (FIRST) {
-            union { u32x4 v; T e[E]; } x, w;
-            x.v = st[i]; w.v = st_gain[i];
-            float q[E / 4];
-            {
+        for (int i = 0; i < kHeld; ++i)
+          if (i0 + i < n_stage) {
+            const int c = threadIdx.x + (i0 + i) * KW * 64;
+            if constexpr (FIRST) {
+              union { u32x4 v; T e[E]; } x, w;
+              x.v = st[i]; w.v = st_gain[i];
+              float q[E / 4];
+              {
 #pragma clang fp contract(off)
 #pragma unroll
-              for (int h = 0; h < E / 4; ++h) {
-                float s[4];
+                for (int h = 0; h < E / 4; ++h) {
+                  float s[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) { const float f = load_f32(&x.e[4 * h + e]); s[e] = f * f; }
-                q[h] = (s[0] + s[1]) + (s[2] + s[3]);
+                  for (int e = 0; e < 4; ++e) { const float f = load_f32(&x.e[4 * h + e]); s[e] = f * f; }
+                  q[h] = (s[0] + s[1]) + (s[2] + s[3]);
+                }
+                // 16 features: the lanes of four (float) or two (bf16) neighbouring chunks of the row
+                float s = E == 4 ? q[0] : q[0] + q[E / 4 - 1];
+                s += __shfl_xor(s, TB, 64);
+                if (E == 4) s += __shfl_xor(s, 2 * TB, 64);
+                const int chunk = c / TB, per = 16 / E;
+                if (c < chunks && chunk % per == 0) ps[chunk / per * TB + c % TB] = s;
               }
-              // 16 features: the lanes of four (float) or two (bf16) neighbouring chunks of the row
-              float s = E == 4 ? q[0] : q[0] + q[E / 4 - 1];
-              s += __shfl_xor(s, TB, 64);
-              if (E == 4) s += __shfl_xor(s, 2 * TB, 64);
-              const int c = threadIdx.x + i * KW * 64, chunk = c / TB, per = 16 / E;
-              if (c < chunks && chunk % per == 0) ps[chunk / per * TB + c % TB] = s;
-            }
 #pragma unroll
-            for (int e = 0; e < E; ++e) store_f32(&x.e[e], load_f32(&x.e[e]) * load_f32(&w.e[e]));
-            st[i] = x.v;
+              for (int e = 0; e < E; ++e) store_f32(&x.e[e], load_f32(&x.e[e]) * load_f32(&w.e[e]));
+              st[i] = x.v;
+            }
+            x_s[c] = st[i];
           }
-          x_s[threadIdx.x + i * KW * 64] = st[i];
-        }
+      };
+      stage(0);
+      if (kHeld < kStage && n_stage > kHeld) {
+        request(kHeld);
+        stage(kHeld);
+      }
       __syncthreads();
       if constexpr (FIRST)
 #pragma unroll

@@ -56,3 +56,9 @@ def test_prefill_gemms_do_not_spill(kernels):
     # five pairs of epilogue and class in three forms; the wide one (waves 4 x 2, four token blocks each) keeps 8 waves a CU
     for name, k in pick(kernels, r"6k_gemmILi\dELi\dENS0_8GemmForm", 15).items():
         assert k["vgprs"] <= 256 and k["spilled"] == 0 and k["scratch"] == 0, (name, k)
+
+
+def test_generic_decode_contractions_do_not_spill(kernels):
+    # float and bf16; up to 4, 8, 16, 32 tokens in 8 and 16 waves; four epilogues, and the opening form of QKV up to 8 tokens
+    for name, k in pick(kernels, r"12k_plain_gemvI[ft]L", 2 * 2 * (4 * 4 + 2)).items():
+        assert k["spilled"] == 0 and k["scratch"] == 0, (name, k)

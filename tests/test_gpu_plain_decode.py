@@ -67,3 +67,35 @@ def test_a_step_opens_alike_whatever_the_alignment(shape, batch, dtype):
             out.append(gst.decode_step(rows))
         gst.destroy()
     assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
+
+
+@pytest.mark.parametrize("batch", [1, 4, 5, 8, 9])
+@pytest.mark.parametrize("dtype,hidden", [("f32", 1100), ("f32", 2064), ("bf16", 2056), ("bf16", 4104)])
+def test_sixteen_waves_against_oracle(dtype, hidden, batch):
+    """QKV contractions of more than 64 tiles along K and few output rows are shared by sixteen waves; with more than 4096
+    chunks of tokens (2064 and 4104 wide, 5 - 8 rows) the opening one stages them in two turns.  Against the oracle, and bit
+    for bit the same from rows that are not aligned, which go through the opening kernel."""
+    import torch
+    from paper_2511_14450_amd import binding
+    shp = synth.BlockShape(hidden, 4, 2, 32, 96, dtype=dtype)
+    layers = [synth.layer_weights(shp, l, 47_200, sigma=hidden ** -0.5) for l in range(2)]  # scores of spread 1
+    x = synth.hidden_states(batch * 3, shp, 47_201)
+    out = []
+    for shift in (0, 1):
+        ost = orc.Stage(shp, layers, batch, 8, "f32")
+        gst = make_gpu_stage(shp, layers, batch, 8, batch * 3, flags=binding.HYP_FLAG_PLAIN_KERNELS)
+        ost.prefill(x, [3] * batch)
+        gst.prefill(to_dev(x, dtype), [3] * batch)
+        for s in range(2):
+            xd = synth.hidden_states(batch, shp, 47_202 + s)
+            room = to_dev(synth.hidden_states(batch + 1, shp, 47_299), dtype).view(-1)
+            rows = room[shift:shift + batch * hidden].view(batch, hidden)
+            rows.copy_(to_dev(xd, dtype))
+            out.append(gst.decode_step(rows))
+            ref = ost.decode_step(xd)
+            # the update, which is small beside the input here: besides its own error it carries the rounding of the output, up to
+            # 2^-8 of an element in bf16
+            got, rounding = to_host(out[-1]), 2.0 ** -8 if dtype == "bf16" else 2.0 ** -24
+            assert abs(got - ref).max() <= TOL[dtype] * abs(ref - xd).max() + rounding * abs(ref).max(), (shift, s)
+        gst.destroy()
+    assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
