@@ -378,6 +378,10 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
       load(kS[0], vS[0], min(kb + step, n_kb - 1));
     }
   }
+  // The lane's places once more, from an opaque copy: kept over the loop they took the float form of 65 - 127 features past 256
+  // registers (8 spilled; 8 requests of 1500 keys, 80 features: a block 41.1 -> 40.1 us) and that of 128 to 250 (195 now).
+  int at = lane;
+  asm volatile("" : "+v"(at));
   // sum of the probabilities over the lanes that hold different keys
   if constexpr (sizeof(T) == 4) {
     l_run += __shfl_xor(l_run, 4, 64);
@@ -385,12 +389,12 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
   }
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
-  if (lane < 4) { m_s[wave][lane] = m_run; l_s[wave][lane] = l_run; }
+  if (at < 4) { m_s[wave][at] = m_run; l_s[wave][at] = l_run; }
 #pragma unroll
   for (int f = 0; f < NF; ++f)
-    if (f < nf) o_s[(wave * nf + f) * 64 + lane] = o[f];
+    if (f < nf) o_s[(wave * nf + f) * 64 + at] = o[f];
   __syncthreads();
-  const int c = lane & 3;
+  const int c = at & 3;
   float m = m_s[0][c];  // -inf: a share without a key, whose weights and sums are 0
 #pragma unroll
   for (int w = 1; w < KW; ++w) m = fmaxf(m, m_s[w][c]);
@@ -400,20 +404,21 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
     wgt[w] = m_s[w][c] == -INFINITY ? 0.f : expf(m_s[w][c] - m);
     l += wgt[w] * l_s[w][c];
   }
+  const int col_at = blockIdx.z * 4 + c, head_at = kvh * a.G + min(col_at, a.G - 1);
   for (int f = wave; f < nf; f += KW) {
     f32x4 r = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < KW; ++w)
-      r += o_s[(w * nf + f) * 64 + lane] * wgt[w];  // zeros of a share without a key
+      r += o_s[(w * nf + f) * 64 + at] * wgt[w];  // zeros of a share without a key
     const float v = rows_sum4(r);  // the rows hold the sums over different keys
-    const int feat = f * 16 + (lane & 12) + quad_reg(row);
-    if (col >= a.G || feat >= d) continue;
+    const int feat = f * 16 + (at & 12) + quad_reg(at >> 4);
+    if (col_at >= a.G || feat >= d) continue;
     if (a.split > 1) {
-      float *dst = a.part + (((size_t)req * a.nq + head) * a.split + share) * (2 + d);
+      float *dst = a.part + (((size_t)req * a.nq + head_at) * a.split + share) * (2 + d);
       if (feat == 0) { dst[0] = m; dst[1] = l; }
       dst[2 + feat] = v;
     } else {
-      store_f32(a.out + plain_offset<T>(req, head * d + feat, a.out_tiles), v / l);
+      store_f32(a.out + plain_offset<T>(req, head_at * d + feat, a.out_tiles), v / l);
     }
   }
 }

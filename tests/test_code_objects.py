@@ -62,3 +62,8 @@ def test_generic_decode_contractions_do_not_spill(kernels):
     # float and bf16; up to 4, 8, 16, 32 tokens in 8 and 16 waves; four epilogues, and the opening form of QKV up to 8 tokens
     for name, k in pick(kernels, r"12k_plain_gemvI[ft]L", 2 * 2 * (4 * 4 + 2)).items():
         assert k["spilled"] == 0 and k["scratch"] == 0, (name, k)
+
+
+def test_generic_decode_attention_does_not_spill(kernels):
+    for name, k in pick(kernels, r"16k_plain_dec_attnI[ft]L", 10).items():
+        assert k["spilled"] == 0 and k["scratch"] == 0, (name, k)
