@@ -379,9 +379,10 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
     }
   }
   // The lane's places once more, from an opaque copy: kept over the loop they took the float form of 65 - 127 features past 256
-  // registers (8 spilled; 8 requests of 1500 keys, 80 features: a block 41.1 -> 40.1 us) and that of 128 to 250 (195 now).
+  // registers (8 spilled; 8 requests of 1500 keys, 80 features: a block 41.1 -> 40.1 us) and that of 128 to 250 (195 now).  Wider
+  // heads have registers to spare, and in float took 2 - 3 % longer this way.
   int at = lane;
-  asm volatile("" : "+v"(at));
+  if constexpr (NF <= 8) asm volatile("" : "+v"(at));
   // sum of the probabilities over the lanes that hold different keys
   if constexpr (sizeof(T) == 4) {
     l_run += __shfl_xor(l_run, 4, 64);
