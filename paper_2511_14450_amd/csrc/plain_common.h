@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "launch_rules.h"
 
 namespace hyp {
 
@@ -62,8 +63,6 @@ template <typename T, int EPI> inline GemmArgs<T> gemm_args(const PlainGemm<T> &
   return a;
 }
 
-constexpr int kPlainMaxSplit = 8;
-constexpr size_t kPlainSplitGroups = 512;  // workgroups that a split may make of a decode step
 template <typename T> struct AttnArgs {
   const T *q, *Kc, *Vc;
   T *out;

@@ -538,17 +538,7 @@ hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *
   AttnArgs<T> a = attn_args<T>(q, q_ld, Kc, Vc, out, cache, dm);
   a.lens = lens; a.part = part;
   const int groups = column_groups(dm), nf = (dm.d + 15) / 16, nc = plain_tiles(dm.d, sizeof(T));
-  // Few (request, KV head) pairs leave most CUs idle: the keys of a head are dealt to `split` workgroups where the rounds of
-  // blocks that this saves (their MFMAs at two waves per SIMD, 2.4 GHz, plus 0.5 us of softmax and latency each) pay for
-  // the merging launch (5 us).
-  const double round_us = (nc * kMmaSteps<T> + nf * 4) * 16.0 / 2400.0 + 0.5;
-  const int blocks = longest / 16 + 1, kw = 8;
-  a.split = 1;
-  double best = (blocks + kw - 1) / kw * round_us;
-  for (int c = 2; c <= kPlainMaxSplit && (size_t)batch * dm.nkv * groups * c <= kPlainSplitGroups; c *= 2) {
-    const double t = (blocks + kw * c - 1) / (kw * c) * round_us + 5.0;
-    if (t < best) { best = t; a.split = c; }
-  }
+  a.split = plain_attn_split((int)sizeof(T), dm.d, (size_t)batch * dm.nkv * groups, longest);
   const dim3 grid(batch * a.split, dm.nkv, groups);
   const int nf_tiles = nc * 4 / (int)sizeof(T);
   hipError_t e = hipErrorInvalidValue;

@@ -69,6 +69,12 @@ def test_a_step_opens_alike_whatever_the_alignment(shape, batch, dtype):
     assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
 
 
+def update_is_near(got, ref, x, dtype):
+    """What a stage of small updates adds to its input x: besides the update's own error the output carries its rounding, up to
+    2^-8 of an element in bf16 (half a unit in the last of 8 bits)."""
+    return abs(got - ref).max() <= TOL[dtype] * abs(ref - x).max() + (2.0 ** -8 if dtype == "bf16" else 2.0 ** -24) * abs(ref).max()
+
+
 @pytest.mark.parametrize("batch", [1, 4, 5, 8, 9])
 @pytest.mark.parametrize("dtype,hidden", [("f32", 1100), ("f32", 2064), ("bf16", 2056), ("bf16", 4104)])
 def test_sixteen_waves_against_oracle(dtype, hidden, batch):
@@ -93,9 +99,28 @@ def test_sixteen_waves_against_oracle(dtype, hidden, batch):
             rows.copy_(to_dev(xd, dtype))
             out.append(gst.decode_step(rows))
             ref = ost.decode_step(xd)
-            # the update, which is small beside the input here: besides its own error it carries the rounding of the output, up to
-            # 2^-8 of an element in bf16
-            got, rounding = to_host(out[-1]), 2.0 ** -8 if dtype == "bf16" else 2.0 ** -24
-            assert abs(got - ref).max() <= TOL[dtype] * abs(ref - xd).max() + rounding * abs(ref).max(), (shift, s)
+            assert update_is_near(to_host(out[-1]), ref, xd, dtype), (shift, s)
         gst.destroy()
     assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [130, 160, 256])
+@pytest.mark.parametrize("batch,longest", [(1, 70), (3, 330), (20, 330), (33, 330)])
+def test_wide_heads_against_oracle(d, batch, longest, dtype):
+    """Heads of more than 128 features take workgroups of four waves, and shares of the keys from short contexts on; with 20
+    requests eight shares would be more workgroups than CUs, with 33 of them four."""
+    from paper_2511_14450_amd import binding
+    shp = synth.BlockShape(64, 10, 2, d, 96, dtype=dtype)
+    lens = [longest if b == 0 else 1 + (b * 37) % 50 for b in range(batch)]
+    layers = [synth.layer_weights(shp, 0, 47_300, sigma=0.05)]
+    x = synth.hidden_states(sum(lens), shp, 47_301)
+    ost = orc.Stage(shp, layers, batch, longest + 4, "f32")
+    gst = make_gpu_stage(shp, layers, batch, longest + 4, sum(lens), flags=binding.HYP_FLAG_PLAIN_KERNELS)
+    ost.prefill(x, lens)
+    gst.prefill(to_dev(x, dtype), lens)
+    for s in range(3):
+        xd = synth.hidden_states(batch, shp, 47_302 + s)
+        ref, got = ost.decode_step(xd), to_host(gst.decode_step(to_dev(xd, dtype)))
+        assert update_is_near(got, ref, xd, dtype), s
+    gst.destroy()
