@@ -43,8 +43,7 @@ namespace {
 //              step ran in an earlier kernel)
 // ----------------------------------------------------------------------------
 // A wave keeps 10 weight loads of 1 KiB in flight (a window of 5 k-tiles of two row blocks, or 10 of
-// one); 16 such waves per CU (124 registers) measured better than 20 loads in flight at 12 waves.
-constexpr int kWavesPerCu = 16;  // 4 per SIMD: NW waves per workgroup, kWavesPerCu / NW workgroups per CU
+// one); 16 such waves per CU (124 registers, kWavesPerCu) measured better than 20 loads in flight at 12 waves.
 constexpr int kBeginRows = 64;  // rows per workgroup of the kernel that opens a step (and per sum of squares it writes)
 
 struct DecGemvParams {
@@ -73,8 +72,8 @@ struct DecGemvParams {
   int *lens_advance;  // DEC_FINAL: cached lengths to bump once the step's last kernel finishes
 };
 
-// FBW row blocks of 32 per workgroup: 2 where the epilogue pairs rows of two blocks (gate and up) and for long K; 1 for QKV,
-// whose RoPE partners lie in one block, and for the residual epilogues at short K, where 32-row workgroups with
+// FBW row blocks of 32 per workgroup: 2 where the epilogue pairs rows of two blocks (gate and up) and for long K; 1 or 2 for QKV,
+// whose RoPE partners lie in one block; 1 for the residual epilogues at short K, where 32-row workgroups with
 // a 10-tile window give as many waves with as much in flight as two slices of 64-row workgroups
 // would, without partial sums, counter and gather at the end.
 // CLS (a hyp_kernel_class_t) only gives each GEMM of a block its own kernel name in a trace.
@@ -507,55 +506,6 @@ __global__ void k_fill_zero(uint4 *p, size_t n16) {
 
 }  // namespace
 
-// How one skinny GEMM of a decode step is cut into workgroups.
-//   fbw     32-row blocks per workgroup: 2 where the epilogue pairs rows of two blocks (gate and up) and
-//           for long K; 1 for QKV and the residual GEMMs at short K, which then run as unsplit 4-wave
-//           workgroups with a 10-tile window
-//   nw      waves per workgroup; they share the k-tiles of the workgroup's K slice.  8 for the
-//           64-row workgroups: the same waves in flight with half the K slices of 4-wave workgroups
-//   ksplit  K slices across workgroups (partial sums in memory, the last to arrive adds them up):
-//           the fewest that put a wave on every slot of the chip (16 per CU), as long as a wave
-//           keeps at least 20 k-tiles (four windows of the streaming loop) and the fp32 partial sums
-//           (written and read once per slice and token) stay a few percent of the weight bytes.
-//           Phi-3-medium shapes: gate/up unsplit (560 workgroups), down 7 slices;
-//           measured against every other admissible cut of each GEMM at batch 8 and 32, this rule's
-//           choices were the fastest or within 1 % of it.
-GemvPlan mfma_gemv_plan(int cls, int N, int K, int batch) {
-  GemvPlan g;
-  const int KT = K / 16;
-  // QKV: a workgroup per 32 rows, which hold whole RoPE pairs; no partial sums, counter and gather.  (Two blocks of 32 in two
-  // slices before: Phi-3 16.2 -> 14.7 us at batch 1, Llama3-8B 16.2 -> 15.0 at batch 8.  8 waves: 0.0 - 1.3 % of a block slower.)
-  if (cls == HYP_K_GEMV_QKV) {
-    g.fbw = 1; g.nw = 4; g.ksplit = 1;
-    return g;
-  }
-  if ((cls == HYP_K_GEMV_O || cls == HYP_K_GEMV_DOWN) && KT / 4 <= 112 && KT % 4 == 0) {
-    g.fbw = 1; g.nw = 4; g.ksplit = 1;
-    return g;
-  }
-  g.fbw = 2; g.nw = 8; g.ksplit = 1;
-  if (KT % g.nw != 0) g.nw = 4;
-  const int groups = N / 64, wave_slots = kWavesPerCu * 256;
-  int cap = (int)(0.025 * K / (batch > 0 ? batch : 1));
-  if (cap < 1) cap = 1;
-  for (int ks = 1; ks <= 64 && ks <= cap; ++ks) {
-    if (KT % (ks * g.nw) != 0 || KT / (ks * g.nw) < 20) continue;
-    g.ksplit = ks;
-    if (groups * ks * g.nw >= wave_slots) break;
-  }
-  // More workgroups than fit the chip at once, but fewer than two rounds: the groups beyond the first round
-  // are cut finer, for what would otherwise be a thin second round of long workgroups.  A CU serves its waves'
-  // loads oldest first, so the late workgroups stream last whatever their size: they should be many (bytes
-  // in flight on every CU to the end) and short.  Four times finer where a wave keeps two windows of
-  // the streaming loop (gate/up: 62.3 -> 59.6 us), else twice.
-  const int units = groups * g.ksplit, slots = wave_slots / g.nw, tpw = KT / (g.ksplit * g.nw);
-  if (units > slots && units < 2 * slots) {
-    if (tpw % 4 == 0 && tpw / 4 >= 10) g.tail = 4;
-    else if (tpw % 2 == 0 && tpw / 2 >= 10) g.tail = 2;
-  }
-  return g;
-}
-
 // Row groups [0, groups1) run as plan.ksplit workgroups each, the rest (beyond the first round of the launch, if the plan
 // cuts those finer) as plan.ksplit * tail.
 static void gemv_cut(const GemvPlan &g, int N, int K, int *groups1, int *tail) {
@@ -572,10 +522,11 @@ size_t mfma_gemv_partial_floats(const GemvPlan &g, int N, int K) {
   return (size_t)g.ksplit * 32 * N + (size_t)g.ksplit * tail * 32 * fine_rows;
 }
 
-// LDS of the gain beside 64 KiB and less of sums
+// LDS of the gain beside 68 KiB and less of sums (64 rows of 32 tokens in eight waves)
 constexpr int kMaxGainBytes = 65536;
-bool mfma_dec_opens(const bf16_t *hidden_in, int H, int N) {
-  return (uintptr_t)hidden_in % 16 == 0 && sizeof(bf16_t) * H <= (size_t)kMaxGainBytes && N / 32 >= H / 64;  // a workgroup per 64 features
+bool mfma_dec_opens(const bf16_t *hidden_in, int H, int N, const GemvPlan &g) {
+  // a workgroup per 64 features
+  return (uintptr_t)hidden_in % 16 == 0 && sizeof(bf16_t) * H <= (size_t)kMaxGainBytes && N / (32 * g.fbw) >= H / 64;
 }
 
 bool mfma_gemv_counts(const GemvPlan &g, int N, int K) {
@@ -585,7 +536,9 @@ bool mfma_gemv_counts(const GemvPlan &g, int N, int K) {
 }
 
 // the (epilogue, blocks per workgroup, waves per workgroup, class) combinations a plan may ask for
-#define HYP_GEMV_QKV(X) X(DEC_QKV, 1, 4, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 1, 4, HYP_K_GEMV_QKV)
+#define HYP_GEMV_QKV(X)                                                                                  \
+  X(DEC_QKV, 1, 4, HYP_K_GEMV_QKV) X(DEC_QKV, 1, 8, HYP_K_GEMV_QKV) X(DEC_QKV, 2, 8, HYP_K_GEMV_QKV)     \
+  X(DEC_QKV_OPEN, 1, 4, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 1, 8, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 2, 8, HYP_K_GEMV_QKV)
 #define HYP_GEMV_VARIANTS(X, NW)                                                                         \
   X(DEC_SWIGLU, 2, NW, HYP_K_GEMV_GATEUP)                                                                \
   X(DEC_RESID, 1, NW, HYP_K_GEMV_O) X(DEC_RESID, 2, NW, HYP_K_GEMV_O)                                    \
@@ -625,7 +578,7 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
   dim3 grid(p.groups1 * ksplit + (groups - p.groups1) * p.tail * ksplit);
   // the waves' sums of the live tokens, and the norm's gain
   const size_t lds = sizeof(float) * nw * a.batch * (fbw * 32 + 4) + (epi == DEC_QKV_OPEN ? sizeof(bf16_t) * a.H : 0);
-  if (epi == DEC_QKV_OPEN && (fbw != 1 || a.K != a.H || !mfma_dec_opens(a.x, a.H, a.N))) return hipErrorInvalidValue;
+  if (epi == DEC_QKV_OPEN && (a.K != a.H || !mfma_dec_opens(a.x, a.H, a.N, a.plan))) return hipErrorInvalidValue;
   bool launched = false;
 #define X(EPI, FBW, NW, CLS)                                                 \
   if (!launched && epi == EPI && fbw == FBW && nw == NW && cls == CLS) {      \

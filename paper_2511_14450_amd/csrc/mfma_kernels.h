@@ -1,6 +1,7 @@
 // Host-side launchers of the MFMA path (bf16 stages with head_dim 128).
 #pragma once
 
+#include "launch_rules.h"
 #include "mfma_common.h"
 
 namespace hyp {
@@ -80,9 +81,6 @@ enum { DEC_QKV = 0, DEC_SWIGLU = 1, DEC_RESID = 2, DEC_FINAL = 3, DEC_QKV_OPEN =
 // One skinny GEMM of a decode step, sum[token, n] = W[n, :] . x[token, :], with
 // its consumer fused in (see k_dec_gemv).  Fields a given epilogue does not use
 // stay null / 0.
-// how a skinny GEMM is cut into workgroups (see mfma_gemv_plan)
-struct GemvPlan { int fbw = 2, nw = 4, ksplit = 1, tail = 1; };  // tail: how many times finer the row groups of a thin second round are cut
-
 struct DecGemv {
   const bf16_t *W = nullptr, *x = nullptr;  // P(N, K), P(32, K)
   float *partial = nullptr;                 // partial sums of the K slices, mfma_gemv_partial_floats(plan, N, K) floats
@@ -109,12 +107,11 @@ struct DecGemv {
   int *lens_advance = nullptr;  // DEC_FINAL: lengths to increment at the end of the step
 };
 hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s);  // cls: as for mfma_gemm
-GemvPlan mfma_gemv_plan(int cls, int N, int K, int batch);  // cls: HYP_K_GEMV_*
 size_t mfma_gemv_partial_floats(const GemvPlan &plan, int N, int K);
 bool mfma_gemv_counts(const GemvPlan &plan, int N, int K);  // whether the GEMM uses its arrival counters
 hipError_t mfma_gemv_init();  // kernel attributes, once per process and device
 // whether DEC_QKV_OPEN takes these rows (x = hidden_in, gain, xres, H set) instead of mfma_dec_begin and DEC_QKV
-bool mfma_dec_opens(const bf16_t *hidden_in, int H, int N);
+bool mfma_dec_opens(const bf16_t *hidden_in, int H, int N, const GemvPlan &plan);
 // x = hidden_in ; xres = x ; y' = x * gain -> P(32, H) ; ssq_out[H/64][32]
 hipError_t mfma_dec_begin(const bf16_t *hidden_in, float *xres, const bf16_t *gain, bf16_t *y_out, float *ssq_out,
                           int H, int batch, hipStream_t s);

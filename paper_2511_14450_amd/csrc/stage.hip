@@ -508,7 +508,7 @@ hyp_status_t decode_step_mfma(hyp_stage *st, hipStream_t s, const DecScratch &sc
   // what reads the caller's rows: the first block's QKV contraction, behind a kernel of its own where they are not aligned
   if (begin) {
     DecGemv a = qkv(0);
-    const bool opens = mfma_dec_opens((const bf16_t *)hidden_in, d.H, a.N);
+    const bool opens = mfma_dec_opens((const bf16_t *)hidden_in, d.H, a.N, a.plan);
     if (opens) { a.x = (const bf16_t *)hidden_in; a.gain = at<bf16_t>(st, L.layers[0].g1); a.ssq_in = nullptr; a.n_ssq = 0; }
     else
       PROF(st, HYP_K_ADD_NORM, mfma_dec_begin((const bf16_t *)hidden_in, base.xres, at<bf16_t>(st, L.layers[0].g1), y, ssq, d.H, st->batch, s));

@@ -12,6 +12,11 @@ int main() {
       size_t pairs;
       if (scanf("%d %d %zu %d", &esize, &d, &pairs, &longest) != 4) return 1;
       printf("%d\n", hyp::plain_attn_split(esize, d, pairs, longest));
+    } else if (!strcmp(what, "gemv")) {
+      int cls, N, K, batch;
+      if (scanf("%d %d %d %d", &cls, &N, &K, &batch) != 4) return 1;
+      const hyp::GemvPlan g = hyp::mfma_gemv_plan(cls, N, K, batch);
+      printf("%d %d %d %d\n", g.fbw, g.nw, g.ksplit, g.tail);
     } else {
       return 1;
     }

@@ -15,9 +15,22 @@ TOL = 2e-2
 @pytest.mark.parametrize("batch", [1, 5, 32])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_opening_against_oracle(hidden, heads, batch, shift):
-    import torch
     # 2816 wide with 10 heads in all: fewer QKV workgroups than groups of 64 features, so the opening kernel again
-    shape = synth.BlockShape(hidden=hidden, n_q_heads=heads, n_kv_heads=2, head_dim=128, ffn_dim=256, dtype="bf16")
+    check_opening(hidden, heads, 2, batch, shift)
+
+
+@pytest.mark.parametrize("hidden,heads,kv_heads", [(256, 64, 16), (1536, 48, 12), (5376, 18, 6)])
+@pytest.mark.parametrize("batch", [1, 17, 32])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_wider_workgroups_against_oracle(hidden, heads, kv_heads, batch, shift):
+    # more than 256 blocks of 32 QKV rows: two blocks to a workgroup of eight waves (with 256 features less than a window of
+    # k-tiles a wave); K beyond 5120: eight waves to one block
+    check_opening(hidden, heads, kv_heads, batch, shift)
+
+
+def check_opening(hidden, heads, kv_heads, batch, shift):
+    import torch
+    shape = synth.BlockShape(hidden=hidden, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=128, ffn_dim=256, dtype="bf16")
     # Queries and keys of spread s = sigma sqrt(hidden) have scores of spread s^2, and rounding them to bf16 (2^-9 each) moves a
     # score by 2^-8 of itself: at 4 s^2 (the largest of a few) s = 1 keeps that below 4 / 256 = 1.6e-2 of a probability, within TOL
     # (0.05 at 2816 wide, s = 2.7, gives 0.11: the outputs are off by up to 4.5e-2, by the kernels of either opening).

@@ -54,3 +54,33 @@ def test_attention_split_stays_inside_its_scratch(ask):
     cases = [(rng.choice((2, 4)), 2 * rng.randint(1, 128), int(2 ** rng.uniform(0, 16)), int(2 ** rng.uniform(0, 20)) - 1) for _ in range(2000)]
     for (split,), (e, d, pairs, longest) in zip(ask([f"attn {e} {d} {p} {n}" for e, d, p, n in cases]), cases):
         assert split in (1, 2, 4, 8) and (split == 1 or pairs * split <= 512), (e, d, pairs, longest, split)
+
+
+# ---------------------------------------------------------------- skinny GEMMs of a decode step
+QKV, O, GATEUP, DOWN = 6, 9, 10, 12  # HYP_K_GEMV_*
+# rows, K, batch: us a block with QKV in (32-row blocks, waves) to a workgroup, unsplit
+QKV_PLANS = [
+    (12288, 8192, 1, {(1, 4): 92.5, (1, 8): 91.8, (2, 8): 87.8}), (12288, 8192, 32, {(1, 4): 123.7, (1, 8): 121.1, (2, 8): 112.2}),
+    (12288, 4096, 1, {(1, 4): 55.3, (1, 8): 58.2, (2, 8): 54.2}), (12288, 4096, 32, {(1, 4): 84.0, (1, 8): 84.7, (2, 8): 79.1}),
+    (9216, 3072, 8, {(1, 4): 47.8, (1, 8): 48.1, (2, 8): 45.8}), (12288, 1024, 8, {(1, 4): 41.6, (1, 8): 42.0, (2, 8): 41.5}),
+    (15360, 5120, 32, {(1, 4): 99.0, (1, 8): 99.2, (2, 8): 92.0}), (7168, 5120, 8, {(1, 4): 52.0, (1, 8): 51.8, (2, 8): 56.2}),
+    (7168, 5120, 32, {(1, 4): 72.1, (1, 8): 72.4, (2, 8): 78.9}), (6144, 4096, 1, {(1, 4): 47.0, (1, 8): 48.5, (2, 8): 51.1}),
+    (6144, 8192, 1, {(1, 4): 63.7, (1, 8): 61.5, (2, 8): 69.7}), (6144, 8192, 32, {(1, 4): 86.0, (1, 8): 84.1, (2, 8): 93.4}),
+    (1536, 8192, 8, {(1, 4): 56.0, (1, 8): 53.5, (2, 8): 62.5}), (1536, 512, 8, {(1, 4): 22.6, (1, 8): 22.6, (2, 8): 23.1}),
+    (6144, 7168, 16, {(1, 4): 64.4, (1, 8): 63.7, (2, 8): 71.8}), (6144, 2048, 1, {(1, 4): 36.7, (1, 8): 36.8, (2, 8): 38.7}),
+]
+
+
+def test_qkv_plans_are_near_the_best_measured(ask):
+    for (fbw, nw, ksplit, tail), (N, K, batch, times) in zip(ask([f"gemv {QKV} {N} {K} {b}" for N, K, b, _ in QKV_PLANS]), QKV_PLANS):
+        assert (ksplit, tail) == (1, 1)
+        assert times[fbw, nw] <= 1.01 * min(times.values()), (N, K, batch, fbw, nw)
+
+
+def test_plans_deal_all_of_k_and_all_rows(ask):
+    rng = random.Random(2)
+    cases = [(rng.choice((QKV, O, GATEUP, DOWN)), 256 * rng.randint(1, 150), 256 * rng.randint(1, 80), rng.randint(1, 32)) for _ in range(3000)]
+    built = {QKV: {(1, 4), (1, 8), (2, 8)}, O: {(1, 4), (2, 8)}, GATEUP: {(2, 8)}, DOWN: {(1, 4), (2, 8)}}
+    for (fbw, nw, ksplit, tail), (cls, N, K, batch) in zip(ask([f"gemv {c} {n} {k} {b}" for c, n, k, b in cases]), cases):
+        assert (fbw, nw) in built[cls], (cls, N, K, batch, fbw, nw)
+        assert N % (32 * fbw) == 0 and K // 16 % (nw * ksplit) == 0 and K // 16 // (nw * ksplit) % tail == 0, (cls, N, K, batch)
