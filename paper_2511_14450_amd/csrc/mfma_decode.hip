@@ -450,7 +450,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
   }
 }
 
-// first kernel of a decode step whose rows are not aligned to 16 bytes (else DEC_QKV_OPEN): x = hidden_in ; xres = x ; y' = x * gain ; ssq
+// first kernel of a decode step that does not open with its QKV contraction (mfma_dec_opens): x = hidden_in ; xres = x ; y' = x * gain ; ssq
 // grid H / 64, 512 threads: a wave per token, a lane per feature, the sum of squares over the wave's lanes.  (Added
 // thread by thread through LDS a request of 16 chat prompts took 0.4 % longer; in a trace the kernel sits at the launch
 // floor, 4.7 us, either way.)
@@ -478,6 +478,12 @@ __global__ void __launch_bounds__(kBeginWaves * 64) k_dec_begin(const bf16_t *__
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
     if (lane == 0) ssq_out[blockIdx.x * 32 + b] = ss;
   }
+}
+
+// rows of a step that are not aligned to 16 bytes, next to each other and aligned, as DEC_QKV_OPEN reads them
+__global__ void __launch_bounds__(256) k_dec_align(const bf16_t *__restrict__ in, bf16_t *__restrict__ out, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) out[i] = in[i];
 }
 
 __global__ void k_export_kv(const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc, CacheGeom geom,
@@ -524,9 +530,8 @@ size_t mfma_gemv_partial_floats(const GemvPlan &g, int N, int K) {
 
 // LDS of the gain beside 68 KiB and less of sums (64 rows of 32 tokens in eight waves)
 constexpr int kMaxGainBytes = 65536;
-bool mfma_dec_opens(const bf16_t *hidden_in, int H, int N, const GemvPlan &g) {
-  // a workgroup per 64 features
-  return (uintptr_t)hidden_in % 16 == 0 && sizeof(bf16_t) * H <= (size_t)kMaxGainBytes && N / (32 * g.fbw) >= H / 64;
+bool mfma_dec_opens(int H, int N, const GemvPlan &g) {
+  return sizeof(bf16_t) * H <= (size_t)kMaxGainBytes && N / (32 * g.fbw) >= H / 64;  // a workgroup per 64 features
 }
 
 bool mfma_gemv_counts(const GemvPlan &g, int N, int K) {
@@ -578,7 +583,7 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
   dim3 grid(p.groups1 * ksplit + (groups - p.groups1) * p.tail * ksplit);
   // the waves' sums of the live tokens, and the norm's gain
   const size_t lds = sizeof(float) * nw * a.batch * (fbw * 32 + 4) + (epi == DEC_QKV_OPEN ? sizeof(bf16_t) * a.H : 0);
-  if (epi == DEC_QKV_OPEN && (a.K != a.H || !mfma_dec_opens(a.x, a.H, a.N, a.plan))) return hipErrorInvalidValue;
+  if (epi == DEC_QKV_OPEN && (a.K != a.H || (uintptr_t)a.x % 16 != 0 || !mfma_dec_opens(a.H, a.N, a.plan))) return hipErrorInvalidValue;
   bool launched = false;
 #define X(EPI, FBW, NW, CLS)                                                 \
   if (!launched && epi == EPI && fbw == FBW && nw == NW && cls == CLS) {      \
@@ -597,6 +602,12 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
 hipError_t mfma_dec_begin(const bf16_t *hidden_in, float *xres, const bf16_t *gain, bf16_t *y_out, float *ssq_out,
                           int H, int batch, hipStream_t s) {
   k_dec_begin<<<H / kBeginRows, kBeginWaves * 64, 0, s>>>(hidden_in, xres, gain, y_out, ssq_out, H, batch);
+  return hipGetLastError();
+}
+
+hipError_t mfma_dec_align(const bf16_t *hidden_in, bf16_t *out, int H, int batch, hipStream_t s) {
+  const int n = H * batch;
+  k_dec_align<<<(n + 255) / 256, 256, 0, s>>>(hidden_in, out, n);
   return hipGetLastError();
 }
 

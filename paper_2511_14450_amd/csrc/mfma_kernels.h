@@ -110,8 +110,11 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s);  //
 size_t mfma_gemv_partial_floats(const GemvPlan &plan, int N, int K);
 bool mfma_gemv_counts(const GemvPlan &plan, int N, int K);  // whether the GEMM uses its arrival counters
 hipError_t mfma_gemv_init();  // kernel attributes, once per process and device
-// whether DEC_QKV_OPEN takes these rows (x = hidden_in, gain, xres, H set) instead of mfma_dec_begin and DEC_QKV
-bool mfma_dec_opens(const bf16_t *hidden_in, int H, int N, const GemvPlan &plan);
+// whether a stage's steps open with DEC_QKV_OPEN (x = the rows, aligned to 16 bytes; gain, xres, H set) instead of
+// mfma_dec_begin and DEC_QKV.  The rows' address has no say in it: where they are not aligned they are copied first, so that
+// the bits of a step, whose sums of squares the two openings group differently, do not depend on it.
+bool mfma_dec_opens(int H, int N, const GemvPlan &plan);
+hipError_t mfma_dec_align(const bf16_t *hidden_in, bf16_t *out, int H, int batch, hipStream_t s);
 // x = hidden_in ; xres = x ; y' = x * gain -> P(32, H) ; ssq_out[H/64][32]
 hipError_t mfma_dec_begin(const bf16_t *hidden_in, float *xres, const bf16_t *gain, bf16_t *y_out, float *ssq_out,
                           int H, int batch, hipStream_t s);

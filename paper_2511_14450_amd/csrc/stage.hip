@@ -505,13 +505,19 @@ hyp_status_t decode_step_mfma(hyp_stage *st, hipStream_t s, const DecScratch &sc
     a.geom = geom; a.nq = d.nq; a.nkv = d.nkv;
     return a;
   };
-  // what reads the caller's rows: the first block's QKV contraction, behind a kernel of its own where they are not aligned
+  // what reads the caller's rows: the first block's QKV contraction (from a copy where they are not aligned, in the room that the
+  // first residual epilogue writes), or a kernel of its own in front of it
   if (begin) {
     DecGemv a = qkv(0);
-    const bool opens = mfma_dec_opens((const bf16_t *)hidden_in, d.H, a.N, a.plan);
-    if (opens) { a.x = (const bf16_t *)hidden_in; a.gain = at<bf16_t>(st, L.layers[0].g1); a.ssq_in = nullptr; a.n_ssq = 0; }
+    const bf16_t *rows = (const bf16_t *)hidden_in;
+    const bool opens = mfma_dec_opens(d.H, a.N, a.plan);
+    if (opens && (uintptr_t)rows % 16 != 0) {
+      PROF(st, HYP_K_ADD_NORM, mfma_dec_align(rows, y, d.H, st->batch, s));
+      rows = y;
+    }
+    if (opens) { a.x = rows; a.gain = at<bf16_t>(st, L.layers[0].g1); a.ssq_in = nullptr; a.n_ssq = 0; }
     else
-      PROF(st, HYP_K_ADD_NORM, mfma_dec_begin((const bf16_t *)hidden_in, base.xres, at<bf16_t>(st, L.layers[0].g1), y, ssq, d.H, st->batch, s));
+      PROF(st, HYP_K_ADD_NORM, mfma_dec_begin(rows, base.xres, at<bf16_t>(st, L.layers[0].g1), y, ssq, d.H, st->batch, s));
     PROF(st, HYP_K_GEMV_QKV, mfma_dec_gemv(opens ? DEC_QKV_OPEN : DEC_QKV, HYP_K_GEMV_QKV, a, s));
   }
   for (int l = 0; layers && l < st->n_layers; ++l) {

@@ -1,6 +1,6 @@
-"""How a bf16 decode step opens: rows aligned to 16 bytes go straight into the first QKV contraction, others through a kernel of
-their own; widths whose waves keep less than one window of k-tiles, several, and with a rest; against the oracle, launched,
-replayed and without allocation (Sec. III-A block, cached decode)."""
+"""How a bf16 decode step opens: with its first QKV contraction, which rows that are not aligned to 16 bytes reach through a
+copy, or, in stages of few QKV rows, with a kernel of its own; widths whose waves keep less than one window of k-tiles,
+several, and with a rest; against the oracle, launched, replayed and without allocation (Sec. III-A block, cached decode)."""
 import pytest
 
 from oracle import hyp_oracle as orc
@@ -52,3 +52,27 @@ def check_opening(hidden, heads, kv_heads, batch, shift):
         ref = ost.decode_step(xd)
         assert max(rel_err(to_host(got), ref), rel_err(to_host(got) - xd, ref - xd)) <= TOL, s
     gst.destroy()
+
+
+@pytest.mark.parametrize("hidden,heads,kv_heads", [(256, 2, 2), (1280, 6, 2), (256, 64, 16), (2816, 6, 2)])
+@pytest.mark.parametrize("batch", [1, 5, 32])
+def test_bits_do_not_depend_on_the_address_of_the_rows(hidden, heads, kv_heads, batch):
+    import torch
+    shape = synth.BlockShape(hidden=hidden, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=128, ffn_dim=256, dtype="bf16")
+    layers = [synth.layer_weights(shape, l, 59_100, sigma=hidden ** -0.5) for l in range(2)]
+    x = to_dev(synth.hidden_states(batch * 2, shape, 59_101), "bf16")
+    seen = []
+    for shift in (0, 1, 4):
+        gst = make_gpu_stage(shape, layers, batch, 8, batch * 2)
+        gst.prefill(x, [2] * batch)
+        room, got = torch.zeros(batch * hidden + 8, dtype=torch.bfloat16, device="cuda"), []
+        out = torch.empty((batch, hidden), dtype=torch.bfloat16, device="cuda")
+        rows = room[shift:shift + batch * hidden].view(batch, hidden)
+        for s in range(4):
+            rows.copy_(to_dev(synth.hidden_states(batch, shape, 59_102 + s), "bf16"))
+            got.append((gst.decode_step_noalloc if s == 3 else gst.decode_step)(rows, out).clone())
+        got += list(gst.export_kv(1, batch - 1))
+        gst.destroy()
+        seen.append(got)
+    for other in seen[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(seen[0], other))
