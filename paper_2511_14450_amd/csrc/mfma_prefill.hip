@@ -635,10 +635,11 @@ __global__ void __launch_bounds__(F::WF * F::WT * 64) k_gemm(GemmParams p) {
       if (tb >= p.tok_blocks) continue;
 #pragma unroll
       for (int th = 0; th < 2; ++th) {
-        // The lane's places come from an opaque copy: worked out once for all token halves and kept, they took the wide form to 256
-        // registers, four of them spilled.  242 now (Phi-3, 2048 rows: O projection 126 -> 122 us; 65536 rows: down 8458 -> 8427).
+        // The wide form takes the lane's places from an opaque copy: worked out once for all token halves and kept, they took it to
+        // 256 registers, four of them spilled.  242 now (Phi-3, 2048 rows: O projection 126 -> 122 us; 65536 rows: down 8458 ->
+        // 8427).  The others have the registers, and O of 1024 x 1024, 553 rows, takes 14.0 us with them kept, 14.6 without.
         int at = lane;
-        asm volatile("" : "+v"(at));
+        if constexpr (kWide) asm volatile("" : "+v"(at));
         const int q4 = (at >> 4) * 4, row = tb * 32 + 16 * th + (at & 15);
         const bool live = p.row_ext[row] >= 0;
         float ss = 0.f;
