@@ -107,4 +107,138 @@ inline GemvPlan mfma_gemv_plan(int cls, int N, int K, int batch) {
   return g;
 }
 
+// ----------------------------------------------------------------------------
+// Prefill GEMMs: the form, and the slices of the K loop.
+// ----------------------------------------------------------------------------
+struct GemmShape { int tok_blocks, feat_blocks, lds_stages; };  // 32-row blocks of tokens and features of a tile, stages in LDS
+constexpr GemmShape kGemmWide = {8, 8, 4}, kGemm64 = {2, 4, 6}, kGemm128 = {4, 4, 4};
+constexpr int kGemmStageTiles = 2;     // k-tiles of 16 in a stage
+constexpr int kGemmSplitUnits = 512;   // most (tile, slice) pairs of a split GEMM
+constexpr int kGemmShortMaxTiles = 511;  // short forms: tiles that may be split, and counters
+// Wide GEMMs of two and a half rounds of 256 tiles or more are never split: a request that fills them alone then has the same
+// bits in any batch, and what splitting the last, partial round saves falls with the number of rounds (Phi-3 block: gate/up 210
+// -> 155 us at 384 rows = 280 tiles, 325 -> 292 at 1024 = 560).
+constexpr int kGemmSplitMaxTiles = 639;
+
+struct GemmCut {
+  int form;               // tokens of a tile: 64, 128, 256
+  int tiles_t, n_tiles;   // token tiles, tiles
+  // tiles from `first` on have their K loop split over `ksplit` workgroups each; finish: a second kernel adds the slices up
+  int first, ksplit;
+  bool finish;
+  int n_static, pool_wgs;     // many rounds: tiles assigned by position, workgroups that draw the rest
+  int first_grid, rest_grid;  // workgroups of unsplit tiles, of slices
+};
+
+// A K loop in slices costs their partial tiles, written and read at 5 TB/s together, and the launch that adds them up.
+inline double gemm_slice_us(int tiles, int c, int tok_blocks, int feat_blocks) {
+  return c == 1 ? 0.0 : (double)tiles * c * tok_blocks * feat_blocks * 4096.0 / 2.5e6 + 5.0;
+}
+
+// Tiles of 128 features x 64 tokens, several of them along the tokens, their K loop in c slices: a stage takes 0.235 us while every
+// workgroup has a CU of its own and 0.325 with two to a CU, which is all that fit; a further round takes 2.5 us to begin and end.
+// Slices cost the second launch (1.5 us more with two to a CU), their partial tiles, most of which stay in the caches (10 TB/s
+// written and read), and a second round trip of the sums beyond eight.
+inline double gemm64_us(int tiles, int stages, int c) {
+  const int units = tiles * c, rounds = units / (2 * kCus), rest = units % (2 * kCus);
+  const double stage_us = rounds * 0.325 + (rest == 0 ? 0.0 : rest <= kCus ? 0.235 : 0.325);
+  double us = 7.8 + 2.5 * (rounds - (rest == 0)) + (stages + c - 1) / c * stage_us;
+  if (c > 1) us += 3.0 + (units > kCus ? 1.5 : 0.0) + units * (double)(kGemm64.tok_blocks * kGemm64.feat_blocks) * 4096.0 / 5.0e6 + (c > 8 ? 1.0 : 0.0);
+  return us;
+}
+inline int gemm64_split(int tiles, int stages) {
+  int split = 1;
+  double best = 0.97 * gemm64_us(tiles, stages, 1);  // a split has to win clearly
+  for (int c = 2; c <= 32 && tiles * c <= kGemmSplitUnits && stages / c >= 2 * kGemm64.lds_stages; ++c) {
+    const double t = gemm64_us(tiles, stages, c);
+    if (t < best) { best = t; split = c; }
+  }
+  return split;
+}
+
+// rows % 32 == 0, N % 256 == 0, K % 32 == 0; swiglu: the gate/up GEMM, whose epilogue stores half as much and reads nothing
+inline GemmCut mfma_gemm_cut(int rows, int N, int K, bool swiglu) {
+  const int tok_blocks = rows / 32, feat_blocks = N / 32, stages = K / 16 / kGemmStageTiles;
+  GemmCut g = {};
+  // The wide form: whole rounds of one tile per CU, then the rest, in as many rounds as its slices take.  Slices are whole
+  // numbers of stages, at least two rounds through the LDS buffers.
+  const GemmShape wide = kGemmWide;
+  const int wide_tiles = (tok_blocks + wide.tok_blocks - 1) / wide.tok_blocks * (feat_blocks / wide.feat_blocks), wide_rest = wide_tiles % kCus;
+  const double tile_us = K * 0.020, start_us = 4.0;  // a 256 x 256 tile on one CU, whatever the others do (K = 5120: 105 us)
+  int wide_split = 1;
+  if (wide_tiles <= kGemmSplitMaxTiles) {
+    double best = 0.95 * (tile_us + start_us);  // a split has to win clearly
+    for (int c = 2; c <= 32 && wide_rest * c <= kGemmSplitUnits && wide_rest > 0 && stages / c >= 2 * wide.lds_stages; ++c) {
+      const int rounds = (wide_rest * c + kCus - 1) / kCus;
+      const double t = rounds * (tile_us / c + start_us) + gemm_slice_us(wide_rest, c, std::min(tok_blocks, wide.tok_blocks), wide.feat_blocks);
+      if (t < best) { best = t; wide_split = c; }
+    }
+  }
+  // Which form?  Up to 128 tokens the weights' streaming time counts, not the products (see GemmForm): one token tile.  Beyond, a
+  // GEMM of few tiles is bound by the latency of a stage and by its epilogue, and takes tiles of 128 features x 64 tokens where
+  // those, in slices or not, come out ahead of the wide form, whose unsplit tiles end in a long epilogue at one workgroup a CU
+  // and whose partial tiles stay in the caches, too (12 TB/s).  (512 wide, 553 rows: QKV 26.7 -> 12.3 us, gate/up 18.8 -> 10.9;
+  // 2048 x 2048, 200 rows: O 20.7 -> 16.6 in 4 slices.  576 tiles of gate/up, K = 2048: 47.2 against 42.7 in the wide form.  Of
+  // 484 GEMMs of 256 - 5120 wide layers and 160 - 3500 rows this picks one that is more than 3 % from the better form.)
+  g.form = 256;
+  const int tiles64 = (tok_blocks + kGemm64.tok_blocks - 1) / kGemm64.tok_blocks * (feat_blocks / kGemm64.feat_blocks), split64 = gemm64_split(tiles64, stages);
+  if (tok_blocks <= kGemm128.tok_blocks) {
+    g.form = tok_blocks <= kGemm64.tok_blocks || 2.0 * N * K <= 16e6 ? 64 : 128;
+  } else {
+    const int rest_rounds = (wide_rest * wide_split + kCus - 1) / kCus;
+    double wide_us = wide_split > 1 && wide_rest == wide_tiles ? 4.0 : swiglu ? 2.0 : 9.0;  // the epilogue
+    wide_us += wide_tiles / kCus * (tile_us + start_us) + rest_rounds * (tile_us / wide_split + start_us);
+    if (wide_split > 1) wide_us += 5.0 + (double)wide_rest * wide_split * std::min(tok_blocks, wide.tok_blocks) * wide.feat_blocks * 4096.0 / 6.0e6;
+    if (gemm64_us(tiles64, stages, split64) < 0.95 * wide_us) g.form = 64;
+  }
+  const GemmShape shape = g.form == 64 ? kGemm64 : g.form == 128 ? kGemm128 : wide;
+  g.tiles_t = (tok_blocks + shape.tok_blocks - 1) / shape.tok_blocks;
+  g.n_tiles = g.tiles_t * (feat_blocks / shape.feat_blocks);
+  g.first = g.n_tiles; g.ksplit = 1; g.finish = true;
+  if (g.form < 256) {
+    if (g.tiles_t > 1) {
+      g.ksplit = split64;
+      if (split64 > 1) g.first = 0;
+    } else if (g.n_tiles <= kGemmShortMaxTiles) {
+      // One token tile, few tiles: the chip streams as much as its workgroups keep in flight over 1.5 us of latency, 6 TB/s at best,
+      // and a CU with one workgroup more than the others is waited for.  (64 rows, slices 10 -> 5: down 51 -> 43 us, O 25 ->
+      // 21; QKV 8 -> 4: 30 -> 26.)
+      const double in_flight = (shape.lds_stages - 1) * (double)shape.feat_blocks * kGemmStageTiles * 1024, bytes = 2.0 * N * K;
+      double best = 1e30;
+      for (int c = 1; c == 1 || (c <= 32 && g.n_tiles * c <= kGemmSplitUnits); ++c) {
+        if (c > 1 && stages / c < 2 * shape.lds_stages) continue;
+        const int units = g.n_tiles * c, per_cu = (units + kCus - 1) / kCus;
+        const double even = units <= kCus ? 1.0 : units / ((double)per_cu * kCus);
+        const double t = bytes / (std::min(6.0e6, units * in_flight / 1.5) * even) + gemm_slice_us(g.n_tiles, c, tok_blocks, shape.feat_blocks);
+        if (t < best) { best = t; g.ksplit = c; g.first = c > 1 ? 0 : g.n_tiles; }
+      }
+      // More tiles than CUs, unsplit: the ones beyond the first 256 (24 of gate/up's 280) would double a few CUs' work.
+      // They are split so that they spread over all CUs beside the others, and added up there.
+      const int rest = g.n_tiles - kCus;
+      if (g.ksplit == 1 && rest > 0)
+        for (int c = 16; c >= 2; --c)
+          if (stages / c >= 2 * shape.lds_stages && rest * c <= kCus) {
+            g.first = kCus; g.ksplit = c; g.finish = false;
+            break;
+          }
+    }
+  } else if (wide_split > 1) {
+    g.ksplit = wide_split; g.first = g.n_tiles - wide_rest;
+  }
+  g.first_grid = (g.first + 7) / 8 * 8;
+  g.rest_grid = ((g.n_tiles - g.first) * g.ksplit + 7) / 8 * 8;
+  // 64 rounds of 256 tiles or more: the last sixteenth of the rounds is drawn from a counter by twice as many
+  // workgroups as it has tiles, so that an XCD can take up to a quarter of it.  (Gate/up at 64 K tokens, 140 rounds:
+  // 2.3 % faster.  With 20 - 30 rounds the drawn tiles' lost L2 neighbourhood and the tile granularity cost more than
+  // the balance brings: down projection 1.7 % slower.)
+  if (g.form == 256 && g.n_tiles >= 64 * kCus) {
+    const int rounds = g.n_tiles / kCus, pool_rounds = (rounds + 8) / 16;
+    g.first = g.n_tiles; g.ksplit = 1; g.rest_grid = 0;
+    g.n_static = (rounds - pool_rounds) * kCus;
+    g.pool_wgs = (2 * (g.n_tiles - g.n_static) + 7) / 8 * 8;
+    g.first_grid = g.n_static + g.pool_wgs;
+  }
+  return g;
+}
+
 }  // namespace hyp

@@ -35,11 +35,6 @@ struct GemmEpilogue {
   unsigned *split_counters = nullptr;  // kGemmShortMaxTiles + 1, zero between launches
 };
 
-// Wide GEMMs of two and a half rounds of 256 tiles or more are never split: a request that fills them alone then has the same
-// bits in any batch, and what splitting the last, partial round saves falls with the number of rounds (Phi-3 block: gate/up 210
-// -> 155 us at 384 rows = 280 tiles, 325 -> 292 at 1024 = 560).
-constexpr int kGemmSplitMaxTiles = 639;
-constexpr int kGemmShortMaxTiles = 511;  // short forms: tiles that may be split, and counters
 size_t mfma_gemm_split_ws_bytes();
 
 // dst = P(N, K) of the row-permuted concatenation [src0; src1; src2]
@@ -57,7 +52,7 @@ hipError_t mfma_rstd(const float *ssq_part, float *rstd, const int *row_ext, int
 
 // whether a QKV or gate/up GEMM adds up the sums of squares of its rows itself (the short forms, and k_gemm_finish where all tiles
 // are split): the launch of mfma_rstd, 4 - 5 us, is saved
-bool mfma_gemm_adds_sums(int rows, int N, int K);
+bool mfma_gemm_adds_sums(int epi, int rows, int N, int K);
 hipError_t mfma_gemm_init();
 // out^T[N, rows] = W[N,K] X[rows,K]^T with the epilogue `epi`; rows % 32 == 0,
 // N % 256 == 0, K % 32 == 0, K >= 128

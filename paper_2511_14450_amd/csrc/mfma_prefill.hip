@@ -186,6 +186,8 @@ template <int WF_, int WT_, int TB_, int NST_> struct GemmForm {
 typedef GemmForm<4, 2, 4, 4> WideForm;
 typedef GemmForm<2, 2, 1, 6> Form64;
 typedef GemmForm<2, 2, 2, 4> Form128;
+template <typename F> constexpr bool is_shape(GemmShape s) { return F::XB == s.tok_blocks && F::NBK == s.feat_blocks && F::NST == s.lds_stages && KTS == kGemmStageTiles; }
+static_assert(is_shape<WideForm>(kGemmWide) && is_shape<Form64>(kGemm64) && is_shape<Form128>(kGemm128), "the rules know the forms' shapes");
 
 struct GemmParams {
   const bf16_t *X;   // P(T', K)
@@ -936,9 +938,6 @@ hipError_t mfma_rstd(const float *ssq_part, float *rstd, const int *row_ext, int
   return hipGetLastError();
 }
 
-constexpr int kGemmSplitCus = 256;    // workgroups that run at once (one per CU)
-constexpr int kGemmSplitUnits = 512;  // most (tile, slice) pairs of a split GEMM
-
 // largest scratch a split GEMM can use: kGemmSplitUnits partial tiles of 256 x 256 fp32
 size_t mfma_gemm_split_ws_bytes() { return (size_t)kGemmSplitUnits * (WideForm::WF * WideForm::WT) * (FB * WideForm::TB * 16 * 64) * sizeof(float); }
 
@@ -958,114 +957,27 @@ hipError_t mfma_gemm_init() {
   return e;
 }
 
-// How a GEMM is cut: its form (tokens of a tile: 64, 128, 256), and for the wide form the slices of the tiles beyond whole rounds
-struct GemmCut { int form, wide_split, wide_rest, wide_tiles; };
-
-// A K loop in slices costs their partial tiles, written and read at 5 TB/s together, and the launch that adds them up.
-static double slice_cost(int tiles, int c, int tok, int feat) { return c == 1 ? 0.0 : (double)tiles * c * tok * feat * 4096.0 / 2.5e6 + 5.0; }
-
-static GemmCut gemm_cut(int rows, int N, int K) {
-  constexpr int NST = WideForm::NST, XB = WideForm::XB, NBK = WideForm::NBK;
-  const int tok_blocks = rows / 32, feat_blocks = N / 32, stages = K / 16 / KTS;
-  // The wide form: whole rounds of one tile per CU, then the rest, in as many rounds as its slices take.  Slices are whole
-  // numbers of stages, at least two rounds through the LDS buffers.
-  const int wide_tiles = (tok_blocks + XB - 1) / XB * (feat_blocks / NBK), wide_rest = wide_tiles % kGemmSplitCus;
-  const double tile_us = K * 0.020, start_us = 4.0;  // a 256 x 256 tile on one CU, whatever the others do (K = 5120: 105 us)
-  int wide_split = 1;
-  double wide_us = wide_rest ? tile_us + start_us : 0.0;
-  if (wide_tiles <= kGemmSplitMaxTiles) {
-    double best = 0.95 * wide_us;  // a split has to win clearly
-    for (int c = 2; c <= 32 && wide_rest * c <= kGemmSplitUnits && wide_rest > 0 && stages / c >= 2 * NST; ++c) {
-      const int rounds = (wide_rest * c + kGemmSplitCus - 1) / kGemmSplitCus;
-      const double t = rounds * (tile_us / c + start_us) + slice_cost(wide_rest, c, std::min(tok_blocks, XB), NBK);
-      if (t < best) { best = wide_us = t; wide_split = c; }
-    }
-  }
-  wide_us += wide_tiles / kGemmSplitCus * (tile_us + start_us) + 6.0;  // and the epilogue
-  // Which form?  Up to 128 tokens the weights' streaming time counts, not the products (see GemmForm): one token tile.  A GEMM
-  // of few tiles is bound by the latency of a stage (0.24 us with 64 tokens a tile, alone on its CU, 0.53 in the wide form) and
-  // by its epilogue, so narrow layers take tiles of 128 features x 64 tokens as long as those fit the chip in a round or two
-  // (two to a CU: 0.40 us, and 0.45 for every 512 more).  512 wide, 553 rows: QKV 26.7 -> 12.3 us, O 17.7 -> 14.7, gate/up 18.8
-  // -> 10.9, down 16.6 -> 12.5; 1024 wide, FFN 2048: gate/up 1024 rows 27 -> 20, but 2000 rows 28 against 33.
-  int form = 256;
-  if (tok_blocks <= Form128::XB) {
-    form = tok_blocks <= Form64::XB || 2.0 * N * K <= 16e6 ? 64 : 128;
-  } else {
-    const int tiles = (tok_blocks + Form64::XB - 1) / Form64::XB * (feat_blocks / Form64::NBK);
-    const double per = 0.24 + 0.16 * std::max(0, std::min(tiles, 512) - 256) / 256.0 + 0.45 * std::max(0, tiles - 512) / 512.0;
-    if (7.5 + stages * per < 0.9 * wide_us) form = 64;
-  }
-  return {form, wide_split, wide_rest, wide_tiles};
-}
-
-bool mfma_gemm_adds_sums(int rows, int N, int K) {
-  const GemmCut cut = gemm_cut(rows, N, K);
-  return cut.form < 256 || (cut.wide_split > 1 && cut.wide_rest == cut.wide_tiles);
+bool mfma_gemm_adds_sums(int epi, int rows, int N, int K) {
+  const GemmCut cut = mfma_gemm_cut(rows, N, K, epi == EPI_SWIGLU);
+  return cut.form < 256 || (cut.ksplit > 1 && cut.first == 0);
 }
 
 hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int rows, int N, int K, bf16_t *out,
                      int out_K, const GemmEpilogue &ep, hipStream_t s) {
   if (rows == 0) return hipSuccess;
-  if (!ep.split_ws || !ep.split_counters || (!ep.rstd && ep.ssq_in && !mfma_gemm_adds_sums(rows, N, K))) return hipErrorInvalidValue;
+  if (!ep.split_ws || !ep.split_counters || (!ep.rstd && ep.ssq_in && !mfma_gemm_adds_sums(epi, rows, N, K))) return hipErrorInvalidValue;
   GemmParams p = {};
   p.X = X; p.W = W; p.KT = K / 16; p.tok_blocks = rows / 32; p.feat_blocks = N / 32;
-  constexpr int XB = WideForm::XB, NBK = WideForm::NBK;
-  const int stages = p.KT / KTS;
-  const GemmCut cut = gemm_cut(rows, N, K);
-  const int form = cut.form;
-  const int tok_tile = form == 64 ? Form64::XB : form == 128 ? Form128::XB : XB;
-  const int tiles_t = (p.tok_blocks + tok_tile - 1) / tok_tile, tiles_n = p.feat_blocks / (form < 256 ? Form64::NBK : NBK);
-  p.gm = tiles_t < 8 ? tiles_t : 8;
-  p.n_tiles = tiles_t * tiles_n;
+  const GemmCut cut = mfma_gemm_cut(rows, N, K, epi == EPI_SWIGLU);
+  p.gm = cut.tiles_t < 8 ? cut.tiles_t : 8;
+  p.n_tiles = cut.n_tiles;
   p.out = out; p.out_K = out_K;
   p.Kc = ep.Kc; p.Vc = ep.Vc; p.geom = ep.geom; p.qd = ep.qd; p.kvd = ep.kvd;
   p.cos_tab = ep.cos_tab; p.sin_tab = ep.sin_tab; p.row_pos = ep.row_pos; p.row_req = ep.row_req; p.row_q = ep.row_q;
   p.rstd = ep.rstd; p.ssq_in = ep.ssq_in; p.ssq_groups = ep.ssq_in ? K / 64 : 0; p.inv_H = 1.0f / (float)K; p.eps = ep.eps; p.xres = ep.xres; p.gain = ep.gain; p.row_ext = ep.row_ext; p.ssq_part = ep.ssq_part;
-  p.first = p.n_tiles; p.ksplit = 1; p.finish = true;
+  p.first = cut.first; p.ksplit = cut.ksplit; p.finish = cut.finish;
+  p.n_static = cut.n_static; p.pool_wgs = cut.pool_wgs; p.first_grid = cut.first_grid; p.rest_grid = cut.rest_grid;
   p.split_ws = ep.split_ws; p.split_counters = ep.split_counters;
-  if (form < 256) {
-    if (p.n_tiles <= kGemmShortMaxTiles) {
-      // The short forms, few tiles: the chip streams as much as its workgroups keep in flight over 1.5 us of latency, 6 TB/s at best,
-      // and a CU with one workgroup more than the others is waited for.  (64 rows, slices 10 -> 5: down 51 -> 43 us, O 25 ->
-      // 21; QKV 8 -> 4: 30 -> 26.)
-      const int nst = form == 64 ? Form64::NST : Form128::NST;
-      const double in_flight = (nst - 1) * (double)Form64::NBK * KTS * 1024, bytes = 2.0 * N * K;
-      double best = 1e30;
-      for (int c = 1; c == 1 || (c <= 32 && p.n_tiles * c <= kGemmSplitUnits); ++c) {
-        if (c > 1 && stages / c < 2 * nst) continue;
-        const int units = p.n_tiles * c, per_cu = (units + kGemmSplitCus - 1) / kGemmSplitCus;
-        const double even = units <= kGemmSplitCus ? 1.0 : units / ((double)per_cu * kGemmSplitCus);
-        const double t = bytes / (std::min(6.0e6, units * in_flight / 1.5) * even) + slice_cost(p.n_tiles, c, p.tok_blocks, Form64::NBK);
-        if (t < best) { best = t; p.ksplit = c; p.first = c > 1 ? 0 : p.n_tiles; }
-      }
-      // More tiles than CUs, unsplit: the ones beyond the first 256 (24 of gate/up's 280) would double a few CUs' work.
-      // They are split so that they spread over all CUs beside the others, and added up there.
-      const int rest = p.n_tiles - kGemmSplitCus;
-      if (p.ksplit == 1 && rest > 0 && tiles_t == 1)
-        for (int c = 16; c >= 2; --c)
-          if (stages / c >= 2 * nst && rest * c <= kGemmSplitCus) {
-            p.first = kGemmSplitCus; p.ksplit = c; p.finish = false;
-            break;
-          }
-    }
-  } else if (cut.wide_split > 1) {
-    p.ksplit = cut.wide_split; p.first = p.n_tiles - cut.wide_rest;
-  }
-  p.first_grid = (p.first + 7) / 8 * 8;
-  p.rest_grid = ((p.n_tiles - p.first) * p.ksplit + 7) / 8 * 8;
-  // 64 rounds of 256 tiles or more: the last sixteenth of the rounds is drawn from a counter by twice as many
-  // workgroups as it has tiles, so that an XCD can take up to a quarter of it.  (Gate/up at 64 K tokens, 140 rounds:
-  // 2.3 % faster.  With 20 - 30 rounds the drawn tiles' lost L2 neighbourhood and the tile granularity cost more than
-  // the balance brings: down projection 1.7 % slower.)
-  p.n_static = 0; p.pool_wgs = 0;
-  if (form == 256 && p.n_tiles >= 64 * kGemmSplitCus) {
-    const int rounds = p.n_tiles / kGemmSplitCus;
-    const int pool_rounds = (rounds + 8) / 16;
-    p.first = p.n_tiles; p.ksplit = 1; p.rest_grid = 0;
-    p.n_static = (rounds - pool_rounds) * kGemmSplitCus;
-    p.pool_wgs = (2 * (p.n_tiles - p.n_static) + 7) / 8 * 8;
-    p.first_grid = p.n_static + p.pool_wgs;
-  }
   const int grid = p.first_grid + p.rest_grid;
   bool launched = false;
 #define Y(EPI, CLS, F)                                                                                              \
@@ -1076,8 +988,8 @@ hipError_t mfma_gemm(int epi, int cls, const bf16_t *X, const bf16_t *W, int row
   }
 #define X(EPI, CLS)                                                                                                 \
   if (!launched && epi == EPI && cls == CLS) {                                                                      \
-    if (form == 64) Y(EPI, CLS, Form64)                                                                             \
-    else if (form == 128) Y(EPI, CLS, Form128)                                                                      \
+    if (cut.form == 64) Y(EPI, CLS, Form64)                                                                         \
+    else if (cut.form == 128) Y(EPI, CLS, Form128)                                                                      \
     else Y(EPI, CLS, WideForm)                                                                                      \
     launched = true;                                                                                                \
   }

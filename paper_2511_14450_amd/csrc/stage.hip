@@ -430,7 +430,7 @@ hyp_status_t run_prefill_mfma(hyp_stage *st, const void *hidden_in, void *hidden
   PROF(st, HYP_K_ADD_NORM, mfma_prefill_begin((const bf16_t *)hidden_in, xres, at<bf16_t>(st, L.layers[0].g1), y, rstd,
                                                row_ext, rows, d.H, d.eps, s));
   // the consumer of a residual GEMM adds up the sums of squares itself, or finds them as factors (the first block's always are)
-  const bool qkv_adds = mfma_gemm_adds_sums(rows, d.qd + 2 * d.kvd, d.H), gu_adds = mfma_gemm_adds_sums(rows, 2 * d.I, d.H);
+  const bool qkv_adds = mfma_gemm_adds_sums(EPI_QKV, rows, d.qd + 2 * d.kvd, d.H), gu_adds = mfma_gemm_adds_sums(EPI_SWIGLU, rows, 2 * d.I, d.H);
   GemmEpilogue split;  // scratch of GEMMs that split their K loop (short prompts leave few output tiles)
   split.split_ws = at<float>(st, L.gemm_ws); split.split_counters = at<unsigned>(st, L.gemm_counters);
   for (int l = 0; l < st->n_layers; ++l) {

@@ -17,6 +17,12 @@ int main() {
       if (scanf("%d %d %d %d", &cls, &N, &K, &batch) != 4) return 1;
       const hyp::GemvPlan g = hyp::mfma_gemv_plan(cls, N, K, batch);
       printf("%d %d %d %d\n", g.fbw, g.nw, g.ksplit, g.tail);
+    } else if (!strcmp(what, "gemm")) {
+      int rows, N, K, swiglu;
+      if (scanf("%d %d %d %d", &rows, &N, &K, &swiglu) != 4) return 1;
+      const hyp::GemmCut g = hyp::mfma_gemm_cut(rows, N, K, swiglu != 0);
+      printf("%d %d %d %d %d %d %d %d %d %d\n", g.form, g.tiles_t, g.n_tiles, g.first, g.ksplit, g.finish ? 1 : 0, g.n_static, g.pool_wgs, g.first_grid,
+             g.rest_grid);
     } else {
       return 1;
     }

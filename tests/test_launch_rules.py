@@ -84,3 +84,64 @@ def test_plans_deal_all_of_k_and_all_rows(ask):
     for (fbw, nw, ksplit, tail), (cls, N, K, batch) in zip(ask([f"gemv {c} {n} {k} {b}" for c, n, k, b in cases]), cases):
         assert (fbw, nw) in built[cls], (cls, N, K, batch, fbw, nw)
         assert N % (32 * fbw) == 0 and K // 16 % (nw * ksplit) == 0 and K // 16 // (nw * ksplit) % tail == 0, (cls, N, K, batch)
+
+
+# ---------------------------------------------------------------- prefill GEMMs
+# internal rows, N, K, gate/up: us of the GEMM in tiles of 128 x 64 (as the rule slices them) and in the wide form
+FORMS = [
+    (576, 1536, 512, 0, 12.8, 27.3), (576, 8192, 2048, 1, 47.2, 42.7), (704, 8192, 1024, 1, 29.1, 27.5), (2016, 3072, 1024, 0, 32.1, 35.2),
+    (1600, 4096, 512, 1, 23.4, 20.6), (3520, 2560, 768, 1, 36.0, 24.7), (224, 2048, 2048, 0, 16.6, 20.7), (2720, 1024, 2048, 0, 28.7, 33.7),
+    (1312, 4096, 1024, 0, 33.8, 36.5), (576, 4096, 4096, 1, 49.7, 39.5), (1600, 1536, 4096, 0, 46.1, 39.5), (416, 1024, 4096, 0, 18.4, 22.0),
+    (2720, 4096, 4096, 1, 144.5, 84.5), (1312, 2560, 1536, 1, 38.8, 43.6), (3520, 512, 1024, 0, 16.2, 31.0), (288, 3072, 2048, 0, 22.2, 24.9),
+]
+
+
+def test_forms_are_near_the_best_measured(ask):
+    got = ask([f"gemm {rows} {N} {K} {gu}" for rows, N, K, gu, _, _ in FORMS])
+    for (form, *_), (rows, N, K, gu, short, wide) in zip(got, FORMS):
+        assert (short if form == 64 else wide) <= 1.05 * min(short, wide), (rows, N, K, gu, form)
+
+
+# internal rows, N, K: us of the GEMM in tiles of 128 x 64 by its slices
+SLICES = [
+    (128, 1024, 1792, {1: 20.27, 2: 15.86, 3: 14.10, 4: 13.49}), (128, 3072, 2048, {1: 23.78, 2: 20.17, 3: 17.86, 4: 17.34, 5: 17.89}),
+    (96, 1024, 4096, {1: 35.06, 2: 24.06, 4: 16.99, 5: 15.99, 6: 15.01, 8: 14.23, 10: 14.76}), (576, 1024, 1024, {1: 14.53, 2: 15.60}),
+    (128, 1536, 5120, {1: 47.05, 3: 25.19, 5: 20.90, 6: 20.01, 8: 19.26, 10: 20.26}), (576, 2048, 4096, {1: 35.55, 2: 31.79, 3: 27.53}),
+    (320, 1024, 2048, {1: 21.53, 2: 17.76, 3: 15.79, 4: 15.37, 5: 14.01}), (800, 1024, 2048, {1: 21.40, 2: 18.46, 3: 18.70, 4: 18.18}),
+    (320, 4096, 2048, {1: 22.13, 2: 26.04, 3: 24.20}), (800, 2048, 2048, {1: 23.30, 2: 24.57}), (96, 512, 1024, {1: 13.79, 2: 13.01}),
+]
+
+
+def test_slices_are_near_the_best_measured(ask):
+    got = ask([f"gemm {rows} {N} {K} 0" for rows, N, K, _ in SLICES])
+    for (form, _, _, _, ksplit, *_), (rows, N, K, times) in zip(got, SLICES):
+        assert form == 64 and ksplit in times and times[ksplit] <= 1.05 * min(times.values()), (rows, N, K, form, ksplit)
+
+
+def test_prefill_cuts_stay_inside_grid_and_scratch(ask):
+    rng = random.Random(3)
+    cases = [(32 * (1 + int(2 ** rng.uniform(0, 11.5))), 256 * rng.randint(1, 140), 256 * rng.randint(1, 72), rng.randint(0, 1)) for _ in range(6000)]
+    feats, toks, lds = {64: 128, 128: 128, 256: 256}, {64: 64, 128: 128, 256: 256}, {64: 6, 128: 4, 256: 4}
+    for got, (rows, N, K, gu) in zip(ask(["gemm %d %d %d %d" % c for c in cases]), cases):
+        form, tiles_t, n_tiles, first, ksplit, finish, n_static, pool, first_grid, rest_grid = got
+        where = (rows, N, K, gu, got)
+        assert tiles_t == -(-rows // toks[form]) and n_tiles == tiles_t * (N // feats[form]), where
+        assert 0 <= first <= n_tiles and (first == n_tiles) == (ksplit == 1), where
+        if ksplit > 1:
+            assert (n_tiles - first) * ksplit <= 512 and K // 32 // ksplit >= 2 * lds[form], where
+            assert rest_grid % 8 == 0 and rest_grid >= (n_tiles - first) * ksplit, where
+            assert finish or n_tiles <= 511, where  # arrival counters
+        else:
+            assert rest_grid == 0, where
+        if pool:
+            assert first == n_tiles and n_static % 256 == 0 and first_grid == n_static + pool and pool >= 2 * (n_tiles - n_static), where
+        else:
+            assert first_grid % 8 == 0 and first_grid >= first, where
+
+
+def test_a_long_request_has_the_cut_of_its_batch(ask):
+    # a request that fills two and a half rounds of wide tiles in every GEMM of its block is cut like any batch it is part of:
+    # nothing is split (Phi-3 blocks from 7937 rows on: 640 tiles of the O projection)
+    shapes = [(7168, 5120, 0), (5120, 5120, 0), (35840, 5120, 1), (5120, 17920, 0)]
+    for rows in (7968, 8192, 16384, 65536):
+        assert all(got[0] == 256 and got[4] == 1 for got in ask([f"gemm {rows} {N} {K} {gu}" for N, K, gu in shapes])), rows
