@@ -145,3 +145,14 @@ def test_a_long_request_has_the_cut_of_its_batch(ask):
     shapes = [(7168, 5120, 0), (5120, 5120, 0), (35840, 5120, 1), (5120, 17920, 0)]
     for rows in (7968, 8192, 16384, 65536):
         assert all(got[0] == 256 and got[4] == 1 for got in ask([f"gemm {rows} {N} {K} {gu}" for N, K, gu in shapes])), rows
+
+
+def test_split_gemm_cases_take_the_paths_they_are_made_for(ask):
+    from tests.test_gpu_split_gemms import CASES
+    for name, ((hidden, nq, nkv, ffn), lens, paths) in CASES.items():
+        rows = -(-sum(lens) // 32) * 32
+        gemms = [((nq + 2 * nkv) * 128, hidden, 0), (hidden, nq * 128, 0), (2 * ffn, hidden, 1), (hidden, ffn, 0)]
+        for got, path in zip(ask([f"gemm {rows} {N} {K} {gu}" for N, K, gu in gemms]), paths):
+            form, _, n_tiles, first, ksplit, finish = got[:6]
+            kind = "unsplit" if ksplit == 1 else "short" if form < 256 else "wide" if first == 0 else "rest"
+            assert kind == path and finish, (name, path, got)
