@@ -21,7 +21,7 @@ __host__ __device__ inline float bf16_to_f32(bf16_t v) {
 
 __host__ __device__ inline bf16_t f32_to_bf16(float f) {
 #ifdef __HIP_DEVICE_COMPILE__
-  return __builtin_bit_cast(bf16_t, (__bf16)f);  // v_cvt_pk_bf16_f32: the bits of the steps below for all 2^32 inputs
+  return __builtin_bit_cast(bf16_t, (__bf16)f);  // v_cvt_pk_bf16_f32 rounds as the steps below do (test_gpu_bf16_rounding.py)
 #else
   union { uint32_t u; float f; } c;
   c.f = f;
