@@ -85,7 +85,6 @@ inline GemvPlan mfma_gemv_plan(int cls, int N, int K, int batch) {
     return g;
   }
   g.fbw = 2; g.nw = 8; g.ksplit = 1;
-  if (KT % g.nw != 0) g.nw = 4;
   const int groups = N / 64, wave_slots = kWavesPerCu * kCus;
   int cap = (int)(0.025 * K / (batch > 0 ? batch : 1));
   if (cap < 1) cap = 1;

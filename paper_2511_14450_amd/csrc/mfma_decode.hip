@@ -18,8 +18,8 @@ namespace {
 // W = P(N, K): the 1 KiB tiles of one 32-row block are contiguous along K and a
 // tile is the MFMA A fragment as it stands, so every wave streams its slice
 // with fully coalesced 1 KiB loads straight into registers.  x = P(32, K) is
-// tiny and stays in L2.  A workgroup owns 64 packed rows (2 blocks; 32 rows in the
-// unsplit form of the O / down projections); its NW waves (4, 8 or 16) split the
+// tiny and stays in L2.  A workgroup owns 64 packed rows (2 blocks), or 32 in unsplit
+// forms of QKV and the O / down projections; its NW waves (4 or 8) split the
 // workgroup's K slice and are reduced through LDS in wave order; the
 // `ksplit` workgroups of one row group (two or four times as many for the row groups that would
 // otherwise form a thin second round of the launch) write fp32 partial sums, and the one that
@@ -28,11 +28,11 @@ namespace {
 // partial sums are written with device-scope (write-through) stores that have
 // completed before the counter is bumped, which keeps cache write-backs and
 // invalidations out of the protocol.  Epilogues:
-//   DEC_QKV_OPEN the same for the first block of a stage: x is hidden_in as the caller gives it, and gain, rounding and sums of
-//              squares of the norm happen on the way to the MFMAs (30 vector instructions per KiB of weights, hidden under
-//              them); every workgroup sees all of K.  Also leaves the residual stream
 //   DEC_QKV    scale by the RMS Norm factor, RoPE at position lens[b], write q
 //              to the decode query buffer and k, v into the cache
+//   DEC_QKV_OPEN  DEC_QKV for the first block of a stage: x is hidden_in, as the caller gives it or copied to be aligned, and
+//              gain, rounding and sums of squares of the norm happen on the way to the MFMAs (30 vector instructions per KiB
+//              of weights, hidden under them); every workgroup sees all of K.  Also leaves the residual stream
 //   DEC_SWIGLU scale, m = silu(gate) * up -> P(32, I)
 //   DEC_RESID  x += sum ; xres = x ; y' = x * gain -> P(32, H) ; per-token sum of
 //              squares of this row group -> ssq_out   (RMS Norm of the next
@@ -114,10 +114,11 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
   float *const part = fine ? p.partial + (size_t)p.ksplit * 32 * p.N : p.partial;
   const int part_n = fine ? (p.n_groups - p.groups1) * kGroupRows : p.N;        // rows per token
   const int part_r0 = fine ? (group - p.groups1) * kGroupRows : fb0 * 32;       // this group's first row
-  // positions of the step's tokens (the QKV epilogue's rotary angles depend on them): fetched under the streaming loop
-  // (ahead of time for the first kPf * 8 tokens, which covers the usual batch; the rest is loaded in place)
-  constexpr int kPf = 2, kPairs = FBW * 16;
-  int pos_pf[kPf] = {0, 0};
+  // positions of the step's tokens (the QKV epilogue's rotary angles depend on them): fetched under the streaming loop, a
+  // thread's pairs of up to 32 tokens
+  constexpr int kPairs = FBW * 16, kPf = (32 * kPairs + NW * 64 - 1) / (NW * 64);
+  static_assert(!kQkv || kPf <= 2, "registers");
+  int pos_pf[kPf] = {};
   if (kQkv) {
 #pragma unroll
     for (int j = 0; j < kPf; ++j) {
@@ -215,8 +216,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
   const int n_pairs = p.batch * kGroupRows;
   // What the epilogue needs from memory besides the sums, requested at once: rotary angles, residual stream and next norm's
   // gain, the sums of squares behind the RMS Norm factor (16 row groups per thread).
-  float cos_pf[kPf] = {0.f, 0.f}, sin_pf[kPf] = {0.f, 0.f};
-  constexpr int kPfR = 4;  // (token, row) pairs per thread fetched ahead: 16 tokens' worth
+  float cos_pf[kPf] = {}, sin_pf[kPf] = {};
+  constexpr int kPfR = 32 * kGroupRows / (NW * 64);  // (token, row) pairs of a thread
   float xres_pf[kPfR], gain_pf[kPfR];
   float ssq_v[16];
   const int ssq_tkn = threadIdx.x & 31, ssq_part_id = threadIdx.x >> 5;
@@ -275,9 +276,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     return s;
   };
   if (split) {
-    // at most 8 (token, row) pairs per thread
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < kPfR; ++j) {
       int idx = threadIdx.x + j * NW * 64;
       if (idx < n_pairs) {
         int f = idx % kGroupRows, token = idx / kGroupRows;
@@ -374,16 +374,15 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
   if (kQkv) {
     const int head = fb0 >> 2;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < kPf; ++j) {
       int idx = threadIdx.x + j * NW * 64;
       if (idx >= p.batch * kPairs) break;
       int x = idx % kPairs, b = idx / kPairs, f = (x >> 4) * 32 + (x & 15);
       float a = total(b, f) * rstd_s[b], c = total(b, f + 16) * rstd_s[b];
       int d0 = (fb0 & 3) * 16 + x, d1 = d0 + 64;
-      int pos = j < kPf ? pos_pf[j] : p.lens[b];
+      const int pos = pos_pf[j];
       if (head < p.nq + p.nkv) {
-        float cs = j < kPf ? cos_pf[j] : p.cos_tab[(size_t)pos * 64 + d0];
-        float sn = j < kPf ? sin_pf[j] : p.sin_tab[(size_t)pos * 64 + d0];
+        const float cs = cos_pf[j], sn = sin_pf[j];
         float lo = a * cs - c * sn, hi = c * cs + a * sn;
         if (head < p.nq) {
           int G = p.nq / p.nkv;
@@ -430,14 +429,14 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
   } else {
     const int n0 = fb0 * 32;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < kPfR; ++j) {
       int idx = threadIdx.x + j * NW * 64;
       if (idx >= n_pairs) break;
       int f = idx % kGroupRows, b = idx / kGroupRows;
-      float xn = (j < kPfR ? xres_pf[j] : p.xres[(size_t)b * p.H + n0 + f]) + total(b, f);
+      float xn = xres_pf[j] + total(b, f);
       if (EPI == DEC_RESID) {
         p.xres[(size_t)b * p.H + n0 + f] = xn;
-        p.y_out[frag_offset(b, n0 + f, p.H)] = f2bf_dev(xn * (j < kPfR ? gain_pf[j] : bf16_to_f32(p.gain[n0 + f])));
+        p.y_out[frag_offset(b, n0 + f, p.H)] = f2bf_dev(xn * gain_pf[j]);
         float ss = xn * xn;  // over the lanes of the token: kGroupRows of them
 #pragma unroll
         for (int o = kGroupRows / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
@@ -541,14 +540,13 @@ bool mfma_gemv_counts(const GemvPlan &g, int N, int K) {
 }
 
 // the (epilogue, blocks per workgroup, waves per workgroup, class) combinations a plan may ask for
-#define HYP_GEMV_QKV(X)                                                                                  \
+#define HYP_GEMV_VARIANTS(X)                                                                             \
   X(DEC_QKV, 1, 4, HYP_K_GEMV_QKV) X(DEC_QKV, 1, 8, HYP_K_GEMV_QKV) X(DEC_QKV, 2, 8, HYP_K_GEMV_QKV)     \
-  X(DEC_QKV_OPEN, 1, 4, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 1, 8, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 2, 8, HYP_K_GEMV_QKV)
-#define HYP_GEMV_VARIANTS(X, NW)                                                                         \
-  X(DEC_SWIGLU, 2, NW, HYP_K_GEMV_GATEUP)                                                                \
-  X(DEC_RESID, 1, NW, HYP_K_GEMV_O) X(DEC_RESID, 2, NW, HYP_K_GEMV_O)                                    \
-  X(DEC_RESID, 1, NW, HYP_K_GEMV_DOWN) X(DEC_RESID, 2, NW, HYP_K_GEMV_DOWN)                              \
-  X(DEC_FINAL, 1, NW, HYP_K_GEMV_DOWN) X(DEC_FINAL, 2, NW, HYP_K_GEMV_DOWN)
+  X(DEC_QKV_OPEN, 1, 4, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 1, 8, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 2, 8, HYP_K_GEMV_QKV) \
+  X(DEC_SWIGLU, 2, 8, HYP_K_GEMV_GATEUP)                                                                 \
+  X(DEC_RESID, 1, 4, HYP_K_GEMV_O) X(DEC_RESID, 2, 8, HYP_K_GEMV_O)                                      \
+  X(DEC_RESID, 1, 4, HYP_K_GEMV_DOWN) X(DEC_RESID, 2, 8, HYP_K_GEMV_DOWN)                                \
+  X(DEC_FINAL, 1, 4, HYP_K_GEMV_DOWN) X(DEC_FINAL, 2, 8, HYP_K_GEMV_DOWN)
 
 // the waves' sums of 32 tokens can pass the 64 KiB a workgroup gets by default
 hipError_t mfma_gemv_init() {
@@ -557,9 +555,7 @@ hipError_t mfma_gemv_init() {
   if (e == hipSuccess)                                                                                           \
     e = hipFuncSetAttribute((const void *)k_dec_gemv<EPI, FBW, NW, CLS>, hipFuncAttributeMaxDynamicSharedMemorySize, \
                             (int)(sizeof(float) * NW * 32 * (FBW * 32 + 4)) + (EPI == DEC_QKV_OPEN ? kMaxGainBytes : 0));
-  HYP_GEMV_QKV(X)
-  HYP_GEMV_VARIANTS(X, 8)
-  HYP_GEMV_VARIANTS(X, 16)
+  HYP_GEMV_VARIANTS(X)
 #undef X
   return e;
 }
@@ -590,10 +586,7 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
     k_dec_gemv<EPI, FBW, NW, CLS><<<grid, NW * 64, lds, s>>>(p);             \
     launched = true;                                                         \
   }
-  HYP_GEMV_QKV(X)
-  HYP_GEMV_VARIANTS(X, 4)
-  HYP_GEMV_VARIANTS(X, 8)
-  HYP_GEMV_VARIANTS(X, 16)
+  HYP_GEMV_VARIANTS(X)
 #undef X
   if (!launched) return hipErrorInvalidValue;
   return hipGetLastError();

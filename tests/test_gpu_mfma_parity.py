@@ -149,7 +149,7 @@ def test_mfma_decode_every_batch_width(batch):
 
 
 # hidden 5120 and FFN 7680 are the smallest widths here at which the skinny GEMMs of a decode step are
-# split along K across workgroups (two slices for QKV and gate/up, three for the down projection)
+# split along K across workgroups (two slices for gate/up, three for the down projection; QKV never is)
 SHAPE_SPLITK = synth.BlockShape(hidden=5120, n_q_heads=8, n_kv_heads=2, head_dim=128, ffn_dim=7680, dtype="bf16")
 
 

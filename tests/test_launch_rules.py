@@ -156,3 +156,9 @@ def test_split_gemm_cases_take_the_paths_they_are_made_for(ask):
             form, _, n_tiles, first, ksplit, finish = got[:6]
             kind = "unsplit" if ksplit == 1 else "short" if form < 256 else "wide" if first == 0 else "rest"
             assert kind == path and finish, (name, path, got)
+
+
+def test_split_decode_case_is_split(ask):
+    # what test_gpu_mfma_parity.py and test_gpu_depth_parity.py say of hidden 5120, FFN 7680
+    for batch in (3, 5, 17, 31):
+        assert [g[2] for g in ask([f"gemv {GATEUP} 15360 5120 {batch}", f"gemv {DOWN} 5120 7680 {batch}"])] == [2, 3]
