@@ -165,7 +165,7 @@ constexpr int FB = 2, KTS = 2;
 // How a workgroup is laid out: WF waves along the features (FB blocks of 32 each) times WT along the tokens (TB
 // blocks each), NST stages in LDS.
 //   <4, 2, 4, 4>  256 features x 256 tokens: the form described above
-//   <2, 2, 1, 6>  128 features x 64 tokens: a short prompt, or a narrow layer at any number of rows (gemm_cut).  A short
+//   <2, 2, 1, 6>  128 features x 64 tokens: a short prompt, or a narrow layer at any number of rows (mfma_gemm_cut).  A short
 //                 prompt is bound by the weights' way out of HBM, and the wide
 //                 form multiplies three tokens of padding for every live one on top (gate/up of 64 tokens: 94 GFLOP,
 //                 100 us, for 367 MB).  Twice as many tiles as 256 features would give put a workgroup on every CU
