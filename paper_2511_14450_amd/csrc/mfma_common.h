@@ -17,6 +17,8 @@
 // store.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace hyp {
@@ -84,6 +86,27 @@ struct CacheGeom {
 };
 
 __device__ inline bf16_t f2bf_dev(float f) { return f32_to_bf16(f); }
+
+// The sum over the 32 lanes of a half wave, or over all 64, in every lane: the additions of a butterfly of __shfl_xor 32 or 16
+// .. 1, in that order, by lane swaps and row rotations (values that agree under an exchange by 8 may as well be rotated by 4).
+// Six of the shuffles, each a trip through the LDS pipe, took 0.3 us at the end of a decode step's residual kernels.
+template <int LANES> __device__ __forceinline__ float lanes_sum(float v) {
+  static_assert(LANES == 32 || LANES == 64, "half a wave or a wave");
+  if (LANES == 64) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  auto moved = [](float x, auto ctrl) {
+    return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v += moved(v, std::integral_constant<int, 0x128>());  // row_ror:8
+  v += moved(v, std::integral_constant<int, 0x124>());  // row_ror:4
+  v += moved(v, std::integral_constant<int, 0x4e>());   // quad_perm:[2,3,0,1]
+  v += moved(v, std::integral_constant<int, 0xb1>());   // quad_perm:[1,0,3,2]
+  return v;
+}
 
 __device__ inline bf16x4_t pack4(float a, float b, float c, float d) {
   bf16x4_t r;

@@ -72,6 +72,9 @@ struct DecGemvParams {
   int *lens_advance;  // DEC_FINAL: cached lengths to bump once the step's last kernel finishes
 };
 
+// k-tiles of a wave that are in flight at once.  One window: with all of a wave's tiles requested at the start
+constexpr int gemv_window(int fbw, bool one_window) { return one_window ? (fbw == 1 ? 16 : 10) : fbw == 1 ? 10 : 5; }
+
 // FBW row blocks of 32 per workgroup: 2 where the epilogue pairs rows of two blocks (gate and up) and for long K; 1 or 2 for QKV,
 // whose RoPE partners lie in one block; 1 for the residual epilogues at short K, where 32-row workgroups with
 // a 10-tile window give as many waves with as much in flight as two slices of 64-row workgroups
@@ -80,10 +83,10 @@ struct DecGemvParams {
 // NW waves per workgroup share the k-tiles of the workgroup's K slice: more waves per workgroup mean
 // fewer K slices across workgroups (fewer partial sums in memory, or none) for the same number of
 // waves in flight.
-template <int EPI, int FBW, int NW, int CLS>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EPI == DEC_QKV_OPEN ? 2 : 4))) k_dec_gemv(DecGemvParams p) {
+template <int EPI, int FBW, int NW, int CLS, bool SHORT>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EPI == DEC_QKV_OPEN || SHORT ? 2 : 4))) k_dec_gemv(DecGemvParams p) {
   constexpr bool kOpen = EPI == DEC_QKV_OPEN, kQkv = EPI == DEC_QKV || kOpen, kSsqIn = EPI == DEC_QKV || EPI == DEC_SWIGLU;
-  constexpr int UNROLL = FBW == 1 ? 10 : 5;
+  constexpr int UNROLL = gemv_window(FBW, SHORT);
   constexpr int kGroupRows = FBW * 32;
   constexpr int kRedStride = kGroupRows + 4;  // keeps 16-byte alignment, spreads tokens over banks
   constexpr int kSsqParts = NW * 2;  // interleaved partial sums of the row groups' sums of squares (one per 32 threads)
@@ -91,7 +94,6 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
   // cross-wave add reads without bank conflicts; reused as fin[token][kGroupRows + 1] once reduced
   extern __shared__ __attribute__((aligned(16))) float red_raw[];
   float (*red)[kRedStride] = (float (*)[kRedStride])red_raw;  // red[wave * batch + token][row]
-  __shared__ float rstd_s[32];
   __shared__ unsigned is_last;
   float (*fin)[kGroupRows + 1] = (float (*)[kGroupRows + 1])red_raw;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -107,7 +109,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     }
   }
   const int fb0 = group * FBW;
-  const bool split = !kQkv && ksplit > 1;  // QKV is never split
+  const bool split = !kQkv && !SHORT && ksplit > 1;  // QKV is never split
   // partial sums [slice][32 tokens][rows]: the finely cut last groups have a narrow array of their own behind the
   // main one (rows of those groups only), so their extra slices do not cost room over all N rows
   const bool fine = group >= p.groups1;
@@ -149,7 +151,10 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
   bf16x8_t xf[UNROLL], wf[FBW][UNROLL];
   auto load_tile = [&](int u, int tile) {
 #pragma unroll
-    for (int i = 0; i < FBW; ++i) wf[i][u] = __builtin_nontemporal_load((const bf16x8_t *)(wp[i] + (size_t)tile * kStep));
+    for (int i = 0; i < FBW; ++i) {
+      const bf16x8_t *w = (const bf16x8_t *)(wp[i] + (size_t)tile * kStep);
+      wf[i][u] = SHORT ? *w : __builtin_nontemporal_load(w);
+    }
     xf[u] = *(const bf16x8_t *)(xp + (size_t)tile * (kOpen ? NW * 16 : kStep));
   };
   // DEC_QKV_OPEN: gain and rounding of the norm on the way to the MFMA, and the tokens' sums of squares of this wave's k-tiles
@@ -184,7 +189,50 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
 #pragma unroll
     for (int i = 0; i < FBW; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i][u], xf[u], acc[i], 0, 0, 0);
   };
-  const int n_win = tiles_per_wave / UNROLL, rem = tiles_per_wave - n_win * UNROLL;
+  const int n_pairs = p.batch * kGroupRows;
+  // What the epilogue needs from memory besides the sums, requested at once: rotary angles, residual stream and next norm's
+  // gain, the sums of squares behind the RMS Norm factor (16 row groups per thread).
+  float cos_pf[kPf] = {}, sin_pf[kPf] = {};
+  constexpr int kPfR = 32 * kGroupRows / (NW * 64);  // (token, row) pairs of a thread
+  float xres_pf[kPfR], gain_pf[kPfR];
+  float ssq_v[16];
+  const int ssq_tkn = threadIdx.x & 31, ssq_part_id = threadIdx.x >> 5;
+  auto fetch_angles = [&] {
+    if (kQkv) {
+#pragma unroll
+      for (int j = 0; j < kPf; ++j) {
+        int idx = threadIdx.x + j * NW * 64;
+        if (idx < p.batch * kPairs) {
+          int d0 = (fb0 & 3) * 16 + idx % kPairs;
+          cos_pf[j] = p.cos_tab[(size_t)pos_pf[j] * 64 + d0];
+          sin_pf[j] = p.sin_tab[(size_t)pos_pf[j] * 64 + d0];
+        }
+      }
+    }
+  };
+  auto fetch = [&] {
+    if (EPI == DEC_RESID || EPI == DEC_FINAL) {
+#pragma unroll
+      for (int j = 0; j < kPfR; ++j) {
+        int idx = threadIdx.x + j * NW * 64;
+        xres_pf[j] = 0.f; gain_pf[j] = 0.f;
+        if (idx < n_pairs) {
+          int f = idx % kGroupRows, b = idx / kGroupRows;
+          xres_pf[j] = p.xres[(size_t)b * p.H + fb0 * 32 + f];
+          if (EPI == DEC_RESID) gain_pf[j] = bf16_to_f32(p.gain[fb0 * 32 + f]);
+        }
+      }
+    }
+    if (kSsqIn) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        int g = ssq_part_id + kSsqParts * u;
+        ssq_v[u] = g < p.n_ssq && ssq_tkn < p.batch ? p.ssq_in[g * 32 + ssq_tkn] : 0.f;
+      }
+    }
+  };
+  const int n_win = SHORT ? 0 : tiles_per_wave / UNROLL, rem = tiles_per_wave - n_win * UNROLL;
+  if (SHORT) fetch();
   if (n_win > 0) {
     int t = 0;
 #pragma unroll
@@ -208,54 +256,41 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u)
       if (u < rem) load_tile(u, u);
+    if (SHORT) fetch_angles();
     open();
   }
 #pragma unroll
   for (int u = 0; u < UNROLL; ++u)
     if (u < rem) use_tile(u, n_win * UNROLL + u);
-  const int n_pairs = p.batch * kGroupRows;
-  // What the epilogue needs from memory besides the sums, requested at once: rotary angles, residual stream and next norm's
-  // gain, the sums of squares behind the RMS Norm factor (16 row groups per thread).
-  float cos_pf[kPf] = {}, sin_pf[kPf] = {};
-  constexpr int kPfR = 32 * kGroupRows / (NW * 64);  // (token, row) pairs of a thread
-  float xres_pf[kPfR], gain_pf[kPfR];
-  float ssq_v[16];
-  const int ssq_tkn = threadIdx.x & 31, ssq_part_id = threadIdx.x >> 5;
-  auto fetch = [&] {
-    if (kQkv) {
-#pragma unroll
-      for (int j = 0; j < kPf; ++j) {
-        int idx = threadIdx.x + j * NW * 64;
-        if (idx < p.batch * kPairs) {
-          int d0 = (fb0 & 3) * 16 + idx % kPairs;
-          cos_pf[j] = p.cos_tab[(size_t)pos_pf[j] * 64 + d0];
-          sin_pf[j] = p.sin_tab[(size_t)pos_pf[j] * 64 + d0];
-        }
-      }
-    }
-    if (EPI == DEC_RESID || EPI == DEC_FINAL) {
-#pragma unroll
-      for (int j = 0; j < kPfR; ++j) {
-        int idx = threadIdx.x + j * NW * 64;
-        xres_pf[j] = 0.f; gain_pf[j] = 0.f;
-        if (idx < n_pairs) {
-          int f = idx % kGroupRows, b = idx / kGroupRows;
-          xres_pf[j] = p.xres[(size_t)b * p.H + fb0 * 32 + f];
-          if (EPI == DEC_RESID) gain_pf[j] = bf16_to_f32(p.gain[fb0 * 32 + f]);
-        }
-      }
-    }
-    if (kSsqIn) {
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        int g = ssq_part_id + kSsqParts * u;
-        ssq_v[u] = g < p.n_ssq && ssq_tkn < p.batch ? p.ssq_in[g * 32 + ssq_tkn] : 0.f;
-      }
-    }
-  };
   // An unsplit workgroup finishes for sure: the requests go out ahead of the waves' meeting (512-wide blocks: 1.1 of 4.4 us
   // of QKV and gate/up were this round trip, with the epilogue's turn through LDS); a slice waits to know that it is the last.
-  if (!split) fetch();
+  if (!split && !SHORT) {
+    fetch_angles();
+    fetch();
+  }
+  // The RMS Norm factor of a token: the row groups' sums of squares, added in a fixed order (kSsqParts interleaved partial sums,
+  // which meet in LDS with the products, then those in order, by every thread that needs the factor: a barrier and a chain of
+  // one wave's additions less).
+  constexpr bool kNorm = kQkv || EPI == DEC_SWIGLU;
+  __shared__ float ssq_part[kNorm ? kSsqParts : 1][32];
+  auto sum_squares = [&] {
+    if constexpr (kOpen) {
+      ssq_part[ssq_part_id][ssq_tkn] = sq;  // a wave's two halves of its k-tiles
+    } else if constexpr (kNorm) {
+      float ss = 0.f;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) ss += ssq_v[u];
+      for (int g = ssq_part_id + kSsqParts * 16; g < p.n_ssq; g += kSsqParts) ss += p.ssq_in[g * 32 + ssq_tkn];
+      ssq_part[ssq_part_id][ssq_tkn] = ss;
+    }
+  };
+  auto rstd = [&](int token) {
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < kSsqParts; ++i) ss += ssq_part[kNorm ? i : 0][token];
+    return 1.0f / sqrtf(ss * p.inv_H + p.eps);
+  };
+  if (!split) sum_squares();
   // accumulator register r of lane l of block i is packed row 32 i + 8 (r/4) + 4 (l/32) + r%4 of
   // token l % 32: four consecutive rows per 16-byte store; token columns beyond the batch stay home
   if ((lane & 31) < p.batch) {
@@ -295,8 +330,6 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     __syncthreads();  // `red` is free from here on
     if (!is_last) return;
     fetch();
-  }
-  if (split) {
     // The finishing workgroup.  Plain loads are enough here: every 256-byte run of `partial` has exactly one
     // writer in this launch, this XCD's L2 was invalidated when the launch began,
     // and nothing in this launch read these lines before, so a line is either
@@ -347,28 +380,9 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
         if (has1) fin[idx1 / kGroupRows][idx1 % kGroupRows] = sum1;
       }
     }
-  }
-  if (kQkv || EPI == DEC_SWIGLU) {
-    // RMS Norm factor of every token: the row groups' sums of squares, added in a
-    // fixed order (kSsqParts interleaved partial sums, then those in order)
-    __shared__ float ssq_part[kSsqParts][32];
-    if constexpr (kOpen) {
-      ssq_part[ssq_part_id][ssq_tkn] = sq;  // a wave's two halves of its k-tiles
-    } else {
-      float ss = 0.f;
-#pragma unroll
-      for (int u = 0; u < 16; ++u) ss += ssq_v[u];
-      for (int g = ssq_part_id + kSsqParts * 16; g < p.n_ssq; g += kSsqParts) ss += p.ssq_in[g * 32 + ssq_tkn];
-      ssq_part[ssq_part_id][ssq_tkn] = ss;
-    }
+    sum_squares();
     __syncthreads();
-    if (threadIdx.x < 32) {
-      float ss = 0.f;
-      for (int i = 0; i < kSsqParts; ++i) ss += ssq_part[i][threadIdx.x];
-      rstd_s[threadIdx.x] = 1.0f / sqrtf(ss * p.inv_H + p.eps);
-    }
   }
-  __syncthreads();
   auto total = [&](int token, int f) { return split ? fin[token][f] : wave_sum(token, f); };
 
   if (kQkv) {
@@ -378,7 +392,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
       int idx = threadIdx.x + j * NW * 64;
       if (idx >= p.batch * kPairs) break;
       int x = idx % kPairs, b = idx / kPairs, f = (x >> 4) * 32 + (x & 15);
-      float a = total(b, f) * rstd_s[b], c = total(b, f + 16) * rstd_s[b];
+      const float rs = rstd(b);
+      float a = total(b, f) * rs, c = total(b, f + 16) * rs;
       int d0 = (fb0 & 3) * 16 + x, d1 = d0 + 64;
       const int pos = pos_pf[j];
       if (head < p.nq + p.nkv) {
@@ -423,7 +438,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     const int f0 = (fb0 >> 3) * 128 + ((fb0 >> 1) & 3) * 32;
     for (int idx = threadIdx.x; idx < p.batch * 32; idx += NW * 64) {
       int x = idx & 31, b = idx >> 5;
-      float g = total(b, x) * rstd_s[b], u = total(b, 32 + x) * rstd_s[b];
+      const float rs = rstd(b);
+      float g = total(b, x) * rs, u = total(b, 32 + x) * rs;
       p.m_out[frag_offset(b, f0 + x, p.I)] = f2bf_dev(g / (1.0f + __expf(-g)) * u);
     }
   } else {
@@ -437,9 +453,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
       if (EPI == DEC_RESID) {
         p.xres[(size_t)b * p.H + n0 + f] = xn;
         p.y_out[frag_offset(b, n0 + f, p.H)] = f2bf_dev(xn * gain_pf[j]);
-        float ss = xn * xn;  // over the lanes of the token: kGroupRows of them
-#pragma unroll
-        for (int o = kGroupRows / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+        const float ss = lanes_sum<kGroupRows>(xn * xn);  // over the lanes of the token
         if (f == 0) p.ssq_out[group * 32 + b] = ss;
       } else {
         p.hidden_out[(size_t)b * p.H + n0 + f] = f2bf_dev(xn);
@@ -472,9 +486,7 @@ __global__ void __launch_bounds__(kBeginWaves * 64) k_dec_begin(const bf16_t *__
     if (b >= batch) break;
     xres[(size_t)b * H + n] = x[u];
     y_out[frag_offset(b, n, H)] = f2bf_dev(x[u] * g);
-    float ss = x[u] * x[u];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    const float ss = lanes_sum<64>(x[u] * x[u]);
     if (lane == 0) ssq_out[blockIdx.x * 32 + b] = ss;
   }
 }
@@ -553,7 +565,10 @@ hipError_t mfma_gemv_init() {
   hipError_t e = hipSuccess;
 #define X(EPI, FBW, NW, CLS)                                                                                     \
   if (e == hipSuccess)                                                                                           \
-    e = hipFuncSetAttribute((const void *)k_dec_gemv<EPI, FBW, NW, CLS>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+    e = hipFuncSetAttribute((const void *)k_dec_gemv<EPI, FBW, NW, CLS, false>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                            (int)(sizeof(float) * NW * 32 * (FBW * 32 + 4)) + (EPI == DEC_QKV_OPEN ? kMaxGainBytes : 0));    \
+  if (e == hipSuccess)                                                                                           \
+    e = hipFuncSetAttribute((const void *)k_dec_gemv<EPI, FBW, NW, CLS, true>, hipFuncAttributeMaxDynamicSharedMemorySize,  \
                             (int)(sizeof(float) * NW * 32 * (FBW * 32 + 4)) + (EPI == DEC_QKV_OPEN ? kMaxGainBytes : 0));
   HYP_GEMV_VARIANTS(X)
 #undef X
@@ -580,10 +595,12 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
   // the waves' sums of the live tokens, and the norm's gain
   const size_t lds = sizeof(float) * nw * a.batch * (fbw * 32 + 4) + (epi == DEC_QKV_OPEN ? sizeof(bf16_t) * a.H : 0);
   if (epi == DEC_QKV_OPEN && (a.K != a.H || (uintptr_t)a.x % 16 != 0 || !mfma_dec_opens(a.H, a.N, a.plan))) return hipErrorInvalidValue;
+  const bool one_window = ksplit == 1 && p.tail == 1 && p.tiles_per_wave <= gemv_window(fbw, true);
   bool launched = false;
 #define X(EPI, FBW, NW, CLS)                                                 \
   if (!launched && epi == EPI && fbw == FBW && nw == NW && cls == CLS) {      \
-    k_dec_gemv<EPI, FBW, NW, CLS><<<grid, NW * 64, lds, s>>>(p);             \
+    if (one_window) k_dec_gemv<EPI, FBW, NW, CLS, true><<<grid, NW * 64, lds, s>>>(p); \
+    else k_dec_gemv<EPI, FBW, NW, CLS, false><<<grid, NW * 64, lds, s>>>(p); \
     launched = true;                                                         \
   }
   HYP_GEMV_VARIANTS(X)
