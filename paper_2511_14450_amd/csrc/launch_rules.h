@@ -48,6 +48,36 @@ inline int plain_attn_split(int esize, int d, size_t pairs, int longest) {
 }
 
 // ----------------------------------------------------------------------------
+// Prefill contractions of generic stages: the form.
+// ----------------------------------------------------------------------------
+enum { PLAIN_GEMM_REGISTERS = 0, PLAIN_GEMM_SMALL = 1, PLAIN_GEMM_WIDE = 2, PLAIN_GEMM_MANY = 3 };
+
+// out^T[N, rows] = W[N, K] X[rows, K]^T in tiles of 32 x 32 from registers, or of 64 x 64 or 128 x 128 through LDS: microseconds
+// by what was measured on 300 contractions of 256 - 5120 wide layers.  A tile costs so many nanoseconds per element of K, on every
+// CU at once, and CUs with a tile more than the others are waited for (not so the small float tiles, whose waves fill in for
+// each other); what comes before and behind the K loop is paid once.  (Float, 64 x 64: 320 x 584 tiles take as long as 512.)
+// MANY: the wide bf16 tiles in four waves, three workgroups to a CU, where there are that many; residual epilogues, which
+// those hide less of, only behind a long K loop (1280 tiles: K = 8960 even, K = 3200 7 % slower).
+inline int plain_gemm_form(int esize, int rows, int N, int K, bool qkv, bool swiglu) {
+  auto tiles = [&](int per) { return (double)((N + per - 1) / per) * ((rows + per - 1) / per); };
+  auto rounds = [](double n) { return (double)(int64_t)((n + kCus - 1) / kCus); };
+  const double n32 = tiles(32), n64 = tiles(64), n128 = tiles(128), k = K * 1e-3;
+  double reg, small, wide;
+  if (esize == 4) {
+    reg = 4.0 + k * 6.5 * std::max(1.0, n32 / kCus);
+    small = 5.0 + k * (n64 <= kCus ? 19.0 : 22.5 * rounds(n64));
+    wide = 5.0 + k * 68.0 * rounds(n128);
+  } else {
+    reg = 3.5 + (qkv || swiglu ? 2.0 : 0.0) + k * 1.9 * rounds(n32);
+    small = 6.5 + (qkv ? 1.5 : 0.0) + k * (n64 <= kCus ? 3.2 : 3.9 * rounds(n64));
+    wide = 6.0 + (qkv ? 1.5 : 0.0) + k * (n128 <= kCus ? 10.0 : 7.8 * rounds(n128));
+  }
+  if (reg <= small && reg <= wide) return PLAIN_GEMM_REGISTERS;
+  if (small <= wide) return PLAIN_GEMM_SMALL;
+  return esize == 2 && n128 >= 3 * kCus && (qkv || swiglu || K >= 6144) ? PLAIN_GEMM_MANY : PLAIN_GEMM_WIDE;
+}
+
+// ----------------------------------------------------------------------------
 // How one skinny GEMM of a decode step is cut into workgroups.
 //   fbw     32-row blocks per workgroup: 2 where the epilogue pairs rows of two blocks (gate and up) and
 //           for long K; 1 for the residual GEMMs at short K, which then run as unsplit 4-wave

@@ -81,20 +81,16 @@ __global__ void __launch_bounds__(256) k_plain_begin(const T *__restrict__ in, f
 // out^T[N, rows] = W[N, K] X[rows, K]^T on fragment-order operands, features on the MFMA M axis:
 // lane l of a 16 x 16 block holds features 4 (l / 16) .. + 3 of token l % 16 in its four registers.
 //
-// A wave owns WM x WN blocks and takes both operands from L2 straight into registers, U tiles of K
-// ahead of their use; FW x TW waves of a workgroup lie side by side, KW waves share the K loop and
-// meet in LDS, in wave order.  No LDS on the operand path: a float contraction spends 32 cycles of
-// the matrix pipe on every 256 bytes (128-wide wave tiles: 16 bytes per clock and CU), far below
-// what L1 delivers.  More than kPlainGemvRows rows (fewer: plain_gemv).
-//   <2, 2, 1, 1, 4>  prompts that leave the wide form's grid short of the chip (920 tokens, float: QKV 61 us = 64
-//                    TFLOP/s, down 90 us = 86 TFLOP/s)
-//   <4, 4, 2, 2, 1>  long prompts: 128 x 128 per workgroup (920 x 8192 x 1024: float 170 us = 91 TFLOP/s, 60 % of what
-//                    the vendor BLAS reaches on 8192^3; 1065 x 8192 x 1024 bf16 52 us = 343 TFLOP/s, bound by L1)
+// Two ways for the operands.  From L2 straight into registers (the first kernel below, <2, 2, 1, 1, 4>): a wave owns WM x WN
+// blocks and requests U tiles of K ahead of their use, KW waves share the K loop and meet in LDS, in wave order.  No barrier in
+// the loop and 32 x 32 outputs a workgroup, so it is the form of short prompts and narrow layers, whose few tiles it spreads
+// over the most CUs.  Through LDS (the second kernel): 64 x 64 or 128 x 128 outputs, for everything that fills the chip with
+// them.  Which one: plain_gemm_form.  More than kPlainGemvRows rows (fewer: plain_gemv).
 // ----------------------------------------------------------------------------
 template <typename T, int EPI, int WM, int WN, int FW, int TW, int KW>
 __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a) {
-  constexpr int U = WM * WN >= 16 ? 2 : WM * WN >= 4 ? 2 : 4;
-  constexpr int E = plain_chunk<T>();
+  constexpr int U = 2;
+  static_assert(KW >= WM * WN, "a wave finishes one block at most");
   const PlainGemm<T> &g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int kw = wave % KW, fw = wave / KW % FW, tw = wave / KW / FW;
@@ -137,34 +133,21 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
             for (int j = 0; j < WN; ++j) acc[i][j] = mma<T>(w[u][i], x[u][j], acc[i][j], e);
   };
   constexpr int kStep = U * KW;
-  // A group's registers are refilled before the other group is used, or right after its own use: the wide float
-  // form is 22 % faster the second way, the wide bf16 form 29 % the first.
-  constexpr bool kLate = sizeof(T) == 4 && WM * WN >= 16;
   const int tl = lane & 15, q4 = (lane >> 4) * 4;
   load(wf[0], xf[0], kw);
-  if (kLate) load(wf[1], xf[1], kw + kStep);
-  // What the epilogue of the small forms (registers) needs from memory is requested under the first
-  // tiles: positions, rotary angles, residual and gain of the blocks this wave finishes.
-  constexpr bool kAhead = KW >= WM * WN;  // at most one block per wave: kw / WN, kw % WN
+  // What the epilogue needs from memory is requested under the first tiles: positions, rotary angles, residual and gain of the
+  // block that this wave finishes, kw / WN, kw % WN.
   PlainAhead<T> pf;
-  if constexpr (kAhead) {
-    if (kw < WM * WN) {
-      const int tok = (tt0 + kw % WN) * 16 + tl;
-      plain_fetch<T, EPI>(pf, g, tok, (ft0 + kw / WN) * 16 + q4);
-    }
-  }
-  // RMS Norm factors: the sums of squares of this wave's tokens, added up by lane groups (four parts at a time).  Waves that
-  // share the K loop share them too and request theirs here, under the first tiles; a wave on its own adds them up behind the
-  // loop.  (Pairs of parts one after the other took 4 of 14 us in a form of 32 x 32, 8 of 36 in the wide one: bf16, 1065 rows, 64
-  // parts.)  It requests 32 parts of a token at once in float, whose accumulators and operands leave one wave a SIMD either way,
-  // and 16 in bf16: 32 took the wide form from 240 to 280 registers and so from two waves to one (a block of 5120 wide, 20 / 4
-  // heads, FFN 8960, 4000 rows: 2991 us against 3479; 1024 wide, FFN 4096, 1065 rows: 168 against 180).
+  if (kw < WM * WN) plain_fetch<T, EPI>(pf, g, (tt0 + kw % WN) * 16 + tl, (ft0 + kw / WN) * 16 + q4);
+  // RMS Norm factors: the sums of squares of this wave's tokens, added up by lane groups (four parts at a time), a share of them
+  // per wave, requested here, under the first tiles.  (Pairs of parts one after the other behind the loop took 4 of 14 us in
+  // bf16: 1065 rows, 64 parts.)
   constexpr bool kNorm = EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU;
-  constexpr int kSsq = 4, kTogether = sizeof(T) == 2 ? 4 : 8;
+  constexpr int kSsq = 4;
   const int row = lane >> 4;
   float sq[WN][kSsq];
   auto part = [&](int p, int j) { return p < g.ssq_parts ? g.ssq_in[(size_t)p * g.rows_pad + min(tt0 + j, a.tt - 1) * 16 + tl] : 0.f; };
-  if constexpr (kNorm && KW > 1) {
+  if constexpr (kNorm) {
 #pragma unroll
     for (int j = 0; j < WN; ++j)
 #pragma unroll
@@ -173,64 +156,218 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
   // pairs of whole groups, then what is left (checked tile by tile)
   int t = kw;
   for (; t + 2 * kStep - KW < a.tiles; t += 2 * kStep) {
-    if (!kLate) load(wf[1], xf[1], t + kStep);
+    load(wf[1], xf[1], t + kStep);
     use(std::true_type(), wf[0], xf[0], t);
     load(wf[0], xf[0], t + 2 * kStep);
     use(std::true_type(), wf[1], xf[1], t + kStep);
-    if (kLate) load(wf[1], xf[1], t + 3 * kStep);
   }
-  if (!kLate) load(wf[1], xf[1], t + kStep);
+  load(wf[1], xf[1], t + kStep);
   use(std::false_type(), wf[0], xf[0], t);
   use(std::false_type(), wf[1], xf[1], t + kStep);
   float rs[WN];
   if constexpr (kNorm) {
 #pragma unroll
-    for (int j = 0; j < WN; ++j) rs[j] = 0.f;
-    if constexpr (KW > 1) {
-#pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        rs[j] = (sq[j][0] + sq[j][1]) + (sq[j][2] + sq[j][3]);
-        for (int p = (kSsq * KW + kw) * 4 + row; p < g.ssq_parts; p += 4 * KW) rs[j] += part(p, j);
-      }
-    } else {
-      for (int p0 = 0; p0 < g.ssq_parts; p0 += 4 * kTogether) {
-        float v[WN][kTogether];
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-          for (int i = 0; i < kTogether; ++i) v[j][i] = part(p0 + i * 4 + row, j);
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-          for (int i = 0; i < kTogether; ++i) rs[j] += v[j][i];
-      }
-    }
-#pragma unroll
     for (int j = 0; j < WN; ++j) {
+      rs[j] = (sq[j][0] + sq[j][1]) + (sq[j][2] + sq[j][3]);
+      for (int p = (kSsq * KW + kw) * 4 + row; p < g.ssq_parts; p += 4 * KW) rs[j] += part(p, j);
       rs[j] += __shfl_xor(rs[j], 16, 64);
       rs[j] += __shfl_xor(rs[j], 32, 64);
     }
   }
 
+  __shared__ f32x4 red[KW][FW * TW][WM * WN][64];
+  const int slot = fw + FW * tw;
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) red[kw][slot][i * WN + j][lane] = acc[i][j];
+  __shared__ float sq_s[KW][FW * TW][WN][16];
+  if (kNorm && lane < 16)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) sq_s[kw][slot][j][lane] = rs[j];
+  __syncthreads();
+  if constexpr (kNorm)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      rs[j] = sq_s[0][slot][j][tl];
+#pragma unroll
+      for (int w = 1; w < KW; ++w) rs[j] += sq_s[w][slot][j][tl];
+    }
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      if ((i * WN + j) % KW != kw) continue;  // block b is finished by wave b % KW
+      f32x4 s = red[0][slot][i * WN + j][lane];
+#pragma unroll
+      for (int w = 1; w < KW; ++w) s += red[w][slot][i * WN + j][lane];
+      acc[i][j] = s;
+    }
+
+  if constexpr (kNorm)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) rs[j] = 1.0f / sqrtf(rs[j] * a.inv_K + g.eps);
+
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      if ((i * WN + j) % KW != kw) continue;
+      if (ft0 + i >= a.ft || tt0 + j >= a.tt) continue;  // uniform over the wave
+      plain_epilogue<T, EPI, true>(g, a.out_tiles, ft0 + i, (tt0 + j) * 16 + tl, q4, acc[i][j],
+                                     EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU ? rs[j] : 1.f, pf);
+    }
+  if (EPI == PLAIN_FINAL && g.lens_advance && blockIdx.x == 0)
+    for (int b = threadIdx.x; b < g.rows; b += FW * TW * KW * 64) g.lens_advance[b] += 1;
+}
+
+// The same contraction with its operands staged through LDS: WF x WT waves of WM x WN blocks side by side, KW sets of them that
+// share K; NST stages of KW x KS tiles along K rotate through LDS, filled by direct global->LDS wave loads.  A tile of 1 KiB is
+// read back as it lies, a lane's 16 bytes each (no bank conflicts).  Bound by the matrix pipe in float (32 cycles an MFMA of
+// 2 KFLOP), by LDS and the meeting of the waves at each stage in bf16, whose products take an eighth of that: so a stage's
+// fragments are read a stage ahead of its products, behind the barrier that opens the stage before.  (With the reads behind
+// their own barrier: float 1000 x 1024 x 4096 in 64 x 64 82 us, as here, but bf16 19.6 against 17.2, and 128 x 128 32.2 against
+// 23.8 at 1000 x 8192 x 1024.)
+//   <2, 2, 2, 2, 2, 1, 4>  64 x 64, two sets of four waves: 1000 x 1024 x 4096 bf16 26.5 us from registers, 17.2; float 91, 82
+//   <2, 4, 4, 2, 1, 1, 4>  128 x 128 bf16: 1000 x 8192 x 1024 33.3 us from registers (as 128 x 128 of four waves), 23.8 = 720
+//                          TFLOP/s; 4000 x 17920 x 5120 1098, 862 = 850
+//   <4, 4, 2, 2, 1, 1, 3>  the same in four waves, three workgroups to a CU: 4600 x 4192 x 664 45.3 us in the form above, 42.0;
+//                          4000 x 4480 x 5120 323, 316; with one or two workgroups to a CU slower (800 x 4688 x 600: 15.1, 16.1)
+//   <2, 4, 4, 2, 1, 2, 2>  128 x 128 float, two tiles along K a stage: 800 x 8192 x 1024 157 us from registers, 143; 4000 x 17920 x
+//                          5120 6215, 5730 = 128 TFLOP/s; with one tile a stage 166, 6461
+template <typename T, int EPI, int WM, int WN, int WF, int WT, int KW, int KS, int NST>
+__global__ void __launch_bounds__(WF * WT * KW * 64) __attribute__((amdgpu_waves_per_eu(2))) k_plain_gemm(GemmArgs<T> a) {
+  constexpr int FT = WM * WF, TT = WN * WT, WAVES = WF * WT * KW, TPS = KW * KS, LPW = (FT + TT) * TPS / WAVES, STAGE = (FT + TT) * TPS * 1024;
+  static_assert(LPW * WAVES == (FT + TT) * TPS, "every wave issues the same number of loads");
+  typedef __attribute__((address_space(3))) void lds_t;
+  typedef __attribute__((address_space(1))) const void gbl_t;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const PlainGemm<T> &g = a.g;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, tl = lane & 15, q4 = (lane >> 4) * 4;
+  const int kw = wave % KW, fw = wave / KW % WF, tw = wave / KW / WF;
+  const int f_groups = (a.ft + FT - 1) / FT, ft0 = (int)(blockIdx.x % f_groups) * FT, tt0 = (int)(blockIdx.x / f_groups) * TT;
+  const int steps = (a.tiles + TPS - 1) / TPS;
+
+  f32x4 acc[WM][WN];
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // wave load i of a stage: tile `blk` of the workgroup (features, then tokens), the stage's `lk`-th along K; past an edge the
+  // last tile again, whose products are not stored (features, tokens) or not formed (K)
+  const char *src[LPW];
+  int lk[LPW];
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
+    const int lid = wave * LPW + i, blk = lid % (FT + TT);
+    lk[i] = lid / (FT + TT);
+    src[i] = (blk < FT ? (const char *)g.W + (size_t)min(ft0 + blk, a.ft - 1) * a.tiles * 1024
+                       : (const char *)g.X + (size_t)min(tt0 + blk - FT, a.tt - 1) * a.tiles * 1024) + lane * 16;
+  }
+  auto issue = [&](int step, int buf) {  // buf: byte offset of the stage's buffer
+#pragma unroll
+    for (int i = 0; i < LPW; ++i)
+      __builtin_amdgcn_global_load_lds((gbl_t *)(src[i] + (size_t)min(step * TPS + lk[i], a.tiles - 1) * 1024),
+                                       (lds_t *)(lds + buf + (wave * LPW + i) * 1024), 16, 0, 0);
+  };
+#pragma unroll
+  for (int s = 0; s < NST; ++s) issue(s, s * STAGE);
+  // sums of squares of the workgroup's tokens, while the first stages arrive: [interleaved parts][token]
+  constexpr bool kNorm = EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU;
+  constexpr int kToks = TT * 16, kParts = WAVES * 64 / kToks;
+  __shared__ float sq_s[kNorm ? kParts : 1][kToks];
+  if constexpr (kNorm) {
+    const int tok = threadIdx.x % kToks, p0 = threadIdx.x / kToks;
+    const float *from = g.ssq_in + min(tt0 * 16 + tok, a.tt * 16 - 1);
+    float s = 0.f;
+    for (int p = p0; p < g.ssq_parts; p += 8 * kParts) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p + u * kParts < g.ssq_parts ? from[(size_t)(p + u * kParts) * g.rows_pad] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    sq_s[p0][tok] = s;
+  }
+  const char *wbase = lds + (kw * KS * (FT + TT) + fw * WM) * 1024 + lane * 16, *xbase = lds + (kw * KS * (FT + TT) + FT + tw * WN) * 1024 + lane * 16;
+  u32x4 w[2][KS][WM], x[2][KS][WN];
+  auto read = [&](auto which, int at) {
+    constexpr int W = decltype(which)::value;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+#pragma unroll
+      for (int i = 0; i < WM; ++i) w[W][k][i] = *(const u32x4 *)(wbase + at + (k * (FT + TT) + i) * 1024);
+#pragma unroll
+      for (int j = 0; j < WN; ++j) x[W][k][j] = *(const u32x4 *)(xbase + at + (k * (FT + TT) + j) * 1024);
+    }
+  };
+  // all loads but those of the youngest NST - 1 stages have landed (vmcnt), all LDS accesses are done (lgkmcnt 0)
+  constexpr auto wait_for = [](int loads) { return 0x0070 | (loads & 15) | ((loads >> 4) << 14); };
+  static_assert((NST - 1) * LPW < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt(wait_for((NST - 1) * LPW));
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  read(std::integral_constant<int, 0>(), 0);
+  int at = 0;
+  // One stage: its fragments are in registers, and behind the barrier the next one's have landed everywhere and this one's buffer
+  // is nobody's any more.
+  auto stage = [&](auto which, int s) {
+    constexpr int W = decltype(which)::value;
+    __builtin_amdgcn_s_waitcnt(wait_for((NST - 2) * LPW));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    const int next = at + STAGE == NST * STAGE ? 0 : at + STAGE;
+    read(std::integral_constant<int, W ^ 1>(), next);
+    issue(s + NST, at);  // past the end: the last tiles again, in a buffer nobody reads
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+      if (TPS == 1 || s * TPS + kw * KS + k < a.tiles)
+#pragma unroll
+        for (int e = 0; e < kMmaSteps<T>; ++e)
+#pragma unroll
+          for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int i = 0; i < WM; ++i) acc[i][j] = mma<T>(w[W][k][i], x[W][k][j], acc[i][j], e);
+    at = next;
+  };
+  // Float sums are taken out of the accumulators every kRun stages, so that no chain of additions is longer than 256 products.
+  // (Two 1024-wide blocks, FFN 4096, against 64 bits: 2.1e-6 in one chain, 1.0e-6 so, 1.7e-6 in the register form's four.)
+  constexpr int kRun = sizeof(T) == 4 ? 8 : 0;
+  f32x4 sum[kRun != 0 ? WM : 1][kRun != 0 ? WN : 1] = {};
+  auto take_out = [&] {
+    if constexpr (kRun != 0)
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+          sum[i][j] += acc[i][j];
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+  };
+  int s = 0;
+  for (; s + 2 <= steps; s += 2) {
+    stage(std::integral_constant<int, 0>(), s);
+    stage(std::integral_constant<int, 1>(), s + 1);
+    if (kRun != 0 && (s + 2) % kRun == 0) take_out();
+  }
+  if (s < steps) stage(std::integral_constant<int, 0>(), s);
+  if constexpr (kRun != 0)
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) acc[i][j] += sum[i][j];
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // the loads past the end have landed
   if constexpr (KW > 1) {
-    __shared__ f32x4 red[KW][FW * TW][WM * WN][64];
-    const int slot = fw + FW * tw;
+    __syncthreads();
+    f32x4 (*red)[WF * WT][WM * WN][64] = (f32x4 (*)[WF * WT][WM * WN][64])lds;
+    static_assert(KW * WF * WT * WM * WN <= NST * (FT + TT) * TPS, "the waves' sums fit the stages");
+    const int slot = fw + WF * tw;
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
       for (int j = 0; j < WN; ++j) red[kw][slot][i * WN + j][lane] = acc[i][j];
-    __shared__ float sq_s[KW][FW * TW][WN][16];
-    if (kNorm && lane < 16)
-#pragma unroll
-      for (int j = 0; j < WN; ++j) sq_s[kw][slot][j][lane] = rs[j];
     __syncthreads();
-    if constexpr (kNorm)
-#pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        rs[j] = sq_s[0][slot][j][tl];
-#pragma unroll
-        for (int w = 1; w < KW; ++w) rs[j] += sq_s[w][slot][j][tl];
-      }
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -242,22 +379,30 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
         acc[i][j] = s;
       }
   }
-
-  if constexpr (kNorm)
+  float rs[WN];
 #pragma unroll
-    for (int j = 0; j < WN; ++j) rs[j] = 1.0f / sqrtf(rs[j] * a.inv_K + g.eps);
-
+  for (int j = 0; j < WN; ++j) {
+    rs[j] = 1.f;
+    if constexpr (kNorm) {
+      const int tok = (tw * WN + j) * 16 + tl;
+      float s = sq_s[0][tok];
+#pragma unroll
+      for (int p = 1; p < kParts; ++p) s += sq_s[p][tok];
+      rs[j] = 1.0f / sqrtf(s * a.inv_K + g.eps);
+    }
+  }
+  const PlainAhead<T> none;
 #pragma unroll
   for (int i = 0; i < WM; ++i)
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
+      const int ft = ft0 + fw * WM + i, tt = tt0 + tw * WN + j;
       if (KW > 1 && (i * WN + j) % KW != kw) continue;
-      if (ft0 + i >= a.ft || tt0 + j >= a.tt) continue;  // uniform over the wave
-      plain_epilogue<T, EPI, kAhead>(g, a.out_tiles, ft0 + i, (tt0 + j) * 16 + tl, q4, acc[i][j],
-                                     EPI == PLAIN_QKV || EPI == PLAIN_SWIGLU ? rs[j] : 1.f, pf);
+      if (ft >= a.ft || tt >= a.tt) continue;  // uniform over the wave
+      plain_epilogue<T, EPI, false>(g, a.out_tiles, ft, tt * 16 + tl, q4, acc[i][j], rs[j], none);
     }
   if (EPI == PLAIN_FINAL && g.lens_advance && blockIdx.x == 0)
-    for (int b = threadIdx.x; b < g.rows; b += FW * TW * KW * 64) g.lens_advance[b] += 1;
+    for (int b = threadIdx.x; b < g.rows; b += WAVES * 64) g.lens_advance[b] += 1;
 }
 
 // ----------------------------------------------------------------------------
@@ -472,15 +617,26 @@ hipError_t plain_begin(const T *hidden_in, float *xres, const T *gain, T *y, flo
   return hipGetLastError();
 }
 
+// The forms of k_plain_gemm that stage through LDS, <WM, WN, WF, WT, KW, KS, NST>
+#define HYP_PLAIN_GEMM_SMALL 2, 2, 2, 2, 2, 1, 4
+#define HYP_PLAIN_GEMM_WIDE_FLOAT 2, 4, 4, 2, 1, 2, 2
+#define HYP_PLAIN_GEMM_WIDE_BF16 2, 4, 4, 2, 1, 1, 4
+#define HYP_PLAIN_GEMM_MANY_BF16 4, 4, 2, 2, 1, 1, 3
+constexpr int plain_gemm_lds(int WM, int WN, int WF, int WT, int KW, int KS, int NST) { return NST * (WM * WF + WN * WT) * KW * KS * 1024; }
+
 template <typename T, int EPI>
 static hipError_t launch_gemm(const PlainGemm<T> &g, hipStream_t s) {
   GemmArgs<T> a = gemm_args<T, EPI>(g);
   auto groups = [](int n, int per) { return (unsigned)((n + per - 1) / per); };
-  // The widest form whose workgroups still fill the chip twice over; below that latency counts, and
-  // more, smaller workgroups with their K loop shared by the waves win.
-  const size_t wide = (size_t)groups(a.ft, 8) * groups(a.tt, 8);
-  if (wide >= 512) k_plain_gemm<T, EPI, 4, 4, 2, 2, 1><<<groups(a.ft, 8) * groups(a.tt, 8), 256, 0, s>>>(a);
-  else k_plain_gemm<T, EPI, 2, 2, 1, 1, 4><<<groups(a.ft, 2) * groups(a.tt, 2), 256, 0, s>>>(a);
+  const int form = plain_gemm_form((int)sizeof(T), g.rows, g.N, g.K, EPI == PLAIN_QKV, EPI == PLAIN_SWIGLU);
+  const unsigned wide = groups(a.ft, 8) * groups(a.tt, 8);
+#define LAUNCH(GRID, THREADS, ...) k_plain_gemm<T, EPI, __VA_ARGS__><<<GRID, THREADS, plain_gemm_lds(__VA_ARGS__), s>>>(a)
+  if (form == PLAIN_GEMM_REGISTERS) k_plain_gemm<T, EPI, 2, 2, 1, 1, 4><<<groups(a.ft, 2) * groups(a.tt, 2), 256, 0, s>>>(a);
+  else if (form == PLAIN_GEMM_SMALL) LAUNCH(groups(a.ft, 4) * groups(a.tt, 4), 512, HYP_PLAIN_GEMM_SMALL);
+  else if constexpr (sizeof(T) == 4) LAUNCH(wide, 512, HYP_PLAIN_GEMM_WIDE_FLOAT);
+  else if (form == PLAIN_GEMM_MANY) LAUNCH(wide, 256, HYP_PLAIN_GEMM_MANY_BF16);
+  else LAUNCH(wide, 512, HYP_PLAIN_GEMM_WIDE_BF16);
+#undef LAUNCH
   return hipGetLastError();
 }
 
@@ -517,6 +673,14 @@ hipError_t plain_init() {
   if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<float, NF, KW>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024);  \
   if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_plain_attn<bf16_t, NF, KW>, hipFuncAttributeMaxDynamicSharedMemorySize, NF * KW * 1024); \
   HYP_PLAIN_ATTN(X)
+#undef X
+#define X(T, EPI, ...)  \
+  if (e == hipSuccess) \
+    e = hipFuncSetAttribute((const void *)k_plain_gemm<T, EPI, __VA_ARGS__>, hipFuncAttributeMaxDynamicSharedMemorySize, plain_gemm_lds(__VA_ARGS__));
+#define Y(T, ...) X(T, PLAIN_QKV, __VA_ARGS__) X(T, PLAIN_SWIGLU, __VA_ARGS__) X(T, PLAIN_RESID, __VA_ARGS__) X(T, PLAIN_FINAL, __VA_ARGS__)
+  Y(float, HYP_PLAIN_GEMM_SMALL) Y(float, HYP_PLAIN_GEMM_WIDE_FLOAT)
+  Y(bf16_t, HYP_PLAIN_GEMM_SMALL) Y(bf16_t, HYP_PLAIN_GEMM_WIDE_BF16) Y(bf16_t, HYP_PLAIN_GEMM_MANY_BF16)
+#undef Y
 #undef X
   return e;
 }
