@@ -28,6 +28,32 @@ template <> __device__ __forceinline__ f32x4 mma<bf16_t>(u32x4 a, u32x4 b, f32x4
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
 }
 
+// Exchanges between the lanes of a wave without the LDS pipe, whose shuffles take 60 ns each, one behind the other: the values of
+// both rows of 16 lanes of a half, of both halves; a lane's value O lanes on in its row, or behind.
+struct LanePair { float a, b; };
+__device__ __forceinline__ LanePair both_rows(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ LanePair both_halves(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+template <int CTRL> __device__ __forceinline__ float lane_dpp(float v) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+template <int O> __device__ __forceinline__ float lane_on(float v) { return lane_dpp<0x100 + O>(v); }      // row_shl; 0 past the row
+template <int O> __device__ __forceinline__ float lane_round(float v) { return lane_dpp<0x120 + O>(v); }   // row_ror
+// over the four lanes l % 16 of the wave's rows: as __shfl_xor 16, then 32
+__device__ __forceinline__ float rows_sum(float v) {
+  const LanePair r = both_rows(v), h = both_halves(r.a + r.b);
+  return h.a + h.b;
+}
+__device__ __forceinline__ float rows_max(float v) {
+  const LanePair r = both_rows(v), h = both_halves(fmaxf(r.a, r.b));
+  return fmaxf(h.a, h.b);
+}
+
 // four consecutive elements: one wide access where `vec` says the address allows it
 template <typename T> struct Four;
 template <> struct Four<float> { typedef f32x4 V; };
@@ -234,8 +260,7 @@ __device__ __forceinline__ void plain_epilogue(const PlainGemm<T> &g, int out_ti
 #pragma clang fp contract(off)
         s = (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
       }
-      s += __shfl_xor(s, 16, 64);
-      s += __shfl_xor(s, 32, 64);
+      s = rows_sum(s);
       if (lane < 16 && live) g.ssq_out[(size_t)ft * g.rows_pad + tok] = s;
     }
   }

@@ -156,8 +156,11 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(FI
                 }
                 // 16 features: the lanes of four (float) or two (bf16) neighbouring chunks of the row
                 float s = E == 4 ? q[0] : q[0] + q[E / 4 - 1];
-                s += __shfl_xor(s, TB, 64);
-                if (E == 4) s += __shfl_xor(s, 2 * TB, 64);
+                s += TB == 4 ? lane_on<4>(s) : lane_round<8>(s);
+                if (E == 4) {
+                  if (TB == 4) s += lane_round<8>(s);
+                  else { const LanePair r = both_rows(s); s = r.a + r.b; }
+                }
                 const int chunk = c / TB, per = 16 / E;
                 if (c < chunks && chunk % per == 0) ps[chunk / per * TB + c % TB] = s;
               }
@@ -227,8 +230,7 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(FI
       float s = (sq[j][0] + sq[j][1]) + (sq[j][2] + sq[j][3]);
       for (int p = wave * 4 + row + kSsq * 4 * KW; p < g.ssq_parts; p += 4 * KW)
         s += FIRST ? ps[p * TB + tl % TB] : g.ssq_in[(size_t)p * g.rows_pad + min(j, a.tt - 1) * 16 + tl];
-      s += __shfl_xor(s, 16, 64);
-      s += __shfl_xor(s, 32, 64);
+      s = rows_sum(s);
       if (lane < 16) sq_s[wave][j][lane] = s;
     }
   }
@@ -265,42 +267,44 @@ __global__ void __launch_bounds__(KW * 64) __attribute__((amdgpu_waves_per_eu(FI
 // ----------------------------------------------------------------------------
 // NF: 16-feature blocks the registers hold, a multiple of what d needs
 // FULL: the head size fills them, so that no access is under a condition
-template <typename T, int NF, int KW, bool FULL>
-__global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
+// NV: blocks of them whose values this workgroup takes, of part `part`; fewer than NF: with FULL only
+template <typename T, int NF, int NV, int KW, bool FULL>
+__device__ __forceinline__ void plain_dec_attn(const AttnArgs<T> &a, int col0, int part) {
+  static_assert(NV == NF || FULL, "parts of a head that fills its registers");
   constexpr int NC = NF * (int)sizeof(T) / 4;  // K tiles: 16 floats or 32 bf16 each
   constexpr int kSets = NF <= 8 ? 2 : 1;       // blocks of a wave in flight or in use
-  extern __shared__ __attribute__((aligned(16))) f32x4 o_s[];  // [KW][nf][64]
+  extern __shared__ __attribute__((aligned(16))) f32x4 o_s[];  // [KW][nv][64]
   __shared__ float m_s[KW][4], l_s[KW][4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, row = lane >> 4, g4 = row * 4;
-  const int d = FULL ? NF * 16 : a.cache.d, nf = (d + 15) / 16, nc = plain_tiles(d, sizeof(T));
+  const int d = FULL ? NF * 16 : a.cache.d, nf = (d + 15) / 16, nv = NV < NF ? NV : nf, f0 = part * NV, nc = plain_tiles(d, sizeof(T));
   const int req = blockIdx.x / a.split, share = blockIdx.x % a.split, kvh = blockIdx.y;
-  const int col = blockIdx.z * 4 + (lane & 3), head = kvh * a.G + min(col, a.G - 1);  // this lane's column
+  const int col = col0 + (lane & 3), head = kvh * a.G + min(col, a.G - 1);  // this lane's column
   const int last = a.lens[req];
   const u32x4 *kp = (const u32x4 *)(a.Kc + ((size_t)req * a.cache.nkv + kvh) * a.cache.k_elems(sizeof(T))) + lane;
   const T *vp = a.Vc + ((size_t)req * a.cache.nkv + kvh) * a.cache.v_elems() + lane * 4;
   const u32x4 *qp = (const u32x4 *)(a.q + ((size_t)req * a.nq + head) * a.q_ld) + row;
   const int first = share * KW + wave, step = a.split * KW;
   u32x4 kS[kSets][NC], qf[NC];
-  typename VRaw<T>::V vS[kSets][NF];
-  auto load = [&](u32x4 (&k)[NC], typename VRaw<T>::V (&v)[NF], int kb) {
+  typename VRaw<T>::V vS[kSets][NV];
+  auto load = [&](u32x4 (&k)[NC], typename VRaw<T>::V (&v)[NV], int kb) {
 #pragma unroll
     for (int c = 0; c < NC; ++c)
       if (c < nc) k[c] = kp[((size_t)kb * nc + c) * 64];
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
-      if (f < nf) v[f] = *(const typename VRaw<T>::V *)(vp + ((size_t)kb * nf + f) * 256);
+    for (int f = 0; f < NV; ++f)
+      if (f < nv) v[f] = *(const typename VRaw<T>::V *)(vp + ((size_t)kb * nf + f0 + f) * 256);
   };
 #pragma unroll
   for (int c = 0; c < NC; ++c)
     if (c < nc) qf[c] = qp[c * 4];
   // before the context's length is known: the request's room bounds what may be read
   load(kS[0], vS[0], min(first, a.cache.key_blocks - 1));
-  f32x4 o[NF];
+  f32x4 o[NV];
 #pragma unroll
-  for (int f = 0; f < NF; ++f) o[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int f = 0; f < NV; ++f) o[f] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
   const int n_kb = (last >> 4) + 1;
-  auto block = [&](u32x4 (&kf)[NC], typename VRaw<T>::V (&v)[NF], int kb) {
+  auto block = [&](u32x4 (&kf)[NC], typename VRaw<T>::V (&v)[NV], int kb) {
     f32x4 s = {0.f, 0.f, 0.f, 0.f}, s1 = s;  // two chains
 #pragma unroll
     for (int c = 0; c < NC; ++c)
@@ -312,18 +316,18 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
           else to = mma<T>(kf[c], qf[c], to, e);
         }
     s += s1;
-    f32x4 vf[NF];
+    f32x4 vf[NV];
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
-      if (f < nf) vf[f] = widen_v4<T>(v[f]);
+    for (int f = 0; f < NV; ++f)
+      if (f < nv) vf[f] = widen_v4<T>(v[f]);
     const bool edge = kb == n_kb - 1;  // the only block with slots past the last key
     float p[4], mx = -INFINITY;
     if constexpr (sizeof(T) == 4) {
       // a lane's score is that of one key: 4 ((lane / 4) % 4) + quad_reg(row)
       p[0] = rows_sum4(s) * a.scale;
       if (edge && kb * 16 + (lane & 12) + quad_reg(row) > last) p[0] = -INFINITY;
-      mx = fmaxf(p[0], __shfl_xor(p[0], 4, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 8, 64));
+      mx = fmaxf(p[0], lane_round<8>(p[0]));
+      mx = fmaxf(mx, lane_round<4>(mx));
     } else {
       // a lane's scores are those of keys 4 row .. + 3
 #pragma unroll
@@ -333,8 +337,7 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
         mx = fmaxf(mx, p[i]);
       }
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = rows_max(mx);
     const float m_new = fmaxf(m_run, mx);
     const float ref = m_new == -INFINITY ? 0.f : m_new;
     const float corr = expf(m_run - ref);
@@ -351,19 +354,19 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
       l_run = l_run * corr + ((p[0] + p[1]) + (p[2] + p[3]));
     }
 #pragma unroll
-    for (int f = 0; f < NF; ++f) o[f] *= corr;
+    for (int f = 0; f < NV; ++f) o[f] *= corr;
     if (edge)
       // slots past the last cached key hold anything: no product may meet them
 #pragma unroll
-      for (int f = 0; f < NF; ++f)
+      for (int f = 0; f < NV; ++f)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (f < nf && kb * 16 + g4 + i > last) vf[f][i] = 0.f;
+          if (f < nv && kb * 16 + g4 + i > last) vf[f][i] = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int f = 0; f < NF; ++f)
-        if (f < nf) o[f] = __builtin_amdgcn_mfma_f32_4x4x1f32(vf[f][i], p[i], o[f], 0, 0, 0);
+      for (int f = 0; f < NV; ++f)
+        if (f < nv) o[f] = __builtin_amdgcn_mfma_f32_4x4x1f32(vf[f][i], p[i], o[f], 0, 0, 0);
   };
   if constexpr (kSets == 2) {
     load(kS[1], vS[1], min(first + step, n_kb - 1));  // past the end: the last block again, not used
@@ -387,15 +390,14 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
   if constexpr (NF <= 8) asm volatile("" : "+v"(at));
   // sum of the probabilities over the lanes that hold different keys
   if constexpr (sizeof(T) == 4) {
-    l_run += __shfl_xor(l_run, 4, 64);
-    l_run += __shfl_xor(l_run, 8, 64);
+    l_run += lane_round<8>(l_run);
+    l_run += lane_round<4>(l_run);
   }
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = rows_sum(l_run);
   if (at < 4) { m_s[wave][at] = m_run; l_s[wave][at] = l_run; }
 #pragma unroll
-  for (int f = 0; f < NF; ++f)
-    if (f < nf) o_s[(wave * nf + f) * 64 + at] = o[f];
+  for (int f = 0; f < NV; ++f)
+    if (f < nv) o_s[(wave * nv + f) * 64 + at] = o[f];
   __syncthreads();
   const int c = at & 3;
   float m = m_s[0][c];  // -inf: a share without a key, whose weights and sums are 0
@@ -407,14 +409,14 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
     wgt[w] = m_s[w][c] == -INFINITY ? 0.f : expf(m_s[w][c] - m);
     l += wgt[w] * l_s[w][c];
   }
-  const int col_at = blockIdx.z * 4 + c, head_at = kvh * a.G + min(col_at, a.G - 1);
-  for (int f = wave; f < nf; f += KW) {
+  const int col_at = col0 + c, head_at = kvh * a.G + min(col_at, a.G - 1);
+  for (int f = wave; f < nv; f += KW) {
     f32x4 r = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < KW; ++w)
-      r += o_s[(w * nf + f) * 64 + at] * wgt[w];  // zeros of a share without a key
+      r += o_s[(w * nv + f) * 64 + at] * wgt[w];  // zeros of a share without a key
     const float v = rows_sum4(r);  // the rows hold the sums over different keys
-    const int feat = f * 16 + (at & 12) + quad_reg(at >> 4);
+    const int feat = (f0 + f) * 16 + (at & 12) + quad_reg(at >> 4);
     if (col_at >= a.G || feat >= d) continue;
     if (a.split > 1) {
       float *dst = a.part + (((size_t)req * a.nq + head_at) * a.split + share) * (2 + d);
@@ -424,6 +426,20 @@ __global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
       store_f32(a.out + plain_offset<T>(req, head_at * d + feat, a.out_tiles), v / l);
     }
   }
+}
+
+template <typename T, int NF, int KW, bool FULL>
+__global__ void __launch_bounds__(KW * 64) k_plain_dec_attn(AttnArgs<T> a) {
+  plain_dec_attn<T, NF, NF, KW, FULL>(a, blockIdx.z * 4, 0);
+}
+
+// A few heads of a short context: each in PARTS workgroups, which all form the head's probabilities and take a share of the value
+// features.  A CU takes 64 bytes a clock, so one of 16 workgroups (4 requests, 4 KV heads) needs 3.6 us for the 536 float keys and
+// values of 128 features alone; nothing has to be merged.  (That kernel: 10.1 us in one part, 8.1 in two, 7.3 in four; bf16 of 64
+// features 6.8, 6.2, 6.0; float of 64 features, one request of 80 keys, 2 heads: 3.7, 3.6, 4.4.)
+template <typename T, int NF, int PARTS, int KW>
+__global__ void __launch_bounds__(KW * 64) k_plain_dec_attn_parts(AttnArgs<T> a) {
+  plain_dec_attn<T, NF, NF / PARTS, KW, true>(a, blockIdx.z / PARTS * 4, blockIdx.z % PARTS);
 }
 
 // one workgroup per (head, request): the shares of a split decode attention in order
@@ -541,6 +557,13 @@ hipError_t plain_attn_decode(const T *q, int q_ld, const T *Kc, const T *Vc, T *
   a.lens = lens; a.part = part;
   const int groups = column_groups(dm), nf = (dm.d + 15) / 16, nc = plain_tiles(dm.d, sizeof(T));
   a.split = plain_attn_split((int)sizeof(T), dm.d, (size_t)batch * dm.nkv * groups, longest);
+  const int parts = plain_attn_parts(dm.d, (size_t)batch * dm.nkv * groups, a.split);
+  if (parts > 1) {
+    const dim3 grid(batch, dm.nkv, groups * parts);
+    if (dm.d == 64) k_plain_dec_attn_parts<T, 4, 2, 8><<<grid, 8 * 64, 8 * 2 * 1024, s>>>(a);
+    else k_plain_dec_attn_parts<T, 8, 4, 8><<<grid, 8 * 64, 8 * 2 * 1024, s>>>(a);
+    return hipGetLastError();
+  }
   const dim3 grid(batch * a.split, dm.nkv, groups);
   const int nf_tiles = nc * 4 / (int)sizeof(T);
   hipError_t e = hipErrorInvalidValue;

@@ -170,8 +170,7 @@ __global__ void __launch_bounds__(FW * TW * KW * 64) k_plain_gemm(GemmArgs<T> a)
     for (int j = 0; j < WN; ++j) {
       rs[j] = (sq[j][0] + sq[j][1]) + (sq[j][2] + sq[j][3]);
       for (int p = (kSsq * KW + kw) * 4 + row; p < g.ssq_parts; p += 4 * KW) rs[j] += part(p, j);
-      rs[j] += __shfl_xor(rs[j], 16, 64);
-      rs[j] += __shfl_xor(rs[j], 32, 64);
+      rs[j] = rows_sum(rs[j]);
     }
   }
 
@@ -470,8 +469,7 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
       if (edge && kb * 16 + g4 + i > qpos) s[i] = -INFINITY;
       mx = fmaxf(mx, s[i]);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = rows_max(mx);
     const float m_new = fmaxf(m_run, mx);
     const float ref = m_new == -INFINITY ? 0.f : m_new;  // nothing visible yet
     const float corr = expf(m_run - ref);
@@ -539,8 +537,7 @@ __global__ void __launch_bounds__(KW * 64) k_plain_attn(AttnArgs<T> a) {
       block(kS[0], vS[0], kb);
     }
   }
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = rows_sum(l_run);
   if (lane < 16) { m_s[wave][tl] = m_run; l_s[wave][tl] = l_run; }
 #pragma unroll
   for (int f = 0; f < NF; ++f)
