@@ -609,11 +609,36 @@ __device__ __forceinline__ void decode_short(const bf16_t *qdec, const bf16_t *K
   out[frag_offset(req, (kvh * G + g) * 128 + d, nq * 128)] = f2bf_dev(o / l);
 }
 
-template <int AHEAD>
+// Workgroup e = id - first beyond those of the attention proper: the first bytes of one row group of the next launch's weights, into
+// the L2 of the XCD that is going to stream them (workgroups go to the XCDs in turn, from the same one in every launch; what L2
+// holds outlives a launch).  Attention over short contexts leaves HBM idle while it waits for lengths, keys and its waves.
+// (With 28 MiB of the 50 of the O projection of a Phi-3 block: batch 1, 64 - 192 keys: attention 4.8 -> 5.8 us, O 11.4 -> 9.4;
+// a decode block of batch 16 x 400 keys 132.9 -> 132.0 us, of 32 x 100 146.3 -> 143.5; Llama3-8B, batch 16 x 400: 100.8 -> 98.5.
+// Beside the merge of longer contexts, which is shorter, it made a block 0.7 % slower.)
+__device__ __forceinline__ void read_ahead(const ReadAhead &r, int first, int id) {
+  const int group = (id - first) / 8 * 8 + id % 8;
+  if (group >= r.groups) return;
+  constexpr int kRound = kShortWaves * 64 * 16, kAtOnce = 8;
+  const char *p = (const char *)r.W + (size_t)group * r.group_stride + threadIdx.x * 16;
+  for (int at = 0; at < r.group_bytes; at += kAtOnce * kRound) {
+    f32x4_t v[kAtOnce];
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) v[u] = *(const f32x4_t *)(p + min(at + u * kRound, r.group_bytes - kRound));
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) asm volatile("" ::"v"(v[u]));
+  }
+}
+
+// READS: with workgroups that read ahead; looking for them costs the others 0.2 us
+template <int AHEAD, bool READS>
 __global__ void __launch_bounds__(kShortWaves * 64) __attribute__((amdgpu_waves_per_eu(AHEAD == 1 ? 4 : 2)))
 k_attn_decode_short(const bf16_t *__restrict__ qdec, const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc, CacheGeom geom,
-                    const int *__restrict__ lens, bf16_t *__restrict__ out, int nq, int G) {
+                    const int *__restrict__ lens, bf16_t *__restrict__ out, int nq, int G, int batch, ReadAhead ahead) {
   __shared__ ShortLds lds;
+  if (READS && (int)blockIdx.y >= batch) {
+    read_ahead(ahead, batch * gridDim.x, blockIdx.y * gridDim.x + blockIdx.x);
+    return;
+  }
   decode_short<AHEAD>(qdec, Kc, Vc, geom, lens, out, nq, G, blockIdx.x, blockIdx.y, lds);
 }
 
@@ -730,13 +755,24 @@ size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks) {
 
 hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
-                            int max_chunks, int chunk_keys, int form, hipStream_t s) {
+                            int max_chunks, int chunk_keys, int form, const ReadAhead &ahead, hipStream_t s) {
   int G = nq / nkv;
   const dim3 chunks(max_chunks, nkv, batch), heads(nkv, batch);
+  // the workgroups that read ahead: one per row group, whole rounds of the XCDs, behind the others; whole rounds of their threads
+  ReadAhead ra = ahead;
+  constexpr int kRound = kShortWaves * 64 * 16;
+  ra.group_bytes = std::min(ra.group_bytes, ra.group_stride) / kRound * kRound;
+  if (ra.group_bytes == 0) ra.groups = 0;
+  const dim3 short_grid(nkv, batch + ((ra.groups + 7) / 8 * 8 + nkv - 1) / nkv);
+  auto launch_short = [&](auto ahead) {
+    constexpr int kAhead = decltype(ahead)::value;
+    if (ra.groups) k_attn_decode_short<kAhead, true><<<short_grid, kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G, batch, ra);
+    else k_attn_decode_short<kAhead, false><<<heads, kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G, batch, ra);
+  };
   hipError_t e = hipSuccess;
   switch (form) {
-    case DEC_ATTN_SHORT: k_attn_decode_short<1><<<heads, kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G); break;
-    case DEC_ATTN_SHORT2: k_attn_decode_short<2><<<heads, kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, out, nq, G); break;
+    case DEC_ATTN_SHORT: launch_short(std::integral_constant<int, 1>()); break;
+    case DEC_ATTN_SHORT2: launch_short(std::integral_constant<int, 2>()); break;
     case DEC_ATTN_CHUNKED:
       k_attn_decode<2, false><<<chunks, 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, max_chunks, chunk_keys);
       if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -130,9 +130,15 @@ constexpr int kShortKeys = 512;
 inline int mfma_decode_attn_form(int longest) {
   return longest <= kShortKeys / 2 ? DEC_ATTN_SHORT : longest <= kShortKeys ? DEC_ATTN_SHORT2 : DEC_ATTN_CHUNKED;
 }
+// What the short forms read into L2 beside their own work, for the launch behind them: the first group_bytes of each of `groups`
+// row groups of group_stride bytes, which workgroup g of that launch is going to stream (XCD g % 8).  No groups: nothing.
+struct ReadAhead {
+  const bf16_t *W = nullptr;
+  int groups = 0, group_stride = 0, group_bytes = 0;
+};
 hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom,
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
-                            int max_chunks, int chunk_keys, int form, hipStream_t s);
+                            int max_chunks, int chunk_keys, int form, const ReadAhead &ahead, hipStream_t s);
 size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks);
 // keys per decode-attention chunk (one wave each, one wave per SIMD): the largest power-of-two
 // multiple of 128 up to 1024 that still gives the longest context about 512 waves over all

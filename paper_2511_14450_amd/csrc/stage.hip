@@ -524,9 +524,16 @@ hyp_status_t decode_step_mfma(hyp_stage *st, hipStream_t s, const DecScratch &sc
     const LayerPtrs &p = L.layers[l];
     const DecGemv a = qkv(l);
     if (l > 0) PROF(st, HYP_K_GEMV_QKV, mfma_dec_gemv(DEC_QKV, HYP_K_GEMV_QKV, a, s));
+    // 28 of the 32 MiB that the L2s hold together; narrow layers' kernels wait for latency, not for bytes (512 wide: 11 % slower)
+    ReadAhead ahead;
+    const size_t o_bytes = (size_t)2 * d.H * d.qd;
+    if (L.g_o.ksplit == 1 && o_bytes >= (16u << 20)) {
+      ahead.W = at<bf16_t>(st, p.wo);
+      ahead.groups = d.H / (32 * L.g_o.fbw); ahead.group_stride = (int)(o_bytes / ahead.groups); ahead.group_bytes = (28 << 20) / ahead.groups;
+    }
     PROF(st, HYP_K_ATTN_DECODE, mfma_attn_decode(a.qdec, a.Kc, a.Vc, geom, a.lens, sc.attn_part,
                                                  attn, d.nq, d.nkv, st->batch,
-                                                 L.max_chunks, L.chunk_keys, attn_form, s));
+                                                 L.max_chunks, L.chunk_keys, attn_form, ahead, s));
     DecGemv o = base;
     o.W = at<bf16_t>(st, p.wo); o.x = attn; o.N = d.H; o.K = d.qd; o.plan = L.g_o;
     o.gain = at<bf16_t>(st, p.g2); o.y_out = y; o.ssq_out = ssq;
