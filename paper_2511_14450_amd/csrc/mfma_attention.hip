@@ -359,11 +359,13 @@ __device__ __forceinline__ void decode_clear(DecodeAcc &a) {
   a.m = -INFINITY;
   a.l = 0.f;
 }
+__device__ __forceinline__ void decode_load(const bf16_t *cache, size_t off, bf16x8_t (&f)[8]) {
+#pragma unroll
+  for (int t = 0; t < 8; ++t) f[t] = __builtin_nontemporal_load((const bf16x8_t *)(cache + off + t * kTileElems));
+}
 __device__ __forceinline__ void decode_load(const bf16_t *Kc, const bf16_t *Vc, size_t off, bf16x8_t (&kf)[8], bf16x8_t (&vf)[8]) {
-#pragma unroll
-  for (int t = 0; t < 8; ++t) kf[t] = __builtin_nontemporal_load((const bf16x8_t *)(Kc + off + t * kTileElems));
-#pragma unroll
-  for (int t = 0; t < 8; ++t) vf[t] = __builtin_nontemporal_load((const bf16x8_t *)(Vc + off + t * kTileElems));
+  decode_load(Kc, off, kf);
+  decode_load(Vc, off, vf);
 }
 // fragments of a block, in registers or fetched as they are used (read ahead they would cost every launch registers, and
 // half its waves)
@@ -382,15 +384,18 @@ struct MemFrags {
 // is rescaled when some maximum of the wave has moved, always, or - the first block - never: the same bits, an unmoved
 // maximum's factor is 1.
 enum { RESCALE_MOVED, RESCALE_ALWAYS, RESCALE_NEVER };
-// q(dt), k(dt), v(4 step + d block): the fragments.
-template <int RESCALE, typename Q, typename K, typename V>
-__device__ __forceinline__ void decode_block(DecodeAcc &a, int kb, int nkeys, int hh, Q q, K k, V v) {
+// q(dt), k(dt), v(4 step + d block): the fragments; keys_read(), values_read(): called once those of k and v are no longer needed.
+struct Nothing { __device__ __forceinline__ void operator()() const {} };
+template <int RESCALE, typename Q, typename K, typename V, typename KeysRead = Nothing, typename ValuesRead = Nothing>
+__device__ __forceinline__ void decode_block(DecodeAcc &a, int kb, int nkeys, int hh, Q q, K k, V v,
+                                             KeysRead keys_read = KeysRead(), ValuesRead values_read = ValuesRead()) {
   const float c = kLog2e * 0.08838834764831845f;
   f32x16_t s;
 #pragma unroll
   for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k(dt), q(dt), s, 0, 0, 0);
+  keys_read();
   float p[16];
   float mx = -INFINITY;
   if ((kb + 1) * 32 > nkeys) {  // only the last block of a request can hold keys past the end
@@ -435,6 +440,7 @@ __device__ __forceinline__ void decode_block(DecodeAcc &a, int kb, int nkeys, in
     a.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v(db), pf0, a.o[db], 0, 0, 0);
     a.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v(4 + db), pf1, a.o[db], 0, 0, 0);
   }
+  values_read();
 }
 
 // A batch whose contexts are all short runs another form (k_attn_decode_short).  The host chooses by the lengths it knows;
@@ -449,17 +455,23 @@ __device__ __forceinline__ float merge_sum(float sum, float w, float l) {
 }
 __device__ __forceinline__ float merge_out(float acc, float w, float o) { return fmaf(w, o, acc); }
 
-template <int NSETS, bool RECORDED>
-__global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ qdec,
-                                                    const bf16_t *__restrict__ Kc,
-                                                    const bf16_t *__restrict__ Vc, CacheGeom geom,
-                                                    const int *__restrict__ lens, float *__restrict__ part,
-                                                    int nq, int G, int max_chunks, int chunk_keys) {
+// A wave streams its chunk through one register set of keys and one of values: the next block's keys are requested as soon as
+// the scores are formed, its values behind P V.  That is 192 registers and two waves per SIMD, which wait in turn; two sets of
+// each left room for one.  The pairs are the fastest dimension of the grid: workgroup i runs on XCD i % 8, and with the chunks
+// fastest the few that a short context has fell on the same XCDs (4 or 8 chunks of which 1 is there: on two or one of the eight).
+// Together: 8 x 10 pairs of 8200 keys 62.6 -> 53.5 us (6.3 TB/s), 32 x 8 of 1000 30.4 -> 25.6, 32 x 10 ragged of 1K - 4K in
+// pages 71.1 -> 69.7 (5.8 TB/s); steps of one block at 32 x 10 pairs of 1000 keys in room for 4000 230 -> 180 us.
+// The last block stands behind the loop: no load sits under a condition between two uses, which would make the compiler wait
+// for everything.
+template <bool RECORDED>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+k_attn_decode(const bf16_t *__restrict__ qdec, const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc, CacheGeom geom,
+              const int *__restrict__ lens, float *__restrict__ part, int nq, int G, int max_chunks, int chunk_keys) {
   const int lane = threadIdx.x, hh = lane >> 5, tl = lane & 31;
-  const int chunk = blockIdx.x, kvh = blockIdx.y, req = blockIdx.z;
+  const int kvh = blockIdx.x, req = blockIdx.y, chunk = blockIdx.z;
   int len;
   if (RECORDED) {
-    const int mine = batch_len(lens, gridDim.z, lane);
+    const int mine = batch_len(lens, gridDim.y, lane);
     if (all_short(mine)) return;
     len = __builtin_amdgcn_readlane(mine, req);
   } else {
@@ -478,53 +490,23 @@ __global__ void __launch_bounds__(64) k_attn_decode(const bf16_t *__restrict__ q
 
   DecodeAcc acc;
   decode_clear(acc);
-  bf16x8_t kS[NSETS][8], vS[NSETS][8];
-  auto load_block = [&](int j, bf16x8_t (&kf)[8], bf16x8_t (&vf)[8]) {
-    decode_load(Kc, Vc, geom.off(req, kvh, kb_begin + j) + lane * 8, kf, vf);
+  bf16x8_t kf[8], vf[8];
+  auto place = [&](int kb) { return geom.off(req, kvh, min(kb, kb_end - 1)) + lane * 8; };
+  auto load = [](const bf16_t *cache, size_t at, bf16x8_t (&f)[8]) {
+    __builtin_amdgcn_sched_barrier(0);
+    decode_load(cache, at, f);
+    __builtin_amdgcn_sched_barrier(0);
   };
-  auto compute_block = [&](int j, const bf16x8_t (&kf)[8], const bf16x8_t (&vf)[8]) {
-    decode_block<RESCALE_MOVED>(acc, kb_begin + j, nkeys, hh, RegFrags{qf}, RegFrags{kf}, RegFrags{vf});
-  };
-  // NSETS register sets: the loads of the next NSETS - 1 blocks are in flight while one is used.
-  // The j-th block lives in set j % NSETS.  No load sits under a condition between two
-  // uses: the compiler counts outstanding loads per path, and a load that may or may not have
-  // been issued makes it wait for everything.  So: a steady loop of whole groups of NSETS
-  // blocks, then one of NSETS straight-line endings chosen by the number of loads still to issue.
-  const int n = kb_end - kb_begin;
-  if (n < NSETS - 1) {
-    for (int j = 0; j < n; ++j) {
-      load_block(j, kS[0], vS[0]);
-      compute_block(j, kS[0], vS[0]);
-    }
-  } else {
-#pragma unroll
-    for (int u = 0; u < NSETS - 1; ++u) load_block(u, kS[u], vS[u]);
-    int i = 0;
-    for (; i + 2 * NSETS - 1 <= n; i += NSETS) {
-#pragma unroll
-      for (int u = 0; u < NSETS; ++u) {
-        load_block(i + u + NSETS - 1, kS[(u + NSETS - 1) % NSETS], vS[(u + NSETS - 1) % NSETS]);
-        __builtin_amdgcn_sched_barrier(0);
-        compute_block(i + u, kS[u], vS[u]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    const int r = n - (i + NSETS - 1);  // loads still to issue, 0 .. NSETS - 1
-    auto ending = [&](auto R) {
-      constexpr int kR = decltype(R)::value;
-#pragma unroll
-      for (int u = 0; u < kR + NSETS - 1; ++u) {
-        if (u < kR) load_block(i + u + NSETS - 1, kS[(u + NSETS - 1) % NSETS], vS[(u + NSETS - 1) % NSETS]);
-        __builtin_amdgcn_sched_barrier(0);
-        compute_block(i + u, kS[u % NSETS], vS[u % NSETS]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    if (r == 0) ending(std::integral_constant<int, 0>());
-    else if (r == 1) ending(std::integral_constant<int, 1>());
-    else if (r == 2 || NSETS < 4) ending(std::integral_constant<int, NSETS < 3 ? 1 : 2>());
-    else ending(std::integral_constant<int, NSETS < 4 ? 1 : 3>());
+  size_t at = place(kb_begin);
+  load(Kc, at, kf);
+  load(Vc, at, vf);
+  at = place(kb_begin + 1);
+  for (int kb = kb_begin; kb < kb_end - 1; ++kb) {
+    decode_block<RESCALE_MOVED>(acc, kb, nkeys, hh, RegFrags{qf}, RegFrags{kf}, RegFrags{vf},
+                                [&] { load(Kc, at, kf); }, [&] { load(Vc, at, vf); });
+    at = place(kb + 2);
   }
+  decode_block<RESCALE_MOVED>(acc, kb_end - 1, nkeys, hh, RegFrags{qf}, RegFrags{kf}, RegFrags{vf});
   // lanes tl < G hold real heads
   float l_tot = xhalf_sum(acc.l);
   if (tl < G) {
@@ -757,7 +739,7 @@ hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
                             int max_chunks, int chunk_keys, int form, const ReadAhead &ahead, hipStream_t s) {
   int G = nq / nkv;
-  const dim3 chunks(max_chunks, nkv, batch), heads(nkv, batch);
+  const dim3 chunks(nkv, batch, max_chunks), heads(nkv, batch);
   // the workgroups that read ahead: one per row group, whole rounds of the XCDs, behind the others; whole rounds of their threads
   ReadAhead ra = ahead;
   constexpr int kRound = kShortWaves * 64 * 16;
@@ -774,12 +756,12 @@ hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *
     case DEC_ATTN_SHORT: launch_short(std::integral_constant<int, 1>()); break;
     case DEC_ATTN_SHORT2: launch_short(std::integral_constant<int, 2>()); break;
     case DEC_ATTN_CHUNKED:
-      k_attn_decode<2, false><<<chunks, 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, max_chunks, chunk_keys);
+      k_attn_decode<false><<<chunks, 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, max_chunks, chunk_keys);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       k_attn_decode_merge<<<dim3(nq, batch), 128, 0, s>>>(part, lens, out, nq, max_chunks, chunk_keys);
       break;
     case DEC_ATTN_RECORDED:
-      k_attn_decode<2, true><<<chunks, 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, max_chunks, chunk_keys);
+      k_attn_decode<true><<<chunks, 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, nq, G, max_chunks, chunk_keys);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       k_attn_decode_recorded_end<<<heads, kShortWaves * 64, 0, s>>>(qdec, Kc, Vc, geom, lens, part, out, nq, G, max_chunks, chunk_keys);
       break;

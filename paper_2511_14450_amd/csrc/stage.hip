@@ -57,6 +57,11 @@ struct LayerPtrs {
   size_t g1, wqkv, wo, g2, wgu, wd;  // offsets into the workspace
 };
 
+// Where the temporaries of a decode step of the MFMA path lie in the GPU's static array.
+struct StaticScratch {
+  size_t counters = 0, xres = 0, ssq = 0, y = 0, attn = 0, m = 0, qdec = 0, partial = 0, attn_part = 0, bytes = 0;
+};
+
 // Where everything lives inside the caller's workspace.
 struct Layout {
   std::vector<LayerPtrs> layers;
@@ -78,6 +83,7 @@ struct Layout {
   int chunk_keys = 128; // keys per chunk
   GemvPlan g_qkv, g_o, g_gu, g_d;  // how the four skinny GEMMs of a decode step are cut into workgroups
   size_t partial_bytes = 0, attn_part_bytes = 0, counters_bytes = 0;
+  StaticScratch stat;
   // paged KV cache (HYP_FLAG_PAGED_KV): pages per layer of the pool, table entries per request
   size_t page_table = 0;
   int pool_pages = 0, pages_per_req = 0;
@@ -113,6 +119,22 @@ Dims dims_of(const hyp_stage_config_t &c) {
   d.I = c.ffn_dim; d.qd = d.nq * d.d; d.kvd = d.nkv * d.d;
   d.max_batch = c.max_batch; d.max_seq = c.max_seq; d.eps = c.rms_eps;
   return d;
+}
+
+StaticScratch static_scratch(const Dims &d, const Layout &L) {
+  const size_t es = 2, H = d.H;
+  StaticScratch o;
+  auto take = [&](size_t bytes) { const size_t at = o.bytes; o.bytes = align_up(o.bytes + bytes); return at; };
+  o.counters = take(L.counters_bytes);
+  o.xres = take(sizeof(float) * 32 * H);
+  o.ssq = take(sizeof(float) * 32 * (H / 32));
+  o.y = take(es * 32 * H);
+  o.attn = take(es * 32 * (size_t)d.qd);
+  o.m = take(es * 32 * (size_t)d.I);
+  o.qdec = take(es * (size_t)d.max_batch * d.nkv * 32 * 128);
+  o.partial = take(L.partial_bytes);
+  o.attn_part = take(L.attn_part_bytes);
+  return o;
 }
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
@@ -216,11 +238,16 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
                                std::max(mfma_gemv_partial_floats(L.g_gu, (int)(2 * I), (int)H), mfma_gemv_partial_floats(L.g_d, (int)H, (int)I)));
     L.partial_bytes = sizeof(float) * pf;
     L.partial = take(L.partial_bytes);
-    L.chunk_keys = mfma_decode_chunk_keys(c.max_seq, c.max_batch * c.n_kv_heads);
-    L.max_chunks = (c.max_seq + L.chunk_keys - 1) / L.chunk_keys;
-    L.attn_part_bytes = sizeof(float) * mfma_attn_decode_part_floats(c.n_q_heads, c.max_batch, L.max_chunks);
-    L.attn_part = take(L.attn_part_bytes);
     L.counters_bytes = sizeof(unsigned) * (2 * I / 64 + (qd + 2 * kvd) / 64 + H / 32);
+    // more chunks per context hold more partial results: not where the static array would become too small for them
+    for (bool even : {true, false}) {
+      L.chunk_keys = mfma_decode_chunk_keys(c.max_seq, c.max_batch * c.n_kv_heads, even);
+      L.max_chunks = (c.max_seq + L.chunk_keys - 1) / L.chunk_keys;
+      L.attn_part_bytes = sizeof(float) * mfma_attn_decode_part_floats(c.n_q_heads, c.max_batch, L.max_chunks);
+      L.stat = static_scratch(dims_of(c), L);
+      if (L.stat.bytes <= kNoAllocScratchBytes) break;
+    }
+    L.attn_part = take(L.attn_part_bytes);
     L.counters = take(L.counters_bytes);
     L.gemm_counters = take(sizeof(unsigned) * (kGemmShortMaxTiles + 1));  // zeroed together with `counters`
     L.ssq = take(sizeof(float) * 32 * (H / 32));
@@ -782,20 +809,14 @@ hyp_status_t do_stage_create(const hyp_stage_config_t *cfg, int32_t l_start, int
     e = static_scratch_of_current_device(&sbase);
     if (e != hipSuccess) { st->err = std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e); return bail(HYP_EDEVICE); }
     {
-      const size_t es = 2, H = d.H;
-      size_t off = 0;
-      auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
-      const size_t o_cnt = take(L.counters_bytes), o_xres = take(sizeof(float) * 32 * H), o_ssq = take(sizeof(float) * 32 * (H / 32)),
-                   o_y = take(es * 32 * H), o_attn = take(es * 32 * (size_t)d.qd), o_m = take(es * 32 * (size_t)d.I),
-                   o_q = take(es * (size_t)d.max_batch * d.nkv * 32 * 128), o_part = take(L.partial_bytes),
-                   o_ap = take(L.attn_part_bytes);
-      st->static_bytes = off;
-      if (off <= kNoAllocScratchBytes) {
+      const StaticScratch &o = L.stat;
+      st->static_bytes = o.bytes;
+      if (o.bytes <= kNoAllocScratchBytes) {
         char *b = (char *)sbase;
         DecScratch &t = st->dec_static;
-        t.counters = (unsigned *)(b + o_cnt); t.xres = (float *)(b + o_xres); t.ssq = (float *)(b + o_ssq);
-        t.y = (bf16_t *)(b + o_y); t.attn = (bf16_t *)(b + o_attn); t.m = (bf16_t *)(b + o_m); t.qdec = (bf16_t *)(b + o_q);
-        t.partial = (float *)(b + o_part); t.attn_part = (float *)(b + o_ap);
+        t.counters = (unsigned *)(b + o.counters); t.xres = (float *)(b + o.xres); t.ssq = (float *)(b + o.ssq);
+        t.y = (bf16_t *)(b + o.y); t.attn = (bf16_t *)(b + o.attn); t.m = (bf16_t *)(b + o.m); t.qdec = (bf16_t *)(b + o.qdec);
+        t.partial = (float *)(b + o.partial); t.attn_part = (float *)(b + o.attn_part);
       }
     }
     rc = pack_weights_mfma(st, layers);
