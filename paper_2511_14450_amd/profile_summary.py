@@ -22,7 +22,7 @@ import sys
 
 # kernel class, as bench.py and hyp_stage.h name it, of every kernel of the MFMA path.  The GEMM
 # kernels carry their class as a template argument (a hyp_kernel_class_t; k_gemm's second, k_dec_gemv's
-# last), so the O and down projections, which share an epilogue, have different names in a trace.
+# last number), so the O and down projections, which share an epilogue, have different names in a trace.
 CLASS_BY_ID = {1: "gemm_qkv", 3: "gemm_o", 4: "gemm_gateup", 5: "gemm_down",
                6: "gemv_qkv", 9: "gemv_o", 10: "gemv_gateup", 12: "gemv_down"}
 CLASS_BY_NAME = [(r"k_attn_prefill", "attn_prefill"), (r"k_attn_decode_merge", "attn_decode_merge"),
@@ -40,7 +40,7 @@ def short(name: str) -> str:
 
 def classify(row) -> str:
     n = short(row["Kernel_Name"])
-    m = re.match(r"k_gemm<\d+, (\d+)|k_dec_gemv<.*?(\d+)>$", n)
+    m = re.match(r"k_gemm<\d+, (\d+)|k_dec_gemv<.*?(\d+)(?:, (?:true|false))?>$", n)
     if m:
         return CLASS_BY_ID.get(int(m.group(1) or m.group(2)), n)
     for pat, cls in CLASS_BY_NAME:
