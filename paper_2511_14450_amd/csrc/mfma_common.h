@@ -87,17 +87,22 @@ struct CacheGeom {
 
 __device__ inline bf16_t f2bf_dev(float f) { return f32_to_bf16(f); }
 
-// The sum over the 32 lanes of a half wave, or over all 64, in every lane: the additions of a butterfly of __shfl_xor 32 or 16
-// .. 1, in that order, by lane swaps and row rotations (values that agree under an exchange by 8 may as well be rotated by 4).
-// Six of the shuffles, each a trip through the LDS pipe, took 0.3 us at the end of a decode step's residual kernels.
-template <int LANES> __device__ __forceinline__ float lanes_sum(float v) {
+// The sum of the squares of x over the 32 lanes of a half wave, or over all 64, in the lowest of them (the others get something
+// else).  The additions are those of a butterfly of __shfl_xor LANES / 2 .. 1, in that order, the first one with a lane's own square
+// fused in (fma(x, x, square from LANES / 2 on)), by lane swaps and row rotations (values that agree under an exchange by 8 may
+// as well be rotated by 4).  As shuffles, each a trip through the LDS pipe, they took 0.3 us at the end of a decode step's residual
+// kernels.
+template <int LANES> __device__ __forceinline__ float lanes_sum_squares(float x) {
   static_assert(LANES == 32 || LANES == 64, "half a wave or a wave");
-  if (LANES == 64) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const unsigned sq = __float_as_uint(x * x);
+  float v;
+  if constexpr (LANES == 64) {
+    v = fmaf(x, x, __uint_as_float(__builtin_amdgcn_permlane32_swap(sq, sq, false, false)[1]));  // [1]: the upper half's values
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  } else {
+    v = fmaf(x, x, __uint_as_float(__builtin_amdgcn_permlane16_swap(sq, sq, false, false)[1]));  // the odd rows'
   }
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   auto moved = [](float x, auto ctrl) {
     return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, true));
   };

@@ -453,7 +453,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
       if (EPI == DEC_RESID) {
         p.xres[(size_t)b * p.H + n0 + f] = xn;
         p.y_out[frag_offset(b, n0 + f, p.H)] = f2bf_dev(xn * gain_pf[j]);
-        const float ss = lanes_sum<kGroupRows>(xn * xn);  // over the lanes of the token
+        const float ss = lanes_sum_squares<kGroupRows>(xn);  // over the lanes of the token
         if (f == 0) p.ssq_out[group * 32 + b] = ss;
       } else {
         p.hidden_out[(size_t)b * p.H + n0 + f] = f2bf_dev(xn);
@@ -486,7 +486,7 @@ __global__ void __launch_bounds__(kBeginWaves * 64) k_dec_begin(const bf16_t *__
     if (b >= batch) break;
     xres[(size_t)b * H + n] = x[u];
     y_out[frag_offset(b, n, H)] = f2bf_dev(x[u] * g);
-    const float ss = lanes_sum<64>(x[u] * x[u]);
+    const float ss = lanes_sum_squares<64>(x[u]);
     if (lane == 0) ssq_out[blockIdx.x * 32 + b] = ss;
   }
 }
