@@ -113,6 +113,10 @@ template <int LANES> __device__ __forceinline__ float lanes_sum_squares(float x)
   return v;
 }
 
+// A value that another workgroup of the same launch has stored at device scope.  A load at device scope, too: a plain one could
+// be served from a line that this XCD's L2 has kept from an earlier launch, as what is read ahead for a later launch is.
+__device__ __forceinline__ float load_shared(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 __device__ inline bf16x4_t pack4(float a, float b, float c, float d) {
   bf16x4_t r;
   r.v[0] = f2bf_dev(a); r.v[1] = f2bf_dev(b); r.v[2] = f2bf_dev(c); r.v[3] = f2bf_dev(d);

@@ -330,11 +330,10 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
     __syncthreads();  // `red` is free from here on
     if (!is_last) return;
     fetch();
-    // The finishing workgroup.  Plain loads are enough here: every 256-byte run of `partial` has exactly one
-    // writer in this launch, this XCD's L2 was invalidated when the launch began,
-    // and nothing in this launch read these lines before, so a line is either
-    // absent (fetched from memory, where the writer's store has completed) or was
-    // put there by a writer on this very XCD.  With more than four slices, two (token, row)
+    // The finishing workgroup.  Its loads are device-scope ones (load_shared): `partial` is the same room in every split GEMV of
+    // every step, and what this XCD's L2 holds of it from an earlier launch must not be taken for this one's.  (Against plain
+    // loads: steps of one block of four widths, 5120 / 17920 to 8192 / 28672, batch 1 - 32, within 0.2 % either way.  An acquire fence,
+    // which invalidates L2 under the other workgroups' streams, costs 10 % of a step.)  With more than four slices, two (token, row)
     // pairs per thread and GW slices of each are in flight at once; slices beyond ksplit are masked
     // rather than peeled, so the gather costs ceil(ksplit / GW) round trips.
     constexpr int GW = 16;
@@ -348,7 +347,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
           const bool has = idx < n_pairs;
           const unsigned off = has ? (unsigned)((idx / kGroupRows) * part_n + part_r0 + idx % kGroupRows) : 0u;
 #pragma unroll
-          for (int u = 0; u < 4; ++u) v[j][u] = has && u < ksplit ? (part + (size_t)u * 32 * part_n)[off] : 0.f;
+          for (int u = 0; u < 4; ++u) v[j][u] = has && u < ksplit ? load_shared(part + (size_t)u * 32 * part_n + off) : 0.f;
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -370,8 +369,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EP
           for (int u = 0; u < GW; ++u) {
             const bool in = s + u < ksplit;
             const float *slice = part + (size_t)(s + u) * 32 * part_n;
-            v0[u] = in ? slice[off0] : 0.f;
-            v1[u] = in && has1 ? slice[off1] : 0.f;
+            v0[u] = in ? load_shared(slice + off0) : 0.f;
+            v1[u] = in && has1 ? load_shared(slice + off1) : 0.f;
           }
 #pragma unroll
           for (int u = 0; u < GW; ++u) { sum0 += v0[u]; sum1 += v1[u]; }

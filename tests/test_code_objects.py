@@ -15,10 +15,10 @@ if not READELF.exists():
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{mangled name: {"vgprs", "spilled", "scratch"}} of every kernel of the library"""
-    blob, magic, found = build.LIB.read_bytes(), b"__CLANG_OFFLOAD_BUNDLE__", {}
-    at, tmp = blob.find(magic), tmp_path_factory.mktemp("code") / "object.elf"
+def objects(tmp_path_factory):
+    """the library's gfx950 code objects, as files"""
+    blob, magic, files = build.LIB.read_bytes(), b"__CLANG_OFFLOAD_BUNDLE__", []
+    at, tmp = blob.find(magic), tmp_path_factory.mktemp("code")
     while at >= 0:
         count, = struct.unpack_from("<Q", blob, at + len(magic))
         entry = at + len(magic) + 8
@@ -28,15 +28,36 @@ def kernels(tmp_path_factory):
             entry += 24 + name_len
             if "gfx950" not in name or not size:
                 continue
-            tmp.write_bytes(blob[at + offset:at + offset + size])
-            notes = subprocess.run([str(READELF), "--notes", str(tmp)], capture_output=True, text=True, check=True).stdout
-            for part in notes.split("  - .agpr_count:")[1:]:
-                def number(key):
-                    return int(re.search(rf"\.{key}:\s+(\d+)", part)[1])
-                found[re.search(r"\.name:\s+(\S+)", part)[1]] = {
-                    "vgprs": number("vgpr_count"), "spilled": number("vgpr_spill_count"), "scratch": number("private_segment_fixed_size")}
+            files.append(tmp / f"object{len(files)}.elf")
+            files[-1].write_bytes(blob[at + offset:at + offset + size])
         at = blob.find(magic, at + 1)
+    return files
+
+
+@pytest.fixture(scope="module")
+def kernels(objects):
+    """{mangled name: {"vgprs", "spilled", "scratch"}} of every kernel of the library"""
+    found = {}
+    for path in objects:
+        notes = subprocess.run([str(READELF), "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+        for part in notes.split("  - .agpr_count:")[1:]:
+            def number(key):
+                return int(re.search(rf"\.{key}:\s+(\d+)", part)[1])
+            found[re.search(r"\.name:\s+(\S+)", part)[1]] = {
+                "vgprs": number("vgpr_count"), "spilled": number("vgpr_spill_count"), "scratch": number("private_segment_fixed_size")}
     assert len(found) > 50
+    return found
+
+
+@pytest.fixture(scope="module")
+def code(objects):
+    """{mangled name: its instructions, one a line}"""
+    found = {}
+    for path in objects:
+        text = subprocess.run([str(READELF.with_name("llvm-objdump")), "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout
+        for part in re.split(r"^[0-9a-f]+ <", text, flags=re.M)[1:]:
+            name, _, body = part.partition(">:")
+            found[name] = body
     return found
 
 
@@ -67,3 +88,15 @@ def test_generic_decode_contractions_do_not_spill(kernels):
 def test_generic_decode_attention_does_not_spill(kernels):
     for name, k in pick(kernels, r"16k_plain_dec_attnI[ft]L", 10).items():
         assert k["spilled"] == 0 and k["scratch"] == 0, (name, k)
+
+
+# The last workgroup of a split row group or tile to arrive reads what the others have stored in the same launch: at device scope (sc1), as
+# they stored it, or a line that its L2 has kept from an earlier launch could answer.
+@pytest.mark.parametrize("pattern,count", [
+    (r"10k_dec_gemvILi1ELi2ELi8ELi10E(Lb0E)?E", 1), (r"10k_dec_gemvILi[23]ELi2ELi8ELi(9|12)E(Lb0E)?E", 3),  # gate/up; O, down and the last down
+    (r"6k_gemmILi\dELi\dENS0_8GemmFormILi\dELi\dELi[12]E", 10)])                                             # the prefill forms of up to 128 tokens
+def test_partial_sums_of_other_workgroups_are_read_at_device_scope(code, pattern, count):
+    for name, text in pick(code, pattern, count).items():
+        lines = [line for line in text.splitlines() if " sc1" in line.split("//")[0]]
+        stores, loads = ([line for line in lines if f"global_{what}_dword" in line] for what in ("store", "load"))
+        assert stores and len(loads) >= 16, (name, len(stores), len(loads))
