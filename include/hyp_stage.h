@@ -61,8 +61,9 @@ typedef enum {
 typedef enum { HYP_F32 = 0, HYP_BF16 = 1 } hyp_dtype_t;
 
 /* hyp_stage_config_t.flags */
-#define HYP_FLAG_NO_GRAPH 2u      /* launch the decode-step kernels one by one in deep stages too    \
-                                     (more than 8 blocks), instead of replaying a recorded HIP graph */
+#define HYP_FLAG_NO_GRAPH 2u      /* launch the decode-step kernels one by one in deep stages too        \
+                                     (more than 8 blocks; more than 2 whose weights are under 128 MiB    \
+                                     a block), instead of replaying a recorded HIP graph                 */
 #define HYP_FLAG_PAGED_KV 4u      /* keep the KV cache in pages of HYP_KV_PAGE_KEYS keys addressed through a \
                                      page table (stage_set_page_table) instead of one slab per request; \
                                      stages on the MFMA kernels only                                   */

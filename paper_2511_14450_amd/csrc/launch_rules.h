@@ -85,6 +85,20 @@ inline int plain_gemm_form(int esize, int rows, int N, int K, bool qkv, bool swi
 }
 
 // ----------------------------------------------------------------------------
+// A decode step's kernels one by one, or a recorded HIP graph of them?  A replay takes the host 25 us + 1.5 us a block, launches
+// 14 us a block; but a replay stands apart from what the stream runs before and behind it: one by one, one Phi-3 block takes 121 us
+// instead of 126 (batch 8 at 2100 keys 143 instead of 147.5, a Llama3-8B block 88 / 92, a 512-wide one 20 / 25), eight Phi-3 blocks 1005 /
+// 1009.  One by one where the host is then no slower, up to two blocks, or where it can't hold up the device: in stages of up to
+// eight blocks whose weights take longer to stream than their launches (128 MiB at 6.6 TB/s: 20 us), however many stages
+// a thread feeds on the GPU.  (Three stages on three streams fed by one thread, us for a step of each, one by one / replayed: 512 wide, one block 64 /
+// 110, two 105 / 114, three 143 / 120, eight 417 / 194; 1024 wide, FFN 4096, two 105 / 112, three 143 / 122, eight 422 / 332.  Two Llama3-8B stages:
+// three blocks 439 / 448, eight 1188 / 1192.)
+// ----------------------------------------------------------------------------
+inline bool decode_step_direct(int blocks, size_t block_weight_bytes) {
+  return blocks <= 2 || (blocks <= 8 && block_weight_bytes >= ((size_t)128 << 20));
+}
+
+// ----------------------------------------------------------------------------
 // How one skinny GEMM of a decode step is cut into workgroups.
 //   fbw     32-row blocks per workgroup: 2 where the epilogue pairs rows of two blocks (gate and up) and
 //           for long K; 1 for the residual GEMMs at short K, which then run as unsplit 4-wave

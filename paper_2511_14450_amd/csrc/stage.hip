@@ -593,19 +593,16 @@ void drop_decode_graph(hyp_stage::DecGraph &g) {
 constexpr size_t kDecGraphs = 12;
 
 // The decode step of a deep stage is recorded into a HIP graph (kernel nodes only) the first time a (batch, output buffer,
-// attention form) is seen and replayed afterwards: the host is done with it in 25 us + 1 us a block instead of 12 us a block.
-// But a replay stands apart from what the stream runs before and behind it: launched one by one, the 5 kernels a block of one
-// Phi-3 block take 121 us instead of 126 (batch 8 at 2100 keys 143 instead of 147.5, a Llama3-8B block 88 / 92, a 512-wide one 21 / 25.5),
-// 8 Phi-3 blocks 1005 / 1009, 3 and 12 512-wide ones 62 / 64.4 and 248 / 258 - and up to a few blocks the host is no slower either (one
-// block 16 us / 24, two 30 / 28, eight 105 / 36).  So stages of at most kDirectBlocks blocks launch their kernels one by one, where
-// the gain shows and the host stays ahead of the narrowest blocks (20 us); so does a step whose kernel classes are being timed, and one
-// that the caller is itself capturing.
-constexpr int kDirectBlocks = 8;
+// attention form) is seen and replayed afterwards.  Others launch their kernels one by one (decode_step_direct); so does a step whose
+// kernel classes are being timed, and one that the caller is itself capturing.
 hyp_status_t run_decode_mfma(hyp_stage *st, const void *hidden_in, void *hidden_out) {
   hipStream_t s = st->stream;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   HIP_TRY(st, hipStreamIsCapturing(s, &cap));
-  bool use_graph = st->n_layers > kDirectBlocks && st->prof_mask == 0 && cap == hipStreamCaptureStatusNone && !(st->cfg.flags & HYP_FLAG_NO_GRAPH);
+  const Dims &d = st->dm;
+  const size_t block_bytes = sizeof(bf16_t) * ((size_t)d.H * (2 * d.qd + 2 * d.kvd) + (size_t)3 * d.H * d.I);
+  const bool use_graph = !decode_step_direct(st->n_layers, block_bytes) && st->prof_mask == 0 && cap == hipStreamCaptureStatusNone &&
+                         !(st->cfg.flags & HYP_FLAG_NO_GRAPH);
   const int attn = decode_attn_form(st, cap != hipStreamCaptureStatusNone);
   if (!use_graph) return decode_step_mfma(st, s, st->dec_ws, hidden_in, hidden_out, attn, true, true);
   // what reads the caller's input stays outside the recording, so a new input address every step does not force a new graph

@@ -17,6 +17,11 @@ int main() {
       if (scanf("%d %d %d %d", &cls, &N, &K, &batch) != 4) return 1;
       const hyp::GemvPlan g = hyp::mfma_gemv_plan(cls, N, K, batch);
       printf("%d %d %d %d\n", g.fbw, g.nw, g.ksplit, g.tail);
+    } else if (!strcmp(what, "direct")) {
+      int blocks;
+      size_t bytes;
+      if (scanf("%d %zu", &blocks, &bytes) != 2) return 1;
+      printf("%d\n", hyp::decode_step_direct(blocks, bytes) ? 1 : 0);
     } else if (!strcmp(what, "gemm")) {
       int rows, N, K, swiglu;
       if (scanf("%d %d %d %d", &rows, &N, &K, &swiglu) != 4) return 1;

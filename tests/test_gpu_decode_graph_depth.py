@@ -1,4 +1,4 @@
-"""Decode steps on either side of the depth at which a stage replays a recorded graph (more than 8 blocks): against the oracle over
+"""Decode steps on either side of the depth at which a stage of narrow blocks replays a recorded graph (more than 2): against the oracle over
 the forms that attention takes as contexts grow, with two output buffers and a prefill in between (Sec. V-A generation), and
 the bits of the same kernels launched one by one."""
 import pytest
@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-2
 
 
-@pytest.mark.parametrize("blocks", [8, 9])
+@pytest.mark.parametrize("blocks", [2, 3, 8, 9])
 def test_steps_of_deep_stages(blocks):
     import torch
     from paper_2511_14450_amd import binding

@@ -86,6 +86,25 @@ def test_plans_deal_all_of_k_and_all_rows(ask):
         assert N % (32 * fbw) == 0 and K // 16 % (nw * ksplit) == 0 and K // 16 // (nw * ksplit) % tail == 0, (cls, N, K, batch)
 
 
+# ---------------------------------------------------------------- decode steps, one by one or recorded
+# weights of a block, blocks: us of a step launched one by one and replayed: a stage on its own stream, and a step of each of several
+# stages that one thread feeds on as many streams (three of 512 and 1024 wide blocks, two Llama3-8B-shaped stages)
+STEPS = [
+    (4.98e6, 1, (20.4, 25.1), (64.2, 110.5)), (4.98e6, 2, (41.9, 44.3), (104.7, 114.0)), (4.98e6, 3, (66.6, 63.9), (142.8, 119.6)),
+    (4.98e6, 4, (84.4, 84.2), (217.0, 120.5)), (4.98e6, 6, (127.8, 127.4), (298.2, 147.4)), (4.98e6, 8, (170.6, 171.0), (416.8, 194.0)),
+    (31.5e6, 1, (28.5, 32.8), (65.6, 105.7)), (31.5e6, 2, (58.5, 63.3), (105.1, 112.0)), (31.5e6, 4, (116.4, 120.7), (214.2, 162.8)),
+    (31.5e6, 8, (231.0, 234.9), (422.1, 332.4)), (436e6, 1, (85.4, 91.1), (142.7, 151.5)), (436e6, 3, (260.7, 265.9), (439.2, 447.8)),
+    (436e6, 8, (695.6, 702.1), (1188.0, 1192.0)),
+]
+
+
+def test_steps_are_launched_one_by_one_only_where_no_thread_is_held_up(ask):
+    for (direct,), (_, blocks, alone, several) in zip(ask([f"direct {n} {int(b)}" for b, n, _, _ in STEPS]), STEPS):
+        for one_by_one, replayed in (alone, several):
+            assert (one_by_one if direct else replayed) <= 1.05 * min(one_by_one, replayed), (blocks, direct)
+    assert ask(["direct 9 1000000000", "direct 20 500000000"]) == [[0], [0]]
+
+
 # ---------------------------------------------------------------- prefill GEMMs
 # internal rows, N, K, gate/up: us of the GEMM in tiles of 128 x 64 (as the rule slices them) and in the wide form
 FORMS = [
