@@ -112,7 +112,7 @@ def test_decode_graph_replays_equal_kernel_by_kernel_launches():
     import torch
     from paper_2511_14450_amd import binding
     shape = SHAPE_G2
-    layers = [synth.layer_weights(shape, l, 708, sigma=0.05) for l in range(2)]
+    layers = [synth.layer_weights(shape, l, 708, sigma=0.05) for l in range(3)]  # more than two narrow blocks: recorded
     lens = [40, 100, 7]
     x = to_dev(synth.hidden_states(sum(lens), shape, 709), "bf16")
     a = make_gpu_stage(shape, layers, 3, 200, 200)
