@@ -157,6 +157,19 @@ inline GemvPlan mfma_gemv_plan(int cls, int N, int K, int batch) {
   return g;
 }
 
+// k-tiles of a wave that are in flight at once.  One window: with all of a wave's tiles requested at the start, in registers that
+// leave room for two or three waves a SIMD instead of four
+constexpr int gemv_window(int fbw, bool one_window) { return one_window ? (fbw == 1 ? 16 : 10) : fbw == 1 ? 10 : 5; }
+
+// One window, for unsplit GEMVs of at most that many tiles a wave whose workgroups all fit the chip at two waves a SIMD: eight-wave ones
+// up to one a CU, four-wave ones up to two.  Beyond, they take a further round, or wait for registers.  (Steps of one block at batch 8, gate/up in one window
+// / in several: 1024 wide, FFN 4096 = 128 workgroups 29.3 / 31.4 us, 8192 = 256 37.5 / 38.7, 8448 = 264 37.3 / 36.8, 16384 = 512
+// 44.2 / 42.8; 1280 wide, FFN 28672 59.1 / 56.7.  QKV: the second of two blocks of 512 x 18432 = 288 workgroups 36.6 / 34.9, of
+// 1280 x 24576 = 384 47.1 / 48.0, of 768 x 36864 = 576 45.4 / 45.0; the opening one there 47.5 / 46.5 and 45.8 / 44.7.)
+inline bool mfma_gemv_one_window(const GemvPlan &g, int N, int K) {
+  return g.ksplit == 1 && g.tail == 1 && K / 16 / g.nw <= gemv_window(g.fbw, true) && N / (32 * g.fbw) * g.nw <= 8 * kCus;
+}
+
 // ----------------------------------------------------------------------------
 // Prefill GEMMs: the form, and the slices of the K loop.
 // ----------------------------------------------------------------------------

@@ -72,9 +72,6 @@ struct DecGemvParams {
   int *lens_advance;  // DEC_FINAL: cached lengths to bump once the step's last kernel finishes
 };
 
-// k-tiles of a wave that are in flight at once.  One window: with all of a wave's tiles requested at the start
-constexpr int gemv_window(int fbw, bool one_window) { return one_window ? (fbw == 1 ? 16 : 10) : fbw == 1 ? 10 : 5; }
-
 // FBW row blocks of 32 per workgroup: 2 where the epilogue pairs rows of two blocks (gate and up) and for long K; 1 or 2 for QKV,
 // whose RoPE partners lie in one block; 1 for the residual epilogues at short K, where 32-row workgroups with
 // a 10-tile window give as many waves with as much in flight as two slices of 64-row workgroups
@@ -83,6 +80,7 @@ constexpr int gemv_window(int fbw, bool one_window) { return one_window ? (fbw =
 // NW waves per workgroup share the k-tiles of the workgroup's K slice: more waves per workgroup mean
 // fewer K slices across workgroups (fewer partial sums in memory, or none) for the same number of
 // waves in flight.
+// SHORT: one window (mfma_gemv_one_window).
 template <int EPI, int FBW, int NW, int CLS, bool SHORT>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(EPI == DEC_QKV_OPEN || SHORT ? 2 : 4))) k_dec_gemv(DecGemvParams p) {
   constexpr bool kOpen = EPI == DEC_QKV_OPEN, kQkv = EPI == DEC_QKV || kOpen, kSsqIn = EPI == DEC_QKV || EPI == DEC_SWIGLU;
@@ -594,7 +592,7 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
   // the waves' sums of the live tokens, and the norm's gain
   const size_t lds = sizeof(float) * nw * a.batch * (fbw * 32 + 4) + (epi == DEC_QKV_OPEN ? sizeof(bf16_t) * a.H : 0);
   if (epi == DEC_QKV_OPEN && (a.K != a.H || (uintptr_t)a.x % 16 != 0 || !mfma_dec_opens(a.H, a.N, a.plan))) return hipErrorInvalidValue;
-  const bool one_window = ksplit == 1 && p.tail == 1 && p.tiles_per_wave <= gemv_window(fbw, true);
+  const bool one_window = mfma_gemv_one_window(a.plan, a.N, a.K);
   bool launched = false;
 #define X(EPI, FBW, NW, CLS)                                                 \
   if (!launched && epi == EPI && fbw == FBW && nw == NW && cls == CLS) {      \

@@ -17,6 +17,10 @@ int main() {
       if (scanf("%d %d %d %d", &cls, &N, &K, &batch) != 4) return 1;
       const hyp::GemvPlan g = hyp::mfma_gemv_plan(cls, N, K, batch);
       printf("%d %d %d %d\n", g.fbw, g.nw, g.ksplit, g.tail);
+    } else if (!strcmp(what, "window")) {
+      int cls, N, K, batch;
+      if (scanf("%d %d %d %d", &cls, &N, &K, &batch) != 4) return 1;
+      printf("%d\n", hyp::mfma_gemv_one_window(hyp::mfma_gemv_plan(cls, N, K, batch), N, K) ? 1 : 0);
     } else if (!strcmp(what, "direct")) {
       int blocks;
       size_t bytes;

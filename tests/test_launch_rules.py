@@ -86,6 +86,20 @@ def test_plans_deal_all_of_k_and_all_rows(ask):
         assert N % (32 * fbw) == 0 and K // 16 % (nw * ksplit) == 0 and K // 16 // (nw * ksplit) % tail == 0, (cls, N, K, batch)
 
 
+# class, rows, K: us of a step of one block (QKV: of the second of two) at batch 8 with that GEMV in one window and in several
+WINDOWS = [
+    (GATEUP, 8192, 1024, 29.3, 31.4), (GATEUP, 16384, 1024, 37.5, 38.7), (GATEUP, 16896, 1024, 37.3, 36.8), (GATEUP, 32768, 1024, 44.2, 42.8),
+    (GATEUP, 16384, 512, 33.6, 35.0), (GATEUP, 24576, 512, 33.6, 33.0), (GATEUP, 49152, 512, 39.9, 37.9), (GATEUP, 20480, 768, 34.9, 34.4),
+    (GATEUP, 18432, 1280, 41.1, 40.1), (GATEUP, 57344, 1280, 59.1, 56.7), (QKV, 18432, 512, 36.6, 34.9), (QKV, 24576, 512, 39.6, 37.3),
+    (QKV, 18432, 1024, 39.3, 39.7), (QKV, 24576, 1024, 43.4, 43.6), (QKV, 24576, 1280, 47.1, 48.0), (QKV, 36864, 768, 45.4, 45.0),
+]
+
+
+def test_windows_are_near_the_best_measured(ask):
+    for (one,), (cls, N, K, in_one, in_several) in zip(ask([f"window {c} {N} {K} 8" for c, N, K, _, _ in WINDOWS]), WINDOWS):
+        assert (in_one if one else in_several) <= 1.02 * min(in_one, in_several), (cls, N, K, one)
+
+
 # ---------------------------------------------------------------- decode steps, one by one or recorded
 # weights of a block, blocks: us of a step launched one by one and replayed: a stage on its own stream, and a step of each of several
 # stages that one thread feeds on as many streams (three of 512 and 1024 wide blocks, two Llama3-8B-shaped stages)
