@@ -548,24 +548,24 @@ bool mfma_gemv_counts(const GemvPlan &g, int N, int K) {
   return g.ksplit > 1 || tail > 1;
 }
 
-// the (epilogue, blocks per workgroup, waves per workgroup, class) combinations a plan may ask for
-#define HYP_GEMV_VARIANTS(X)                                                                             \
-  X(DEC_QKV, 1, 4, HYP_K_GEMV_QKV) X(DEC_QKV, 1, 8, HYP_K_GEMV_QKV) X(DEC_QKV, 2, 8, HYP_K_GEMV_QKV)     \
-  X(DEC_QKV_OPEN, 1, 4, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 1, 8, HYP_K_GEMV_QKV) X(DEC_QKV_OPEN, 2, 8, HYP_K_GEMV_QKV) \
-  X(DEC_SWIGLU, 2, 8, HYP_K_GEMV_GATEUP)                                                                 \
-  X(DEC_RESID, 1, 4, HYP_K_GEMV_O) X(DEC_RESID, 2, 8, HYP_K_GEMV_O)                                      \
-  X(DEC_RESID, 1, 4, HYP_K_GEMV_DOWN) X(DEC_RESID, 2, 8, HYP_K_GEMV_DOWN)                                \
-  X(DEC_FINAL, 1, 4, HYP_K_GEMV_DOWN) X(DEC_FINAL, 2, 8, HYP_K_GEMV_DOWN)
+// the (epilogue, blocks per workgroup, waves per workgroup, class, one window) combinations a plan may ask for; one window ends at
+// 1024 features of K with four waves and at 1280 with eight, and eight share the K of a 32-row workgroup, or of a residual GEMV, only far beyond
+#define HYP_GEMV_VARIANTS(X)                                                                                                   \
+  X(DEC_QKV, 1, 4, HYP_K_GEMV_QKV, false) X(DEC_QKV, 1, 8, HYP_K_GEMV_QKV, false) X(DEC_QKV, 2, 8, HYP_K_GEMV_QKV, false)      \
+  X(DEC_QKV, 1, 4, HYP_K_GEMV_QKV, true) X(DEC_QKV, 2, 8, HYP_K_GEMV_QKV, true)                                                \
+  X(DEC_QKV_OPEN, 1, 4, HYP_K_GEMV_QKV, false) X(DEC_QKV_OPEN, 1, 8, HYP_K_GEMV_QKV, false) X(DEC_QKV_OPEN, 2, 8, HYP_K_GEMV_QKV, false) \
+  X(DEC_QKV_OPEN, 1, 4, HYP_K_GEMV_QKV, true) X(DEC_QKV_OPEN, 2, 8, HYP_K_GEMV_QKV, true)                                      \
+  X(DEC_SWIGLU, 2, 8, HYP_K_GEMV_GATEUP, false) X(DEC_SWIGLU, 2, 8, HYP_K_GEMV_GATEUP, true)                                   \
+  X(DEC_RESID, 1, 4, HYP_K_GEMV_O, false) X(DEC_RESID, 2, 8, HYP_K_GEMV_O, false) X(DEC_RESID, 1, 4, HYP_K_GEMV_O, true)       \
+  X(DEC_RESID, 1, 4, HYP_K_GEMV_DOWN, false) X(DEC_RESID, 2, 8, HYP_K_GEMV_DOWN, false) X(DEC_RESID, 1, 4, HYP_K_GEMV_DOWN, true) \
+  X(DEC_FINAL, 1, 4, HYP_K_GEMV_DOWN, false) X(DEC_FINAL, 2, 8, HYP_K_GEMV_DOWN, false) X(DEC_FINAL, 1, 4, HYP_K_GEMV_DOWN, true)
 
 // the waves' sums of 32 tokens can pass the 64 KiB a workgroup gets by default
 hipError_t mfma_gemv_init() {
   hipError_t e = hipSuccess;
-#define X(EPI, FBW, NW, CLS)                                                                                     \
-  if (e == hipSuccess)                                                                                           \
-    e = hipFuncSetAttribute((const void *)k_dec_gemv<EPI, FBW, NW, CLS, false>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                            (int)(sizeof(float) * NW * 32 * (FBW * 32 + 4)) + (EPI == DEC_QKV_OPEN ? kMaxGainBytes : 0));    \
-  if (e == hipSuccess)                                                                                           \
-    e = hipFuncSetAttribute((const void *)k_dec_gemv<EPI, FBW, NW, CLS, true>, hipFuncAttributeMaxDynamicSharedMemorySize,  \
+#define X(EPI, FBW, NW, CLS, SHORT)                                                                                          \
+  if (e == hipSuccess)                                                                                                       \
+    e = hipFuncSetAttribute((const void *)k_dec_gemv<EPI, FBW, NW, CLS, SHORT>, hipFuncAttributeMaxDynamicSharedMemorySize,  \
                             (int)(sizeof(float) * NW * 32 * (FBW * 32 + 4)) + (EPI == DEC_QKV_OPEN ? kMaxGainBytes : 0));
   HYP_GEMV_VARIANTS(X)
 #undef X
@@ -594,11 +594,10 @@ hipError_t mfma_dec_gemv(int epi, int cls, const DecGemv &a, hipStream_t s) {
   if (epi == DEC_QKV_OPEN && (a.K != a.H || (uintptr_t)a.x % 16 != 0 || !mfma_dec_opens(a.H, a.N, a.plan))) return hipErrorInvalidValue;
   const bool one_window = mfma_gemv_one_window(a.plan, a.N, a.K);
   bool launched = false;
-#define X(EPI, FBW, NW, CLS)                                                 \
-  if (!launched && epi == EPI && fbw == FBW && nw == NW && cls == CLS) {      \
-    if (one_window) k_dec_gemv<EPI, FBW, NW, CLS, true><<<grid, NW * 64, lds, s>>>(p); \
-    else k_dec_gemv<EPI, FBW, NW, CLS, false><<<grid, NW * 64, lds, s>>>(p); \
-    launched = true;                                                         \
+#define X(EPI, FBW, NW, CLS, SHORT)                                                                   \
+  if (!launched && epi == EPI && fbw == FBW && nw == NW && cls == CLS && one_window == SHORT) {         \
+    k_dec_gemv<EPI, FBW, NW, CLS, SHORT><<<grid, NW * 64, lds, s>>>(p);                                 \
+    launched = true;                                                                                    \
   }
   HYP_GEMV_VARIANTS(X)
 #undef X

@@ -90,10 +90,18 @@ def test_generic_decode_attention_does_not_spill(kernels):
         assert k["spilled"] == 0 and k["scratch"] == 0, (name, k)
 
 
+def test_decode_gemvs_do_not_spill_and_one_window_is_built_where_a_plan_has_one(kernels):
+    # (epilogue, row blocks, waves, class): QKV and the opening one in three forms, gate/up in one, O, down and the last down in two
+    in_several, in_one = (pick(kernels, rf"10k_dec_gemvILi\dELi\dELi\dELi\d+ELb{short}EE", count) for short, count in ((0, 13), (1, 8)))
+    for name, k in (in_several | in_one).items():
+        assert k["spilled"] == 0 and k["scratch"] == 0, (name, k)
+        assert k["vgprs"] <= (256 if name in in_one or "k_dec_gemvILi4E" in name else 128), (name, k)  # waves a SIMD: two, four
+
+
 # The last workgroup of a split row group or tile to arrive reads what the others have stored in the same launch: at device scope (sc1), as
 # they stored it, or a line that its L2 has kept from an earlier launch could answer.
 @pytest.mark.parametrize("pattern,count", [
-    (r"10k_dec_gemvILi1ELi2ELi8ELi10E(Lb0E)?E", 1), (r"10k_dec_gemvILi[23]ELi2ELi8ELi(9|12)E(Lb0E)?E", 3),  # gate/up; O, down and the last down
+    (r"10k_dec_gemvILi1ELi2ELi8ELi10ELb0EE", 1), (r"10k_dec_gemvILi[23]ELi2ELi8ELi(9|12)ELb0EE", 3),  # gate/up; O, down and the last down
     (r"6k_gemmILi\dELi\dENS0_8GemmFormILi\dELi\dELi[12]E", 10)])                                             # the prefill forms of up to 128 tokens
 def test_partial_sums_of_other_workgroups_are_read_at_device_scope(code, pattern, count):
     for name, text in pick(code, pattern, count).items():

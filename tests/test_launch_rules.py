@@ -100,6 +100,13 @@ def test_windows_are_near_the_best_measured(ask):
         assert (in_one if one else in_several) <= 1.02 * min(in_one, in_several), (cls, N, K, one)
 
 
+def test_one_window_stays_with_the_forms_it_is_built_for(ask):
+    cases = [(c, N, K, 1) for c in (QKV, O, GATEUP, DOWN) for N in range(256, 65536, 512) for K in range(256, 16384, 256)]
+    plans, windows = ask([f"gemv {c} {n} {k} {b}" for c, n, k, b in cases]), ask([f"window {c} {n} {k} {b}" for c, n, k, b in cases])
+    seen = {(case[0], fbw, nw) for case, (fbw, nw, _, _), (one,) in zip(cases, plans, windows) if one}
+    assert seen == {(QKV, 1, 4), (QKV, 2, 8), (O, 1, 4), (GATEUP, 2, 8), (DOWN, 1, 4)}
+
+
 # ---------------------------------------------------------------- decode steps, one by one or recorded
 # weights of a block, blocks: us of a step launched one by one and replayed: a stage on its own stream, and a step of each of several
 # stages that one thread feeds on as many streams (three of 512 and 1024 wide blocks, two Llama3-8B-shaped stages)
