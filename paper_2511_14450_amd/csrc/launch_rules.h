@@ -170,6 +170,23 @@ inline bool mfma_gemv_one_window(const GemvPlan &g, int N, int K) {
   return g.ksplit == 1 && g.tail == 1 && K / 16 / g.nw <= gemv_window(g.fbw, true) && N / (32 * g.fbw) * g.nw <= 8 * kCus;
 }
 
+// Keys per chunk of decode attention (one wave each, at most two waves per SIMD): the largest power-of-two
+// multiple of 128 up to 1024 that still gives the longest context about 512 waves over all
+// (request, KV head) pairs - chunks of 256 for 8 x 10 pairs in room for 2K keys, 1024 for 8 x 10 pairs at 9K and for 32 x 10
+// pairs from 1025 keys on, 512 up to there (asking for 768 or 1024 waves instead costs a step of one block at 4 x 10 pairs of
+// 6K keys 146.6 -> 151.7 us, 16 x 8 of 3K 126.0 -> 128.7: fewer, longer waves win until a wave's own serial time shows) -
+// doubled until a context has at most 64 chunks.  Between one wave and two per SIMD (1024 .. 2048 waves)
+// some SIMDs would hold two and take longer than the others: `even` halves the chunk there (32 x 10 pairs in room for 3073 - 6144
+// keys; ragged ones of 1K - 4K in pages: the attention 79.6 -> 69.7 us; within 1 % where the contexts are alike).
+inline int mfma_decode_chunk_keys(int max_seq, int heads_in_flight, bool even) {
+  int c = 1024;
+  auto waves = [&] { return (long)heads_in_flight * ((max_seq + c - 1) / c); };
+  while (c > 128 && waves() < 512) c /= 2;
+  if (even && waves() > 1024 && waves() < 2048) c /= 2;
+  while ((max_seq + c - 1) / c > 64) c *= 2;
+  return c;
+}
+
 // ----------------------------------------------------------------------------
 // Prefill GEMMs: the form, and the slices of the K loop.
 // ----------------------------------------------------------------------------

@@ -140,22 +140,6 @@ hipError_t mfma_attn_decode(const bf16_t *qdec, const bf16_t *Kc, const bf16_t *
                             const int *lens, float *part, bf16_t *out, int nq, int nkv, int batch,
                             int max_chunks, int chunk_keys, int form, const ReadAhead &ahead, hipStream_t s);
 size_t mfma_attn_decode_part_floats(int nq, int batch, int max_chunks);
-// keys per decode-attention chunk (one wave each, at most two waves per SIMD): the largest power-of-two
-// multiple of 128 up to 1024 that still gives the longest context about 512 waves over all
-// (request, KV head) pairs - chunks of 256 for 8 x 10 pairs at 2K keys, 1024 for 32 x 10
-// pairs at 1K and for 8 x 10 pairs at 9K (asking for 768 or 1024 waves instead costs a step of one block at 4 x 10 pairs of
-// 6K keys 146.6 -> 151.7 us, 16 x 8 of 3K 126.0 -> 128.7: fewer, longer waves win until a wave's own serial time shows) -
-// doubled until a context has at most 64 chunks.  Between one wave and two per SIMD (1024 .. 2048 waves)
-// some SIMDs would hold two and take longer than the others: `even` halves the chunk there (32 x 10 ragged pairs of 1K - 4K
-// keys in pages: the attention 79.6 -> 69.7 us; within 1 % where the contexts are alike).
-inline int mfma_decode_chunk_keys(int max_seq, int heads_in_flight, bool even) {
-  int c = 1024;
-  auto waves = [&] { return (long)heads_in_flight * ((max_seq + c - 1) / c); };
-  while (c > 128 && waves() < 512) c /= 2;
-  if (even && waves() > 1024 && waves() < 2048) c /= 2;
-  while ((max_seq + c - 1) / c > 64) c *= 2;
-  return c;
-}
 // cache -> plain [len, nkv*128] rows
 hipError_t mfma_export_kv(const bf16_t *Kc, const bf16_t *Vc, CacheGeom geom, bf16_t *k_out,
                           bf16_t *v_out, int request, int len, int nkv, hipStream_t s);

@@ -21,6 +21,10 @@ int main() {
       int cls, N, K, batch;
       if (scanf("%d %d %d %d", &cls, &N, &K, &batch) != 4) return 1;
       printf("%d\n", hyp::mfma_gemv_one_window(hyp::mfma_gemv_plan(cls, N, K, batch), N, K) ? 1 : 0);
+    } else if (!strcmp(what, "chunk")) {
+      int max_seq, pairs, even;
+      if (scanf("%d %d %d", &max_seq, &pairs, &even) != 3) return 1;
+      printf("%d\n", hyp::mfma_decode_chunk_keys(max_seq, pairs, even != 0));
     } else if (!strcmp(what, "direct")) {
       int blocks;
       size_t bytes;

@@ -86,6 +86,25 @@ def test_plans_deal_all_of_k_and_all_rows(ask):
         assert N % (32 * fbw) == 0 and K // 16 % (nw * ksplit) == 0 and K // 16 // (nw * ksplit) % tail == 0, (cls, N, K, batch)
 
 
+# ---------------------------------------------------------------- chunks of decode attention
+def test_chunks_fill_the_chip_with_whole_rounds(ask):
+    got = ask([f"chunk {n} {pairs} {even}" for n, pairs, even, _ in CHUNKS])
+    assert [c for c, in got] == [c for *_, c in CHUNKS]
+    rng = random.Random(4)
+    cases = [(int(2 ** rng.uniform(0, 17.5)), 2 * rng.randint(1, 640)) for _ in range(3000)]
+    for (plain,), (even,), (n, pairs) in zip(ask([f"chunk {n} {p} 0" for n, p in cases]), ask([f"chunk {n} {p} 1" for n, p in cases]), cases):
+        for c in (plain, even):
+            assert c % 128 == 0 and c & (c - 1) == 0 and -(-n // c) <= 64, (n, pairs, c)
+        one_to_two = 1024 < pairs * -(-n // 1024) < 2048  # waves of 1024-key chunks: some SIMDs with two
+        assert even == (plain // 2 if one_to_two and n <= 64 * 512 else plain), (n, pairs, plain, even)
+        assert plain == 1024 or n > 64 * 1024 or pairs * -(-n // (2 * plain)) < 512, (n, pairs, plain)
+
+
+# room for keys, (request, KV head) pairs, even: keys a chunk
+CHUNKS = [(2048, 80, 1, 256), (9216, 80, 1, 1024), (1024, 320, 1, 512), (1025, 320, 1, 1024), (3072, 320, 1, 1024), (3073, 320, 1, 512),
+          (6144, 320, 1, 512), (6145, 320, 1, 1024), (4000, 320, 0, 1024), (100, 2, 1, 128), (100000, 2, 1, 2048), (64 * 128, 2, 1, 128)]
+
+
 # class, rows, K: us of a step of one block (QKV: of the second of two) at batch 8 with that GEMV in one window and in several
 WINDOWS = [
     (GATEUP, 8192, 1024, 29.3, 31.4), (GATEUP, 16384, 1024, 37.5, 38.7), (GATEUP, 16896, 1024, 37.3, 36.8), (GATEUP, 32768, 1024, 44.2, 42.8),
