@@ -67,10 +67,19 @@ def pick(kernels, pattern, count):
     return got
 
 
-def test_wide_bf16_generic_gemms_keep_two_waves_a_simd(kernels):
-    # four epilogues; registers of a wave, accumulators among them: 512 / 2
-    for name, k in pick(kernels, r"12k_plain_gemmItLi\dELi4ELi4ELi2ELi2ELi1E", 4).items():
-        assert k["vgprs"] <= 256 and k["scratch"] == 0, (name, k)
+def test_staged_generic_gemms_keep_their_workgroups_a_cu(kernels):
+    # four epilogues each; registers of a wave, accumulators among them: 512 / 3 with three workgroups of four waves to a CU, 512 / 2 else
+    for pattern, vgprs in ((r"12k_plain_gemmItLi\dELi4ELi4ELi2ELi2ELi1ELi1ELi3E", 168), (r"12k_plain_gemmItLi\dELi2ELi4ELi4ELi2ELi1ELi1ELi4E", 256),
+                           (r"12k_plain_gemmIfLi\dELi2ELi4ELi4ELi2ELi1ELi2ELi2E", 256), (r"12k_plain_gemmI[ft]Li\dELi2ELi2ELi2ELi2ELi2ELi1ELi4E", 256)):
+        for name, k in pick(kernels, pattern, 8 if "[ft]" in pattern else 4).items():
+            assert k["vgprs"] <= vgprs and k["spilled"] == 0 and k["scratch"] == 0, (name, k)
+
+
+def test_decode_attention_keeps_two_waves_a_simd(kernels):
+    # chunked: called directly and recorded; short: one block ahead (four waves a SIMD) and two, with and without reading ahead
+    for pattern, count, vgprs in ((r"13k_attn_decodeILb", 2, 256), (r"19k_attn_decode_shortILi1E", 2, 128), (r"19k_attn_decode_shortILi2E", 2, 256)):
+        for name, k in pick(kernels, pattern, count).items():
+            assert k["vgprs"] <= vgprs and k["spilled"] == 0 and k["scratch"] == 0, (name, k)
 
 
 def test_prefill_gemms_do_not_spill(kernels):
@@ -86,7 +95,7 @@ def test_generic_decode_contractions_do_not_spill(kernels):
 
 
 def test_generic_decode_attention_does_not_spill(kernels):
-    for name, k in pick(kernels, r"16k_plain_dec_attnI[ft]L", 10).items():
+    for name, k in (pick(kernels, r"16k_plain_dec_attnI[ft]L", 10) | pick(kernels, r"22k_plain_dec_attn_partsI[ft]L", 4)).items():
         assert k["spilled"] == 0 and k["scratch"] == 0, (name, k)
 
 

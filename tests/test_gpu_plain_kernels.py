@@ -61,15 +61,25 @@ def test_generic_block_against_oracle(shape, rows, dtype):
     gst.destroy()
 
 
-# 4090 rows and projections of 2048 - 2052 features: QKV, O and down in the wide form (32 x 16 workgroup tiles and more),
-# rows that end inside a tile; a residual whose rows are read four features at a time, and one whose are not
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("shape", [dict(hidden=2050, n_q_heads=24, n_kv_heads=4, head_dim=64, ffn_dim=72),
-                                   dict(hidden=2048, n_q_heads=21, n_kv_heads=3, head_dim=76, ffn_dim=72)],
-                         ids=["hidden2050", "hidden2048"])
+# 4090 rows, which end inside a tile: projections in tiles of 64 x 64, of 128 x 128 and, bf16, of 128 x 128 in four waves, each with a
+# residual whose rows are read four features at a time and one whose are not (the forms they take: WIDE_FORMS, checked on the host)
+WIDE_SHAPES = {"hidden2050": dict(hidden=2050, n_q_heads=24, n_kv_heads=4, head_dim=64, ffn_dim=72),
+               "hidden2048": dict(hidden=2048, n_q_heads=21, n_kv_heads=3, head_dim=76, ffn_dim=72),
+               "hidden2046": dict(hidden=2046, n_q_heads=24, n_kv_heads=4, head_dim=64, ffn_dim=72),
+               "hidden3070": dict(hidden=3070, n_q_heads=96, n_kv_heads=4, head_dim=66, ffn_dim=6150),
+               "hidden3072": dict(hidden=3072, n_q_heads=96, n_kv_heads=4, head_dim=66, ffn_dim=6150)}
+WIDE_LENS = [1500, 1333, 1000, 257]
+# the forms of QKV, gate/up, O, down: registers, 64 x 64 (small), 128 x 128 (wide), the same in four waves (many)
+WIDE_FORMS = {("hidden2050", "f32"): "wide registers small registers", ("hidden2050", "bf16"): "wide small wide wide",
+              ("hidden2048", "f32"): "small registers wide wide", ("hidden2048", "bf16"): "wide small wide wide",
+              ("hidden2046", "f32"): "wide registers wide wide", ("hidden3070", "bf16"): "many many many many",
+              ("hidden3072", "bf16"): "many many many many"}
+
+
+@pytest.mark.parametrize("shape,dtype", list(WIDE_FORMS))
 def test_wide_projections_against_oracle(shape, dtype):
     from paper_2511_14450_amd import binding
-    shp, lens = synth.BlockShape(dtype=dtype, **shape), [1500, 1333, 1000, 257]
+    shp, lens = synth.BlockShape(dtype=dtype, **WIDE_SHAPES[shape]), WIDE_LENS
     w = synth.layer_weights(shp, 0, 35_000, sigma=0.02)
     x = synth.hidden_states(sum(lens), shp, 35_001)
     gst = make_gpu_stage(shp, [w], len(lens), max(lens), sum(lens), flags=binding.HYP_FLAG_PLAIN_KERNELS)

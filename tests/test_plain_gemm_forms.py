@@ -1,5 +1,5 @@
 """Which form a prefill contraction of a generic stage takes (csrc/launch_rules.h): near the best of what was measured, on the host; and
-every form against the oracle at the edges of its tiles, on the device."""
+the forms against the oracle at the edges of their tiles, on the device (the wide ones with every epilogue: test_gpu_plain_kernels.py)."""
 import pathlib
 import shutil
 import subprocess
@@ -10,6 +10,7 @@ import pytest
 from oracle import hyp_oracle as orc
 from workloads import synth
 from tests.helpers import make_gpu_stage, rel_err, to_dev, to_host
+from tests.test_gpu_plain_kernels import WIDE_FORMS, WIDE_LENS, WIDE_SHAPES
 
 ROOT = pathlib.Path(__file__).resolve().parents[1]
 REGISTERS, SMALL, WIDE, MANY = range(4)
@@ -75,6 +76,14 @@ def test_cases_take_the_forms_they_are_made_for(form):
         e, rows = 4 if dtype == "f32" else 2, sum(lens)
         gemms = [((nq + 2 * nkv) * d, H), (2 * I, H), (H, nq * d), (H, I)]
         assert tuple(form([(e, rows, N, K, epi) for epi, (N, K) in enumerate(gemms)])) == forms, name
+
+
+def test_wide_projections_take_the_forms_they_are_made_for(form):
+    for (shape, dtype), forms in WIDE_FORMS.items():
+        b, e, rows = WIDE_SHAPES[shape], 4 if dtype == "f32" else 2, sum(WIDE_LENS)
+        H, q, kv, I = b["hidden"], b["n_q_heads"] * b["head_dim"], b["n_kv_heads"] * b["head_dim"], b["ffn_dim"]
+        got = form([(e, rows, N, K, epi) for epi, (N, K) in enumerate([(q + 2 * kv, H), (2 * I, H), (H, q), (H, I)])])
+        assert [("registers", "small", "wide", "many")[f] for f in got] == forms.split(), (shape, dtype)
 
 
 @pytest.mark.gpu
