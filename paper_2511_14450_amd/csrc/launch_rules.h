@@ -48,7 +48,8 @@ inline int plain_attn_split(int esize, int d, size_t pairs, int longest) {
 }
 
 // Parts of a head's value features that unsplit heads are dealt to, a workgroup each, where every workgroup then still has a CU of
-// its own: four of 128 features, two of 64 (k_plain_dec_attn_parts; other head sizes: one).
+// its own: four of 128 features, two of 64.  Other head sizes: one, since k_plain_dec_attn_parts is built for heads that fill its
+// registers, not because those of 80 or 96 features would not gain.
 inline int plain_attn_parts(int d, size_t pairs, int split) {
   const int parts = d == 128 ? 4 : d == 64 ? 2 : 1;
   return split == 1 && pairs * parts <= (size_t)kCus ? parts : 1;

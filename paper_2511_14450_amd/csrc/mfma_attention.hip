@@ -459,8 +459,8 @@ __device__ __forceinline__ float merge_out(float acc, float w, float o) { return
 // the scores are formed, its values behind P V.  That is 192 registers and two waves per SIMD, which wait in turn; two sets of
 // each left room for one.  The pairs are the fastest dimension of the grid: workgroup i runs on XCD i % 8, and with the chunks
 // fastest the few that a short context has fell on the same XCDs (4 or 8 chunks of which 1 is there: on two or one of the eight).
-// Together: 8 x 10 pairs of 8200 keys 62.6 -> 53.5 us (6.3 TB/s), 32 x 8 of 1000 30.4 -> 25.6, 32 x 10 ragged of 1K - 4K in
-// pages 71.1 -> 69.7 (5.8 TB/s); steps of one block at 32 x 10 pairs of 1000 keys in room for 4000 230 -> 180 us.
+// Together, traced: 8 x 10 pairs of 8200 keys in room for 9216 53.8 -> 52.4 us (6.4 TB/s), in room for 8256 55.2 -> 55.5; 32 x 8 of 1000
+// 31.5 -> 26.2; 32 x 10 ragged of 1K - 4K in pages 71.9 -> 70.2 (5.8 TB/s); 32 x 10 of 1000 in room for 4000 81.7 -> 29.0.
 // The last block stands behind the loop: no load sits under a condition between two uses, which would make the compiler wait
 // for everything.
 template <bool RECORDED>

@@ -239,7 +239,8 @@ void make_layout(const hyp_stage_config_t &c, int n_layers, Layout &L) {
     L.partial_bytes = sizeof(float) * pf;
     L.partial = take(L.partial_bytes);
     L.counters_bytes = sizeof(unsigned) * (2 * I / 64 + (qd + 2 * kvd) / 64 + H / 32);
-    // more chunks per context hold more partial results: not where the static array would become too small for them
+    // More chunks per context hold more partial results: not where the static array would become too small for them.  Both steps go by
+    // it, the one that uses the array and the one in the workspace: the same chunks give them the same bits.
     for (bool even : {true, false}) {
       L.chunk_keys = mfma_decode_chunk_keys(c.max_seq, c.max_batch * c.n_kv_heads, even);
       L.max_chunks = (c.max_seq + L.chunk_keys - 1) / L.chunk_keys;
@@ -506,8 +507,8 @@ int decode_attn_form(const hyp_stage *st, bool recorded_by_caller) {
 }
 
 // One decode step through the MFMA kernels (a single block of 32 token rows):
-// 5 launches per block (and one in front where the rows are not aligned), every
-// reduction finished inside the kernel that produced it.
+// 5 launches per block, 6 where the contexts' chunks are merged (and one in front where the rows are not aligned or the first
+// QKV contraction does not open the step); every other reduction is finished inside the kernel that produced it.
 hyp_status_t decode_step_mfma(hyp_stage *st, hipStream_t s, const DecScratch &sc, const void *hidden_in, void *hidden_out,
                               int attn_form, bool begin, bool layers) {
   const Dims &d = st->dm;
@@ -551,7 +552,10 @@ hyp_status_t decode_step_mfma(hyp_stage *st, hipStream_t s, const DecScratch &sc
     const LayerPtrs &p = L.layers[l];
     const DecGemv a = qkv(l);
     if (l > 0) PROF(st, HYP_K_GEMV_QKV, mfma_dec_gemv(DEC_QKV, HYP_K_GEMV_QKV, a, s));
-    // 28 of the 32 MiB that the L2s hold together; narrow layers' kernels wait for latency, not for bytes (512 wide: 11 % slower)
+    // 28 of the 32 MiB that the L2s hold together; narrow layers' kernels wait for latency, not for bytes.  (Steps of one block at batch 8,
+    // 200 keys, without / with, by the O projection's size: 1 MiB 21.1 / 21.6 us, 2 MiB 28.8 / 29.5, 4 MiB 48.6 / 48.9 of 2048 x 1024 and 31.2 /
+    // 30.5 of 1024 x 2048, 8 MiB 50.9 / 50.4, 12 MiB 56.4 / 55.9, 16 MiB 63.8 / 63.5, 18 MiB 58.9 / 58.1, 24 MiB 82.5 / 81.8, 32 MiB 87.3 / 87.1:
+    // mixed at 4 MiB; from 8 on it would pay a little, too.)
     ReadAhead ahead;
     const size_t o_bytes = (size_t)2 * d.H * d.qd;
     if (L.g_o.ksplit == 1 && o_bytes >= (16u << 20)) {
